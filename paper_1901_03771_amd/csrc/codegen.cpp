@@ -302,8 +302,8 @@ void emit_scalar_program(Em& e, const std::vector<Instr>& prog, const std::vecto
 }
 
 // Common kernel head: Args, extents.
-void kernel_head(Em& e, const std::string& name) {
-  e.o << "extern \"C\" __global__ __launch_bounds__(256) void " << name << "(Args a) {\n";
+void kernel_head(Em& e, const std::string& name, int threads = 256) {
+  e.o << "extern \"C\" __global__ __launch_bounds__(" << threads << ") void " << name << "(Args a) {\n";
 }
 
 // Declares p<g>: pointer of each access group advanced by its base offset.
@@ -802,6 +802,154 @@ void gen_rowred(Em& e) {
 
 // ---- REDUCE (generic reduction root) --------------------------------------------
 
+void reduce_combine(Em& e) {
+  const GroupPlan& g = e.g;
+  const Phase& ph = g.phases[0];
+  const char* T = cty(ph.out_dtype);
+  // Stage 2 (Section 3.2: "a separate kernel ... only uses the binary operation"): combines the
+  // NSPLIT partial results of every output in a fixed order.
+  kernel_head(e, kernel_name(g) + "_combine");
+  e.o << "  const long long NOUT = " << e.S(e.L.extra) << ", NSPLIT = " << e.S(e.L.extra + 3) << " & 0xffffffffll;\n";
+  e.o << "  const GM " << T << "* const ws = (const GM " << T << "*)" << e.slot(e.L.extra + 2) << ";\n";
+  e.o << "  GM " << T << "* const out = (GM " << T << "*)" << e.slot(e.L.out) << ";\n";
+  e.o << "  __shared__ long long gr_sm[4];\n";
+  e.o << "  if (NOUT >= 1024) {\n"
+         "    const long long o = (long long)blockIdx.x * 256 + threadIdx.x;\n"
+         "    if (o < NOUT) {\n      " << T << " acc = ws[o];\n"
+         "      long long s = 1;\n"
+         "      for (; s + 8 <= NSPLIT; s += 8) {\n"   // eight independent loads in flight, combined in the fixed order
+         "        const " << T << " v0 = ws[s * NOUT + o], v1 = ws[(s + 1) * NOUT + o], v2 = ws[(s + 2) * NOUT + o], v3 = ws[(s + 3) * NOUT + o];\n"
+         "        const " << T << " v4 = ws[(s + 4) * NOUT + o], v5 = ws[(s + 5) * NOUT + o], v6 = ws[(s + 6) * NOUT + o], v7 = ws[(s + 7) * NOUT + o];\n"
+         "        acc = gr_comb0(gr_comb0(gr_comb0(gr_comb0(gr_comb0(gr_comb0(gr_comb0(gr_comb0(acc, v0), v1), v2), v3), v4), v5), v6), v7);\n"
+         "      }\n"
+         "      for (; s < NSPLIT; ++s) acc = gr_comb0(acc, ws[s * NOUT + o]);\n"
+         "      out[o] = acc;\n    }\n"
+         "  } else {\n"
+         "    const long long o = blockIdx.x;\n    " << T << " acc = " << Em::identity(ph) << ";\n"
+         "    for (long long s = threadIdx.x; s < NSPLIT; s += 256) acc = gr_comb0(acc, ws[s * NOUT + o]);\n"
+         "    acc = gr_lanes0(acc);\n"
+         "    " << T << "* sm = (" << T << "*)gr_sm;\n"
+         "    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = acc;\n"
+         "    __syncthreads();\n"
+         "    if (threadIdx.x == 0) out[o] = gr_comb0(gr_comb0(sm[0], sm[1]), gr_comb0(sm[2], sm[3]));\n"
+         "  }\n}\n";
+}
+
+// Mode 0: the kept dimension is the contiguous one (column sums).  A workgroup of 512 lanes is BX
+// lanes across the outputs by BY = 512 / BX along the reduced range; a lane takes four consecutive
+// outputs with one dwordx4 per array and reduced element (one output where the kept dimension is
+// strided or shorter than four) and every BY-th element of its chunk, the BY partial results of an
+// output are combined in order through LDS.  BX is an argument: the planner fits it to the shape.
+// The last group of four outputs of a ragged dimension starts four from its end: it overlaps the
+// group before it, both store the same values, and no load leaves the array.
+void gen_reduce_columns(Em& e) {
+  const GroupPlan& g = e.g;
+  const int rank = g.rank, kr = g.red_kept_rank, kd = kr - 1;
+  const Phase& ph = g.phases[0];
+  const char* T = cty(ph.out_dtype);
+  const int W = g.red_vec ? 4 : 1;
+  int n_loads = 0;
+  for (const Instr& in : g.prog) if (in.kind == IKind::LOAD) ++n_loads;
+  // loads in flight per lane and array: written out, all first (a wave-wide vote in the body keeps the compiler from
+  // unrolling a loop with a remainder); what is left at the end of a chunk is one more batch with clamped positions,
+  // whose surplus values are not combined
+  const int U = n_loads <= 2 && g.prog.size() <= 12 ? 8 : 4;
+  kernel_head(e, kernel_name(g), kReduceLanes);
+  e.o << "  const long long NOUT = " << e.S(e.L.extra) << ", LEN = " << e.S(e.L.extra + 1) << ", NSPLIT = " << e.S(e.L.extra + 3) << " & 0xffffffffll;\n"
+         "  const unsigned BX = (unsigned)(" << e.slot(e.L.extra + 3) << " >> 32), BY = " << kReduceLanes << "u / BX;\n"
+         "  const unsigned ty = threadIdx.x / BX, tx = threadIdx.x - ty * BX;\n"
+         "  const long long D = " << e.dim(kd) << ", VD = (D + " << W - 1 << ") / " << W << ", V = " << (kr == 1 ? "VD" : "NOUT / D * VD") << ";\n"
+         "  const long long blocks_o = (V + BX - 1) / BX;\n"
+         "  long long orem = (long long)(blockIdx.x % blocks_o) * BX + tx;\n"
+         "  const long long split = blockIdx.x / blocks_o;\n"
+         "  const bool ok = orem < V && ty < BY;\n"
+         "  if (!ok) orem = 0;\n"
+         "  const long long chunk = (LEN + NSPLIT - 1) / NSPLIT, jbeg = split * chunk, jend = (jbeg + chunk < LEN) ? jbeg + chunk : LEN;\n";
+  if (kr == 1) e.o << "  const long long v" << kd << " = orem;\n";
+  else e.o << "  const long long v" << kd << " = gr_peel(orem, VD);\n";
+  if (W == 4) e.o << "  const long long i" << kd << " = 4 * v" << kd << " + 4 <= D ? 4 * v" << kd << " : D - 4;\n";
+  else e.o << "  const long long i" << kd << " = v" << kd << ";\n";
+  e.o << "  const long long o = " << (kr == 1 ? "" : "orem * D + ") << "i" << kd << ";\n";
+  for (int k = kd - 1; k >= 0; --k) {
+    if (k == 0) e.o << "  const long long i0 = orem;\n";
+    else e.o << "  const long long i" << k << " = gr_peel(orem, " << e.dim(k) << ");\n";
+  }
+  group_pointers(e, "  ");
+  for (size_t gi = 0; gi < g.groups.size(); ++gi) {
+    const AccessGroup& ag = g.groups[gi];
+    e.o << "  const GM " << cty(ag.dtype) << "* const p" << gi << " = q" << gi;
+    for (int k = 0; k < kr; ++k) if (!ag.structural_zero[k]) e.o << " + i" << k << " * " << e.coef((int)gi, k);
+    e.o << ";\n";
+  }
+  for (int c = 0; c < W; ++c) e.o << "  " << T << " acc" << c << " = " << Em::identity(ph) << ";\n";
+  auto loads = [&](int u, const std::string& jx, const char* ind) {
+    const std::string su = "_" + std::to_string(u);
+    if (rank > kr) {
+      e.o << ind << "long long jrem" << su << " = " << jx << ";\n";
+      for (int k = rank - 1; k >= kr; --k) {
+        if (k == kr) e.o << ind << "const long long i" << k << su << " = jrem" << su << ";\n";
+        else e.o << ind << "const long long i" << k << su << " = gr_peel(jrem" << su << ", " << e.dim(k) << ");\n";
+      }
+    }
+    for (size_t i = 0; i < g.prog.size(); ++i) {
+      const Instr& in = g.prog[i];
+      if (in.kind != IKind::LOAD) continue;
+      const AccessGroup& ag = g.groups[in.group];
+      std::ostringstream at;
+      at << "p" << in.group << " + 0";
+      for (int k = 0; k < rank; ++k) {
+        if (ag.structural_zero[k]) continue;
+        if (k >= kr) at << " + (i" << k << su << " + " << in.delta[k] << ") * " << e.coef(in.group, k);
+        else if (in.delta[k]) at << " + " << in.delta[k] << " * " << e.coef(in.group, k);
+      }
+      if (W == 1 || ag.structural_zero[kd]) e.o << ind << "const " << cty(in.dtype) << " w" << i << su << " = (" << at.str() << ")[0];\n";
+      else e.o << ind << "const " << vty4(in.dtype) << " w" << i << su << " = " << e.ld(in.group, vty4(in.dtype), at.str()) << ";\n";
+    }
+  };
+  auto compute = [&](int u, const std::string& guard) {
+    const std::string su = "_" + std::to_string(u);
+    e.o << "      " << guard << "{\n";
+    for (int c = 0; c < W; ++c) {
+      const std::string pre = "v" + std::to_string(c) + "_", a = "acc" + std::to_string(c);
+      emit_scalar_program(e, g.prog, {ph.value},
+                          [&](const Instr& in, int id) {
+                            const std::string w = "w" + std::to_string(id) + su;
+                            return W == 1 || g.groups[in.group].structural_zero[kd] ? w : w + "[" + std::to_string(c) + "]";
+                          },
+                          "0.0f", pre, "        ");
+      e.o << "        " << a << " = " << Em::combine(ph, a, pre + std::to_string(ph.value)) << ";\n";
+    }
+    e.o << "      }\n";
+  };
+  e.o << "  if (ok) {\n    long long j = jbeg + ty;\n    for (; j + " << U - 1 << "ll * BY < jend; j += " << U << "ll * BY) {\n";
+  for (int u = 0; u < U; ++u) loads(u, "j + " + std::to_string(u) + "ll * BY", "      ");
+  e.o << "      __builtin_amdgcn_sched_barrier(0);\n";
+  for (int u = 0; u < U; ++u) compute(u, "");
+  e.o << "    }\n    if (j < jend) {\n";
+  for (int u = 0; u < U; ++u) loads(u, u == 0 ? std::string("j") : "(j + " + std::to_string(u) + "ll * BY < jend ? j + " + std::to_string(u) + "ll * BY : j)", "      ");
+  e.o << "      __builtin_amdgcn_sched_barrier(0);\n";
+  for (int u = 0; u < U; ++u) compute(u, u == 0 ? std::string() : "if (j + " + std::to_string(u) + "ll * BY < jend) ");
+  e.o << "    }\n  }\n";
+  e.o << "  GM " << T << "* const dst = NSPLIT > 1 ? (GM " << T << "*)" << e.slot(e.L.extra + 2) << " + split * NOUT : (GM " << T << "*)" << e.slot(e.L.out) << ";\n";
+  e.o << "  if (BY == 1) {\n    if (ok) { ";
+  for (int c = 0; c < W; ++c) e.o << "dst[o + " << c << "] = acc" << c << "; ";
+  e.o << "}\n    return;\n  }\n"
+         "  __shared__ " << T << " sm[" << W << "][" << kReduceLanes << "];\n";
+  for (int c = 0; c < W; ++c) e.o << "  sm[" << c << "][threadIdx.x] = acc" << c << ";\n";
+  e.o << "  __syncthreads();\n"
+         "  if (ok) for (unsigned c = ty; c < " << W << "u; c += BY) {\n"
+         "    " << T << " r = sm[c][tx];\n"
+         "    unsigned q = 1;\n"
+         "    for (; q + 8 <= BY; q += 8) {\n"   // eight LDS reads in flight
+         "      " << T << " w[8];\n"
+         "#pragma unroll\n      for (int u = 0; u < 8; ++u) w[u] = sm[c][(q + u) * BX + tx];\n"
+         "#pragma unroll\n      for (int u = 0; u < 8; ++u) r = gr_comb0(r, w[u]);\n"
+         "    }\n"
+         "    for (; q < BY; ++q) r = gr_comb0(r, sm[c][q * BX + tx]);\n"
+         "    dst[o + c] = r;\n  }\n}\n";
+  reduce_combine(e);
+}
+
 void gen_reduce(Em& e) {
   const GroupPlan& g = e.g;
   const int rank = g.rank, kr = g.red_kept_rank;
@@ -810,20 +958,11 @@ void gen_reduce(Em& e) {
   prelude(e);
   phase_helpers(e, 0, 64);
   // Stage 1 (Section 3.2: map fused with a per-block combine): every output's reduced range is
-  // cut into NSPLIT chunks; a thread (mode 0) or a workgroup (mode 1) combines one chunk.
+  // cut into NSPLIT chunks; a column of lanes (mode 0) or a workgroup (mode 1) combines one chunk.
+  if (g.red_mode == 0) { gen_reduce_columns(e); return; }
   kernel_head(e, kernel_name(g));
   e.o << "  const long long NOUT = " << e.S(e.L.extra) << ", LEN = " << e.S(e.L.extra + 1) << ", NSPLIT = " << e.S(e.L.extra + 3) << ";\n";
-  if (g.red_mode == 0 && g.red_vec) {
-    e.o << "  const long long blocks_o = (NOUT / 4 + 255) / 256;\n"
-           "  const long long o = 4 * ((long long)(blockIdx.x % blocks_o) * 256 + threadIdx.x), split = blockIdx.x / blocks_o;\n"
-           "  if (o >= NOUT) return;\n";
-  } else if (g.red_mode == 0) {
-    e.o << "  const long long blocks_o = (NOUT + 255) / 256;\n"
-           "  const long long o = (long long)(blockIdx.x % blocks_o) * 256 + threadIdx.x, split = blockIdx.x / blocks_o;\n"
-           "  if (o >= NOUT) return;\n";
-  } else {
-    e.o << "  const long long o = blockIdx.x % NOUT, split = blockIdx.x / NOUT;\n  __shared__ long long gr_sm[4];\n";
-  }
+  e.o << "  const long long o = blockIdx.x % NOUT, split = blockIdx.x / NOUT;\n  __shared__ long long gr_sm[4];\n";
   e.o << "  const long long chunk = (LEN + NSPLIT - 1) / NSPLIT, jbeg = split * chunk, jend = (jbeg + chunk < LEN) ? jbeg + chunk : LEN;\n";
   e.o << "  long long orem = o;\n";
   for (int k = kr - 1; k >= 0; --k) {
@@ -850,65 +989,6 @@ void gen_reduce(Em& e) {
     if (in.kind == IKind::LOAD && !g.groups[in.group].structural_zero[rd] && access_class(g.groups[in.group], rd) != '1') vec = false;
   }
   if (vec && rank > kr + 1) e.o << "  const long long chunk4 = (chunk + 3) / 4 * 4, jbeg4 = split * chunk4, jend4 = (jbeg4 + chunk4 < LEN) ? jbeg4 + chunk4 : LEN;\n";
-  if (g.red_mode == 0 && g.red_vec) {
-    // four consecutive outputs per thread: one dwordx4 per array and reduced element
-    const int kd = kr - 1;
-    // (four steps of j written out with all loads first, like the loop of the workgroup-per-chunk kernels below:
-    // "#pragma unroll 4" is dropped by the compiler when the body holds a wave-wide vote)
-    e.o << "  " << T << " acc1 = acc, acc2 = acc, acc3 = acc;\n";
-    auto loads0 = [&](int u, const char* ind) {
-      const std::string su = "_" + std::to_string(u);
-      if (rank > kr) {
-        e.o << ind << "long long jrem" << su << " = j + " << u << ";\n";
-        for (int k = rank - 1; k >= kr; --k) {
-          if (k == kr) e.o << ind << "const long long i" << k << su << " = jrem" << su << ";\n";
-          else e.o << ind << "const long long i" << k << su << " = gr_peel(jrem" << su << ", " << e.dim(k) << ");\n";
-        }
-      }
-      for (size_t i = 0; i < g.prog.size(); ++i) {
-        const Instr& in = g.prog[i];
-        if (in.kind != IKind::LOAD) continue;
-        const AccessGroup& ag = g.groups[in.group];
-        std::ostringstream at;
-        at << "p" << in.group << " + 0";
-        for (int k = 0; k < rank; ++k) {
-          if (ag.structural_zero[k]) continue;
-          if (k >= kr) at << " + (i" << k << su << " + " << in.delta[k] << ") * " << e.coef(in.group, k);
-          else if (in.delta[k]) at << " + " << in.delta[k] << (k == kd ? std::string("") : " * " + e.coef(in.group, k));
-        }
-        if (ag.structural_zero[kd]) e.o << ind << "const " << cty(in.dtype) << " u" << i << su << " = (" << at.str() << ")[0];\n";
-        else e.o << ind << "const " << vty4(in.dtype) << " w" << i << su << " = " << e.ld(in.group, vty4(in.dtype), at.str()) << ";\n";
-      }
-    };
-    auto compute0 = [&](int u, const std::string& ind) {
-      const std::string su = "_" + std::to_string(u);
-      e.o << ind << "{\n";
-      for (int k = rank - 1; k >= kr; --k) e.o << ind << "  const long long i" << k << " = i" << k << su << "; (void)i" << k << ";\n";
-      for (int c4 = 0; c4 < 4; ++c4) {
-        const std::string pre = "v" + std::to_string(c4) + "_";
-        emit_scalar_program(e, g.prog, {ph.value},
-                            [&](const Instr& in, int id) {
-                              const AccessGroup& ag = g.groups[in.group];
-                              if (ag.structural_zero[kd]) return "u" + std::to_string(id) + su;
-                              return "w" + std::to_string(id) + su + "[" + std::to_string(c4) + "]";
-                            },
-                            "0.0f", pre, ind + "  ");
-        const std::string a = c4 == 0 ? "acc" : "acc" + std::to_string(c4);
-        e.o << ind << "  " << a << " = " << Em::combine(ph, a, pre + std::to_string(ph.value)) << ";\n";
-      }
-      e.o << ind << "}\n";
-    };
-    e.o << "  long long j = jbeg;\n  for (; j + 4 <= jend; j += 4) {\n";
-    for (int u = 0; u < 4; ++u) loads0(u, "    ");
-    e.o << "    __builtin_amdgcn_sched_barrier(0);\n";
-    for (int u = 0; u < 4; ++u) compute0(u, "    ");
-    e.o << "  }\n  for (; j < jend; ++j) {\n";
-    loads0(0, "    ");
-    compute0(0, "    ");
-    e.o << "  }\n";
-    e.o << "  GM " << T << "* const dst = NSPLIT > 1 ? (GM " << T << "*)" << e.slot(e.L.extra + 2) << " + split * NOUT : (GM " << T << "*)" << e.slot(e.L.out) << ";\n";
-    e.o << "  dst[o] = acc; dst[o + 1] = acc1; dst[o + 2] = acc2; dst[o + 3] = acc3;\n}\n";
-  } else {
   if (vec) {
     const bool multi = rank > kr + 1;
     const char* jb = multi ? "jbeg4" : "jbeg";
@@ -973,9 +1053,9 @@ void gen_reduce(Em& e) {
     e.o << "    }\n    acc = gr_comb0(gr_comb0(acc, acc1), gr_comb0(acc2, acc3));\n  }\n";
     e.o << "  for (; j < " << je << "; ++j) {\n";   // at most one lane still has (fewer than four) elements
   } else {
-    // one element per step (of a thread, or of each of a workgroup's 256 threads): four steps written out with their
+    // one element per step of each of the workgroup's 256 threads: four steps written out with their
     // loads first, for the same reason as above; the accumulator takes the elements in the order of j
-    const int STEP = g.red_mode == 0 ? 1 : 256;
+    const int STEP = 256;
     auto idx = [&](const std::string& su, const std::string& jx, const char* ind) {
       if (rank > kr) {
         e.o << ind << "long long jrem" << su << " = " << jx << ";\n";
@@ -985,7 +1065,7 @@ void gen_reduce(Em& e) {
         }
       }
     };
-    e.o << "  long long j = " << (g.red_mode == 0 ? "jbeg" : "jbeg + threadIdx.x") << ";\n  for (; j + " << 3 * STEP << " < jend; j += " << 4 * STEP << ") {\n";
+    e.o << "  long long j = jbeg + threadIdx.x;\n  for (; j + " << 3 * STEP << " < jend; j += " << 4 * STEP << ") {\n";
     for (int u = 0; u < 4; ++u) {
       const std::string su = "_" + std::to_string(u);
       idx(su, "j + " + std::to_string(u * STEP), "    ");
@@ -1035,45 +1115,13 @@ void gen_reduce(Em& e) {
                       "0.0f", "t", "    ");
   e.o << "    acc = " << Em::combine(ph, "acc", "t" + std::to_string(ph.value)) << ";\n  }\n";
   e.o << "  GM " << T << "* const dst = NSPLIT > 1 ? (GM " << T << "*)" << e.slot(e.L.extra + 2) << " + split * NOUT : (GM " << T << "*)" << e.slot(e.L.out) << ";\n";
-  if (g.red_mode == 1) {
-    e.o << "  acc = gr_lanes0(acc);\n"
-           "  " << T << "* const sm = (" << T << "*)gr_sm;\n"
-           "  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = acc;\n"
-           "  __syncthreads();\n"
-           "  acc = gr_comb0(gr_comb0(sm[0], sm[1]), gr_comb0(sm[2], sm[3]));\n"
-           "  if (threadIdx.x == 0) dst[o] = acc;\n";
-  } else {
-    e.o << "  dst[o] = acc;\n";
-  }
-  e.o << "}\n";
-  }
-  // Stage 2 (Section 3.2: "a separate kernel ... only uses the binary operation"): combines the
-  // NSPLIT partial results of every output in a fixed order.
-  kernel_head(e, kernel_name(g) + "_combine");
-  e.o << "  const long long NOUT = " << e.S(e.L.extra) << ", NSPLIT = " << e.S(e.L.extra + 3) << ";\n";
-  e.o << "  const GM " << T << "* const ws = (const GM " << T << "*)" << e.slot(e.L.extra + 2) << ";\n";
-  e.o << "  GM " << T << "* const out = (GM " << T << "*)" << e.slot(e.L.out) << ";\n";
-  e.o << "  __shared__ long long gr_sm[4];\n";
-  e.o << "  if (NOUT >= 1024) {\n"
-         "    const long long o = (long long)blockIdx.x * 256 + threadIdx.x;\n"
-         "    if (o < NOUT) {\n      " << T << " acc = ws[o];\n"
-         "      long long s = 1;\n"
-         "      for (; s + 8 <= NSPLIT; s += 8) {\n"   // eight independent loads in flight, combined in the fixed order
-         "        const " << T << " v0 = ws[s * NOUT + o], v1 = ws[(s + 1) * NOUT + o], v2 = ws[(s + 2) * NOUT + o], v3 = ws[(s + 3) * NOUT + o];\n"
-         "        const " << T << " v4 = ws[(s + 4) * NOUT + o], v5 = ws[(s + 5) * NOUT + o], v6 = ws[(s + 6) * NOUT + o], v7 = ws[(s + 7) * NOUT + o];\n"
-         "        acc = gr_comb0(gr_comb0(gr_comb0(gr_comb0(gr_comb0(gr_comb0(gr_comb0(gr_comb0(acc, v0), v1), v2), v3), v4), v5), v6), v7);\n"
-         "      }\n"
-         "      for (; s < NSPLIT; ++s) acc = gr_comb0(acc, ws[s * NOUT + o]);\n"
-         "      out[o] = acc;\n    }\n"
-         "  } else {\n"
-         "    const long long o = blockIdx.x;\n    " << T << " acc = " << Em::identity(ph) << ";\n"
-         "    for (long long s = threadIdx.x; s < NSPLIT; s += 256) acc = gr_comb0(acc, ws[s * NOUT + o]);\n"
-         "    acc = gr_lanes0(acc);\n"
-         "    " << T << "* sm = (" << T << "*)gr_sm;\n"
-         "    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = acc;\n"
-         "    __syncthreads();\n"
-         "    if (threadIdx.x == 0) out[o] = gr_comb0(gr_comb0(sm[0], sm[1]), gr_comb0(sm[2], sm[3]));\n"
-         "  }\n}\n";
+  e.o << "  acc = gr_lanes0(acc);\n"
+         "  " << T << "* const sm = (" << T << "*)gr_sm;\n"
+         "  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = acc;\n"
+         "  __syncthreads();\n"
+         "  acc = gr_comb0(gr_comb0(sm[0], sm[1]), gr_comb0(sm[2], sm[3]));\n"
+         "  if (threadIdx.x == 0) dst[o] = acc;\n}\n";
+  reduce_combine(e);
 }
 
 // ---- SCAN (map-scan) ------------------------------------------------------------

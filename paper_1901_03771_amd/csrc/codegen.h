@@ -26,6 +26,9 @@ struct ArgLayout {
 
 ArgLayout arg_layout(const GroupPlan& g);
 
+// Lanes of a workgroup of the column reductions (REDUCE mode 0).
+constexpr int kReduceLanes = 512;
+
 // 'Z': no leaf dimension follows this iteration dimension; '1': unit stride; 'G': anything else.
 char access_class(const AccessGroup& ag, int dim);
 

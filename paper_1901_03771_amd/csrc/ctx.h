@@ -19,7 +19,7 @@ struct gr_program {
   struct Launch {
     hipFunction_t fn = nullptr;
     std::string name;
-    unsigned grid = 0;
+    unsigned grid = 0, threads = 256;
     std::vector<uint64_t> args;
     std::vector<std::pair<int, int>> patch;  // (argument slot, source): source k >= 0 = leaf k, -1 = the output
   };

@@ -192,8 +192,9 @@ struct GroupPlan {
   int diag = 0;                          // MAP with staged operands: tile rows are taken diagonally (row block + column block)
   int tail = 0;                          // MAP: columns mod 4 of a narrow array (1..3): its last lanes get straight-line code too
   int nt = 0;                            // non-temporal load hint: 0 none, 1 arrays read once, 2 all vector loads
-  int red_mode = 0;                      // REDUCE: 0 thread-per-output, 1 block-per-output
-  int red_vec = 0;                       // REDUCE mode 0: a thread owns four consecutive outputs (dwordx4 loads)
+  int red_mode = 0;                      // REDUCE: 0 lanes across the outputs, 1 block-per-output
+  int red_vec = 0;                       // REDUCE mode 0: a lane owns four consecutive outputs (dwordx4 loads)
+  int red_bx = 1;                        // REDUCE mode 0: lanes of a workgroup across the outputs
   int64_t red_out = 0, red_len = 0;      // REDUCE: outputs, reduced elements per output
   int red_kept_rank = 0;
 
@@ -219,6 +220,13 @@ struct GroupPlan {
 
   std::string signature;
 };
+
+// REDUCE mode 0: lanes' worth of outputs (a lane owns four outputs of the innermost kept dimension, or one).
+inline int64_t reduce_units(const GroupPlan& g) {
+  if (!g.red_vec) return g.red_out;
+  const int64_t D = g.dims[g.red_kept_rank - 1];
+  return D > 0 ? g.red_out / D * ((D + 3) / 4) : 0;
+}
 
 // Strided destination of the requested root (slice assignment); NULL = C-contiguous buffer.
 struct OutSpec {

@@ -30,6 +30,7 @@
 #include <functional>
 #include <sstream>
 
+#include "codegen.h"
 #include "ctx.h"
 
 namespace gr {
@@ -684,6 +685,40 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g) {
   g->tail = (g->rank >= 2 && C < 64 && (C & 3) && g->UC == 1 && !g->stage_mask) ? (int)(C & 3) : 0;
 }
 
+// REDUCE mode 0: how many lanes of a workgroup lie across the outputs (the rest along the reduced range) and
+// how many workgroups share one output's range (their partial results are combined by a second launch).
+// Bound by HBM for long ranges, by load latency times the elements one lane takes in turn for short ones: with a
+// lane per four outputs and chunks of 256 elements (128 where the outputs were no multiple of four, scalar loads)
+// few lanes ran and each waited for its loads 64 times over.  Standardisation of columns (two such sums and a map),
+// before and after: 768 x 444 77.9 -> 15.7 us, 192 x 6848 61 -> 15, 112160 x 90 77.7 -> 56.8, 100003 x 257 109 -> 99
+// (first sum 26 us = 4 TB/s, second 20 us), 3977 x 7342 110 -> 111; column sums of 4096 x 512 19 -> 9.
+void choose_column_split(gr_ctx* c, GroupPlan* g) {
+  const int64_t V = std::max<int64_t>(1, reduce_units(*g)), LEN = std::max<int64_t>(1, g->red_len);
+  auto even = [&](int64_t bx) { const int64_t nb = (V + bx - 1) / bx; return (V + nb - 1) / nb; };   // blocks of equal width
+  // One launch where that leaves a lane at most 32 elements, or where the outputs alone fill the chip: blocks as
+  // wide as still give 512 workgroups, 16 lanes (256 bytes) at least.
+  int64_t bx = kReduceLanes;
+  while (bx > 16 && (V + bx - 1) / bx < 512) bx /= 2;
+  g->red_bx = (int)even(bx);
+  g->slabs = 1;
+  if ((bx >= 64 && (V + bx - 1) / bx >= 512) || LEN <= 32 * (kReduceLanes / g->red_bx)) return;
+  // Otherwise wide blocks (whole rows up to 128 lanes = 2 KiB) and enough chunks for two workgroups per compute unit, of
+  // 16 elements per lane at least.
+  g->red_bx = (int)even(128);
+  const int64_t blocks = (V + g->red_bx - 1) / g->red_bx, by = kReduceLanes / g->red_bx;
+  int64_t nsplit = std::min<int64_t>((512 + blocks - 1) / blocks, std::max<int64_t>(1, LEN / (16 * by)));
+  if (c->plan_static) {
+    // Partial results of a request that must not allocate come out of the static scratch array, beside the request's
+    // stored results: no more of them than chunks of 256 elements (128 where a lane owns one output) by 256-lane
+    // workgroups would give, so that what fits does not depend on how wide the blocks are.
+    const bool quads = g->red_vec && g->dims[g->red_kept_rank - 1] % 4 == 0;
+    const int64_t groups = ((quads ? g->red_out / 4 : g->red_out) + 255) / 256;
+    nsplit = std::min<int64_t>(nsplit, std::max<int64_t>(1, g->red_out < 64 && LEN >= 4096 ? std::min<int64_t>(2048 / g->red_out, LEN / 4096)
+                                                                                          : std::min<int64_t>(2048 / groups, LEN / (quads ? 256 : 128))));
+  }
+  g->slabs = (int)nsplit;
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -1150,14 +1185,13 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         if (g->rank > kept_rank && ag.coef[g->rank - 1] == 1) red_unit = true;
       }
       g->red_mode = (kept_unit && !red_unit) ? 0 : ((red_unit && !kept_unit) ? 1 : (g->red_out >= 4096 ? 0 : 1));
-      // a handful of outputs (column sums of an array of points): a thread per output would leave
-      // most lanes idle, so the lanes go along the reduced range even though it is strided
-      if (g->red_mode == 0 && g->red_out < 64 && g->red_len >= 4096) g->red_mode = 1;
-      // split the reduced range so that about 2048 workgroups run (two-stage reduction, Section 3.2)
-      // mode 0 with four consecutive outputs per thread: the innermost kept dimension is contiguous
-      // (or absent) in every array read, holds a multiple of four, and all values are 32 bits wide
+      // a handful of outputs whose elements are not contiguous: lanes across them would leave most of a workgroup's
+      // loads apart, so the lanes go along the reduced range even though it is strided
+      if (g->red_mode == 0 && !kept_unit && g->red_out < 64 && g->red_len >= 4096) g->red_mode = 1;
+      // mode 0 with four consecutive outputs per lane: the innermost kept dimension is contiguous
+      // (or absent) in every array read, has four elements or more, and all values are 32 bits wide
       g->red_vec = 0;
-      if (g->red_mode == 0 && kept_rank >= 1 && g->dims[kept_rank - 1] % 4 == 0 && p.in_dtype != GR_I64) {
+      if (g->red_mode == 0 && kept_rank >= 1 && g->dims[kept_rank - 1] >= 4 && p.in_dtype != GR_I64) {
         bool ok = true;
         for (const AccessGroup& ag : g->groups)
           if (ag.dtype == GR_I64 || (!ag.structural_zero[kept_rank - 1] && ag.coef[kept_rank - 1] != 1)) ok = false;
@@ -1167,13 +1201,12 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
       // mode 1 over several reduced dimensions: four consecutive elements per lane as long as they
       // cannot straddle the innermost one
       if (g->red_mode == 1 && g->rank > kept_rank + 1 && g->dims[g->rank - 1] % 4 == 0) g->red_vec = 1;
-      int64_t units = g->red_mode == 0 ? ((g->red_vec ? g->red_out / 4 : g->red_out) + 255) / 256 : g->red_out;
-      // measured on MI355X (column sums of 8192^2): fewer, longer chunks win once a thread streams
-      // dwordx4 rows (32 splits: 53 us, 128 splits: 61 us, 512 splits: 72 us)
-      int64_t min_chunk = g->red_mode == 0 ? (g->red_vec ? 256 : 128) : 256 * 16;
-      const int64_t target = 2048;
-      int64_t nsplit = std::min<int64_t>(std::max<int64_t>(1, target / std::max<int64_t>(units, 1)), std::max<int64_t>(1, g->red_len / min_chunk));
-      g->slabs = (int)std::min<int64_t>(nsplit, 4096);
+      // split the reduced range so that about 2048 workgroups run (two-stage reduction, Section 3.2)
+      if (g->red_mode == 0) choose_column_split(c, g);
+      else {
+        const int64_t nsplit = std::min<int64_t>(std::max<int64_t>(1, 2048 / std::max<int64_t>(g->red_out, 1)), std::max<int64_t>(1, g->red_len / 4096));
+        g->slabs = (int)std::min<int64_t>(nsplit, 4096);
+      }
     } else {
       // ---- row-resident reductions fused with producers and consumers -----
       g->kind = GroupKind::ROWRED;

@@ -367,7 +367,7 @@ gr_status compile_group(gr_ctx* c, GroupPlan& g, gr_ctx::Kernel** out) {
   return collect_job(c, g.signature, out);
 }
 
-static gr_status launch(gr_ctx* c, hipFunction_t fn, const std::string& name, int64_t grid, std::vector<uint64_t>& args) {
+static gr_status launch(gr_ctx* c, hipFunction_t fn, const std::string& name, int64_t grid, std::vector<uint64_t>& args, unsigned threads = 256) {
   if (grid <= 0) return GR_OK;
   if (grid > 0x7fffffffLL) return fail(c, GR_ERR_UNSUPPORTED, "launch: grid too large");
   if (c->capture) {
@@ -376,6 +376,7 @@ static gr_status launch(gr_ctx* c, hipFunction_t fn, const std::string& name, in
     l.fn = fn;
     l.name = name;
     l.grid = (unsigned)grid;
+    l.threads = threads;
     l.args = args;
     l.patch = c->capture->cur_patch;
     c->capture->launches.push_back(std::move(l));
@@ -393,7 +394,7 @@ static gr_status launch(gr_ctx* c, hipFunction_t fn, const std::string& name, in
     }
     GR_HIP(c, hipEventRecord(e0, c->stream));
   }
-  GR_HIP(c, hipModuleLaunchKernel(fn, (unsigned)grid, 1, 1, 256, 1, 1, 0, c->stream, nullptr, extra));
+  GR_HIP(c, hipModuleLaunchKernel(fn, (unsigned)grid, 1, 1, threads, 1, 1, 0, c->stream, nullptr, extra));
   if (profile) {
     GR_HIP(c, hipEventRecord(e1, c->stream));
     c->prof.push_back({name, e0, e1});
@@ -581,8 +582,9 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
         if (wst != GR_OK) return wst;
         s[L.extra + 2] = (uint64_t)(uintptr_t)ws;
       }
-      int64_t units = g.red_mode == 0 ? ((g.red_vec ? g.red_out / 4 : g.red_out) + 255) / 256 : g.red_out;
-      gr_status st = launch(c, k->fn, k->name, units * g.slabs, s);
+      if (g.red_mode == 0) s[L.extra + 3] |= (uint64_t)g.red_bx << 32;
+      const int64_t units = g.red_mode == 0 ? (reduce_units(g) + g.red_bx - 1) / g.red_bx : g.red_out;
+      gr_status st = launch(c, k->fn, k->name, units * g.slabs, s, g.red_mode == 0 ? kReduceLanes : 256);
       if (st != GR_OK || g.slabs <= 1) return st;
       return launch(c, k->fn2, k->name + "_combine", g.red_out >= 1024 ? (g.red_out + 255) / 256 : g.red_out, s);
     }
@@ -1017,7 +1019,7 @@ gr_status gr_program_run(gr_program* prog, void* const* leaf_ptrs, void* out_ptr
   }
   for (gr_program::Launch& l : prog->launches) {
     for (const auto& pt : l.patch) l.args[pt.first] = (uint64_t)(uintptr_t)(pt.second < 0 ? out_ptr : leaf_ptrs[pt.second]);
-    gr_status st = launch(c, l.fn, l.name, l.grid, l.args);
+    gr_status st = launch(c, l.fn, l.name, l.grid, l.args, l.threads);
     if (st != GR_OK) return st;
   }
   return GR_OK;

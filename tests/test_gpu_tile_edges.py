@@ -1,0 +1,66 @@
+"""Kernels that are picked by a rule on sizes, at the sizes where their tiles end: against the CPU oracle, every element."""
+import os
+
+import numpy as np
+import pytest
+
+import oracle as ora
+from helpers import reduction_check
+
+pytestmark = pytest.mark.gpu
+f32 = np.float32
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_1901_03771_amd import lazy as gr
+    ctx = gr.Context()
+    ctx.set_option("interp", 0)       # always the generated kernels
+    ctx.set_option("plan_cache", 2)   # remembered plans and kernels against fresh ones
+    ora.set_threads(min(16, os.cpu_count() or 1))
+    yield gr, ctx, torch
+    ctx.sync()
+    ctx.close()
+
+
+def both(env, program, **arrays):
+    gr, ctx, torch = env
+    keep = {k: torch.from_numpy(np.ascontiguousarray(v)).cuda() for k, v in arrays.items()}
+    got = program(gr, **{k: ctx.array(t) for k, t in keep.items()}).numpy()
+    ref = program(ora, **{k: ora.array(v) for k, v in arrays.items()}).numpy()
+    assert got.shape == ref.shape and got.dtype == ref.dtype
+    return got, ref
+
+
+def positive(shape, seed):
+    return (np.random.default_rng(seed).random(shape) + 0.25).astype(f32)
+
+
+# outputs: below and at a group of four, ragged groups, one block, several blocks, blocks of the whole workgroup;
+# reduced lengths: none, one, one batch of loads and its neighbours, one launch and two
+@pytest.mark.parametrize("shape,axis", [
+    ((1, 5), 0), ((2, 4), 0), ((7, 3), 0), ((8, 1027), 0), ((9, 65), 0), ((257, 257), 0), ((1025, 514), 0), ((5000, 24), 0),
+    ((2, 1 << 20), 0), ((33, 40001), 0), ((1200, 33000), 0), ((20011, 90), 0), ((100000, 3), 0), ((6, 70, 9), 1), ((3, 2000, 130), 1),
+    ((40, 6, 50, 7), (0, 2)), ((50, 30, 6), (0, 1)), ((0, 300), 0)])
+def test_column_reductions(env, shape, axis):
+    a = positive(shape, 7)
+    if 0 not in shape:
+        a.reshape(-1)[:: max(1, a.size // 5)] = -3.5
+        for op in ("max", "min"):
+            got, ref = both(env, lambda xp, a: getattr(xp, op)(a, axis=axis), a=a)
+            assert np.array_equal(got, ref), op
+        a = np.abs(a)
+    got, ref = both(env, lambda xp, a: xp.sum(a * a, axis=axis), a=a)   # positive terms: 1e-5 of every element
+    assert reduction_check(got, ref)[0].all()
+    i = np.random.default_rng(8).integers(-2**31, 2**31 - 1, shape, dtype=np.int64).astype(np.int32)
+    got, ref = both(env, lambda xp, i: xp.sum(i, axis=axis), i=i)
+    assert np.array_equal(got, ref)
+
+
+def test_column_reductions_keep_infinities_and_nan(env):
+    a = positive((3000, 70), 9)
+    a[5, 0], a[2999, 69], a[17, 33], a[18, 33] = np.inf, np.nan, np.inf, -np.inf
+    for op in ("sum", "max", "min"):
+        got, ref = both(env, lambda xp, a: getattr(xp, op)(a, axis=0), a=a)
+        assert reduction_check(got, ref)[0].all(), op
