@@ -327,15 +327,16 @@ void gen_map(Em& e) {
   kernel_head(e, kernel_name(g));
   e.o << "  const long long C = " << e.dim(cd) << ";\n";
   e.o << "  const long long R = " << (rank >= 2 ? e.dim(rd) : std::string("1")) << ";\n";
+  if (g.flat == 1) e.o << "  const long long nvc = (C + 3) / 4, nrg = (R + " << g.VR - 1 << ") / " << g.VR << ";\n";
   // tile bookkeeping in 32-bit unsigned arithmetic (the grid has fewer than 2^31 tiles)
-  e.o << "  const unsigned nbx = (unsigned)((C + " << g.cphase + TC - 1 << ") / " << TC << "), nby = (unsigned)((R + " << TR - 1 << ") / " << TR << ");\n";
+  else e.o << "  const unsigned nbx = (unsigned)((C + " << g.cphase + TC - 1 << ") / " << TC << "), nby = (unsigned)((R + " << TR - 1 << ") / " << TR << ");\n";
   e.o << "  unsigned tile = blockIdx.x;\n";
   if (g.xcd_remap) {
     // consecutive tiles go to the same XCD (workgroups are dealt round-robin over the 8 XCDs),
     // so tiles that share halo rows also share an L2
     e.o << "  { unsigned outer = 1;\n";
     for (int k = 0; k + 2 < rank; ++k) e.o << "    outer *= (unsigned)" << e.dim(k) << ";\n";
-    e.o << "    const unsigned ntiles = nbx * nby * outer, per = (ntiles + 7) / 8;\n"
+    e.o << "    const unsigned ntiles = " << (g.flat == 1 ? "(unsigned)((nvc * nrg * outer + 255) / 256)" : "nbx * nby * outer") << ", per = (ntiles + 7) / 8;\n"
            "    tile = (blockIdx.x % 8) * per + blockIdx.x / 8;\n"
            "    if (tile >= ntiles) return; }\n";
   }
@@ -350,14 +351,28 @@ void gen_map(Em& e) {
            "  unsigned bx, by;\n"
            "  if ((nbx & 7) == 0) { const unsigned nq = nbx >> 3, l = sl >> 3; bx = (sl & 7) * nq + l % nq; by = (l / nq + bx) % nby; }\n"
            "  else { bx = sl % nbx; by = (sl / nbx + bx) % nby; }\n";
-  else
+  else if (g.flat == 1) {
+    // lanes in order over (outer index, row group, column group): no lane without a patch but the last workgroup's, and the
+    // last group of columns (rows) starts four (VR) from the end, so that every patch lies inside the array
+    e.o << "  long long frem = (long long)tile * 256 + threadIdx.x;\n  if (frem >= nvc * nrg";
+    for (int k = 0; k + 2 < rank; ++k) e.o << " * " << e.dim(k);
+    e.o << ") return;\n"
+           "  const long long cg = gr_peel(frem, nvc), rg = gr_peel(frem, nrg);\n"
+           "  const long long c0 = 4 * cg + 4 <= C ? 4 * cg : C - 4, r0 = " << g.VR << " * rg + " << g.VR << " <= R ? " << g.VR << " * rg : R - " << g.VR << ";\n";
+  } else
     e.o << "  const unsigned bx = tile % nbx, t2 = tile / nbx, by = t2 % nby, olin = t2 / nby;\n";
   if (rank > 2) {
-    e.o << "  unsigned orem = olin;\n";
+    e.o << "  unsigned orem = " << (g.flat == 1 ? "(unsigned)frem" : "olin") << ";\n";
     for (int k = rank - 3; k >= 0; --k) e.o << "  const long long i" << k << " = orem % (unsigned)" << e.dim(k) << "; orem /= (unsigned)" << e.dim(k) << ";\n";
   }
-  e.o << "  const int tx = threadIdx.x % " << g.BX << ", ty = threadIdx.x / " << g.BX << ";\n";
-  e.o << "  const long long r0 = (long long)by * " << TR << " + ty * " << g.VR << ", c0 = (long long)bx * " << TC << " + tx * 4" << (g.cphase ? " - " + std::to_string(g.cphase) : std::string()) << ";\n";
+  if (g.flat != 1) {
+    e.o << "  const int tx = threadIdx.x % " << g.BX << ", ty = threadIdx.x / " << g.BX << ";\n";
+    const char* q = g.flat ? "q" : "";   // (of the tile; below: of a patch that lies inside the array)
+    e.o << "  const long long r0" << q << " = (long long)by * " << TR << " + ty * " << g.VR << ", c0" << q << " = (long long)bx * " << TC << " + tx * 4" << (g.cphase ? " - " + std::to_string(g.cphase) : std::string()) << ";\n";
+    if (g.flat)
+      e.o << "  if (r0q >= R || c0q >= C) return;\n"
+             "  const long long c0 = c0q + 4 <= C ? c0q : C - 4, r0 = r0q + " << g.VR << " <= R ? r0q : R - " << g.VR << ";\n";
+  }
   group_pointers(e, "  ");
   for (size_t gi = 0; gi < g.groups.size(); ++gi) {
     const AccessGroup& ag = g.groups[gi];
@@ -430,7 +445,8 @@ void gen_map(Em& e) {
     e.o << "  __syncthreads();\n";
   }
   // ---- lanes whose whole patch lies inside the array: straight-line ----
-  e.o << "  if (r0 + " << g.VR << " <= R && c0 + " << (g.UC - 1) * g.BX * 4 + 4 << " <= C" << (g.cphase ? " && c0 >= 0" : "") << ") {\n";
+  if (g.flat) e.o << "  {\n";
+  else e.o << "  if (r0 + " << g.VR << " <= R && c0 + " << (g.UC - 1) * g.BX * 4 + 4 << " <= C" << (g.cphase ? " && c0 >= 0" : "") << ") {\n";
   // group the contiguous loads of the patch program into vector loads
   std::map<int, std::string> load_name;  // instr -> expression
   {
@@ -516,6 +532,7 @@ void gen_map(Em& e) {
         ri += 4;
       }
   }
+  if (g.flat) { e.o << "  }\n}\n"; return; }
   // ---- narrow arrays: the lanes of the last, incomplete group of four columns (all rows of
   // their patch inside): the same patch program restricted to the columns that exist, scalar
   // loads and stores, no guards ----

@@ -189,6 +189,8 @@ struct GroupPlan {
   bool xcd_remap = false;
   int cphase = 0;     // map: lanes own columns 4k - cphase .. 4k - cphase + 3, so that their vector stores are 16-byte aligned in the output
   int stage_mask = 0;                    // MAP: access groups (bit per group) read through a transposing LDS tile
+  int flat = 0;                          // MAP: every patch lies inside the array, the last ones overlap: 1 lanes numbered over
+                                         // row and column groups, 2 in tiles
   int diag = 0;                          // MAP with staged operands: tile rows are taken diagonally (row block + column block)
   int tail = 0;                          // MAP: columns mod 4 of a narrow array (1..3): its last lanes get straight-line code too
   int nt = 0;                            // non-temporal load hint: 0 none, 1 arrays read once, 2 all vector loads

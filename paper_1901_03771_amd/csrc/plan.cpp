@@ -473,7 +473,7 @@ void make_signature(GroupPlan* g) {
   std::string s;
   s.reserve(256 + 32 * (g->prog.size() + g->prog1.size()));
   for (int64_t v : {(int64_t)g->kind, (int64_t)g->rank, (int64_t)g->out_dtype, (int64_t)g->out_per_row, (int64_t)g->BX, (int64_t)g->BY,
-                    (int64_t)g->VR + (g->kind == GroupKind::GEMM && g->VR == 2 && g->slabs > 1 ? 1024 : 0) /* (the direct-to-LDS product kernels compile the split of K in or out) */, (int64_t)g->UC, (int64_t)g->NP, (int64_t)g->row_threads + 1024 * (int64_t)g->row_iters, (int64_t)g->xcd_remap + 2 * (int64_t)g->stage_mask + (((int64_t)g->tail) << 40) + (((int64_t)g->diag) << 44) + (((int64_t)g->cphase) << 48), (int64_t)g->red_mode + 16 * (int64_t)g->red_vec,
+                    (int64_t)g->VR + (g->kind == GroupKind::GEMM && g->VR == 2 && g->slabs > 1 ? 1024 : 0) /* (the direct-to-LDS product kernels compile the split of K in or out) */, (int64_t)g->UC, (int64_t)g->NP, (int64_t)g->row_threads + 1024 * (int64_t)g->row_iters, (int64_t)g->xcd_remap + 2 * (int64_t)g->stage_mask + (((int64_t)g->tail) << 40) + (((int64_t)g->diag) << 44) + (((int64_t)g->cphase) << 48) + (((int64_t)g->flat) << 52), (int64_t)g->red_mode + 16 * (int64_t)g->red_vec,
                     (int64_t)g->red_kept_rank, (int64_t)g->gemv_mode, (int64_t)g->LPR, (int64_t)g->KV, (int64_t)g->mat_group,
                     (int64_t)g->vec_group, (int64_t)g->nt, (int64_t)g->unroll, (int64_t)g->scan_mode + 16 * (int64_t)g->scan_vec + (g->scan_mode >= 2 ? 256 * g->scan_chunk : 0) /* (a one-pass scan's tile size is compiled in) */, (int64_t)g->out_unit, (int64_t)g->groups.size()})
     put(s, v);
@@ -592,7 +592,7 @@ struct Planner {
   }
 };
 
-void choose_map_schedule(gr_ctx* c, GroupPlan* g) {
+void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
   int64_t C = g->dims[g->rank - 1];
   int64_t R = g->rank >= 2 ? g->dims[g->rank - 2] : 1;
   int64_t outer = 1;
@@ -682,7 +682,35 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g) {
   // Narrow arrays (points, pixels: a few columns): the lanes that own the last, incomplete group
   // of four columns are a large share of all lanes (all of them below four columns).  The kernel
   // is specialised on columns mod 4 and gives those lanes straight-line code as well.
-  g->tail = (g->rank >= 2 && C < 64 && (C & 3) && g->UC == 1 && !g->stage_mask) ? (int)(C & 3) : 0;
+  // Rows that are no multiple of four: the last group of columns starts four from the row's end (the last rows of a tile
+  // VR from the array's), overlapping the group before it with the same values, and no lane needs the guarded path, whose
+  // serial scalar loads its whole wave waits for (x * row + 1 on 300000 x 90: 58.9 -> 41.0 us, 192105 x 131: 64.1 -> 39.5,
+  // 5033164 x 5: 92.6 -> 55.2, 8190^2: 95.3 -> 93.5).  Not for the destination of a slice assignment, which the value may read:
+  // an element computed twice would see its own result.
+  // Rows a little longer than a tile of 1024 columns leave most of the second tile's lanes idle: there the lanes are
+  // numbered over all groups of four columns instead (24480 x 1028: 53.5 -> 40.3 us, 16777 x 1500: 46.7 -> 38.9; from 85 % of
+  // lanes in use on and in narrower tiles the idle lanes cost less than the index arithmetic: 8388 x 3000 37.8 against
+  // 38.7, 74017 x 340 36.3 against 40.5), unless the program is long enough for the idle lanes' issue slots to count
+  // (division and square root per element on 100003 x 257, 65 of 128 lanes: 43 -> 35 us).  Such lanes share cache lines across waves, so their loads carry no hint.
+  if (own_output && !narrow_tile && g->rank >= 2 && R > 1 && C >= 4 && g->UC == 1 && !g->stage_mask && !g->cphase && g->out_unit &&
+      c->opt_map_rows == 0 && c->opt_map_chunks == 0 && c->opt_map_bx == 0) {
+    const int64_t tc = (int64_t)g->BX * 4, padded = (C + tc - 1) / tc * tc;
+    int64_t ops = 0;   // per element, in simple operations
+    for (const Instr& in : g->prog1)
+      if (!in.uniform && (in.kind == IKind::UNARY || in.kind == IKind::BINARY))
+        ops += in.dtype == GR_F32 && (in.op == GR_DIV || in.op == GR_EXP || in.op == GR_LOG || in.op == GR_SQRT || in.op == GR_TANH || in.op == GR_ERF) ? 8 : 1;
+    const bool heavy = ops >= 16 && C * 100 < padded * 80;
+    if (heavy || (g->BX >= 128 && C > tc && C * 100 < padded * 85)) {
+      g->flat = 1;
+      g->BX = 256; g->BY = 1; g->VR = 1;
+      if (c->opt_nontemporal == 1) g->nt &= ~7;
+      for (int vr = 4; vr >= 2; vr >>= 1)
+        if ((R % vr == 0 || R >= 16 * vr) && outer * ((C + 3) / 4) * ((R + vr - 1) / vr) >= 256 * (shifted_rows ? 256 : 1024)) { g->VR = vr; break; }
+    } else if (C % 4 != 0) g->flat = 2;
+  }
+  // (rows shorter than 256 bytes share cache lines with other waves as well: 3145728 x 8 52.6 -> 42.6 us without the hint)
+  if (c->opt_nontemporal == 1 && g->rank >= 2 && R > 1 && C < 64) g->nt &= ~7;
+  g->tail = (g->rank >= 2 && !g->flat && C < 64 && (C & 3) && g->UC == 1 && !g->stage_mask) ? (int)(C & 3) : 0;
 }
 
 // REDUCE mode 0: how many lanes of a workgroup lie across the outputs (the rest along the reduced range) and
@@ -702,9 +730,12 @@ void choose_column_split(gr_ctx* c, GroupPlan* g) {
   g->red_bx = (int)even(bx);
   g->slabs = 1;
   if ((bx >= 64 && (V + bx - 1) / bx >= 512) || LEN <= 32 * (kReduceLanes / g->red_bx)) return;
-  // Otherwise wide blocks (whole rows up to 128 lanes = 2 KiB) and enough chunks for two workgroups per compute unit, of
-  // 16 elements per lane at least.
-  g->red_bx = (int)even(128);
+  // Otherwise enough chunks for two workgroups per compute unit, of 16 elements per lane at least.  Rows of whole
+  // 128-byte lines: blocks of 32 lanes (8192^2 47.5 us; 16 lanes 50.5, 64 52.3, 128 58.9, 256 62.9; 16384 x 4096 50.6, 52.4,
+  // 58.3, 60.6, 73.1); ragged rows: whole rows up to 128 lanes, else 64 (100003 x 257 22.5 us with 65 lanes, 24.0 with 33,
+  // 27.5 with 22; 3977 x 7342 30.1 with 32, 28.6 with 64, 29.4 with 128).  1024 or 2048 workgroups are no better.
+  const int64_t D = g->dims[g->red_kept_rank - 1];
+  g->red_bx = (int)even(D % 32 == 0 ? 32 : (V <= 128 ? 128 : 64));
   const int64_t blocks = (V + g->red_bx - 1) / g->red_bx, by = kReduceLanes / g->red_bx;
   int64_t nsplit = std::min<int64_t>((512 + blocks - 1) / blocks, std::max<int64_t>(1, LEN / (16 * by)));
   if (c->plan_static) {
@@ -1327,7 +1358,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
     bool barrier[MAXD] = {false};
     collapse_dims(g, barrier, ps, 1);
     pop_output_group(g);
-    choose_map_schedule(c, g);
+    choose_map_schedule(c, g, !(r == pl.root && pl.out));
     g->owned = owned;
   }
 

@@ -64,3 +64,28 @@ def test_column_reductions_keep_infinities_and_nan(env):
     for op in ("sum", "max", "min"):
         got, ref = both(env, lambda xp, a: getattr(xp, op)(a, axis=0), a=a)
         assert reduction_check(got, ref)[0].all(), op
+
+
+# columns: ragged and whole groups of four, narrow arrays, one tile and a little more; rows: below, at and beside a patch
+@pytest.mark.parametrize("shape", [(2, 5), (3, 4), (5, 6), (17, 9), (4, 257), (63, 63), (66, 1027), (1031, 1028), (70, 1501), (4100, 1537), (3, 65, 7), (5, 130, 1030),
+                                   (2, 3, 4, 5), (70001, 33)])
+def test_maps_of_ragged_rows(env, shape):
+    a, b = positive(shape, 10), positive(shape[-1:], 11)
+    got, ref = both(env, lambda xp, a, b: xp.sqrt(a * b + 1.0) / (a + b), a=a, b=b)   # operations that round once: the same bits
+    assert np.array_equal(got, ref)
+    if len(shape) == 2 and min(shape) > 4:
+        got, ref = both(env, lambda xp, a: a[2:, 2:] - a[:-2, :-2] * a[1:-1, 1:-1], a=a)
+        assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("shape", [(40, 9), (66, 1027), (1031, 1030)])
+def test_in_place_maps_of_ragged_rows(env, shape):
+    # a value that reads the elements it overwrites is computed once per element
+    gr, ctx, torch = env
+    a = positive(shape, 12)
+    t = torch.from_numpy(a.copy()).cuda()
+    A, B = ctx.array(t), ora.array(a.copy())
+    for X in (A, B):
+        X[:] = X * X + 0.5
+        X[1:-1, 1:] = X[1:-1, 1:] * 3.0
+    assert np.array_equal(A.numpy(), B.numpy()) and np.array_equal(t.cpu().numpy(), B.numpy())
