@@ -572,8 +572,150 @@ void gen_map(Em& e) {
 
 // ---- ROWRED -------------------------------------------------------------------
 
+// Short rows whose elements come from pairs of operands, one that follows the first kept dimension
+// and one that follows the second (points and centres: sum over k of f(P[m,k], C[n,k])), one value
+// per row.  A lane keeps the K elements of its own operand's row in registers and walks the other
+// operand's rows, whose elements are the same for all lanes and come through the scalar unit; the
+// groups of lanes of the general kernel load both elements of every pair instead.  Bound by vector
+// issue.  The elements of a row are combined in the order in which the general kernel's lanes
+// (and the interpreter's) combine them: four in turn per lane, lanes in a butterfly.
+void gen_rowred_pairs(Em& e) {
+  const GroupPlan& g = e.g;
+  const int ld = g.pair_lane, ud = 1 - ld, K = g.pair_k, RT = g.row_threads, UJ = 4;
+  const Phase& ph = g.phases[0];
+  const std::string T = cty(ph.out_dtype);
+  prelude(e);
+  phase_helpers(e, 0, RT);
+  e.o << "#define CM __attribute__((address_space(4)))\n";
+  kernel_head(e, kernel_name(g));
+  // (results of a lane are neighbours in the output: they pass through LDS, so that a wave's stores cover whole runs of it)
+  const bool turn = ud == 1 && g.out_dtype != GR_I64;
+  const char* OT = cty(g.out_dtype);
+  const char* OV = g.out_dtype == GR_F32 ? "f4" : "i4";
+  // workgroups of the same 256 rows, which write neighbouring pieces of the same output rows, share an XCD (8 of them, dealt in turn)
+  e.o << "  const long long NL = " << e.dim(ld) << ", NU = " << e.dim(ud) << ", CH = " << e.S(e.L.extra) << ";\n"
+         "  const unsigned NUB = (unsigned)" << e.S(e.L.extra + 1) << ", set = blockIdx.x / (8 * NUB), in_set = blockIdx.x % (8 * NUB);\n"
+         "  const long long lbeg = (long long)(set * 8 + in_set % 8) * 256, lraw = lbeg + threadIdx.x, ubeg = in_set / 8 * CH, uend = ubeg + CH < NU ? ubeg + CH : NU;\n"
+         "  if (lbeg >= NL || ubeg >= NU) return;\n"
+         "  const bool ok = lraw < NL;\n"
+         "  const long long lane = ok ? lraw : NL - 1;\n";
+  if (turn) e.o << "  __shared__ __attribute__((aligned(16))) " << OT << " sm[256][" << kPairBlock + 4 << "];\n";   // (this pitch: four-element writes and reads without bank conflicts)
+  std::vector<char> in_value(g.prog.size(), 0);
+  {
+    std::vector<int> work{ph.value};
+    while (!work.empty()) {
+      const int i = work.back();
+      work.pop_back();
+      if (i < 0 || in_value[i]) continue;
+      in_value[i] = 1;
+      work.push_back(g.prog[i].a);
+      work.push_back(g.prog[i].b);
+    }
+  }
+  auto kexpr = [&](const Instr& in, int k) -> std::string {
+    const AccessGroup& ag = g.groups[in.group];
+    if (ag.structural_zero[2]) return "0";
+    if (access_class(ag, 2) == '1') return std::to_string(k + in.delta[2]);
+    return std::to_string(k + in.delta[2]) + " * " + e.coef(in.group, 2);
+  };
+  // the lane's own operand elements
+  for (size_t i = 0; i < g.prog.size(); ++i) {
+    const Instr& in = g.prog[i];
+    if (in.kind != IKind::LOAD || !in_value[i]) continue;
+    const AccessGroup& ag = g.groups[in.group];
+    if (ag.structural_zero[ld]) continue;
+    const std::string id = std::to_string(i);
+    e.o << "  const GM " << cty(in.dtype) << "* const pl" << id << " = (const GM " << cty(in.dtype) << "*)" << e.slot(e.L.ptr[in.group]) << " + " << e.S(e.L.base[in.group])
+        << " + (lane + " << in.delta[ld] << ") * " << e.coef(in.group, ld) << ";\n";
+    if (ag.structural_zero[2]) { e.o << "  const " << cty(in.dtype) << " x" << id << "_0 = pl" << id << "[0];\n"; continue; }
+    int k = 0;
+    if (access_class(ag, 2) == '1')
+      for (; k + 4 <= K; k += 4) {
+        e.o << "  const " << vty4(in.dtype) << " xv" << id << "_" << k << " = *(const GM " << vty4(in.dtype) << "*)(pl" << id << " + " << kexpr(in, k) << ");\n";
+        for (int j = 0; j < 4; ++j) e.o << "  const " << cty(in.dtype) << " x" << id << "_" << k + j << " = xv" << id << "_" << k << "[" << j << "];\n";
+      }
+    for (; k < K; ++k) e.o << "  const " << cty(in.dtype) << " x" << id << "_" << k << " = pl" << id << "[" << kexpr(in, k) << "];\n";
+  }
+  e.o << "  GM " << cty(g.out_dtype) << "* const out = (GM " << cty(g.out_dtype) << "*)" << e.slot(e.L.out) << ";\n";
+  e.o << "  for (long long u0 = ubeg; u0 < uend; u0 += " << UJ << ") {\n";
+  for (int j = 0; j < UJ; ++j) {
+    e.o << "    const long long u_" << j << " = u0 + " << j << " < NU ? u0 + " << j << " : NU - 1;\n    (void)u_" << j << ";\n";
+    for (size_t i = 0; i < g.prog.size(); ++i) {
+      const Instr& in = g.prog[i];
+      if (in.kind != IKind::LOAD || !in_value[i] || !g.groups[in.group].structural_zero[ld]) continue;
+      e.o << "    const CM " << cty(in.dtype) << "* const pu" << i << "_" << j << " = (const CM " << cty(in.dtype) << "*)(" << e.slot(e.L.ptr[in.group]) << " + 4 * (" << e.S(e.L.base[in.group]);
+      if (!g.groups[in.group].structural_zero[ud]) e.o << " + (u_" << j << " + " << in.delta[ud] << ") * " << e.coef(in.group, ud);
+      e.o << "));\n";
+    }
+  }
+  // leaves of the butterfly in the order in which lane 0 meets them, the rows of UJ results side by side
+  int next = 0;
+  std::function<int(int, int)> tree = [&](int off, int stride) -> int {
+    const int me = next++;
+    if (stride == RT) {
+      for (int j = 0; j < UJ; ++j) {
+        const std::string acc = "t" + std::to_string(me) + "_" + std::to_string(j);
+        e.o << "    " << T << " " << acc << " = " << Em::identity(ph) << ";\n";
+        for (int q = 0; q < 4 && 4 * off + q < K; ++q) {
+          const int k = 4 * off + q;
+          e.o << "    {\n";
+          emit_scalar_program(e, g.prog, {ph.value},
+                              [&](const Instr& in, int id) -> std::string {
+                                const AccessGroup& ag = g.groups[in.group];
+                                if (!ag.structural_zero[ld]) return "x" + std::to_string(id) + "_" + std::to_string(ag.structural_zero[2] ? 0 : k);
+                                return "pu" + std::to_string(id) + "_" + std::to_string(j) + "[" + kexpr(in, k) + "]";
+                              },
+                              "0.0f", "v", "      ");
+          e.o << "      " << acc << " = " << Em::combine(ph, acc, "v" + std::to_string(ph.value)) << ";\n    }\n";
+        }
+      }
+      return me;
+    }
+    const int a = tree(off, 2 * stride), b = tree(off + stride, 2 * stride);
+    for (int j = 0; j < UJ; ++j)
+      e.o << "    const " << T << " t" << me << "_" << j << " = gr_comb0(t" << a << "_" << j << ", t" << b << "_" << j << ");\n";
+    return me;
+  };
+  const int top = tree(0, 1);
+  const char* const at[2] = {ld == 0 ? "lane" : "u_", ld == 0 ? "u_" : "lane"};
+  for (int j = 0; j < UJ; ++j) {
+    const std::string sj = std::to_string(j);
+    e.o << "    " << cty(g.out_dtype) << " o" << j << ";\n    {\n      const " << T << " red0 = t" << top << "_" << j << "; (void)red0;\n";
+    emit_scalar_program(e, g.prog, {g.results[0]},
+                        [&](const Instr& in, int) -> std::string {
+                          const AccessGroup& ag = g.groups[in.group];
+                          std::string p = "((const GM " + std::string(cty(in.dtype)) + "*)" + e.slot(e.L.ptr[in.group]) + " + " + e.S(e.L.base[in.group]);
+                          for (int d = 0; d < 2; ++d)
+                            if (!ag.structural_zero[d]) p += " + (" + std::string(at[d]) + (d == ud ? sj : "") + " + " + std::to_string(in.delta[d]) + ") * " + e.coef(in.group, d);
+                          return p + ")[0]";
+                        },
+                        "0.0f", "w", "      ");
+    e.o << "      o" << j << " = w" << g.results[0] << ";\n    }\n";
+  }
+  if (turn) {
+    e.o << "    { " << OV << " ov; ov[0] = o0; ov[1] = o1; ov[2] = o2; ov[3] = o3; *(" << OV << "*)&sm[threadIdx.x][u0 - ubeg] = ov; }\n  }\n"
+           "  __syncthreads();\n"
+           "  const unsigned nu = (unsigned)(uend - ubeg), lpr = (nu + 3) / 4, step = 256 / lpr, c4 = threadIdx.x % lpr * 4;\n"
+           "  if (threadIdx.x >= step * lpr) return;\n"
+           "  for (unsigned r = threadIdx.x / lpr; r < 256 && lbeg + r < NL; r += step) {\n"
+           "    const " << OV << " ov = *(const " << OV << "*)&sm[r][c4];\n"
+           "    GM " << OT << "* const po = out + (lbeg + r) * NU + ubeg + c4;\n"
+           "    if (c4 + 4 <= nu) *(GM " << OV << "u*)po = ov;\n"
+           "    else { po[0] = ov[0]; if (c4 + 1 < nu) po[1] = ov[1]; if (c4 + 2 < nu) po[2] = ov[2]; }\n"
+           "  }\n}\n";
+    return;
+  }
+  e.o << "    if (ok) {\n";
+  for (int j = 0; j < UJ; ++j) {
+    if (ud == 1) e.o << "      if (u0 + " << j << " < uend) out[lane * NU + u0 + " << j << "] = o" << j << ";\n";
+    else e.o << "      if (u0 + " << j << " < uend) out[(u0 + " << j << ") * NL + lane] = o" << j << ";\n";
+  }
+  e.o << "    }\n  }\n}\n";
+}
+
 void gen_rowred(Em& e) {
   const GroupPlan& g = e.g;
+  if (g.pair_k) { gen_rowred_pairs(e); return; }
   const int rank = g.rank, cd = rank - 1;
   const int RT = g.row_threads, NP = g.NP, RB = 256 / RT;
   const int nph = (int)g.phases.size();

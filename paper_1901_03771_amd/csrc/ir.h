@@ -186,6 +186,8 @@ struct GroupPlan {
   int NP = 1;                            // ROWRED: vec4 positions per lane
   int row_threads = 64;                  // ROWRED: lanes cooperating on one row (64 or 256)
   int row_iters = 1;                     // ROWRED: rows a lane group takes in one launch (short rows, one value per row)
+  int pair_k = 0;                        // ROWRED: row length, if a row combines an operand of each of the two kept dimensions and a lane
+  int pair_lane = 0;                     // holds the operand row of kept dimension pair_lane
   bool xcd_remap = false;
   int cphase = 0;     // map: lanes own columns 4k - cphase .. 4k - cphase + 3, so that their vector stores are 16-byte aligned in the output
   int stage_mask = 0;                    // MAP: access groups (bit per group) read through a transposing LDS tile

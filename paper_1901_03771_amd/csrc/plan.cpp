@@ -473,7 +473,7 @@ void make_signature(GroupPlan* g) {
   std::string s;
   s.reserve(256 + 32 * (g->prog.size() + g->prog1.size()));
   for (int64_t v : {(int64_t)g->kind, (int64_t)g->rank, (int64_t)g->out_dtype, (int64_t)g->out_per_row, (int64_t)g->BX, (int64_t)g->BY,
-                    (int64_t)g->VR + (g->kind == GroupKind::GEMM && g->VR == 2 && g->slabs > 1 ? 1024 : 0) /* (the direct-to-LDS product kernels compile the split of K in or out) */, (int64_t)g->UC, (int64_t)g->NP, (int64_t)g->row_threads + 1024 * (int64_t)g->row_iters, (int64_t)g->xcd_remap + 2 * (int64_t)g->stage_mask + (((int64_t)g->tail) << 40) + (((int64_t)g->diag) << 44) + (((int64_t)g->cphase) << 48) + (((int64_t)g->flat) << 52), (int64_t)g->red_mode + 16 * (int64_t)g->red_vec,
+                    (int64_t)g->VR + (g->kind == GroupKind::GEMM && g->VR == 2 && g->slabs > 1 ? 1024 : 0) /* (the direct-to-LDS product kernels compile the split of K in or out) */, (int64_t)g->UC, (int64_t)g->NP, (int64_t)g->row_threads + 1024 * (int64_t)g->row_iters + (((int64_t)g->pair_k) << 32) + (((int64_t)g->pair_lane) << 40) /* (a pair kernel compiles its row length in) */, (int64_t)g->xcd_remap + 2 * (int64_t)g->stage_mask + (((int64_t)g->tail) << 40) + (((int64_t)g->diag) << 44) + (((int64_t)g->cphase) << 48) + (((int64_t)g->flat) << 52), (int64_t)g->red_mode + 16 * (int64_t)g->red_vec,
                     (int64_t)g->red_kept_rank, (int64_t)g->gemv_mode, (int64_t)g->LPR, (int64_t)g->KV, (int64_t)g->mat_group,
                     (int64_t)g->vec_group, (int64_t)g->nt, (int64_t)g->unroll, (int64_t)g->scan_mode + 16 * (int64_t)g->scan_vec + (g->scan_mode >= 2 ? 256 * g->scan_chunk : 0) /* (a one-pass scan's tile size is compiled in) */, (int64_t)g->out_unit, (int64_t)g->groups.size()})
     put(s, v);
@@ -711,6 +711,38 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
   // (rows shorter than 256 bytes share cache lines with other waves as well: 3145728 x 8 52.6 -> 42.6 us without the hint)
   if (c->opt_nontemporal == 1 && g->rank >= 2 && R > 1 && C < 64) g->nt &= ~7;
   g->tail = (g->rank >= 2 && !g->flat && C < 64 && (C & 3) && g->UC == 1 && !g->stage_mask) ? (int)(C & 3) : 0;
+}
+
+// Rows of at most 64 elements over two kept dimensions, each element a function of one operand that follows the first
+// of them and one that follows the second: a lane per row of the longer one (see gen_rowred_pairs).
+// (Squared distances, general kernel against this one, us: 262144 points to 32 centres in 16 dimensions 44.6 / 15.0, vector issue
+// alone 11; 811856 x 7 x 38 284 / 32; 178688 x 27 x 47 205 / 24; 65536 x 64 x 64 79 / 24; 100000 x 8 x 8 5.3 / 5.1.  The row length is
+// compiled in: beyond 64 elements the lane groups read whole lines of both operands and stay.)
+void choose_pair_rows(GroupPlan* g) {
+  if (!g->out_per_row || g->phases.size() != 1 || g->rank != 3 || g->results.empty()) return;
+  const int64_t K = g->dims[2];
+  if (K < 2 || K > 64 || g->NP != 1 || std::min(g->dims[0], g->dims[1]) < 4 || std::max(g->dims[0], g->dims[1]) < 256) return;
+  std::vector<char> seen(g->prog.size(), 0);
+  std::vector<int> work{g->phases[0].value};
+  bool follows[2] = {false, false};
+  while (!work.empty()) {
+    const int i = work.back();
+    work.pop_back();
+    if (i < 0 || seen[i]) continue;
+    seen[i] = 1;
+    const Instr& in = g->prog[i];
+    if (in.dtype == GR_I64 || in.kind == IKind::RED) return;
+    if (in.kind == IKind::LOAD) {
+      const AccessGroup& ag = g->groups[in.group];
+      if (!ag.structural_zero[0] && !ag.structural_zero[1]) return;
+      if (!ag.structural_zero[2]) for (int d = 0; d < 2; ++d) if (!ag.structural_zero[d]) follows[d] = true;
+    }
+    work.push_back(in.a);
+    work.push_back(in.b);
+  }
+  if (!follows[0] || !follows[1] || seen.size() > 24) return;
+  g->pair_k = (int)K;
+  g->pair_lane = g->dims[0] >= g->dims[1] ? 0 : 1;
 }
 
 // REDUCE mode 0: how many lanes of a workgroup lie across the outputs (the rest along the reduced range) and
@@ -1320,6 +1352,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
       int64_t rows = 1;
       for (int k = 0; k + 1 < g->rank; ++k) rows *= g->dims[k];
       g->row_iters = (g->out_per_row && C <= 64 && rows >= (int64_t)1 << 18 && c->opt_rowred_rows != 1) ? 4 : 1;  // (measured: 2 and 8 rows are no better, 256-element rows lose)
+      if (c->opt_rowred_threads == 0 && c->opt_rowred_rows == 0) choose_pair_rows(g);
       if (c->opt_rowred_rows > 1 && g->out_per_row && g->row_threads <= 64) g->row_iters = (int)std::min<int64_t>(c->opt_rowred_rows, 8);
     }
   } else {

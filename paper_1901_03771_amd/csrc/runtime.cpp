@@ -570,6 +570,15 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
       int64_t rows = 1;
       for (int k2 = 0; k2 + 1 < g.rank; ++k2) rows *= g.dims[k2];
       if (rows == 0) return GR_OK;
+      if (g.pair_k) {
+        // 256 lanes along one kept dimension by CH (a multiple of four, at most kPairBlock) rows of the other, in even
+        // blocks: about 1024 workgroups where the shape allows
+        const int64_t nl = (g.dims[g.pair_lane] + 255) / 256, quads = (g.dims[1 - g.pair_lane] + 3) / 4;
+        const int64_t want = std::min<int64_t>(quads, std::max<int64_t>((quads * 4 + kPairBlock - 1) / kPairBlock, 1024 / nl)), ch = (quads + want - 1) / want, nub = (quads + ch - 1) / ch;
+        s[L.extra] = (uint64_t)(4 * ch);
+        s[L.extra + 1] = (uint64_t)nub;
+        return launch(c, k->fn, k->name, (nl + 7) / 8 * 8 * nub, s);
+      }
       int rb = 256 / g.row_threads * g.row_iters;
       return launch(c, k->fn, k->name, (rows + rb - 1) / rb, s);
     }

@@ -89,3 +89,31 @@ def test_in_place_maps_of_ragged_rows(env, shape):
         X[:] = X * X + 0.5
         X[1:-1, 1:] = X[1:-1, 1:] * 3.0
     assert np.array_equal(A.numpy(), B.numpy()) and np.array_equal(t.cpu().numpy(), B.numpy())
+
+
+# pairs of rows: a lane per row of the longer operand; row lengths around the groups of four and the lane groups of the
+# general kernel (whose order of additions is kept), few and many rows of the other operand, either operand the longer one
+@pytest.mark.parametrize("n,c,d", [(256, 4, 2), (257, 5, 4), (300, 7, 5), (1000, 19, 16), (1001, 33, 17), (4099, 6, 31), (511, 64, 33), (2049, 9, 63), (700, 3, 64),
+                                   (5, 1030, 12), (260, 260, 54)])
+def test_rows_over_pairs(env, n, c, d):
+    gr, ctx, torch = env
+    a, b, w = positive((n, d), 13), positive((c, d), 14), positive((n, c), 15)
+
+    def distances(xp, a, b, w):
+        diff = a - b
+        return xp.sqrt(xp.sum(diff * diff, axis=2)) + w
+
+    arrays = dict(a=a[:, None, :], b=b[None, :, :], w=w)
+    got, ref = both(env, distances, **arrays)
+    assert reduction_check(got, ref)[0].all()
+    other = gr.Context()
+    other.set_option("interp", 2)      # the byte-code interpreter: the same bits
+    keep = {k: torch.from_numpy(np.ascontiguousarray(v)).cuda() for k, v in arrays.items()}
+    assert np.array_equal(distances(gr, **{k: other.array(t) for k, t in keep.items()}).numpy(), got)
+    other.sync()
+    other.close()
+    got, ref = both(env, lambda xp, a, b: xp.max(xp.minimum(a, b), axis=2), a=a[:, None, :], b=b[None, :, :])
+    assert np.array_equal(got, ref)
+    i, j = (np.random.default_rng(16 + k).integers(-2**31, 2**31 - 1, s, dtype=np.int64).astype(np.int32) for k, s in enumerate(((n, 1, d), (1, c, d))))
+    got, ref = both(env, lambda xp, i, j: xp.sum(i * j, axis=2), i=i, j=j)
+    assert np.array_equal(got, ref)
