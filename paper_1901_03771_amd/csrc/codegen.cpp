@@ -1305,6 +1305,7 @@ void gen_scan(Em& e) {
          "static __device__ __forceinline__ long long gr_up(long long v, int d) {\n"
          "  int lo = __shfl_up((int)(v & 0xffffffffll), d, 64), hi = __shfl_up((int)(v >> 32), d, 64);\n"
          "  return ((long long)hi << 32) | (unsigned int)lo;\n}\n";
+  if (ph.out_dtype == GR_I64) e.o << "typedef long long l2 __attribute__((ext_vector_type(2)));\ntypedef l2 l2u __attribute__((aligned(8)));\n";
   const std::string ident = Em::identity(ph);
   auto conv = [&](const std::string& x) { return ph.out_dtype == GR_I64 && ph.in_dtype == GR_I32 ? "(long long)" + x : x; };
   auto load_at = [&](const std::string& col) {
@@ -1322,7 +1323,7 @@ void gen_scan(Em& e) {
   auto head = [&](int per_block_line) {
     // (the chunk-count slot of a one-pass scan carries the poll limit in its upper half)
     // (one-pass scans: the chunk slot carries, in its upper half, the tag that marks a cell as published by this launch)
-    if (g.scan_mode >= 2) e.o << "  const long long LINES = " << e.S(e.L.extra) << ", CH = " << e.S(e.L.extra + 1) << " & 0xffffffffll, NCHUNK = " << e.S(e.L.extra + 3) << " & 0xffffffffll;\n"
+    if (g.scan_mode == 2 || g.scan_mode == 3) e.o << "  const long long LINES = " << e.S(e.L.extra) << ", CH = " << e.S(e.L.extra + 1) << " & 0xffffffffll, NCHUNK = " << e.S(e.L.extra + 3) << " & 0xffffffffll;\n"
                                  "  const unsigned EPOCH = (unsigned)(" << e.slot(e.L.extra + 1) << " >> 32);\n";
     else e.o << "  const long long LINES = " << e.S(e.L.extra) << ", CH = " << e.S(e.L.extra + 1) << ", NCHUNK = " << e.S(e.L.extra + 3) << " & 0xffffffffll;\n";
     e.o << "  const long long L = " << e.dim(sd) << ";\n";
@@ -1337,6 +1338,7 @@ void gen_scan(Em& e) {
              "  const bool colok = cb * " << W << " + lx * 4 < D;\n"
              "  const long long line = (chain / NCB) * D + (colok ? cb * " << W << " + lx * 4 : 0);\n";
     }
+    else if (per_block_line == 3) e.o << "  const long long line = (long long)blockIdx.x * " << 256 / g.BX << " + threadIdx.x / " << g.BX << ";\n  if (line >= LINES) return;\n";
     else if (per_block_line) e.o << "  const long long line = blockIdx.x / NCHUNK, chunk = blockIdx.x % NCHUNK;\n";
     else if (g.scan_vec) e.o << "  const long long gt = (long long)blockIdx.x * 256 + threadIdx.x;\n  if (gt >= (LINES / 4) * NCHUNK) return;\n"
                 "  const long long line = 4 * (gt % (LINES / 4)), chunk = gt / (LINES / 4);\n  (void)chunk;\n";  // four lines per thread
@@ -1437,7 +1439,7 @@ void gen_scan(Em& e) {
       }
       if (store) {
         if (ph.out_dtype == GR_I64)
-          e.o << ind << "po[(" << jx << ") * ostep] = acc0; po[(" << jx << ") * ostep + 1] = acc1; po[(" << jx << ") * ostep + 2] = acc2; po[(" << jx << ") * ostep + 3] = acc3;\n";
+          e.o << ind << "{ l2u ov; ov[0] = acc0; ov[1] = acc1; *(GM l2u*)(po + (" << jx << ") * ostep) = ov; ov[0] = acc2; ov[1] = acc3; *(GM l2u*)(po + (" << jx << ") * ostep + 2) = ov; }\n";
         else {
           const char* vt = ph.out_dtype == GR_F32 ? "f4u" : "i4u";
           e.o << ind << "{ " << vt << " ov; ov[0] = acc0; ov[1] = acc1; ov[2] = acc2; ov[3] = acc3; *(GM " << vt << "*)(po + (" << jx << ") * ostep) = ov; }\n";
@@ -1771,6 +1773,94 @@ void gen_scan(Em& e) {
     return;
   }
 
+  if (g.scan_mode == 4) {
+    // ---- mode 4: short contiguous lines, LG = 16 or 64 lanes each, several lines to a workgroup and no barrier.  A line is
+    // NP positions of four elements per lane, all loaded at once; the last position, which may stick out of the line, is
+    // loaded from the line's last four elements and shifted into place.  Each position is scanned across its lanes with
+    // row shifts (and row broadcasts for 64 lanes); the positions' totals are combined in a tree.  Bound by HBM.
+    const int LG = g.BX, NP = g.NP;
+    const bool wide = ph.out_dtype == GR_I64;
+    const std::string bits = ph.out_dtype == GR_F32 ? "__float_as_uint" : "(unsigned)";
+    const std::string unbits = ph.out_dtype == GR_F32 ? "__uint_as_float" : "(int)";
+    if (wide)
+      e.o << "#define GR_DPP(idn, v, ctrl, rmask) ((long long)(((unsigned long long)(unsigned)__builtin_amdgcn_update_dpp((int)((idn) >> 32), (int)((v) >> 32), ctrl, rmask, 0xf, false) << 32) | "
+             "(unsigned)__builtin_amdgcn_update_dpp((int)(idn), (int)(v), ctrl, rmask, 0xf, false)))\n";
+    else e.o << "#define GR_DPP(idn, v, ctrl, rmask) " << unbits << "((unsigned)__builtin_amdgcn_update_dpp((int)" << bits << "(idn), (int)" << bits << "(v), ctrl, rmask, 0xf, false))\n";
+    e.o << "static __device__ __forceinline__ " << TA << " gr_gscan(" << TA << " x) {\n  const " << TA << " idn = " << ident << ";\n"
+           "  x = gr_comb0(GR_DPP(idn, x, 0x111, 0xf), x);\n  x = gr_comb0(GR_DPP(idn, x, 0x112, 0xf), x);\n"
+           "  x = gr_comb0(GR_DPP(idn, x, 0x114, 0xf), x);\n  x = gr_comb0(GR_DPP(idn, x, 0x118, 0xf), x);\n";
+    if (LG == 64) e.o << "  x = gr_comb0(GR_DPP(idn, x, 0x142, 0xa), x);\n  x = gr_comb0(GR_DPP(idn, x, 0x143, 0xc), x);\n";
+    e.o << "  return x;\n}\n";
+    if (wide)
+      e.o << "static __device__ __forceinline__ long long gr_bc(long long v, int l) {\n"
+             "  const int lo = __shfl((int)(v & 0xffffffffll), l, 64), hi = __shfl((int)(v >> 32), l, 64);\n  return ((long long)hi << 32) | (unsigned int)lo;\n}\n";
+    else e.o << "static __device__ __forceinline__ " << TA << " gr_bc(" << TA << " v, int l) { return __shfl(v, l, 64); }\n";
+    kernel_head(e, "gr_scan");
+    head(3);
+    e.o << "  const int lane = threadIdx.x & " << LG - 1 << ", last = (threadIdx.x & 63) | " << LG - 1 << ", c0 = lane * 4, n = (int)L;\n";
+    const std::string clast = "(c0 + " + std::to_string((NP - 1) * LG * 4) + ")";
+    e.o << "  const int cl = " << clast << " + 4 <= n ? " << clast << " : n - 4, sh = " << clast << " - cl;\n";
+    for (int p = 0; p < NP; ++p) {
+      const std::string sp = std::to_string(p), at = p + 1 < NP ? "c0 + " + std::to_string(p * LG * 4) : std::string("cl");
+      for (size_t i = 0; i < g.prog.size(); ++i) {
+        const Instr& in = g.prog[i];
+        if (in.kind != IKind::LOAD) continue;
+        const AccessGroup& ag = g.groups[in.group];
+        std::ostringstream base;
+        base << "p" << in.group;
+        for (int k = 0; k < sd; ++k) if (!ag.structural_zero[k] && in.delta[k]) base << " + " << in.delta[k] << " * " << e.coef(in.group, k);
+        if (ag.structural_zero[sd]) { if (p == 0) e.o << "  const " << cty(in.dtype) << " u" << i << " = (" << base.str() << ")[0];\n"; }
+        else e.o << "  const " << vty4(in.dtype) << " w" << i << "_" << sp << " = " << e.ld(in.group, vty4(in.dtype), base.str() + " + " + at + " + " + std::to_string(in.delta[sd])) << ";\n";
+      }
+    }
+    e.o << "  __builtin_amdgcn_sched_barrier(0);\n";
+    for (int p = 0; p < NP; ++p) {
+      const std::string sp = std::to_string(p);
+      e.o << "  " << TA << " v" << sp << "[4];\n";
+      for (int j = 0; j < 4; ++j) {
+        const std::string pre = "t" + std::to_string(j) + "_";
+        e.o << "  {\n";
+        emit_scalar_program(e, g.prog, {ph.value},
+                            [&](const Instr& in, int id) { return g.groups[in.group].structural_zero[sd] ? "u" + std::to_string(id) : "w" + std::to_string(id) + "_" + sp + "[" + std::to_string(j) + "]"; },
+                            "0.0f", pre, "    ");
+        e.o << "    v" << sp << "[" << j << "] = " << conv(pre + std::to_string(ph.value)) << ";\n  }\n";
+      }
+      if (p + 1 == NP) {
+        // into place: elements sh .. 3 move to the front, the rest lies behind the line's end
+        e.o << "  if (sh) {\n    const " << TA << " a1 = v" << sp << "[1], a2 = v" << sp << "[2], a3 = v" << sp << "[3];\n"
+               "    v" << sp << "[0] = sh == 1 ? a1 : sh == 2 ? a2 : sh == 3 ? a3 : " << ident << ";\n"
+               "    v" << sp << "[1] = sh == 1 ? a2 : sh == 2 ? a3 : " << ident << ";\n"
+               "    v" << sp << "[2] = sh == 1 ? a3 : " << ident << ";\n    v" << sp << "[3] = " << ident << ";\n  }\n";
+      }
+      e.o << "  for (int j = 1; j < 4; ++j) v" << sp << "[j] = gr_comb0(v" << sp << "[j - 1], v" << sp << "[j]);\n"
+             "  const " << TA << " x" << sp << " = gr_gscan(v" << sp << "[3]);\n";
+      if (p + 1 < NP) e.o << "  const " << TA << " s" << sp << "_0 = gr_bc(x" << sp << ", last);\n";
+    }
+    // inclusive scan of the positions' totals, log2(NP) combines deep
+    int level = 0;
+    for (int d = 1; d < NP - 1; d *= 2, ++level)
+      for (int p = 0; p + 1 < NP; ++p) {
+        const std::string lv = "_" + std::to_string(level);
+        e.o << "  const " << TA << " s" << p << "_" << level + 1 << " = " << (p >= d ? "gr_comb0(s" + std::to_string(p - d) + lv + ", s" + std::to_string(p) + lv + ")" : "s" + std::to_string(p) + lv) << ";\n";
+      }
+    for (int p = 0; p < NP; ++p) {
+      const std::string sp = std::to_string(p), c = "c0 + " + std::to_string(p * LG * 4);
+      e.o << "  {\n    const " << TA << " idn = " << ident << ", ex = GR_DPP(idn, x" << sp << ", " << (LG == 64 ? "0x138" : "0x111") << ", 0xf), b = "
+          << (p ? "lane ? gr_comb0(s" + std::to_string(p - 1) + "_" + std::to_string(level) + ", ex) : s" + std::to_string(p - 1) + "_" + std::to_string(level) : std::string("ex")) << ";\n"
+             "    if (" << (p == 0 ? "lane" : "true") << ") for (int j = 0; j < 4; ++j) v" << sp << "[j] = gr_comb0(b, v" << sp << "[j]);\n    const int c = " << c << ";\n    ";
+      if (p + 1 == NP) e.o << "if (c + 4 <= n) ";
+      if (wide) e.o << "{ l2u ov; ov[0] = v" << sp << "[0]; ov[1] = v" << sp << "[1]; *(GM l2u*)(po + c) = ov; ov[0] = v" << sp << "[2]; ov[1] = v" << sp << "[3]; *(GM l2u*)(po + c + 2) = ov; }\n";
+      else {
+        const std::string vt = ph.out_dtype == GR_F32 ? "f4u" : "i4u";
+        e.o << "{ " << vt << " ov; for (int j = 0; j < 4; ++j) ov[j] = v" << sp << "[j]; " << ((g.nt & 8) ? "__builtin_nontemporal_store(ov, (GM " + vt + "*)(po + c))" : "*(GM " + vt + "*)(po + c) = ov") << "; }\n";
+      }
+      if (p + 1 == NP) e.o << "    else { if (c < n) po[c] = v" << sp << "[0]; if (c + 1 < n) po[c + 1] = v" << sp << "[1]; if (c + 2 < n) po[c + 2] = v" << sp << "[2]; }\n";
+      e.o << "  }\n";
+    }
+    e.o << "}\n";
+    return;
+  }
+
   // ---- mode 0, kernel 1 of 3: chunk totals (only launched when a line has several chunks)
   kernel_head(e, "gr_scan_sums");
   head(true);
@@ -1804,7 +1894,8 @@ void gen_scan(Em& e) {
   e.o << "    " << TA << " base = carry;\n    for (int q = 0; q < wave; ++q) base = gr_comb0(base, sm[q]);\n";
   e.o << "    { " << TA << " ex = gr_up(x, 1); if (lane != 0) base = gr_comb0(base, ex); }\n";
   if (ph.out_dtype == GR_I64)
-    e.o << "    for (int j = 0; j < 4; ++j) if (c + j < cend) po[c + j] = gr_comb0(base, v[j]);\n";
+    e.o << "    if (c + 4 <= cend) { l2u ov; for (int j = 0; j < 2; ++j) ov[j] = gr_comb0(base, v[j]); *(GM l2u*)(po + c) = ov; for (int j = 0; j < 2; ++j) ov[j] = gr_comb0(base, v[j + 2]); *(GM l2u*)(po + c + 2) = ov; }\n"
+           "    else { for (int j = 0; j < 4; ++j) if (c + j < cend) po[c + j] = gr_comb0(base, v[j]); }\n";
   else {
     const char* vt = ph.out_dtype == GR_F32 ? "f4u" : "i4u";
     e.o << "    if (c + 4 <= cend) { " << vt << " ov; for (int j = 0; j < 4; ++j) ov[j] = gr_comb0(base, v[j]); "

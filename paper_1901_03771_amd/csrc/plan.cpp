@@ -975,6 +975,20 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
       g->scan_chunk = chunk;
       g->scan_nchunk = (int)nch;
     }
+    // Lines of up to 1024 elements: a lane group per line (16 lanes up to 256 elements, a wave beyond), see mode 4 of gen_scan.  A
+    // workgroup per line leaves most of its lanes idle and pays a barrier and two LDS exchanges per line (2^25 values,
+    // workgroup per line against lane groups, us: lines of 64 422 / 45, 144 200 / 47, 320 101 / 45, 703 69 / 49, 1024 47.6 / 45.0;
+    // i32 to i64: lines of 100 329 / 80, 703 120 / 84).  Longer lines fill the workgroup (2048: 47 us).
+    if (g->scan_mode == 0 && lines > 1 && L >= 4 && L <= 1024 && p.in_dtype != GR_I64 && n_loads <= 4) {
+      bool narrow = true;
+      for (const Instr& in : g->prog) if (in.dtype == GR_I64) narrow = false;
+      if (narrow) {
+        g->scan_mode = 4;
+        g->BX = L <= 256 ? 16 : 64;
+        g->NP = (int)((L + g->BX * 4 - 1) / (g->BX * 4));
+        g->scan_chunk = 0;
+      }
+    }
     g->red_out = g->scan_vec ? lines * 4 : lines;
     g->red_len = L;
   } else if (dot && dot->ndim == 2) {
@@ -1589,7 +1603,7 @@ std::string describe_plan(const Plan& plan) {
       s << "]]";
     }
     if (g.kind == GroupKind::ROWRED) s << " phases=" << g.phases.size() << " row_threads=" << g.row_threads << " NP=" << g.NP << (g.row_iters > 1 ? " rows_per_group=" + std::to_string(g.row_iters) : std::string());
-    if (g.kind == GroupKind::SCAN) s << " mode=" << (g.scan_mode == 3 ? "one-pass-line-tiles" : (g.scan_mode == 2 ? "one-pass-tiles" : (g.scan_mode ? "thread-per-line" : "lanes-along-axis"))) << " lines=" << g.red_out << " length=" << g.red_len << " chunks=" << g.scan_nchunk;
+    if (g.kind == GroupKind::SCAN) s << " mode=" << (g.scan_mode == 4 ? "lines-in-lane-groups" : g.scan_mode == 3 ? "one-pass-line-tiles" : (g.scan_mode == 2 ? "one-pass-tiles" : (g.scan_mode ? "thread-per-line" : "lanes-along-axis"))) << " lines=" << g.red_out << " length=" << g.red_len << " chunks=" << g.scan_nchunk;
     if (g.kind == GroupKind::MAP) s << " tile=" << g.BY * g.VR << "x" << g.BX * 4 * g.UC << " patch=" << g.VR << "x" << g.UC * 4;
     s << '\n';
   }

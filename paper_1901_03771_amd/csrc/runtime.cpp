@@ -231,7 +231,7 @@ static void disk_store(const std::string& path, const std::string& key, const st
 static void kernel_entry_points(const GroupPlan& g, std::string* name, bool* combine, int* scan) {
   *name = kernel_name(g);
   *combine = (g.kind == GroupKind::GEMV && g.gemv_mode >= 1) || g.kind == GroupKind::REDUCE || g.kind == GroupKind::GEMM;
-  *scan = g.kind == GroupKind::SCAN ? (g.scan_mode >= 2 ? 2 : 1) : 0;
+  *scan = g.kind == GroupKind::SCAN ? (g.scan_mode == 4 ? 0 : g.scan_mode >= 2 ? 2 : 1) : 0;
 }
 
 // Loads a code object and publishes the kernel in the in-memory cache.
@@ -603,6 +603,7 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
       for (int k2 = 0; k2 < g.rank; ++k2) s[L.ocoef + k2] = (uint64_t)g.out_coef[k2];
       s[L.extra] = (uint64_t)g.red_out;
       s[L.extra + 1] = (uint64_t)g.scan_chunk;
+      if (g.scan_mode == 4) return launch(c, k->fn, k->name, (g.red_out + 256 / g.BX - 1) / (256 / g.BX), s);
       s[L.extra + 3] = (uint64_t)g.scan_nchunk | (g.scan_mode >= 2 ? (uint64_t)c->opt_scan_polls << 32 : 0);
       if (g.scan_mode >= 2) {
         // one pass: the tiles publish their totals in cells (cleared first unless they carry launch numbers)

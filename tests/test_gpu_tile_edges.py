@@ -117,3 +117,23 @@ def test_rows_over_pairs(env, n, c, d):
     i, j = (np.random.default_rng(16 + k).integers(-2**31, 2**31 - 1, s, dtype=np.int64).astype(np.int32) for k, s in enumerate(((n, 1, d), (1, c, d))))
     got, ref = both(env, lambda xp, i, j: xp.sum(i * j, axis=2), i=i, j=j)
     assert np.array_equal(got, ref)
+
+
+# lines of a few lane groups: positions that stick out of the line by every count, one to four positions, both widths of
+# group; lines that do not fill the last workgroup
+@pytest.mark.parametrize("shape", [(3, 4), (17, 5), (40, 63), (33, 64), (37, 65), (50, 66), (21, 67), (16, 144), (7, 255), (5, 256), (9, 257), (100, 511), (6, 513),
+                                   (1001, 703), (4, 1021), (3, 1024), (2, 9, 130)])
+def test_scans_of_short_lines(env, shape):
+    a = positive(shape, 17)
+    got, ref = both(env, lambda xp, a: xp.cumsum(a * 0.5 + 1.0, -1), a=a)   # positive terms: 1e-5 of every prefix
+    assert reduction_check(got, ref)[0].all()
+    for op in ("cummax", "cummin"):
+        got, ref = both(env, lambda xp, a: getattr(xp, op)(a - 0.75, -1), a=a)
+        assert np.array_equal(got, ref)
+    b = a.copy()
+    b.reshape(-1)[:: 97] = np.inf
+    got, ref = both(env, lambda xp, a: xp.cumsum(a, -1), a=b)
+    assert reduction_check(got, ref)[0].all()
+    i = np.random.default_rng(18).integers(-2**31, 2**31 - 1, shape, dtype=np.int64).astype(np.int32)
+    got, ref = both(env, lambda xp, i: xp.cumsum(i, -1), i=i)
+    assert got.dtype == np.int64 and np.array_equal(got, ref)
