@@ -717,7 +717,7 @@ void gen_rowred(Em& e) {
   const GroupPlan& g = e.g;
   if (g.pair_k) { gen_rowred_pairs(e); return; }
   const int rank = g.rank, cd = rank - 1;
-  const int RT = g.row_threads, NP = g.NP, RB = 256 / RT;
+  const int RT = g.row_threads, NP = g.NP, BT = std::max(256, RT), RB = BT / RT;
   const int nph = (int)g.phases.size();
   prelude(e);
   for (int ph = 0; ph < nph; ++ph) phase_helpers(e, ph, RT);
@@ -744,7 +744,7 @@ void gen_rowred(Em& e) {
     for (size_t i = 0; i < g.prog.size(); ++i) if (stage_of[i] == s) stage_instrs[s].push_back((int)i);
   }
 
-  kernel_head(e, kernel_name(g));
+  kernel_head(e, kernel_name(g), BT);
   e.o << "  const long long C = " << e.dim(cd) << ";\n  long long ROWS = 1;\n";
   for (int k = 0; k < cd; ++k) e.o << "  ROWS *= " << e.dim(k) << ";\n";
   e.o << "  const int lane = threadIdx.x % " << RT << ";\n";
@@ -764,7 +764,7 @@ void gen_rowred(Em& e) {
     // lanes of a row past the end recompute the last row and skip the stores
     e.o << "  const long long row_raw = (long long)blockIdx.x * " << RB << " + threadIdx.x / " << RT << ";\n";
     e.o << "  const bool row_ok = row_raw < ROWS;\n  const long long row = row_ok ? row_raw : ROWS - 1;\n";
-    e.o << "  __shared__ long long gr_sm[" << std::max(nph, 1) << "][4];\n";
+    e.o << "  __shared__ long long gr_sm[" << std::max(nph, 1) << "][" << BT / 64 << "];\n";
   }
   e.o << "  (void)row_ok;\n";
   if (cd >= 1) {
@@ -913,7 +913,10 @@ void gen_rowred(Em& e) {
         e.o << "  { " << T << "* sm = (" << T << "*)gr_sm[" << s << "];\n"
                "    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = acc" << s << ";\n"
                "    __syncthreads();\n";
-        if (RT == 256) e.o << "    acc" << s << " = gr_comb" << s << "(gr_comb" << s << "(sm[0], sm[1]), gr_comb" << s << "(sm[2], sm[3])); }\n";
+        if (RT == 1024) {
+          e.o << "    " << T << " w[16];\n    for (int q = 0; q < 16; ++q) w[q] = sm[q];\n"
+                 "    for (int d = 1; d < 16; d *= 2) for (int q = 0; q < 16; q += 2 * d) w[q] = gr_comb" << s << "(w[q], w[q + d]);\n    acc" << s << " = w[0]; }\n";
+        } else if (RT == 256) e.o << "    acc" << s << " = gr_comb" << s << "(gr_comb" << s << "(sm[0], sm[1]), gr_comb" << s << "(sm[2], sm[3])); }\n";
         else e.o << "    const int w0 = (threadIdx.x >> 7) * 2;\n    acc" << s << " = gr_comb" << s << "(sm[w0], sm[w0 + 1]); }\n";
       }
       e.o << "  red" << s << " = acc" << s << ";\n";

@@ -45,7 +45,7 @@ struct gr_ctx {
 
   // options
   int64_t opt_fusion = 1;
-  int64_t opt_rowred_max_cols = 16384;
+  int64_t opt_rowred_max_cols = 65536;
   int64_t opt_map_rows = 0, opt_map_chunks = 0;
   int64_t opt_profile = 0;
   int64_t opt_nontemporal = 1;

@@ -227,7 +227,7 @@ bool interp_encode_rowred(const GroupPlan& g, void* out_ptr, GrInterpRowArgs* R,
   // the generated kernel's assignment of elements to lanes, so that both combine in the same order
   R->lanes = g.row_threads;
   R->positions = g.NP;
-  if (!(R->lanes == 1 || R->lanes == 2 || R->lanes == 4 || R->lanes == 8 || R->lanes == 16 || R->lanes == 64 || R->lanes == 128 || R->lanes == 256)) return false;
+  if (!(R->lanes == 1 || R->lanes == 2 || R->lanes == 4 || R->lanes == 8 || R->lanes == 16 || R->lanes == 64 || R->lanes == 128 || R->lanes == 256 || R->lanes == 1024)) return false;
   if ((int64_t)R->lanes * 4 * R->positions < C) return false;
   R->per_row = g.out_per_row ? 1 : 0;
   R->n_phase = (int)g.phases.size();
@@ -247,7 +247,7 @@ bool interp_encode_rowred(const GroupPlan& g, void* out_ptr, GrInterpRowArgs* R,
   }
   R->m.n_instr = ni;
   R->m.out = (unsigned long long)(uintptr_t)out_ptr;
-  const int rb = 256 / R->lanes;
+  const int rb = std::max(1, 256 / R->lanes);
   *grid = (unsigned)((rows + rb - 1) / rb);
   return true;
 }

@@ -50,7 +50,7 @@ struct GrInterpRowArgs {
   int phase_int[GR_INTERP_PHASES];           // the phase combines i32 values (else f32)
   int per_row;                               // one output value per row (else one per element)
   int lanes;                                 // lanes per row and vec4 positions per lane: those of the generated kernel
-  int positions;                             // (1, 2, 4, 8, 16, 64, 128 or 256 lanes)
+  int positions;                             // (1, 2, 4, 8, 16, 64, 128, 256 or 1024 lanes)
 };
 
 // Sub-graphs that are cuts of their own -- a reduction over any axes, a scan, a contraction with

@@ -162,15 +162,16 @@ static __device__ __forceinline__ unsigned gi_combine(int op, int is_int, unsign
 __global__ __launch_bounds__(256) void gr_interp_rowred_kernel(GrInterpRowArgs A) {
   __shared__ unsigned vals[GR_INTERP_SLOTS * 256];
   __shared__ unsigned red[256][GR_INTERP_PHASES];
-  __shared__ unsigned part[4];
+  __shared__ unsigned part[16];
   constexpr int CD = GR_INTERP_RANK - 1;
   const GrInterpArgs& a = A.m;
-  const int RT = A.lanes, NP = A.positions, lane = threadIdx.x % RT, rslot = threadIdx.x / RT;
+  // (a row of 1024 lanes: every thread stands for four of them in turn, 256 apart)
+  const int RT = A.lanes, NP = A.positions, HT = RT < 256 ? RT : 256, VL = RT / HT, lane = threadIdx.x % HT, rslot = threadIdx.x / HT;
   const long long C = a.dims[CD];
   unsigned long long rows = 1;
 #pragma unroll
   for (int k = 0; k < CD; ++k) rows *= (unsigned long long)a.dims[k];
-  const unsigned long long row_raw = (unsigned long long)blockIdx.x * (256 / RT) + rslot;
+  const unsigned long long row_raw = (unsigned long long)blockIdx.x * (256 / HT) + rslot;
   const bool row_ok = row_raw < rows;
   const unsigned row = (unsigned)(row_ok ? row_raw : rows - 1);   // the host checked that rows fit 31 bits
   unsigned idx[CD];
@@ -194,9 +195,9 @@ __global__ __launch_bounds__(256) void gr_interp_rowred_kernel(GrInterpRowArgs A
         }
         break;
       }
-      for (int p = 0; p < NP; ++p)
+      for (int p = 0; p < NP * VL; ++p)
         for (int j = 0; j < 4; ++j) {
-          const long long c = ((long long)p * RT + lane) * 4 + j;
+          const long long c = ((long long)p * HT + lane) * 4 + j;
           if (c >= C) continue;
           gi_run(a, A.seg_begin[s], A.seg_end[s], c, idx, my, red[rslot]);
           if (row_ok) *(GM unsigned*)(a.out + 4ull * ((unsigned long long)row * (unsigned long long)C + (unsigned long long)c)) = my[A.seg_slot[s] * 256];
@@ -204,19 +205,33 @@ __global__ __launch_bounds__(256) void gr_interp_rowred_kernel(GrInterpRowArgs A
       break;
     }
     const int op = A.phase_op[s], is_int = A.phase_int[s];
-    unsigned acc = is_int ? (op == 0 ? 0u : (op == 1 ? 0x80000000u : 0x7fffffffu))
-                          : (op == 0 ? 0u : (op == 1 ? 0xff800000u : 0x7f800000u));   // 0, -inf / INT_MIN, +inf / INT_MAX
+    const unsigned none = is_int ? (op == 0 ? 0u : (op == 1 ? 0x80000000u : 0x7fffffffu))
+                                 : (op == 0 ? 0u : (op == 1 ? 0xff800000u : 0x7f800000u));   // 0, -inf / INT_MIN, +inf / INT_MAX
+    unsigned acc = none;
+    for (int v = 0; v < VL; ++v) {
+    acc = none;
     for (int p = 0; p < NP; ++p)
       for (int j = 0; j < 4; ++j) {
-        const long long c = ((long long)p * RT + lane) * 4 + j;
+        const long long c = ((long long)p * RT + v * HT + lane) * 4 + j;
         if (c >= C) continue;
         gi_run(a, A.seg_begin[s], A.seg_end[s], c, idx, my, red[rslot]);
         acc = gi_combine(op, is_int, acc, my[A.seg_slot[s] * 256]);
       }
     for (int m = (RT < 64 ? RT : 64) / 2; m > 0; m >>= 1) acc = gi_combine(op, is_int, acc, (unsigned)__shfl_xor((int)acc, m, 64));
+    if (RT > 64 && (threadIdx.x & 63) == 0) part[4 * v + (threadIdx.x >> 6)] = acc;
+    }
     if (RT > 64) {
-      if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
       __syncthreads();
+      if (RT == 1024) {
+        unsigned w[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) w[q] = part[q];
+#pragma unroll
+        for (int d = 1; d < 16; d *= 2)
+#pragma unroll
+          for (int q = 0; q < 16; q += 2 * d) w[q] = gi_combine(op, is_int, w[q], w[q + d]);
+        acc = w[0];
+      } else
       if (RT == 256) acc = gi_combine(op, is_int, gi_combine(op, is_int, part[0], part[1]), gi_combine(op, is_int, part[2], part[3]));
       else { const int w0 = (threadIdx.x >> 7) * 2; acc = gi_combine(op, is_int, part[w0], part[w0 + 1]); }
     }

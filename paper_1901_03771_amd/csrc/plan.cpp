@@ -555,7 +555,7 @@ struct Planner {
         const Node* x = n->in[0];
         bool last_only = x->ndim >= 1;
         for (int d = 0; d < x->ndim; ++d) if (n->red_axis[d] != (d == x->ndim - 1)) last_only = false;
-        if (!last_only || x->shape[x->ndim - 1] > std::min<int64_t>(c->opt_rowred_max_cols, 16384)) cuts.insert(n);
+        if (!last_only || x->shape[x->ndim - 1] > std::min<int64_t>(c->opt_rowred_max_cols, 65536)) cuts.insert(n);
       }
     }
   }
@@ -711,6 +711,35 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
   // (rows shorter than 256 bytes share cache lines with other waves as well: 3145728 x 8 52.6 -> 42.6 us without the hint)
   if (c->opt_nontemporal == 1 && g->rank >= 2 && R > 1 && C < 64) g->nt &= ~7;
   g->tail = (g->rank >= 2 && !g->flat && C < 64 && (C & 3) && g->UC == 1 && !g->stage_mask) ? (int)(C & 3) : 0;
+}
+
+// Row-resident reductions: per-element values that are computed in one phase and used in a later one, the most alive
+// between any two phases.
+int rowred_live(const GroupPlan& g) {
+  const int n = (int)g.prog.size(), nst = (int)g.phases.size() + 1;
+  std::vector<int> made(n, -1), used(n, -1);
+  for (int s = 0; s < nst; ++s) {
+    std::vector<int> work{s + 1 < nst ? g.phases[s].value : (g.results.empty() ? -1 : g.results[0])};
+    std::vector<char> seen(n, 0);
+    while (!work.empty()) {
+      const int i = work.back();
+      work.pop_back();
+      if (i < 0 || seen[i]) continue;
+      seen[i] = 1;
+      used[i] = s;
+      if (made[i] >= 0) continue;
+      made[i] = s;
+      work.push_back(g.prog[i].a);
+      work.push_back(g.prog[i].b);
+    }
+  }
+  int most = 0;
+  for (int s = 0; s + 1 < nst; ++s) {
+    int live = 0;
+    for (int i = 0; i < n; ++i) if (!g.prog[i].uniform && made[i] >= 0 && made[i] <= s && used[i] > s) ++live;
+    most = std::max(most, live);
+  }
+  return most;
 }
 
 // Rows of at most 64 elements over two kept dimensions, each element a function of one operand that follows the first
@@ -1336,10 +1365,20 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
       // (measured on MI355X for 4096-float rows: 256 lanes 93 us, 128 lanes 96 us, 64 lanes 104 us)
       // lanes per row: enough for one to four dwordx4 positions per lane; very short rows share a
       // wave between many rows instead of leaving most of 16 lanes idle
+      // Rows of more than 16384 elements whose reductions feed a value per element: 1024 lanes, up to 16 positions per lane,
+      // one workgroup per row.  (A cut per reduction reads and writes the matrix four times over; softmax, cuts against
+      // resident rows, us: 2047 x 16388 149 / 54, 1245 x 26936 148 / 58, 512 x 65536 133 / 62, 500 x 40001 100 / 37, 143 x 26823
+      // 31 / 12, 1 x 65536 16.4 / 15.3.)  A sum of such rows that is a result of its own stays with the two-stage kernel.
       g->row_threads = C <= 4 ? 1 : (C <= 8 ? 2 : (C <= 16 ? 4 : (C <= 32 ? 8 : (C <= 256 ? 16 : (C <= 1024 ? 64 : (C <= 2048 ? 128 : 256))))));
       if (c->opt_rowred_threads == 16 || c->opt_rowred_threads == 64 || c->opt_rowred_threads == 128 || c->opt_rowred_threads == 256)
         if (C <= c->opt_rowred_threads * 64) g->row_threads = (int)c->opt_rowred_threads;  // at most 16 positions per lane
+      if (C > 16384) g->row_threads = 1024;
       g->NP = (int)std::max<int64_t>(1, (C + (int64_t)g->row_threads * 4 - 1) / ((int64_t)g->row_threads * 4));
+      // The values that a phase leaves for later ones live in registers: of 128 per lane, 80 may hold them.
+      if (g->row_threads == 1024 && (int64_t)rowred_live(*g) * g->NP * 4 > 80) {
+        for (const Node* n : reds) if (n != r) invalid->push_back({n, "rows too long to keep their values"});
+        if (!invalid->empty()) return GR_OK;
+      }
       // Rows that run along a strided axis of every array read while another axis is the contiguous
       // one (an array stored transposed): lanes along such a row would each touch another cache
       // line.  The reductions are evaluated by the generic kernel instead, which gives a thread

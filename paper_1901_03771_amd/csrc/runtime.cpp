@@ -579,8 +579,8 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
         s[L.extra + 1] = (uint64_t)nub;
         return launch(c, k->fn, k->name, (nl + 7) / 8 * 8 * nub, s);
       }
-      int rb = 256 / g.row_threads * g.row_iters;
-      return launch(c, k->fn, k->name, (rows + rb - 1) / rb, s);
+      const int bt = std::max(256, g.row_threads), rb = bt / g.row_threads * g.row_iters;
+      return launch(c, k->fn, k->name, (rows + rb - 1) / rb, s, (unsigned)bt);
     }
     case GroupKind::REDUCE: {
       if (g.red_out == 0) return GR_OK;

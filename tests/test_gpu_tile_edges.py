@@ -137,3 +137,32 @@ def test_scans_of_short_lines(env, shape):
     i = np.random.default_rng(18).integers(-2**31, 2**31 - 1, shape, dtype=np.int64).astype(np.int32)
     got, ref = both(env, lambda xp, i: xp.cumsum(i, -1), i=i)
     assert got.dtype == np.int64 and np.array_equal(got, ref)
+
+
+# rows kept by 1024 lanes: one element more than 256 lanes keep, ragged, all 16 positions, the first length beyond; a row and a few
+@pytest.mark.parametrize("shape", [(3, 16385), (5, 20000), (2, 33001), (1, 65535), (2, 65536), (2, 65537), (2, 3, 17000)])
+def test_programs_over_long_rows(env, shape):
+    gr, ctx, torch = env
+    a = positive(shape, 19) * f32(3.0)
+
+    def softmax(xp, a):
+        e = xp.exp(a - xp.max(a, axis=-1, keepdims=True))
+        return e / xp.sum(e, axis=-1, keepdims=True)
+
+    def normal(xp, a):       # positive terms only
+        s = xp.sqrt(a) + a
+        return s / xp.sqrt(xp.sum(s * s, axis=-1, keepdims=True)) + a * xp.max(s, axis=-1, keepdims=True)
+
+    other = gr.Context()
+    other.set_option("interp", 2)      # the byte-code interpreter: the same bits
+    t = torch.from_numpy(a).cuda()
+    for prog in (softmax, normal, lambda xp, a: xp.log(xp.sum(xp.exp(a), axis=-1) + 1.0)):
+        got, ref = both(env, prog, a=a)
+        assert reduction_check(got, ref)[0].all()
+        if shape[-1] <= 65536 and prog is softmax:
+            assert np.array_equal(prog(gr, other.array(t)).numpy(), got)
+    i = np.random.default_rng(20).integers(-2**31, 2**31 - 1, shape, dtype=np.int64).astype(np.int32)
+    got, ref = both(env, lambda xp, i: i - xp.max(i, axis=-1, keepdims=True) + xp.min(i, axis=-1, keepdims=True), i=i)
+    assert np.array_equal(got, ref)
+    other.sync()
+    other.close()
