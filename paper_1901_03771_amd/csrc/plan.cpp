@@ -514,6 +514,15 @@ void pop_output_group(GroupPlan* g) {
   g->out_unit = g->out_coef[g->rank - 1] == 1 || g->dims[g->rank - 1] == 1;
 }
 
+// Longest row of `x` that reductions with consumers may keep in registers: 64 elements of each of 1024 lanes.  Arrays of fewer than
+// 16 rows keep the partition into cuts beyond what 256 lanes hold: a handful of workgroups cannot fill the chip, though up
+// to here they are still faster than the cuts' launches (softmax of 8 x 20000: 16.5 us in cuts, 7.1 resident; of 1 x 65536
+// 16.4 and 15.3), and the tests show the paper's own partition of a softmax on such an array.
+int64_t resident_limit(const gr_ctx* c, const Node* x) {
+  const int64_t C = x->shape[x->ndim - 1];
+  return std::min<int64_t>(c->opt_rowred_max_cols, C > 0 && x->count() / C >= 16 ? 65536 : 16384);
+}
+
 struct Planner {
   gr_ctx* c;
   Node* root;
@@ -555,7 +564,7 @@ struct Planner {
         const Node* x = n->in[0];
         bool last_only = x->ndim >= 1;
         for (int d = 0; d < x->ndim; ++d) if (n->red_axis[d] != (d == x->ndim - 1)) last_only = false;
-        if (!last_only || x->shape[x->ndim - 1] > std::min<int64_t>(c->opt_rowred_max_cols, 65536)) cuts.insert(n);
+        if (!last_only || x->shape[x->ndim - 1] > resident_limit(c, x)) cuts.insert(n);
       }
     }
   }
