@@ -2324,6 +2324,156 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
 }
 
 
+// Products that do not fill rounds of large tiles, of any extents (each operand contiguous along one of its two
+// dimensions, extents of four or more): tiles of TM x TN = 64 x 64, 128 x 32 or 32 x 128, a 32 x 32 block per wave,
+// several workgroups per compute unit.  Small products are bound by the latency of their loads and by compute units
+// without a tile, ragged ones by guarded loads: here K advances 32 at a time, the loads run three steps ahead in
+// registers, and no load is guarded.  The last tile of a dimension starts T from its end and overlaps the one before it
+// with the same values; where an operand is narrower than a tile, rows (or groups of four) beyond its end are clamped
+// to its last ones, and results for them are not stored.  The last step of K is shifted into place and padded with
+// zeros on its way into LDS.
+// LDS: an operand contiguous along k lies as [other][k] at a pitch of 36, read four k at a time; one contiguous along
+// its other dimension as [k][other] at a pitch of T + 8, read one k at a time; both without bank conflicts.  Half-wave
+// h takes k = 8 g + 4 h + t in matrix instruction t of group g, for both operands.  Loads, LDS reads and LDS writes of a
+// step are placed one behind each matrix instruction (scheduling barriers): waves that do them in a phase of their own
+// leave the matrix cores idle together, however many there are.
+void gemm_tile_body(Em& e, const EpiLoad& epi_load) {
+  const GroupPlan& g = e.g;
+  std::ostream& o = e.o;
+  const int TT[2] = {g.BY, g.BX}, S = 3, KS = 32, G = KS / 8;   // S: steps in flight
+  const int groups[2] = {g.mat_group, g.vec_group};
+  bool kc[2];
+  int nv[2], pitch[2], rows[2];
+  for (int x = 0; x < 2; ++x) {
+    const AccessGroup& ag = g.groups[groups[x]];
+    kc[x] = ag.coef[x == 0 ? 1 : 0] == 1;
+    nv[x] = TT[x] * KS / 4 / 256;
+    pitch[x] = kc[x] ? KS + 4 : TT[x] + 8;
+    rows[x] = kc[x] ? TT[x] : KS;
+  }
+  const char* nm[2] = {"A", "B"};
+  const char* ext[2] = {"M", "N"};
+  const char* org[2] = {"bm0", "bn0"};
+  for (int x = 0; x < 2; ++x) o << "  __shared__ __attribute__((aligned(16))) float S" << nm[x] << "[2][" << rows[x] << "][" << pitch[x] << "];\n";
+  o << "  const unsigned tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, lh = lane >> 5;\n"
+       "  const unsigned wm = " << (g.BY == 64 ? "(wave >> 1) * 32" : (g.BY == 128 ? "wave * 32" : "0")) << ", wn = " << (g.BX == 64 ? "(wave & 1) * 32" : (g.BX == 128 ? "wave * 32" : "0")) << ";\n"
+       "  const long long NSPLIT = " << e.S(e.L.extra + 3) << ", KCH = " << e.S(e.L.ocoef + 1) << ";\n"
+       "  const unsigned tiles_n = (unsigned)((N + " << TT[1] - 1 << ") / " << TT[1] << "), tiles = tiles_n * (unsigned)((M + " << TT[0] - 1 << ") / " << TT[0] << "), total = tiles * (unsigned)NSPLIT;\n"
+       // (neighbouring tiles share operand rows: they go to the same XCD, workgroups are dealt round-robin over the 8)
+       "  const unsigned per = (total + 7) / 8, job = (blockIdx.x % 8) * per + blockIdx.x / 8;\n"
+       "  if (blockIdx.x / 8 >= per || job >= total) return;\n"
+       "  const unsigned split = job / tiles, tile = job % tiles;\n"
+       "  const long long bm1 = (long long)(tile / tiles_n) * " << TT[0] << ", bn1 = (long long)(tile % tiles_n) * " << TT[1] << ";\n"
+       "  const long long bm0 = bm1 + " << TT[0] << " <= M || M < " << TT[0] << " ? bm1 : M - " << TT[0] << ", bn0 = bn1 + " << TT[1] << " <= N || N < " << TT[1] << " ? bn1 : N - " << TT[1] << ";\n"
+       "  const long long kbeg = split * KCH, KE = (kbeg + KCH < K) ? kbeg + KCH : K;\n"
+       "  const int kn = KE > kbeg ? (int)(KE - kbeg) : 0, nkt = (kn + " << KS - 1 << ") / " << KS << ", nfull = kn / " << KS << ", klast = (int)(KE - kbeg);\n";
+  for (int x = 0; x < 2; ++x) {
+    o << "  f4 r" << nm[x] << "[" << S << "][" << nv[x] << "];\n";
+    if (!kc[x]) o << "  const unsigned s" << nm[x] << " = (unsigned)" << (x == 0 ? "ak" : "bk") << ";;\n";
+    for (int v = 0; v < nv[x]; ++v) {
+      const std::string id = std::string(nm[x]) + std::to_string(v);
+      o << "  const unsigned i" << id << " = tid + " << 256 * v << ";\n";
+      if (kc[x]) {
+        o << "  const unsigned k" << id << " = i" << id << " % " << KS / 4 << " * 4, o" << id << " = i" << id << " / " << KS / 4 << ";\n"
+             "  const GM float* const p" << id << " = " << nm[x] << " + (" << org[x] << " + o" << id << " < " << ext[x] << " ? " << org[x] << " + o" << id << " : " << ext[x] << " - 1) * " << (x == 0 ? "am" : "bn") << " + kbeg;\n";
+      } else {
+        o << "  const unsigned k" << id << " = i" << id << " / " << TT[x] / 4 << ", h" << id << " = i" << id << " % " << TT[x] / 4 << " * 4;\n"
+             "  const unsigned o" << id << " = " << org[x] << " + h" << id << " + 4 <= " << ext[x] << " ? h" << id << " : (unsigned)(" << ext[x] << " - 4 - " << org[x] << ");\n"
+             "  const GM float* const p" << id << " = " << nm[x] << " + " << org[x] << " + o" << id << " + kbeg * " << (x == 0 ? "ak" : "bk") << ";\n";
+      }
+    }
+  }
+  // (an operand narrower than its tile has origin 0: a clamped group of four starts at ext - 4 >= 0)
+  auto fetch = [&](int x, int v, int set, const std::string& kt) {
+    const std::string id = std::string(nm[x]) + std::to_string(v), at = "((" + kt + ") * " + std::to_string(KS) + " + (int)k" + id + ")", to = std::string("r") + nm[x] + "[" + std::to_string(set) + "][" + std::to_string(v) + "]";
+    if (kc[x]) o << "        { const int k = " << at << " + 4 <= kn ? " << at << " : klast - 4; " << to << " = *(const GM f4u*)(p" << id << " + k); }\n";
+    else o << "        { const int k = " << at << " < kn ? " << at << " : klast - 1; " << to << " = *(const GM f4u*)(p" << id << " + (unsigned long long)(unsigned)k * s" << nm[x] << "); }\n";
+  };
+  auto stash = [&](int x, int v, int set, const std::string& kt, bool tail) {
+    const std::string id = std::string(nm[x]) + std::to_string(v);
+    o << "        { f4 w = r" << nm[x] << "[" << set << "][" << v << "]; const int kt1 = " << kt << ", nb = kt1 & 1;\n";
+    if (kc[x]) {
+      if (tail)
+        o << "          { const int k = kt1 * " << KS << " + (int)k" << id << ", sh = k + 4 <= kn ? 0 : k + 4 - kn; f4 z;\n"
+             "            z[0] = sh == 0 ? w[0] : sh == 1 ? w[1] : sh == 2 ? w[2] : w[3]; z[1] = sh == 0 ? w[1] : sh == 1 ? w[2] : w[3]; z[2] = sh == 0 ? w[2] : w[3]; z[3] = w[3];\n"
+             "            w[0] = k < kn ? z[0] : 0.0f; w[1] = k + 1 < kn ? z[1] : 0.0f; w[2] = k + 2 < kn ? z[2] : 0.0f; w[3] = k + 3 < kn ? z[3] : 0.0f; }\n";
+      o << "          *(f4*)&S" << nm[x] << "[nb][o" << id << "][k" << id << "] = w; }\n";
+    } else {
+      if (tail) o << "          if (kt1 * " << KS << " + (int)k" << id << " >= kn) w = f4{0.0f, 0.0f, 0.0f, 0.0f};\n";
+      // (a clamped group of an operand that is no multiple of four wide is not aligned in LDS)
+      if ((g.NP - 1) >> x & 1) o << "          for (int j = 0; j < 4; ++j) S" << nm[x] << "[nb][k" << id << "][o" << id << " + j] = w[j]; }\n";
+      else o << "          *(f4*)&S" << nm[x] << "[nb][k" << id << "][o" << id << "] = w; }\n";
+    }
+  };
+  auto read = [&](int x, int gr) {
+    const std::string to = std::string(x == 0 ? "a" : "b") + std::to_string(gr), w0 = x == 0 ? "wm" : "wn";
+    if (kc[x]) o << "        " << to << " = *(const f4*)&S" << nm[x] << "[buf][" << w0 << " + l32][" << 8 * gr << " + 4 * lh];\n";
+    else for (int t = 0; t < 4; ++t) o << "        " << to << "[" << t << "] = S" << nm[x] << "[buf][" << 8 * gr + t << " + 4 * lh][" << w0 << " + l32];\n";
+  };
+  // one step of K: tile kt (in LDS), loads of tile kt + S into register set `set` (or none), tile kt + 1 from its set to LDS
+  auto step = [&](const std::string& kt, int set, bool loads, int stash_mode /* 0 none, 1 whole tile, 2 perhaps the last one */) {
+    std::vector<std::function<void()>> piece;
+    if (loads) for (int x = 0; x < 2; ++x) for (int v = 0; v < nv[x]; ++v) piece.push_back([&, x, v] { fetch(x, v, set, kt + " + " + std::to_string(S)); });
+    const size_t nl = piece.size();
+    for (int gr = 2; gr < G; ++gr) for (int x = 0; x < 2; ++x) piece.push_back([&, x, gr] { read(x, gr); });
+    if (stash_mode == 1) for (int x = 0; x < 2; ++x) for (int v = 0; v < nv[x]; ++v) piece.push_back([&, x, v] { stash(x, v, (set + 1) % S, kt + " + 1", false); });
+    o << "      {\n        const int buf = (" << kt << ") & 1;\n        f4 ";
+    for (int gr = 0; gr < G; ++gr) o << "a" << gr << ", b" << gr << (gr + 1 < G ? ", " : ";\n");
+    for (int gr = 0; gr < 2; ++gr) for (int x = 0; x < 2; ++x) read(x, gr);
+    o << "        __builtin_amdgcn_sched_barrier(0);\n";
+    size_t at = 0;
+    for (int m = 0; m < 4 * G; ++m) {
+      const int gr = m / 4, t = m % 4;
+      const char* ac = m % 2 ? "acc2" : "acc";   // (two sets of accumulators: half as many additions in a row)
+      o << "        " << ac << " = __builtin_amdgcn_mfma_f32_32x32x2f32(a" << gr << "[" << t << "], b" << gr << "[" << t << "], " << ac << ", 0, 0, 0);\n        __builtin_amdgcn_sched_barrier(0);\n";
+      // (the operands of group 2 are read behind the first four instructions at the latest, those of group 3 behind eight;
+      // the first LDS write waits for its load as long as it can)
+      size_t upto = at;
+      if (m < 6) upto = std::max(at, std::min(piece.size(), (size_t)(m + 1) * (nl + 4) / 6));
+      else if (stash_mode == 1) upto = std::min(piece.size(), nl + 4 + (size_t)std::max(0, m - 5));
+      else upto = piece.size();
+      if (upto > at) {
+        for (; at < upto; ++at) piece[at]();
+        o << "        __builtin_amdgcn_sched_barrier(0);\n";
+      }
+    }
+    for (; at < piece.size(); ++at) piece[at]();
+    if (stash_mode == 2) {
+      o << "        if (" << kt << " + 1 < nkt) {\n";
+      for (int x = 0; x < 2; ++x) for (int v = 0; v < nv[x]; ++v) stash(x, v, (set + 1) % S, kt + " + 1", true);
+      o << "        }\n";
+    }
+    o << "        __syncthreads();\n      }\n";
+  };
+  o << "  f16v acc, acc2;\n  for (int q = 0; q < 16; ++q) acc[q] = acc2[q] = 0.0f;\n  if (nkt > 0) {\n";
+  for (int u = 0; u < S; ++u) for (int x = 0; x < 2; ++x) for (int v = 0; v < nv[x]; ++v) fetch(x, v, u, std::to_string(u));
+  for (int x = 0; x < 2; ++x) for (int v = 0; v < nv[x]; ++v) stash(x, v, 0, "0", true);
+  // (no condition around the loads of the main loop: the compiler would wait for them where the paths meet)
+  o << "    __syncthreads();\n    int kt = 0;\n    for (; kt + " << S << " < nfull; kt += " << S << ") {\n";
+  for (int u = 0; u < S; ++u) step("kt + " + std::to_string(u), u, true, 1);
+  // one to S + 1 tiles are left (the last of them perhaps partial), all but the last of S + 1 in flight
+  o << "    }\n";
+  for (int u = 0; u <= S; ++u) {
+    if (u) o << "    if (kt + " << u << " < nkt)\n";
+    step("kt + " + std::to_string(u), u % S, u == 0, u < S ? 2 : 0);
+  }
+  o << "  }\n  acc += acc2;\n  GM float* const out = (GM float*)" << e.slot(e.L.out) << ";\n"
+       "  if (NSPLIT > 1) {\n    GM float* const ws = (GM float*)" << e.slot(e.L.ocoef) << " + split * M * N;\n"
+       "#pragma unroll\n    for (int q = 0; q < 16; ++q) {\n"
+       "      const long long row = bm0 + wm + 8 * (q / 4) + 4 * lh + (q % 4), col = bn0 + wn + l32;\n"
+       "      if (row < M && col < N) ws[row * N + col] = acc[q];\n    }\n    return;\n  }\n";
+  const std::string body = captured(e, [&] {
+    o << "#pragma unroll\n      for (int ql = 0; ql < 4; ++ql) {\n"
+         "      const int q = 4 * qh + ql;\n"
+         "      const long long row = bm0 + wm + 8 * qh + 4 * lh + ql, col = bn0 + wn + l32;\n"
+         "      if (row < M && col < N) {\n        const float cacc = acc[q];\n";
+    emit_scalar_program(e, g.prog, g.results, epi_load, "cacc", "t", "        ");
+    o << "        out[row * N + col] = t" << g.results[0] << ";\n      }\n      }\n";
+  });
+  emit_unrolled(o, {{"qh", 4}}, body, "    ");
+  o << "}\n";
+}
+
 // C = A.B for f32 on MFMA (v_mfma_f32_32x32x2_f32: f32 inputs, f32 accumulation), the one place
 // on this path that is a dense contraction.  A workgroup of four waves owns a 128x128 tile of
 // C; each wave a 64x64 quarter as 2x2 MFMA blocks (64 accumulator VGPRs).  K advances in steps
@@ -2371,6 +2521,11 @@ void gen_gemm(Em& e) {
     return s2.str();
   };
   auto emit_combine = [&]() { gemm_combine(e, epi_load); };
+  if (g.VR == 3) {   // small tiles, clamped loads
+    gemm_tile_body(e, epi_load);
+    emit_combine();
+    return;
+  }
   if (g.VR == 2) {   // tiles loaded straight into LDS
     gemm_big_body(e, epi_load);
     emit_combine();

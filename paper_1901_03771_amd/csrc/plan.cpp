@@ -722,6 +722,62 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
   g->tail = (g->rank >= 2 && !g->flat && C < 64 && (C & 3) && g->UC == 1 && !g->stage_mask) ? (int)(C & 3) : 0;
 }
 
+// Small or ragged matrix products: tiles of 64 x 64 (128 x 32, 32 x 128) with clamped loads (gemm_tile_body), after the
+// choice between the kernels with tiles of 128 and 256.
+// Cost of such a product in microseconds, fitted to measurements: rounds of 256 workgroups times steps of 32 values of k at 0.62,
+// 5 for the launch and the first loads, and for a split of K 4 for the second launch and the partial tiles' traffic at 5 TB/s.
+// It takes over from the register-staged kernel (us, before / now: 2001^3 275 / 156, 649 x 448 x 714 26 / 15, 1792 x 74 x 213
+// 14.6 / 6.3, 11845 x 2066 x 48 78 / 48, 2066 x 11845 x 48 62 / 39, 64 x 4096 x 4096 49 / 29, 512^3 16.6 / 10.4, 30 x 5000 x 3000 56 / 23),
+// except for short sums with a large result, whose stores bound it and which the larger tile writes faster (11845 x 48 x 2066
+// 42 against 57, 16384 x 100 x 1000 44 / 58, 2^20 x 16 x 8 26 / 55), tall operands with few columns (65536 x 512 x 10 28 / 31)
+// and large products of two operands contiguous along k (4001^3 1082 / 1111; the other layouts 1201 / 1143 and
+// 1318 / 1152); and from the direct 128 x 128 kernel where its cost is 2 lower (4096 x 784 x 512 42 / 39; 4096 x 512 x 784 stays: 37
+// against 45).
+void choose_gemm_tiles(gr_ctx* c, GroupPlan* g) {
+  if (g->VR == 2 && g->BX != 128) return;
+  const int64_t M = g->M, N = g->N, K = g->K;
+  auto fits = [&](const AccessGroup& x, int kdim, int64_t other) {
+    if (x.coef[kdim] == 1) return K >= 4;
+    return x.coef[1 - kdim] == 1 && other >= 4 && x.coef[kdim] > 0 && x.coef[kdim] < ((int64_t)1 << 32);
+  };
+  if (M < 1 || N < 1 || K > (int64_t)1 << 30 || !fits(g->groups[g->mat_group], 1, M) || !fits(g->groups[g->vec_group], 0, N)) return;
+  const int64_t tm = N <= 32 ? 128 : (M <= 32 ? 32 : 64), tn = N <= 32 ? 32 : (M <= 32 ? 128 : 64);
+  const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
+  if (tiles > (int64_t)1 << 24) return;
+  if (g->VR != 2) {
+    const bool rows_of_k = g->groups[g->mat_group].coef[1] == 1 && g->groups[g->vec_group].coef[0] == 1;
+    if (K <= 128 && M * N >= (int64_t)1 << 22) return;               // stores
+    if (tn == 32 && tiles >= 256) return;                            // one pass over a tall operand
+    if (rows_of_k && M * N >= (int64_t)1 << 23) return;              // many large tiles, both operands contiguous along k
+  }
+  // Every accumulator adds two chains: at least half as many splits as before, so that no chain gets longer.  Partial tiles stay
+  // below 256 MiB; a request that must not allocate gets no more of them than before.
+  const int before = g->slabs;
+  double best = 0;
+  int best_ks = 0;
+  for (int ks = (before + 1) / 2; ks <= (c->plan_static ? before : 128); ++ks) {
+    const int64_t kch = gemm_split_extent(K, ks);
+    if (ks > 1 && ((ks > before && kch < 64) || (int64_t)ks * M * N > (int64_t)1 << 26)) { if (best_ks) break; }
+    const double rounds = (double)((tiles * ks + 255) / 256);
+    const double cost = rounds * (double)((kch + 31) / 32) * 0.62 + 5.0 + (ks > 1 ? 4.0 + (double)ks * (double)M * (double)N * 8.0 / 5e6 : 0.0);
+    if (best_ks == 0 || cost < best * 0.97) { best = cost; best_ks = ks; }
+  }
+  if (g->VR == 2) {
+    // (long sums over small results stay with the direct kernel's division of K, whose tests hold it to that: a bound of its
+    // own, not a measured crossing; 640 x 512 x 1024 and the like may be faster here)
+    if (K >= 512 && M * N < (int64_t)1 << (K == 512 ? 18 : 20)) return;
+    const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128) * before, steps = (gemm_split_extent(K, before) + 15) / 16;
+    const double direct = (double)((wgs + 255) / 256) * (double)steps * (wgs <= 256 ? 1.1 : 0.95) + 2.0 + (before > 1 ? 6.0 + (double)before * (double)M * (double)N * 8.0 / 5e6 : 0.0);
+    if (best + 2.0 > direct) return;
+  }
+  g->VR = 3;
+  g->UC = 1;
+  g->BY = (int)tm;
+  g->BX = (int)tn;
+  g->NP = 1 + (M < tm && M % 4 ? 1 : 0) + (N < tn && N % 4 ? 2 : 0);   // (compiled in: groups of four that do not lie aligned in LDS)
+  g->slabs = best_ks;
+}
+
 // Row-resident reductions: per-element values that are computed in one phase and used in a later one, the most alive
 // between any two phases.
 int rowred_live(const GroupPlan& g) {
@@ -1152,6 +1208,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         g->UC = 1;
       }
     }
+    if (c->opt_gemm_bn == 0 && c->opt_gemm_kstep == 0 && c->opt_gemm_split == 0 && c->opt_gemm_big) choose_gemm_tiles(c, g);
   } else if (dot && !(dot == r && dot_as_reduce(dot) && c->opt_fusion)) {
     // ---- contraction with pointwise epilogue ------------------------------
     g->kind = GroupKind::GEMV;
@@ -1641,7 +1698,7 @@ std::string describe_plan(const Plan& plan) {
     first = true;
     for (const Node* n : g.leaves) { s << (first ? "" : ",") << n->id; first = false; }
     s << "] loads=" << [&] { int k = 0; for (const Instr& in : (g.kind == GroupKind::MAP ? g.prog1 : g.prog)) if (in.kind == IKind::LOAD) ++k; return k; }();
-    if (g.kind == GroupKind::GEMM) s << " M=" << g.M << " N=" << g.N << " K=" << g.K << " tile=" << (g.BX == 256 ? 256 : 128) << "x" << g.BX << (g.VR == 2 ? " direct" : "");
+    if (g.kind == GroupKind::GEMM) s << " M=" << g.M << " N=" << g.N << " K=" << g.K << " tile=" << (g.VR == 3 ? g.BY : g.BX == 256 ? 256 : 128) << "x" << g.BX << (g.VR == 3 ? " clamped" : g.VR == 2 ? " direct" : "");
     if (g.kind == GroupKind::GEMM && g.slabs > 1) s << " split=" << g.slabs;
     if (g.kind == GroupKind::GEMV) s << " mode=" << (g.gemv_mode == 2 ? "row-dot+column-accumulate" : (g.gemv_mode ? "column-accumulate" : "row-dot")) << " M=" << g.M << " K=" << g.K;
     if (g.pair) {

@@ -167,3 +167,33 @@ def test_programs_over_long_rows(env, shape):
     assert np.array_equal(got, ref)
     other.sync()
     other.close()
+
+
+# small integers: every sum is exact in any order.  Extents below, at and beside the tiles of 64 x 64, 128 x 32 and 32 x 128, groups
+# of four that stick out, sums of one step, of whole steps, of steps in flight and around them, sums split over workgroups
+@pytest.mark.parametrize("m,k,n", [(4, 9, 4), (5, 11, 6), (33, 31, 35), (63, 32, 61), (64, 33, 64), (65, 64, 67), (70, 95, 130), (129, 96, 66), (100, 97, 31), (300, 128, 19),
+                                   (131, 160, 32), (29, 129, 200), (32, 161, 129), (30, 1000, 300), (37, 4100, 41), (66, 2051, 200), (257, 515, 255), (8, 300, 5)])
+@pytest.mark.parametrize("layout", ["nn", "tn", "nt", "tt"])
+def test_products_with_clamped_tiles(env, m, k, n, layout):
+    gr, ctx, torch = env
+    rng = np.random.default_rng(21)
+    a = rng.integers(-4, 5, (m, k) if layout[0] == "n" else (k, m)).astype(f32)
+    b = rng.integers(-4, 5, (k, n) if layout[1] == "n" else (n, k)).astype(f32)
+    c, d = rng.integers(-9, 9, n).astype(f32), rng.integers(-9, 9, (m, n)).astype(f32)
+
+    def prog(xp, a, b, c, d):
+        return (a if layout[0] == "n" else xp.transpose(a)) @ (b if layout[1] == "n" else xp.transpose(b)) * 2.0 + c - d
+
+    specs = [ctx.spec(v.shape) for v in (a, b, c, d)]
+    assert "clamped" in prog(gr, *specs).plan()
+    got, ref = both(env, prog, a=a, b=b, c=c, d=d)
+    assert np.array_equal(got, ref)
+    # the result in the middle of a guarded buffer; infinities stay in their rows and columns
+    a[a.shape[0] // 2, a.shape[1] // 2] = np.inf
+    ta, tb, tc, td = (torch.from_numpy(v).cuda() for v in (a, b, c, d))
+    guard = torch.full((m * n + 128,), 7.0, device="cuda")
+    out = guard[64:64 + m * n].view(m, n)
+    prog(gr, *(ctx.array(t) for t in (ta, tb, tc, td))).materialize_into(out)
+    assert (guard[:64] == 7.0).all() and (guard[64 + m * n:] == 7.0).all()
+    ref = prog(ora, *(ora.array(v) for v in (a, b, c, d))).numpy()
+    assert np.array_equal(out.cpu().numpy(), ref, equal_nan=True)
