@@ -127,6 +127,7 @@ struct gr_ctx {
   unsigned char* static_base = nullptr;
   size_t static_cap = 0, static_used = 0;
   bool static_mode = false;
+  bool static_tight = false;    // the running request of that kind takes the fewest partial results
   bool plan_static = false;     // the request being planned is one of those: the planner keeps optional partial results within the array
 
   // gr_program_create: the request being recorded instead of executed, and the programs alive

@@ -733,7 +733,7 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
 // and large products of two operands contiguous along k (4001^3 1082 / 1111; the other layouts 1201 / 1143 and
 // 1318 / 1152); and from the direct 128 x 128 kernel where its cost is 2 lower (4096 x 784 x 512 42 / 39; 4096 x 512 x 784 stays: 37
 // against 45).
-void choose_gemm_tiles(gr_ctx* c, GroupPlan* g) {
+void choose_gemm_tiles(GroupPlan* g) {
   if (g->VR == 2 && g->BX != 128) return;
   const int64_t M = g->M, N = g->N, K = g->K;
   auto fits = [&](const AccessGroup& x, int kdim, int64_t other) {
@@ -750,14 +750,13 @@ void choose_gemm_tiles(gr_ctx* c, GroupPlan* g) {
     if (tn == 32 && tiles >= 256) return;                            // one pass over a tall operand
     if (rows_of_k && M * N >= (int64_t)1 << 23) return;              // many large tiles, both operands contiguous along k
   }
-  // Every accumulator adds two chains: at least half as many splits as before, so that no chain gets longer.  Partial tiles stay
-  // below 256 MiB; a request that must not allocate gets no more of them than before.
+  // Every accumulator adds two chains: at least half as many splits as the larger tiles would take, so that no chain gets
+  // longer, and no more than those, so that the partial tiles need no more memory (of a request that must not allocate).
   const int before = g->slabs;
   double best = 0;
   int best_ks = 0;
-  for (int ks = (before + 1) / 2; ks <= (c->plan_static ? before : 128); ++ks) {
+  for (int ks = (before + 1) / 2; ks <= before; ++ks) {
     const int64_t kch = gemm_split_extent(K, ks);
-    if (ks > 1 && ((ks > before && kch < 64) || (int64_t)ks * M * N > (int64_t)1 << 26)) { if (best_ks) break; }
     const double rounds = (double)((tiles * ks + 255) / 256);
     const double cost = rounds * (double)((kch + 31) / 32) * 0.62 + 5.0 + (ks > 1 ? 4.0 + (double)ks * (double)M * (double)N * 8.0 / 5e6 : 0.0);
     if (best_ks == 0 || cost < best * 0.97) { best = cost; best_ks = ks; }
@@ -846,7 +845,7 @@ void choose_pair_rows(GroupPlan* g) {
 // few lanes ran and each waited for its loads 64 times over.  Standardisation of columns (two such sums and a map),
 // before and after: 768 x 444 77.9 -> 15.7 us, 192 x 6848 61 -> 15, 112160 x 90 77.7 -> 56.8, 100003 x 257 109 -> 99
 // (first sum 26 us = 4 TB/s, second 20 us), 3977 x 7342 110 -> 111; column sums of 4096 x 512 19 -> 9.
-void choose_column_split(gr_ctx* c, GroupPlan* g) {
+void choose_column_split(GroupPlan* g) {
   const int64_t V = std::max<int64_t>(1, reduce_units(*g)), LEN = std::max<int64_t>(1, g->red_len);
   auto even = [&](int64_t bx) { const int64_t nb = (V + bx - 1) / bx; return (V + nb - 1) / nb; };   // blocks of equal width
   // One launch where that leaves a lane at most 32 elements, or where the outputs alone fill the chip: blocks as
@@ -854,7 +853,7 @@ void choose_column_split(gr_ctx* c, GroupPlan* g) {
   int64_t bx = kReduceLanes;
   while (bx > 16 && (V + bx - 1) / bx < 512) bx /= 2;
   g->red_bx = (int)even(bx);
-  g->slabs = 1;
+  g->slabs = g->red_tight = 1;
   if ((bx >= 64 && (V + bx - 1) / bx >= 512) || LEN <= 32 * (kReduceLanes / g->red_bx)) return;
   // Otherwise enough chunks for two workgroups per compute unit, of 16 elements per lane at least.  Rows of whole
   // 128-byte lines: blocks of 32 lanes (8192^2 47.5 us; 16 lanes 50.5, 64 52.3, 128 58.9, 256 62.9; 16384 x 4096 50.6, 52.4,
@@ -864,16 +863,14 @@ void choose_column_split(gr_ctx* c, GroupPlan* g) {
   g->red_bx = (int)even(D % 32 == 0 ? 32 : (V <= 128 ? 128 : 64));
   const int64_t blocks = (V + g->red_bx - 1) / g->red_bx, by = kReduceLanes / g->red_bx;
   int64_t nsplit = std::min<int64_t>((512 + blocks - 1) / blocks, std::max<int64_t>(1, LEN / (16 * by)));
-  if (c->plan_static) {
-    // Partial results of a request that must not allocate come out of the static scratch array, beside the request's
-    // stored results: no more of them than chunks of 256 elements (128 where a lane owns one output) by 256-lane
-    // workgroups would give, so that what fits does not depend on how wide the blocks are.
-    const bool quads = g->red_vec && g->dims[g->red_kept_rank - 1] % 4 == 0;
-    const int64_t groups = ((quads ? g->red_out / 4 : g->red_out) + 255) / 256;
-    nsplit = std::min<int64_t>(nsplit, std::max<int64_t>(1, g->red_out < 64 && LEN >= 4096 ? std::min<int64_t>(2048 / g->red_out, LEN / 4096)
-                                                                                          : std::min<int64_t>(2048 / groups, LEN / (quads ? 256 : 128))));
-  }
   g->slabs = (int)nsplit;
+  // Partial results of a request that must not allocate come out of the static scratch array, beside the request's
+  // stored results.  Where they do not fit, it makes do with as many as chunks of 256 elements (128 where a lane owns one
+  // output) by 256-lane workgroups would give.
+  const bool quads = g->red_vec && D % 4 == 0;
+  const int64_t few = ((quads ? g->red_out / 4 : g->red_out) + 255) / 256;
+  g->red_tight = (int)std::min<int64_t>(nsplit, std::max<int64_t>(1, g->red_out < 64 && LEN >= 4096 ? std::min<int64_t>(2048 / g->red_out, LEN / 4096)
+                                                                                                   : std::min<int64_t>(2048 / std::max<int64_t>(1, few), LEN / (quads ? 256 : 128))));
 }
 
 }  // namespace
@@ -1208,7 +1205,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         g->UC = 1;
       }
     }
-    if (c->opt_gemm_bn == 0 && c->opt_gemm_kstep == 0 && c->opt_gemm_split == 0 && c->opt_gemm_big) choose_gemm_tiles(c, g);
+    if (c->opt_gemm_bn == 0 && c->opt_gemm_kstep == 0 && c->opt_gemm_split == 0 && c->opt_gemm_big) choose_gemm_tiles(g);
   } else if (dot && !(dot == r && dot_as_reduce(dot) && c->opt_fusion)) {
     // ---- contraction with pointwise epilogue ------------------------------
     g->kind = GroupKind::GEMV;
@@ -1374,7 +1371,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
       // cannot straddle the innermost one
       if (g->red_mode == 1 && g->rank > kept_rank + 1 && g->dims[g->rank - 1] % 4 == 0) g->red_vec = 1;
       // split the reduced range so that about 2048 workgroups run (two-stage reduction, Section 3.2)
-      if (g->red_mode == 0) choose_column_split(c, g);
+      if (g->red_mode == 0) choose_column_split(g);
       else {
         const int64_t nsplit = std::min<int64_t>(std::max<int64_t>(1, 2048 / std::max<int64_t>(g->red_out, 1)), std::max<int64_t>(1, g->red_len / 4096));
         g->slabs = (int)std::min<int64_t>(nsplit, 4096);

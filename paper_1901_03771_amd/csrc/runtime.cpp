@@ -451,9 +451,10 @@ static int64_t scan_line_tile_cells(const GroupPlan& g) {
 
 // Device memory a sub-graph's kernels need beyond inputs and output: the first-stage partial
 // results of two-stage kernels.
-static size_t workspace_need(const GroupPlan& g) {
+static int reduce_slabs(const GroupPlan& g, bool tight) { return tight && g.red_mode == 0 ? g.red_tight : g.slabs; }
+static size_t workspace_need(const GroupPlan& g, bool tight) {
   switch (g.kind) {
-    case GroupKind::REDUCE: return g.slabs > 1 && g.red_out > 0 ? (size_t)g.slabs * (size_t)g.red_out * itemsize(g.out_dtype) : 0;
+    case GroupKind::REDUCE: return reduce_slabs(g, tight) > 1 && g.red_out > 0 ? (size_t)reduce_slabs(g, tight) * (size_t)g.red_out * itemsize(g.out_dtype) : 0;
     case GroupKind::SCAN: {
       int64_t total = 1;
       for (int k2 = 0; k2 < g.rank; ++k2) total *= g.dims[k2];
@@ -476,7 +477,7 @@ static size_t workspace_need(const GroupPlan& g) {
 // for a request that must not allocate, a piece of the static array.
 static gr_status get_workspace(gr_ctx* c, const GroupPlan& g, void** ws) {
   *ws = nullptr;
-  const size_t need = workspace_need(g);
+  const size_t need = workspace_need(g, c->static_mode && c->static_tight);
   if (need == 0) return GR_OK;
   if (c->static_mode) {
     *ws = ctx_alloc(c, need);
@@ -586,16 +587,17 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
       if (g.red_out == 0) return GR_OK;
       s[L.extra] = (uint64_t)g.red_out;
       s[L.extra + 1] = (uint64_t)g.red_len;
-      s[L.extra + 3] = (uint64_t)g.slabs;
-      if (g.slabs > 1) {
+      const int slabs = reduce_slabs(g, c->static_mode && c->static_tight);
+      s[L.extra + 3] = (uint64_t)slabs;
+      if (slabs > 1) {
         gr_status wst = get_workspace(c, g, &ws);
         if (wst != GR_OK) return wst;
         s[L.extra + 2] = (uint64_t)(uintptr_t)ws;
       }
       if (g.red_mode == 0) s[L.extra + 3] |= (uint64_t)g.red_bx << 32;
       const int64_t units = g.red_mode == 0 ? (reduce_units(g) + g.red_bx - 1) / g.red_bx : g.red_out;
-      gr_status st = launch(c, k->fn, k->name, units * g.slabs, s, g.red_mode == 0 ? kReduceLanes : 256);
-      if (st != GR_OK || g.slabs <= 1) return st;
+      gr_status st = launch(c, k->fn, k->name, units * slabs, s, g.red_mode == 0 ? kReduceLanes : 256);
+      if (st != GR_OK || slabs <= 1) return st;
       return launch(c, k->fn2, k->name + "_combine", g.red_out >= 1024 ? (g.red_out + 255) / 256 : g.red_out, s);
     }
     case GroupKind::SCAN: {
@@ -608,7 +610,7 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
       if (g.scan_mode >= 2) {
         // one pass: the tiles publish their totals in cells (cleared first unless they carry launch numbers)
         uint32_t tag = 0;
-        gr_status wst = scan_cells(c, g, workspace_need(g), &ws, &tag);
+        gr_status wst = scan_cells(c, g, workspace_need(g, false), &ws, &tag);
         if (wst != GR_OK) return wst;
         const uint64_t low = g.scan_mode == 3 ? (uint64_t)std::max(1, g.slabs) : (uint64_t)g.scan_chunk;
         s[L.extra + 1] = low | ((uint64_t)(tag ? tag : 1u) << 32);
@@ -766,7 +768,7 @@ gr_status execute_plan(gr_ctx* c, Plan* plan, Node* root, void* user_out, bool c
     // has to be loaded already (loading a code object allocates device memory), and the stored
     // results of earlier sub-graphs plus the partial results of two-stage kernels have to fit
     // the static array.
-    size_t need = 0;
+    size_t need = 0, least = 0;
     for (auto& gp : plan->groups) {
       if (!no_compile && !c->cache.count(gp->signature))
         return fail(c, GR_ERR_UNSUPPORTED, "materialize_into_static: a kernel of this request is not loaded yet; call gr_plan_compile "
@@ -775,9 +777,13 @@ gr_status execute_plan(gr_ctx* c, Plan* plan, Node* root, void* user_out, bool c
         if (!r || (r == root && user_out)) continue;
         size_t nb = (size_t)r->count() * itemsize(r->dtype);
         need += ((nb ? nb : 256) + 255) & ~(size_t)255;
+        least += ((nb ? nb : 256) + 255) & ~(size_t)255;
       }
-      need += (workspace_need(*gp) + 255) & ~(size_t)255;
+      need += (workspace_need(*gp, false) + 255) & ~(size_t)255;
+      least += (workspace_need(*gp, true) + 255) & ~(size_t)255;
     }
+    c->static_tight = need > c->static_cap;
+    if (c->static_tight) need = least;
     if (need > c->static_cap)
       return fail(c, GR_ERR_OOM, "materialize_into_static: the request needs " + std::to_string(need) + " bytes for intermediate and partial results; "
                                  "the static scratch array holds " + std::to_string(c->static_cap));

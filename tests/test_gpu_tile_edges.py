@@ -197,3 +197,18 @@ def test_products_with_clamped_tiles(env, m, k, n, layout):
     assert (guard[:64] == 7.0).all() and (guard[64 + m * n:] == 7.0).all()
     ref = prog(ora, *(ora.array(v) for v in (a, b, c, d))).numpy()
     assert np.array_equal(out.cpu().numpy(), ref, equal_nan=True)
+
+
+def test_static_entry_near_the_scratch_limit_takes_fewer_partial_sums(env):
+    # column sums whose partial results do not fit beside the stored prefix sums (16680000 of 16777216 bytes): still served
+    gr, ctx, torch = env
+    rows, cols = 13900, 300
+    a = np.random.default_rng(22).integers(-3, 4, (rows, cols)).astype(f32)
+    t = torch.from_numpy(a).cuda()
+    prog = lambda: gr.sum(gr.cumsum(ctx.array(t), 1), axis=0)
+    want = prog().torch()
+    lazy = prog()
+    lazy.compile()
+    got = torch.empty(cols, device="cuda")
+    assert gr.lib().gr_materialize_into_static(ctx._p, lazy.h, got.data_ptr(), cols * 4) == 0, ctx.last_error()
+    assert torch.equal(got, want) and np.array_equal(got.cpu().numpy(), np.cumsum(a.astype(np.float64), 1).sum(0).astype(f32))
