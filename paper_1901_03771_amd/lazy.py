@@ -238,6 +238,10 @@ class Context:
     # -- leaves ---------------------------------------------------------------
     def from_device(self, ptr: int, dtype: int, shape: Sequence[int], strides: Optional[Sequence[int]] = None,
                     owner=None) -> "Array":
+        if _fastbind is not None:
+            a = _fastbind.leaf(Array, self, ptr, dtype, shape, strides, owner)
+            if a is not None:
+                return a
         n = len(shape)
         T = _I64_ARRAYS[n]
         h = ctypes.c_uint64()
@@ -533,7 +537,7 @@ class Array(_PyArrayBase if _fastbind is None else _fastbind.ArrayBase, _ArrayMe
 def _bind_fast_paths(L):
     if _fastbind is None:
         return
-    names = ["gr_unary", "gr_binary", "gr_binary_scalar", "gr_slice", "gr_transpose", "gr_dot", "gr_assign",
+    names = ["gr_array_from_device", "gr_unary", "gr_binary", "gr_binary_scalar", "gr_slice", "gr_transpose", "gr_dot", "gr_assign",
              "gr_materialize", "gr_release", "gr_reduce", "gr_ndim", "gr_shape", "gr_materialize_into",
              "gr_materialize_into_static", "gr_is_materialized", "gr_program_run"]
     _fastbind.bind({n: ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in names})
