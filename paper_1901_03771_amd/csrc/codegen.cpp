@@ -1098,16 +1098,21 @@ void gen_reduce_columns(Em& e) {
   e.o << "}\n    return;\n  }\n"
          "  __shared__ " << T << " sm[" << W << "][" << kReduceLanes << "];\n";
   for (int c = 0; c < W; ++c) e.o << "  sm[" << c << "][threadIdx.x] = acc" << c << ";\n";
-  e.o << "  __syncthreads();\n"
+  // (many lanes to an output: sixteen of them first, so that no lane adds more than a sixteenth of the partial results in turn)
+  e.o << "  __syncthreads();\n  unsigned ny = BY;\n  if (BY > 16) {\n    if (ok && ty < 16) for (unsigned q = ty + 16; q < BY; q += 16) {\n";
+  for (int c = 0; c < W; ++c) e.o << "      acc" << c << " = gr_comb0(acc" << c << ", sm[" << c << "][q * BX + tx]);\n";
+  e.o << "    }\n    __syncthreads();\n    if (ok && ty < 16) {\n";
+  for (int c = 0; c < W; ++c) e.o << "      sm[" << c << "][threadIdx.x] = acc" << c << ";\n";
+  e.o << "    }\n    __syncthreads();\n    ny = 16;\n  }\n"
          "  if (ok) for (unsigned c = ty; c < " << W << "u; c += BY) {\n"
          "    " << T << " r = sm[c][tx];\n"
          "    unsigned q = 1;\n"
-         "    for (; q + 8 <= BY; q += 8) {\n"   // eight LDS reads in flight
+         "    for (; q + 8 <= ny; q += 8) {\n"   // eight LDS reads in flight
          "      " << T << " w[8];\n"
          "#pragma unroll\n      for (int u = 0; u < 8; ++u) w[u] = sm[c][(q + u) * BX + tx];\n"
          "#pragma unroll\n      for (int u = 0; u < 8; ++u) r = gr_comb0(r, w[u]);\n"
          "    }\n"
-         "    for (; q < BY; ++q) r = gr_comb0(r, sm[c][q * BX + tx]);\n"
+         "    for (; q < ny; ++q) r = gr_comb0(r, sm[c][q * BX + tx]);\n"
          "    dst[o + c] = r;\n  }\n}\n";
   reduce_combine(e);
 }
