@@ -846,14 +846,15 @@ void choose_pair_rows(GroupPlan* g) {
 // before and after: 768 x 444 77.9 -> 15.7 us, 192 x 6848 61 -> 15, 112160 x 90 77.7 -> 56.8, 100003 x 257 109 -> 99
 // (first sum 26 us = 4 TB/s, second 20 us), 3977 x 7342 110 -> 111; column sums of 4096 x 512 19 -> 9.
 void choose_column_split(GroupPlan* g) {
-  const int64_t V = std::max<int64_t>(1, reduce_units(*g)), LEN = std::max<int64_t>(1, g->red_len);
+  g->slabs = g->red_tight = 1;
+  if (g->red_out == 0) return;   // nothing to launch
+  const int64_t V = reduce_units(*g), LEN = std::max<int64_t>(1, g->red_len);
   auto even = [&](int64_t bx) { const int64_t nb = (V + bx - 1) / bx; return (V + nb - 1) / nb; };   // blocks of equal width
   // One launch where that leaves a lane at most 32 elements, or where the outputs alone fill the chip: blocks as
   // wide as still give 512 workgroups, 16 lanes (256 bytes) at least.
   int64_t bx = kReduceLanes;
   while (bx > 16 && (V + bx - 1) / bx < 512) bx /= 2;
   g->red_bx = (int)even(bx);
-  g->slabs = g->red_tight = 1;
   if ((bx >= 64 && (V + bx - 1) / bx >= 512) || LEN <= 32 * (kReduceLanes / g->red_bx)) return;
   // Otherwise enough chunks for two workgroups per compute unit, of 16 elements per lane at least.  Rows of whole
   // 128-byte lines: blocks of 32 lanes (8192^2 47.5 us; 16 lanes 50.5, 64 52.3, 128 58.9, 256 62.9; 16384 x 4096 50.6, 52.4,

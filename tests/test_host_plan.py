@@ -7,6 +7,8 @@ compiles for gfx950."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -433,6 +435,20 @@ def test_row_resident_limit_turns_reduction_into_a_cut(ctx):
     ctx.set_option("rowred_max_cols", 512)
     assert [k for k, _ in groups(wl.softmax(gr, ctx.spec((8, 1000))))] == ["REDUCE", "MAP", "REDUCE", "MAP"]
     assert [k for k, _ in groups(wl.softmax(gr, ctx.spec((8, 512))))] == ["ROWRED"]
+
+
+@pytest.mark.parametrize("shape,axis", [((40000, 0), 0), ((40000, 3, 0), 0), ((40000, 0, 5), 0), ((3, 40000, 0), 1), ((0, 40000, 5), 1)])
+def test_reductions_without_outputs_are_planned(ctx, shape, axis):
+    # (in a process of its own: dividing the reduced range among no outputs would end the whole run)
+    code = f"""from paper_1901_03771_amd import lazy as gr
+ctx = gr.Context(device=-1)
+ctx.set_option("dry_run", 2)
+y = gr.sum(ctx.spec({shape}) * 2.0, axis={axis})
+print(y.plan())
+y.materialize()
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert r.returncode == 0 and "REDUCE" in r.stdout, (r.returncode, r.stderr)
 
 
 # ------------------------------------------------- code generation on the host ----
