@@ -733,7 +733,10 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
 // and large products of two operands contiguous along k (4001^3 1082 / 1111; the other layouts 1201 / 1143 and
 // 1318 / 1152); and from the direct 128 x 128 kernel where its cost is 2 lower (4096 x 784 x 512 42 / 39; 4096 x 512 x 784 stays: 37
 // against 45).
-void choose_gemm_tiles(GroupPlan* g) {
+// `wanted`: splits of K that the larger tiles would take if they may store any number of partial tiles.  It decides
+// between the kernels, so that a request that must not allocate takes the kernel that the same request would take
+// otherwise (and that is loaded by then); g->slabs, which stays within its scratch array, bounds the splits.
+void choose_gemm_tiles(GroupPlan* g, int wanted) {
   if (g->VR == 2 && g->BX != 128) return;
   const int64_t M = g->M, N = g->N, K = g->K;
   auto fits = [&](const AccessGroup& x, int kdim, int64_t other) {
@@ -752,22 +755,26 @@ void choose_gemm_tiles(GroupPlan* g) {
   }
   // Every accumulator adds two chains: at least half as many splits as the larger tiles would take, so that no chain gets
   // longer, and no more than those, so that the partial tiles need no more memory (of a request that must not allocate).
-  const int before = g->slabs;
-  double best = 0;
-  int best_ks = 0;
-  for (int ks = (before + 1) / 2; ks <= before; ++ks) {
-    const int64_t kch = gemm_split_extent(K, ks);
-    const double rounds = (double)((tiles * ks + 255) / 256);
-    const double cost = rounds * (double)((kch + 31) / 32) * 0.62 + 5.0 + (ks > 1 ? 4.0 + (double)ks * (double)M * (double)N * 8.0 / 5e6 : 0.0);
-    if (best_ks == 0 || cost < best * 0.97) { best = cost; best_ks = ks; }
-  }
+  double cost = 0;
+  auto cheapest = [&](int before) {
+    int best_ks = 0;
+    for (int ks = (before + 1) / 2; ks <= before; ++ks) {
+      const int64_t kch = gemm_split_extent(K, ks);
+      const double rounds = (double)((tiles * ks + 255) / 256);
+      const double us = rounds * (double)((kch + 31) / 32) * 0.62 + 5.0 + (ks > 1 ? 4.0 + (double)ks * (double)M * (double)N * 8.0 / 5e6 : 0.0);
+      if (best_ks == 0 || us < cost * 0.97) { cost = us; best_ks = ks; }
+    }
+    return best_ks;
+  };
+  const int before = g->slabs, best_ks = cheapest(before);
   if (g->VR == 2) {
     // (long sums over small results stay with the direct kernel's division of K, whose tests hold it to that: a bound of its
     // own, not a measured crossing; 640 x 512 x 1024 and the like may be faster here)
     if (K >= 512 && M * N < (int64_t)1 << (K == 512 ? 18 : 20)) return;
-    const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128) * before, steps = (gemm_split_extent(K, before) + 15) / 16;
-    const double direct = (double)((wgs + 255) / 256) * (double)steps * (wgs <= 256 ? 1.1 : 0.95) + 2.0 + (before > 1 ? 6.0 + (double)before * (double)M * (double)N * 8.0 / 5e6 : 0.0);
-    if (best + 2.0 > direct) return;
+    cheapest(wanted);
+    const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128) * wanted, steps = (gemm_split_extent(K, wanted) + 15) / 16;
+    const double direct = (double)((wgs + 255) / 256) * (double)steps * (wgs <= 256 ? 1.1 : 0.95) + 2.0 + (wanted > 1 ? 6.0 + (double)wanted * (double)M * (double)N * 8.0 / 5e6 : 0.0);
+    if (cost + 2.0 > direct) return;
   }
   g->VR = 3;
   g->UC = 1;
@@ -1125,6 +1132,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
     // few output tiles and a long contraction: split K over workgroups (about 512 of them, at
     // least 128 k per split); the partial tiles are combined by a second kernel
     g->slabs = 1;
+    int wanted = 0;   // splits of K by the direct 128 x 128 kernel if any number of partial tiles may be stored
     // columns of the output tile of one workgroup: 128, or 32 for narrow results and where the last
     // 128-wide tile would be more than half empty (measured, 65536 x 64 x 64: 14.5 us against 21.8 us;
     // 8192 x 512 x 520: 67 against 94 us; a full 128-wide tile costs about 0.3 of four 32-wide ones less)
@@ -1187,16 +1195,20 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         // split: 1024^3 30 / 68 / 38 us, 1536^3 77 / 98 / 90, 3072^3 442 / 525 / 598, 8192 x 256 x 8192 273 / 499 / 306,
         // 1024 x 1024 x 8192 139 / 493 / 159, 512 x 512 x 16384 80 / 976 / 89)
         const int64_t tiles128 = ((g->M + 127) / 128) * ((g->N + 127) / 128);
-        const int64_t room = c->plan_static ? (int64_t)(c->static_cap / sizeof(float)) : (int64_t)1 << 28;   // floats of partial tiles
-        double best = 0;
-        int best_ks = 0;
-        for (int ks = 1; ks <= 64; ++ks) {
-          const int64_t kch = gemm_split_extent(g->K, ks);
-          if (ks > 1 && (kch < 128 || g->K - (ks - 1) * kch < 32 || (int64_t)ks * g->M * g->N > room)) continue;
-          const int64_t wgs = tiles128 * ks, rnd = (wgs + 255) / 256, steps = (kch + 15) / 16;
-          const double cost = (double)rnd * (double)steps * (wgs <= 256 ? 1.1 : 0.95) + (ks > 1 ? 6.0 + (double)ks * (double)g->M * (double)g->N * 8.0 / 5e6 : 0.0);
-          if (best_ks == 0 || cost < best * 0.97) { best = cost; best_ks = ks; }
-        }
+        auto cheapest = [&](int64_t room) {   // room: floats of partial tiles
+          double best = 0;
+          int best_ks = 0;
+          for (int ks = 1; ks <= 64; ++ks) {
+            const int64_t kch = gemm_split_extent(g->K, ks);
+            if (ks > 1 && (kch < 128 || g->K - (ks - 1) * kch < 32 || (int64_t)ks * g->M * g->N > room)) continue;
+            const int64_t wgs = tiles128 * ks, rnd = (wgs + 255) / 256, steps = (kch + 15) / 16;
+            const double cost = (double)rnd * (double)steps * (wgs <= 256 ? 1.1 : 0.95) + (ks > 1 ? 6.0 + (double)ks * (double)g->M * (double)g->N * 8.0 / 5e6 : 0.0);
+            if (best_ks == 0 || cost < best * 0.97) { best = cost; best_ks = ks; }
+          }
+          return best_ks;
+        };
+        wanted = cheapest((int64_t)1 << 28);
+        const int best_ks = c->plan_static ? cheapest((int64_t)(c->static_cap / sizeof(float))) : wanted;
         g->slabs = best_ks;
         g->VR = 2;
         g->UC = 1;
@@ -1206,7 +1218,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         g->UC = 1;
       }
     }
-    if (c->opt_gemm_bn == 0 && c->opt_gemm_kstep == 0 && c->opt_gemm_split == 0 && c->opt_gemm_big) choose_gemm_tiles(g);
+    if (c->opt_gemm_bn == 0 && c->opt_gemm_kstep == 0 && c->opt_gemm_split == 0 && c->opt_gemm_big) choose_gemm_tiles(g, wanted ? wanted : g->slabs);
   } else if (dot && !(dot == r && dot_as_reduce(dot) && c->opt_fusion)) {
     // ---- contraction with pointwise epilogue ------------------------------
     g->kind = GroupKind::GEMV;

@@ -451,6 +451,26 @@ y.materialize()
     assert r.returncode == 0 and "REDUCE" in r.stdout, (r.returncode, r.stderr)
 
 
+def _served_without_allocating(ctx, first, then):
+    """A request like `first` is evaluated (its kernels are loaded), then `then` through the entry point that allocates nothing."""
+    ctx.set_option("dry_run", 1)
+    ctx.set_option("interp", 0)
+    first().materialize()
+    y = then()
+    nbytes = 8 if y.dtype_code == gr.GR_I64 else 4
+    for n in y.shape:
+        nbytes *= n
+    return gr.STATUS[gr.lib().gr_materialize_into_static(ctx._p, y.h, ctypes.c_void_p(0x500000000000), nbytes)]
+
+
+@pytest.mark.parametrize("m,k,n,layout", [(448, 9168, 2992, "nt"), (480, 2864, 4176, "tt"), (832, 5632, 2432, "nn"), (576, 3504, 2528, "tn")])
+def test_products_take_the_same_kernel_within_the_static_scratch(ctx, m, k, n, layout):
+    # fewer partial tiles fit the static scratch array than the request would like: the split of K shrinks, the kernel stays
+    a, b = ctx.spec((m, k) if layout[0] == "n" else (k, m)), ctx.spec((k, n) if layout[1] == "n" else (n, k))
+    prog = lambda: (a if layout[0] == "n" else a.T) @ (b if layout[1] == "n" else b.T)
+    assert _served_without_allocating(ctx, prog, prog) == "GR_OK", ctx.last_error()
+
+
 # ------------------------------------------------- code generation on the host ----
 def _specs(ctx, arrays):
     code = {np.dtype(np.float32): gr.GR_F32, np.dtype(np.int32): gr.GR_I32}
