@@ -813,36 +813,88 @@ int rowred_live(const GroupPlan& g) {
   return most;
 }
 
-// Rows of at most 64 elements over two kept dimensions, each element a function of one operand that follows the first
-// of them and one that follows the second: a lane per row of the longer one (see gen_rowred_pairs).
+// Vector instructions per element of a row's value, about; 0 for a program with an operation that is a sequence of its own
+// (division, square root, exp, ...).
+int simple_issue(const GroupPlan& g, const std::vector<char>& in_value) {
+  int n = g.phases[0].out_dtype == GR_I64 ? 2 : (g.phases[0].op == GR_SUM ? 1 : (g.phases[0].in_dtype == GR_F32 ? 3 : 2));
+  for (size_t i = 0; i < g.prog.size(); ++i) {
+    const Instr& in = g.prog[i];
+    if (!in_value[i]) continue;
+    if (in.kind == IKind::UNARY) {
+      if (in.op == GR_NEG || in.op == GR_ABS) n += in.dtype == GR_F32 ? 0 : 1;   // (modifiers of the instruction that reads them)
+      else if (in.op == GR_SQUARE) n += in.dtype == GR_F32 ? 1 : 2;
+      else return 0;
+    } else if (in.kind == IKind::BINARY) {
+      if (in.op == GR_ADD || in.op == GR_SUB) n += 1;
+      else if (in.op == GR_MUL) n += in.dtype == GR_F32 ? 1 : 2;
+      else if (in.op == GR_MAXIMUM || in.op == GR_MINIMUM) n += in.dtype == GR_F32 ? 3 : 2;
+      else return 0;
+    } else if (in.kind != IKind::LOAD && in.kind != IKind::CONST) return 0;
+  }
+  return n;
+}
+
+// Rows of at most 64 elements over two kept dimensions, each element a function of operands that follow the first
+// of them and operands that follow the second: a lane per row of the longer one (see gen_rowred_pairs).
 // (Squared distances, general kernel against this one, us: 262144 points to 32 centres in 16 dimensions 44.6 / 15.0, vector issue
 // alone 11; 811856 x 7 x 38 284 / 32; 178688 x 27 x 47 205 / 24; 65536 x 64 x 64 79 / 24; 100000 x 8 x 8 5.3 / 5.1.  The row length is
 // compiled in: beyond 64 elements the lane groups read whole lines of both operands and stay.)
+// Where it loses, general / this one, us:
+// - anything but additions, products, minima and the like: issue bounds both kernels, and K x 4 copies of an exp or a
+//   division leave one wave per SIMD or spill (65536 x 32 x 64: sum of exp 72 / 173, of sqrt 63 / 127, of a log(a / b) 98 /
+//   203, of exp(a - b) tanh(a b) 136 / 936; 200000 x 8 x 8: a / b 8.3 / 9.2);
+// - long rows of several operands: their registers (three 300 x 3000 x 64 29 / 42; two 65536 x 32 x 64 55 / 35), or the
+//   scalar unit's (two 200000 x 8 x 64 35 / 37), or many instructions for each (seven, 20000 x 64 x 64 28 / 29, 20000 x 16 x 32 5.2 / 7.5);
+// - few pairs, which leave compute units idle: the cheapest programs below 2^17 (5000 x 16 x 64 4.7 / 5.6; 10000 x 16 x 64
+//   7.0 / 5.7), others below 2^18 and with rows over 24 elements below 2^20 (cheb 20000 x 16 x 32 5.7 / 6.9; 20000 x 64 x 32 16.7 / 12.1);
+// - rows of four, which the general kernel reads with one load each, unless the program is short (seven instructions 20000 x 64 4.4 / 4.9);
+// - short rows whose results a lane stores, or reads, apart: 64-bit results and operands of the epilogue that follow both
+//   dimensions, where the lane's is the outer one (i32 sums 65536 x 32 of 4 6.9 / 12.6, of 8 10.3 / 13.0, of 12 25.0 / 13.1; a matrix
+//   added to 20000 x 64 of 8 7.8 / 8.6, of 12 18.6 / 8.5).
 void choose_pair_rows(GroupPlan* g) {
   if (!g->out_per_row || g->phases.size() != 1 || g->rank != 3 || g->results.empty()) return;
-  const int64_t K = g->dims[2];
+  const int64_t K = g->dims[2], pairs = g->dims[0] * g->dims[1];
   if (K < 2 || K > 64 || g->NP != 1 || std::min(g->dims[0], g->dims[1]) < 4 || std::max(g->dims[0], g->dims[1]) < 256) return;
-  std::vector<char> seen(g->prog.size(), 0);
-  std::vector<int> work{g->phases[0].value};
-  bool follows[2] = {false, false};
-  while (!work.empty()) {
-    const int i = work.back();
-    work.pop_back();
-    if (i < 0 || seen[i]) continue;
-    seen[i] = 1;
-    const Instr& in = g->prog[i];
-    if (in.dtype == GR_I64 || in.kind == IKind::RED) return;
-    if (in.kind == IKind::LOAD) {
-      const AccessGroup& ag = g->groups[in.group];
-      if (!ag.structural_zero[0] && !ag.structural_zero[1]) return;
-      if (!ag.structural_zero[2]) for (int d = 0; d < 2; ++d) if (!ag.structural_zero[d]) follows[d] = true;
+  const int ld = g->dims[0] >= g->dims[1] ? 0 : 1;
+  auto value = [&](int root) {
+    std::vector<char> seen(g->prog.size(), 0);
+    std::vector<int> work{root};
+    while (!work.empty()) {
+      const int i = work.back();
+      work.pop_back();
+      if (i < 0 || seen[i]) continue;
+      seen[i] = 1;
+      work.push_back(g->prog[i].a);
+      work.push_back(g->prog[i].b);
     }
-    work.push_back(in.a);
-    work.push_back(in.b);
+    return seen;
+  };
+  const std::vector<char> in_value = value(g->phases[0].value);
+  int held[2] = {0, 0};   // operands whose rows a lane holds, and that come through the scalar unit
+  bool follows[2] = {false, false};
+  for (size_t i = 0; i < g->prog.size(); ++i) {
+    const Instr& in = g->prog[i];
+    if (!in_value[i]) continue;
+    if (in.dtype == GR_I64 || in.kind == IKind::RED) return;
+    if (in.kind != IKind::LOAD) continue;
+    const AccessGroup& ag = g->groups[in.group];
+    if (!ag.structural_zero[0] && !ag.structural_zero[1]) return;
+    if (ag.structural_zero[2]) continue;
+    for (int d = 0; d < 2; ++d) if (!ag.structural_zero[d]) follows[d] = true;
+    ++held[ag.structural_zero[ld] ? 1 : 0];
   }
-  if (!follows[0] || !follows[1] || seen.size() > 24) return;
+  if (!follows[0] || !follows[1]) return;
+  const int issue = simple_issue(*g, in_value);
+  if (issue == 0 || issue > (K <= 4 ? 4 : (K <= 24 ? 8 : 5)) || held[0] * K > 128 || held[1] * K > 64) return;
+  const bool cheap = issue <= 3 && held[0] == 1 && held[1] == 1;
+  if (pairs < (int64_t)1 << (cheap ? 17 : (K <= 24 ? 18 : 20))) return;
+  bool apart = g->out_dtype == GR_I64;
+  const std::vector<char> in_result = value(g->results[0]);
+  for (size_t i = 0; i < g->prog.size(); ++i)
+    if (in_result[i] && !in_value[i] && g->prog[i].kind == IKind::LOAD && !g->groups[g->prog[i].group].structural_zero[0] && !g->groups[g->prog[i].group].structural_zero[1]) apart = true;
+  if (apart && ld == 0 && K <= 8) return;
   g->pair_k = (int)K;
-  g->pair_lane = g->dims[0] >= g->dims[1] ? 0 : 1;
+  g->pair_lane = ld;
 }
 
 // REDUCE mode 0: how many lanes of a workgroup lie across the outputs (the rest along the reduced range) and
@@ -1717,7 +1769,11 @@ std::string describe_plan(const Plan& plan) {
       for (const Node* n : g.pair->members) { if (n->is_view()) continue; s << (f2 ? "" : ",") << n->id << ':' << node_label(n); f2 = false; }
       s << "]]";
     }
-    if (g.kind == GroupKind::ROWRED) s << " phases=" << g.phases.size() << " row_threads=" << g.row_threads << " NP=" << g.NP << (g.row_iters > 1 ? " rows_per_group=" + std::to_string(g.row_iters) : std::string());
+    if (g.kind == GroupKind::ROWRED) {
+      s << " phases=" << g.phases.size() << " row_threads=" << g.row_threads << " NP=" << g.NP;
+      if (g.pair_k) s << " pairs: length=" << g.pair_k << " lanes_along=" << g.pair_lane;
+      else if (g.row_iters > 1) s << " rows_per_group=" << g.row_iters;
+    }
     if (g.kind == GroupKind::SCAN) s << " mode=" << (g.scan_mode == 4 ? "lines-in-lane-groups" : g.scan_mode == 3 ? "one-pass-line-tiles" : (g.scan_mode == 2 ? "one-pass-tiles" : (g.scan_mode ? "thread-per-line" : "lanes-along-axis"))) << " lines=" << g.red_out << " length=" << g.red_len << " chunks=" << g.scan_nchunk;
     if (g.kind == GroupKind::MAP) s << " tile=" << g.BY * g.VR << "x" << g.BX * 4 * g.UC << " patch=" << g.VR << "x" << g.UC * 4;
     s << '\n';

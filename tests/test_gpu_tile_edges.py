@@ -91,19 +91,41 @@ def test_in_place_maps_of_ragged_rows(env, shape):
     assert np.array_equal(A.numpy(), B.numpy()) and np.array_equal(t.cpu().numpy(), B.numpy())
 
 
+def planned(env, program, **arrays):
+    gr, ctx, torch = env
+    code = {np.dtype(f32): gr.GR_F32, np.dtype(np.int32): gr.GR_I32}
+    return program(gr, **{k: ctx.spec(v.shape, code[v.dtype]) for k, v in arrays.items()}).plan()
+
+
 # pairs of rows: a lane per row of the longer operand; row lengths around the groups of four and the lane groups of the
-# general kernel (whose order of additions is kept), few and many rows of the other operand, either operand the longer one
-@pytest.mark.parametrize("n,c,d", [(256, 4, 2), (257, 5, 4), (300, 7, 5), (1000, 19, 16), (1001, 33, 17), (4099, 6, 31), (511, 64, 33), (2049, 9, 63), (700, 3, 64),
-                                   (5, 1030, 12), (260, 260, 54)])
-def test_rows_over_pairs(env, n, c, d):
+# general kernel (whose order of additions is kept), few and many rows of the other operand, either operand the longer one,
+# workgroups along the longer one that are fewer than the chiplets, a multiple of their number, beside one, and many.  `kernels`: of squared
+# distances with and without a matrix added to them, of a maximum of minima and of an i32 sum: P the pairs' kernel, - the general one
+@pytest.mark.parametrize("n,c,d,kernels", [
+    (256, 4, 2, "----"), (257, 5, 4, "----"), (300, 7, 5, "----"), (1000, 19, 16, "----"), (1001, 33, 17, "----"), (4099, 6, 31, "----"), (511, 64, 33, "----"), (2049, 9, 63, "----"),
+    (700, 3, 64, "----"), (5, 1030, 12, "----"), (260, 260, 54, "----"),
+    (32768, 4, 2, "-P--"), (32768, 5, 4, "-P--"), (28001, 5, 7, "-P--"), (65536, 4, 16, "PPPP"), (20001, 14, 9, "PPPP"), (4099, 65, 24, "PPPP"), (363, 362, 64, "PP--"), (300, 1030, 17, "PPPP"),
+    (1030, 300, 17, "PPPP"), (1100, 1030, 25, "PP-P"), (1030, 1100, 33, "PP-P"), (40001, 33, 63, "PP-P"), (65536, 18, 65, "----"), (400000, 3, 16, "----"), (5, 70000, 31, "PP--")])
+def test_rows_over_pairs(env, n, c, d, kernels):
     gr, ctx, torch = env
     a, b, w = positive((n, d), 13), positive((c, d), 14), positive((n, c), 15)
 
-    def distances(xp, a, b, w):
+    def squares(xp, a, b):
         diff = a - b
-        return xp.sqrt(xp.sum(diff * diff, axis=2)) + w
+        return xp.sum(diff * diff, axis=2)
 
+    def distances(xp, a, b, w):
+        return xp.sqrt(squares(xp, a, b)) + w
+
+    def route(program, **arrays):
+        return "P" if "pairs:" in planned(env, program, **arrays) else "-"
+
+    largest = lambda xp, a, b: xp.max(xp.minimum(a, b), axis=2)
+    products = lambda xp, i, j: xp.sum(i * j, axis=2)
+    i, j = (np.random.default_rng(16 + k).integers(-2**31, 2**31 - 1, s, dtype=np.int64).astype(np.int32) for k, s in enumerate(((n, 1, d), (1, c, d))))
     arrays = dict(a=a[:, None, :], b=b[None, :, :], w=w)
+    two = dict(a=a[:, None, :], b=b[None, :, :])
+    assert route(distances, **arrays) + route(squares, **two) + route(largest, **two) + route(products, i=i, j=j) == kernels
     got, ref = both(env, distances, **arrays)
     assert reduction_check(got, ref)[0].all()
     other = gr.Context()
@@ -112,10 +134,11 @@ def test_rows_over_pairs(env, n, c, d):
     assert np.array_equal(distances(gr, **{k: other.array(t) for k, t in keep.items()}).numpy(), got)
     other.sync()
     other.close()
-    got, ref = both(env, lambda xp, a, b: xp.max(xp.minimum(a, b), axis=2), a=a[:, None, :], b=b[None, :, :])
+    got, ref = both(env, squares, **two)
+    assert reduction_check(got, ref)[0].all()
+    got, ref = both(env, largest, **two)
     assert np.array_equal(got, ref)
-    i, j = (np.random.default_rng(16 + k).integers(-2**31, 2**31 - 1, s, dtype=np.int64).astype(np.int32) for k, s in enumerate(((n, 1, d), (1, c, d))))
-    got, ref = both(env, lambda xp, i, j: xp.sum(i * j, axis=2), i=i, j=j)
+    got, ref = both(env, products, i=i, j=j)
     assert np.array_equal(got, ref)
 
 

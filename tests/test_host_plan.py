@@ -7,6 +7,7 @@ compiles for gfx950."""
 import ctypes
 import os
 import re
+import shutil
 import subprocess
 import sys
 
@@ -819,6 +820,62 @@ def test_generated_kernels_keep_their_values_in_registers(ctx, tmp_path):
         text = asm.read_text()
         assert "scratch_" not in text, name
         assert all(int(v) == 0 for v in re.findall(r"\.private_segment_fixed_size:\s+(\d+)", text)), name
+
+
+def _registers(out, tmp_path):
+    """(vector registers, bytes of scratch memory) per lane of the request's first kernel, compiled with the library's options."""
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not found")
+    src, asm = tmp_path / "k.hip", tmp_path / "k.s"
+    src.write_text("#include <hip/hip_runtime.h>\n" + out.source(0))
+    subprocess.run([hipcc, "--offload-arch=gfx950", "-O3", "-ffp-contract=off", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                    "-S", "--cuda-device-only", "-o", str(asm), str(src)], check=True, capture_output=True, timeout=600)
+    text = asm.read_text()
+    return tuple(max(int(v) for v in re.findall(key + r":\s+(\d+)", text)) for key in (r"\.vgpr_count", r"\.private_segment_fixed_size"))
+
+
+PAIR_PROGRAMS = {   # program, dtype, longest row that the kernel for pairs takes
+    "squares": (lambda a, b: gr.sum((a - b) * (a - b), axis=2), gr.GR_F32, 64),
+    "products": (lambda a, b: gr.sum(a * b, axis=2), gr.GR_F32, 64),
+    "largest difference": (lambda a, b: gr.max(abs(a - b), axis=2), gr.GR_F32, 64),
+    "smaller ones": (lambda a, b: gr.sum(gr.minimum(a, b), axis=2), gr.GR_F32, 64),
+    "largest of the smaller": (lambda a, b: gr.max(gr.minimum(a, b), axis=2), gr.GR_F32, 24),
+    "seven instructions": (lambda a, b: gr.sum((a - b) * (a + b) * (a * b + 1.0), axis=2), gr.GR_F32, 24),
+    "integers": (lambda a, b: gr.sum((a - b) * (a - b), axis=2), gr.GR_I32, 64),
+    "exp": (lambda a, b: gr.sum(gr.exp(-(a - b) * (a - b)), axis=2), gr.GR_F32, 0),
+    "exp and tanh": (lambda a, b: gr.sum(gr.exp(a - b) * gr.tanh(a * b), axis=2), gr.GR_F32, 0),
+    "log of a quotient": (lambda a, b: gr.sum(a * gr.log(a / b), axis=2), gr.GR_F32, 0),
+    "quotients": (lambda a, b: gr.sum(a / b, axis=2), gr.GR_F32, 0),
+    "roots": (lambda a, b: gr.sum(gr.sqrt(a * b), axis=2), gr.GR_F32, 0),
+}
+
+
+@pytest.mark.parametrize("name", sorted(PAIR_PROGRAMS))
+def test_row_pairs_are_taken_where_their_registers_suffice(ctx, tmp_path, name):
+    prog, dtype, longest = PAIR_PROGRAMS[name]
+
+    def planned(d, n=65536, c=32):
+        return prog(ctx.spec((n, 1, d), dtype), ctx.spec((1, c, d), dtype))
+
+    for d in (8, 12, 16, 24, 25, 32, 64, 65):
+        assert ("pairs:" in planned(d).plan()) == (d <= longest and (d > 8 or dtype == gr.GR_F32)), d
+    if longest:
+        vgprs, scratch = _registers(planned(longest), tmp_path)
+        assert scratch == 0 and vgprs <= 128   # four waves per SIMD
+
+
+def test_row_pairs_are_taken_where_they_fill_the_device(ctx):
+    def squares(n, c, d, operands=1):
+        a, b = [ctx.spec((n, 1, d)) for _ in range(operands)], ctx.spec((1, c, d))
+        x = a[0] - b
+        for t in a[1:]:
+            x = x + t
+        return "pairs:" in gr.sum(x * b, axis=2).plan()
+
+    assert not squares(5000, 16, 64) and not squares(127, 1024, 16) and squares(8192, 16, 64) and squares(16, 8192, 64) and not squares(200000, 3, 64)
+    assert not squares(8192, 16, 16, 2) and squares(16384, 16, 16, 2) and not squares(16384, 16, 32, 2) and squares(65536, 16, 32, 2)
+    assert squares(65536, 32, 42, 3) and not squares(65536, 32, 43, 3)   # (three operands: at most 128 registers of them)
 
 
 @pytest.mark.parametrize("seed", [1, 2, 3])
