@@ -592,10 +592,13 @@ void gen_rowred_pairs(Em& e) {
   const bool turn = ud == 1 && g.out_dtype != GR_I64;
   const char* OT = cty(g.out_dtype);
   const char* OV = g.out_dtype == GR_F32 ? "f4" : "i4";
-  // workgroups of the same 256 rows, which write neighbouring pieces of the same output rows, share an XCD (8 of them, dealt in turn)
+  // Workgroups of the same 256 rows, which write neighbouring pieces of the same output rows, share an XCD (8 of them, dealt in
+  // turn).  Fewer than 16 blocks of 256 rows are dealt without that: XCDs would be left without work (of 4 blocks half of them:
+  // 1000 x 1000 squared distances in 16 dimensions 6.6 -> 5.4 us, in 32 12.2 -> 8.4; of 12 a quarter, 3000 x 2000 x 32 20.2 -> 18.5;
+  // of 20 blocks the sharing is worth more, 5000 x 64 x 32 4.8 against 5.3).
   e.o << "  const long long NL = " << e.dim(ld) << ", NU = " << e.dim(ud) << ", CH = " << e.S(e.L.extra) << ";\n"
-         "  const unsigned NUB = (unsigned)" << e.S(e.L.extra + 1) << ", set = blockIdx.x / (8 * NUB), in_set = blockIdx.x % (8 * NUB);\n"
-         "  const long long lbeg = (long long)(set * 8 + in_set % 8) * 256, lraw = lbeg + threadIdx.x, ubeg = in_set / 8 * CH, uend = ubeg + CH < NU ? ubeg + CH : NU;\n"
+         "  const unsigned NUB = (unsigned)" << e.S(e.L.extra + 1) << ", NLB = (unsigned)((NL + 255) / 256), GRP = NLB < " << kPairSpread << " ? NLB : 8, set = blockIdx.x / (GRP * NUB), in_set = blockIdx.x % (GRP * NUB);\n"
+         "  const long long lbeg = (long long)(set * GRP + in_set % GRP) * 256, lraw = lbeg + threadIdx.x, ubeg = in_set / GRP * CH, uend = ubeg + CH < NU ? ubeg + CH : NU;\n"
          "  if (lbeg >= NL || ubeg >= NU) return;\n"
          "  const bool ok = lraw < NL;\n"
          "  const long long lane = ok ? lraw : NL - 1;\n";

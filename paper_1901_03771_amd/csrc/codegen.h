@@ -30,6 +30,8 @@ ArgLayout arg_layout(const GroupPlan& g);
 // (LDS for 256 lanes' results: 20 KiB, seven workgroups per compute unit.  Blocks of 32 against 16 rows, us: 262144 x 32
 // pairs of 16 elements 19.2 / 15.0, 292509 x 24 of 11 16.3 / 13.3, 65536 x 64 of 64 23.4 / 23.8, 973632 x 24 of 3 27.5 / 30.4.)
 constexpr int kPairBlock = 16;
+// Blocks of 256 of the lanes' rows from which on those of the same rows share an XCD.
+constexpr int kPairSpread = 16;
 
 // Lanes of a workgroup of the column reductions (REDUCE mode 0).
 constexpr int kReduceLanes = 512;

@@ -578,7 +578,7 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
         const int64_t want = std::min<int64_t>(quads, std::max<int64_t>((quads * 4 + kPairBlock - 1) / kPairBlock, 1024 / nl)), ch = (quads + want - 1) / want, nub = (quads + ch - 1) / ch;
         s[L.extra] = (uint64_t)(4 * ch);
         s[L.extra + 1] = (uint64_t)nub;
-        return launch(c, k->fn, k->name, (nl + 7) / 8 * 8 * nub, s);
+        return launch(c, k->fn, k->name, (nl < kPairSpread ? nl : (nl + 7) / 8 * 8) * nub, s);
       }
       const int bt = std::max(256, g.row_threads), rb = bt / g.row_threads * g.row_iters;
       return launch(c, k->fn, k->name, (rows + rb - 1) / rb, s, (unsigned)bt);
