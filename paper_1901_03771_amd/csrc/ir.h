@@ -224,6 +224,7 @@ struct GroupPlan {
   int unroll = 8;     // gemv column-accumulate: rows in flight per lane
 
   std::string signature;
+  std::string general;                   // pair_k: signature of the lane groups' kernel of the same program, which serves other row lengths too
 };
 
 // REDUCE mode 0: lanes' worth of outputs (a lane owns four outputs of the innermost kept dimension, or one).

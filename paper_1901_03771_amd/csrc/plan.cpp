@@ -1580,6 +1580,14 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
   std::sort(g->members.begin(), g->members.end(), [](const Node* a, const Node* b2) { return a->id < b2->id; });
   for (const Node* n : b.leaves_seen) g->leaves.push_back(n);
   std::sort(g->leaves.begin(), g->leaves.end(), [](const Node* a, const Node* b2) { return a->id < b2->id; });
+  if (g->pair_k) {
+    const int k = g->pair_k, ld = g->pair_lane;
+    g->pair_k = g->pair_lane = 0;
+    make_signature(g);
+    g->general = g->signature;
+    g->pair_k = k;
+    g->pair_lane = ld;
+  }
   make_signature(g);
   return GR_OK;
 }

@@ -262,7 +262,24 @@ static gr_status finish_kernel(gr_ctx* c, const std::string& sig, const std::str
 // execution (the paper names JIT time as its main bottleneck and pipelining as the remedy).
 static void bound_pending(gr_ctx* c);
 
+// A kernel for rows over pairs has its row length compiled in.  The kernel of the lane groups gives the same bits for every
+// length of its lane group; it is prepared and loaded along with it, serves lengths whose own kernel is still in the
+// compiler, and a request that must not wait for one.  While an object of this type lives, `g` is planned for that kernel.
+struct AsGeneral {
+  GroupPlan& g;
+  const int k, lane;
+  explicit AsGeneral(GroupPlan& plan) : g(plan), k(plan.pair_k), lane(plan.pair_lane) { g.pair_k = g.pair_lane = 0; g.signature.swap(g.general); }
+  ~AsGeneral() { g.pair_k = k; g.pair_lane = lane; g.signature.swap(g.general); }
+  AsGeneral(const AsGeneral&) = delete;
+  AsGeneral& operator=(const AsGeneral&) = delete;
+};
+
 gr_status prepare_group(gr_ctx* c, GroupPlan& g) {
+  if (g.pair_k) {
+    AsGeneral general(g);
+    gr_status st = prepare_group(c, g);
+    if (st != GR_OK) return st;
+  }
   if (c->cache.count(g.signature) || c->pending.count(g.signature)) return GR_OK;
   gr_status est = expand_patch(c, &g);
   if (est != GR_OK) return est;
@@ -337,15 +354,20 @@ static void bound_pending(gr_ctx* c) {
   }
 }
 
-// True while the kernel of `g` is neither cached nor ready to be collected without waiting.
-static bool still_compiling(gr_ctx* c, const GroupPlan& g) {
-  if (c->cache.count(g.signature)) return false;
-  auto pit = c->pending.find(g.signature);
+// True while a kernel is neither cached nor ready to be collected without waiting.
+static bool still_compiling(gr_ctx* c, const std::string& sig) {
+  if (c->cache.count(sig)) return false;
+  auto pit = c->pending.find(sig);
   if (pit == c->pending.end()) return false;
   return pit->second.second.wait_for(std::chrono::seconds(0)) == std::future_status::timeout;
 }
 
 gr_status compile_group(gr_ctx* c, GroupPlan& g, gr_ctx::Kernel** out) {
+  if (g.pair_k && c->pending.count(g.general) && (c->opt_interp != 1 || c->capture || !still_compiling(c, g.general))) {
+    gr_status st = prepare_group(c, g);   // (both compile at the same time)
+    if (st == GR_OK && c->pending.count(g.general)) st = collect_job(c, g.general, nullptr);
+    if (st != GR_OK) return st;
+  }
   auto it = c->cache.find(g.signature);
   if (it != c->cache.end()) {
     c->stats.cache_hits++;
@@ -365,6 +387,12 @@ gr_status compile_group(gr_ctx* c, GroupPlan& g, gr_ctx::Kernel** out) {
   it = c->cache.find(g.signature);
   if (it != c->cache.end()) { *out = &it->second; return GR_OK; }  // served from disk
   return collect_job(c, g.signature, out);
+}
+
+// Whether the lane groups' kernel runs a plan for rows over pairs: it is loaded, and that plan's own is not (nor can
+// be had at once, unless the request must not load kernels at all).
+static bool use_general(gr_ctx* c, const GroupPlan& g) {
+  return g.pair_k && !c->cache.count(g.signature) && c->cache.count(g.general) && (c->static_mode || still_compiling(c, g.signature));
 }
 
 static gr_status launch(gr_ctx* c, hipFunction_t fn, const std::string& name, int64_t grid, std::vector<uint64_t>& args, unsigned threads = 256) {
@@ -770,7 +798,7 @@ gr_status execute_plan(gr_ctx* c, Plan* plan, Node* root, void* user_out, bool c
     // the static array.
     size_t need = 0, least = 0;
     for (auto& gp : plan->groups) {
-      if (!no_compile && !c->cache.count(gp->signature))
+      if (!no_compile && !c->cache.count(gp->signature) && !use_general(c, *gp))
         return fail(c, GR_ERR_UNSUPPORTED, "materialize_into_static: a kernel of this request is not loaded yet; call gr_plan_compile "
                                            "(or evaluate a request of the same structure with gr_materialize_into) once first");
       for (const Node* r : {(const Node*)gp->root, gp->pair ? (const Node*)gp->pair->root : nullptr}) {
@@ -798,11 +826,13 @@ gr_status execute_plan(gr_ctx* c, Plan* plan, Node* root, void* user_out, bool c
   for (auto& gp : plan->groups) {
     GroupPlan& g = *gp;
     gr_ctx::Kernel* k = nullptr;
+    std::unique_ptr<AsGeneral> general;
+    if (!c->capture && use_general(c, g)) general.reset(new AsGeneral(g));
     // A map sub-graph whose kernel is still in the compiler runs through the byte-code
     // interpreter instead of waiting; the job stays pending and a later request collects it.
     // (option "interp" = 2: every map sub-graph the interpreter covers, compiled or not)
     const bool try_interp = !c->static_mode && !c->capture &&
-                            (c->opt_interp >= 2 || (c->opt_interp == 1 && still_compiling(c, g)));
+                            (c->opt_interp >= 2 || (c->opt_interp == 1 && still_compiling(c, g.signature)));
     if (no_compile) k = &dry_kernel;
     if (no_compile && c->opt_plan_cache >= 2) {
       // self-checking dry run: nothing is compiled, but the source is generated and has to be the one that any

@@ -822,6 +822,23 @@ def test_generated_kernels_keep_their_values_in_registers(ctx, tmp_path):
         assert all(int(v) == 0 for v in re.findall(r"\.private_segment_fixed_size:\s+(\d+)", text)), name
 
 
+@pytest.mark.parametrize("d", [9, 12, 16])
+def test_one_kernel_of_row_pairs_serves_every_length_without_allocating(ctx, d):
+    # an evaluated request of 13 elements per row loads what a request of another length of the same lane group needs
+    def prog(k):
+        diff = ctx.spec((65536, 1, k)) - ctx.spec((1, 32, k))
+        return lambda: gr.sum(diff * diff, axis=2)
+
+    assert _served_without_allocating(ctx, prog(13), prog(d)) == "GR_OK", ctx.last_error()
+    misses = ctx.stats()["cache_misses"]
+    prog(13)().materialize()
+    assert ctx.stats()["cache_misses"] == misses
+    ctx.set_option("interp", 1)
+    prog(d)().materialize()   # its own kernel is started
+    ctx.compile_wait()
+    assert ctx.stats()["cache_misses"] == misses + 1
+
+
 def _registers(out, tmp_path):
     """(vector registers, bytes of scratch memory) per lane of the request's first kernel, compiled with the library's options."""
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
