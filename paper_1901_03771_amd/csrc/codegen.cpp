@@ -982,10 +982,10 @@ void reduce_combine(Em& e) {
          "    const long long o = (long long)blockIdx.x * 256 + threadIdx.x;\n"
          "    if (o < NOUT) {\n      " << T << " acc = ws[o];\n"
          "      long long s = 1;\n"
-         "      for (; s + 8 <= NSPLIT; s += 8) {\n"   // eight independent loads in flight, combined in the fixed order
+         "      for (; s + 8 <= NSPLIT; s += 8) {\n"   // eight independent loads in flight, combined in a fixed order, pairs first
          "        const " << T << " v0 = ws[s * NOUT + o], v1 = ws[(s + 1) * NOUT + o], v2 = ws[(s + 2) * NOUT + o], v3 = ws[(s + 3) * NOUT + o];\n"
          "        const " << T << " v4 = ws[(s + 4) * NOUT + o], v5 = ws[(s + 5) * NOUT + o], v6 = ws[(s + 6) * NOUT + o], v7 = ws[(s + 7) * NOUT + o];\n"
-         "        acc = gr_comb0(gr_comb0(gr_comb0(gr_comb0(gr_comb0(gr_comb0(gr_comb0(gr_comb0(acc, v0), v1), v2), v3), v4), v5), v6), v7);\n"
+         "        acc = gr_comb0(acc, gr_comb0(gr_comb0(gr_comb0(v0, v1), gr_comb0(v2, v3)), gr_comb0(gr_comb0(v4, v5), gr_comb0(v6, v7))));\n"
          "      }\n"
          "      for (; s < NSPLIT; ++s) acc = gr_comb0(acc, ws[s * NOUT + o]);\n"
          "      out[o] = acc;\n    }\n"
@@ -1000,26 +1000,16 @@ void reduce_combine(Em& e) {
          "  }\n}\n";
 }
 
-// Mode 0: the kept dimension is the contiguous one (column sums).  A workgroup of 512 lanes is BX
-// lanes across the outputs by BY = 512 / BX along the reduced range; a lane takes four consecutive
-// outputs with one dwordx4 per array and reduced element (one output where the kept dimension is
-// strided or shorter than four) and every BY-th element of its chunk, the BY partial results of an
-// output are combined in order through LDS.  BX is an argument: the planner fits it to the shape.
-// The last group of four outputs of a ragged dimension starts four from its end: it overlaps the
-// group before it, both store the same values, and no load leaves the array.
-void gen_reduce_columns(Em& e) {
+// One kernel of mode 0 (see gen_reduce_columns).  Loads in flight per lane and array: U, written out, all first (a wave-wide
+// vote in the body keeps the compiler from unrolling a loop with a remainder); what is left of a lane's share is loaded together
+// with clamped positions, whose surplus values are not combined.
+void reduce_columns_kernel(Em& e, bool wide, int U) {
   const GroupPlan& g = e.g;
   const int rank = g.rank, kr = g.red_kept_rank, kd = kr - 1;
   const Phase& ph = g.phases[0];
   const char* T = cty(ph.out_dtype);
   const int W = g.red_vec ? 4 : 1;
-  int n_loads = 0;
-  for (const Instr& in : g.prog) if (in.kind == IKind::LOAD) ++n_loads;
-  // loads in flight per lane and array: written out, all first (a wave-wide vote in the body keeps the compiler from
-  // unrolling a loop with a remainder); what is left at the end of a chunk is one more batch with clamped positions,
-  // whose surplus values are not combined
-  const int U = n_loads <= 2 && g.prog.size() <= 12 ? 8 : 4;
-  kernel_head(e, kernel_name(g), kReduceLanes);
+  kernel_head(e, kernel_name(g) + (wide ? "_wide" : ""), kReduceLanes);
   e.o << "  const long long NOUT = " << e.S(e.L.extra) << ", LEN = " << e.S(e.L.extra + 1) << ", NSPLIT = " << e.S(e.L.extra + 3) << " & 0xffffffffll;\n"
          "  const unsigned BX = (unsigned)(" << e.slot(e.L.extra + 3) << " >> 32), BY = " << kReduceLanes << "u / BX;\n"
          "  const unsigned ty = threadIdx.x / BX, tx = threadIdx.x - ty * BX;\n"
@@ -1071,52 +1061,123 @@ void gen_reduce_columns(Em& e) {
       else e.o << ind << "const " << vty4(in.dtype) << " w" << i << su << " = " << e.ld(in.group, vty4(in.dtype), at.str()) << ";\n";
     }
   };
-  auto compute = [&](int u, const std::string& guard) {
+  // values of element u: v<u>_<c>
+  auto values = [&](int u) {
     const std::string su = "_" + std::to_string(u);
-    e.o << "      " << guard << "{\n";
     for (int c = 0; c < W; ++c) {
-      const std::string pre = "v" + std::to_string(c) + "_", a = "acc" + std::to_string(c);
+      const std::string pre = "t" + std::to_string(c) + "_";
+      e.o << "      " << T << " v" << u << "_" << c << ";\n      {\n";
       emit_scalar_program(e, g.prog, {ph.value},
                           [&](const Instr& in, int id) {
                             const std::string w = "w" + std::to_string(id) + su;
                             return W == 1 || g.groups[in.group].structural_zero[kd] ? w : w + "[" + std::to_string(c) + "]";
                           },
                           "0.0f", pre, "        ");
-      e.o << "        " << a << " = " << Em::combine(ph, a, pre + std::to_string(ph.value)) << ";\n";
+      e.o << "        v" << u << "_" << c << " = " << pre << ph.value << ";\n      }\n";
     }
-    e.o << "      }\n";
   };
-  e.o << "  if (ok) {\n    long long j = jbeg + ty;\n    for (; j + " << U - 1 << "ll * BY < jend; j += " << U << "ll * BY) {\n";
+  auto join = [&](const char* to, int u) {
+    for (int c = 0; c < W; ++c) e.o << "      " << to << c << " = gr_comb0(" << to << c << ", v" << u << "_" << c << ");\n";
+  };
+  // A chain of additions as long as a lane's share of the range loses digits (4096 x 262144 uniform values, relative error 2.2e-7
+  // with one, 1.2e-7 with chunks of 512): the wide kernel adds up 64 elements before they join the accumulator.  The other
+  // one's shares are short (choose_column_split); its registers are worth more.
+  const std::string more = "j + " + std::to_string(U - 1) + "ll * BY < jend";
+  const bool blocked = wide && ph.op == GR_SUM && ph.out_dtype == GR_F32;
+  const char* const to = blocked ? "b" : "acc";
+  e.o << "  if (ok) {\n    long long j = jbeg + ty;\n";
+  if (blocked) {
+    e.o << "    while (" << more << ") {\n";
+    for (int c = 0; c < W; ++c) e.o << "      " << T << " b" << c << " = " << Em::identity(ph) << ";\n";
+  }
+  e.o << "    for (" << (blocked ? "int n = 0; n < " + std::to_string(64 / U) + " && " : std::string("; ")) << more << "; " << (blocked ? "++n, " : "") << "j += " << U << "ll * BY) {\n";
   for (int u = 0; u < U; ++u) loads(u, "j + " + std::to_string(u) + "ll * BY", "      ");
   e.o << "      __builtin_amdgcn_sched_barrier(0);\n";
-  for (int u = 0; u < U; ++u) compute(u, "");
-  e.o << "    }\n    if (j < jend) {\n";
-  for (int u = 0; u < U; ++u) loads(u, u == 0 ? std::string("j") : "(j + " + std::to_string(u) + "ll * BY < jend ? j + " + std::to_string(u) + "ll * BY : j)", "      ");
-  e.o << "      __builtin_amdgcn_sched_barrier(0);\n";
-  for (int u = 0; u < U; ++u) compute(u, u == 0 ? std::string() : "if (j + " + std::to_string(u) + "ll * BY < jend) ");
-  e.o << "    }\n  }\n";
+  if (blocked) {   // (pairs first)
+    std::function<void(int, int)> tree = [&](int lo, int n) {
+      if (n == 1) { values(lo); return; }
+      tree(lo, n / 2);
+      tree(lo + n / 2, n / 2);
+      join(("v" + std::to_string(lo) + "_").c_str(), lo + n / 2);
+    };
+    tree(0, U);
+    join(to, 0);
+  } else
+    for (int u = 0; u < U; ++u) { e.o << "      {\n"; values(u); join(to, u); e.o << "      }\n"; }
+  e.o << "    }\n";
+  if (blocked) {
+    for (int c = 0; c < W; ++c) e.o << "    acc" << c << " = gr_comb0(acc" << c << ", b" << c << ");\n";
+    e.o << "    }\n";
+  }
+  if (U > 1) {
+    e.o << "    if (j < jend) {\n";
+    for (int u = 0; u + 1 < U; ++u) loads(u, u == 0 ? std::string("j") : "(j + " + std::to_string(u) + "ll * BY < jend ? j + " + std::to_string(u) + "ll * BY : j)", "      ");
+    e.o << "      __builtin_amdgcn_sched_barrier(0);\n";
+    for (int u = 0; u + 1 < U; ++u) {
+      e.o << "      " << (u ? "if (j + " + std::to_string(u) + "ll * BY < jend) " : std::string()) << "{\n";
+      values(u);
+      join("acc", u);
+      e.o << "      }\n";
+    }
+    e.o << "    }\n";
+  }
+  e.o << "  }\n";
   e.o << "  GM " << T << "* const dst = NSPLIT > 1 ? (GM " << T << "*)" << e.slot(e.L.extra + 2) << " + split * NOUT : (GM " << T << "*)" << e.slot(e.L.out) << ";\n";
   e.o << "  if (BY == 1) {\n    if (ok) { ";
   for (int c = 0; c < W; ++c) e.o << "dst[o + " << c << "] = acc" << c << "; ";
   e.o << "}\n    return;\n  }\n"
          "  __shared__ " << T << " sm[" << W << "][" << kReduceLanes << "];\n";
   for (int c = 0; c < W; ++c) e.o << "  sm[" << c << "][threadIdx.x] = acc" << c << ";\n";
-  // (many lanes to an output: sixteen of them first, so that no lane adds more than a sixteenth of the partial results in turn)
-  e.o << "  __syncthreads();\n  unsigned ny = BY;\n  if (BY > 16) {\n    if (ok && ty < 16) for (unsigned q = ty + 16; q < BY; q += 16) {\n";
-  for (int c = 0; c < W; ++c) e.o << "      acc" << c << " = gr_comb0(acc" << c << ", sm[" << c << "][q * BX + tx]);\n";
+  // (many lanes to an output: sixteen of them first, in four chains where they are very many, so that no lane adds many partial results in turn)
+  e.o << "  __syncthreads();\n  unsigned ny = BY;\n  if (BY > 16) {\n    if (ok && ty < 16) {\n      unsigned q = ty + 16;\n      if (BY >= 128) {\n";
+  for (int c = 0; c < W; ++c) e.o << "        " << T << " f" << c << "_0 = acc" << c << ", f" << c << "_1 = " << Em::identity(ph) << ", f" << c << "_2 = f" << c << "_1, f" << c << "_3 = f" << c << "_1;\n";
+  e.o << "        for (; q + 48 < BY; q += 64) {\n";
+  for (int c = 0; c < W; ++c)
+    for (int u = 0; u < 4; ++u) e.o << "          f" << c << "_" << u << " = gr_comb0(f" << c << "_" << u << ", sm[" << c << "][(q + " << 16 * u << ") * BX + tx]);\n";
+  e.o << "        }\n";
+  for (int c = 0; c < W; ++c) e.o << "        acc" << c << " = gr_comb0(gr_comb0(f" << c << "_0, f" << c << "_1), gr_comb0(f" << c << "_2, f" << c << "_3));\n";
+  e.o << "      }\n      for (; q < BY; q += 16) {\n";
+  for (int c = 0; c < W; ++c) e.o << "        acc" << c << " = gr_comb0(acc" << c << ", sm[" << c << "][q * BX + tx]);\n";
+  e.o << "      }\n";
   e.o << "    }\n    __syncthreads();\n    if (ok && ty < 16) {\n";
   for (int c = 0; c < W; ++c) e.o << "      sm[" << c << "][threadIdx.x] = acc" << c << ";\n";
   e.o << "    }\n    __syncthreads();\n    ny = 16;\n  }\n"
          "  if (ok) for (unsigned c = ty; c < " << W << "u; c += BY) {\n"
          "    " << T << " r = sm[c][tx];\n"
          "    unsigned q = 1;\n"
-         "    for (; q + 8 <= ny; q += 8) {\n"   // eight LDS reads in flight
+         "    for (; q + 8 <= ny; q += 8) {\n"   // eight LDS reads in flight, pairs first
          "      " << T << " w[8];\n"
          "#pragma unroll\n      for (int u = 0; u < 8; ++u) w[u] = sm[c][(q + u) * BX + tx];\n"
-         "#pragma unroll\n      for (int u = 0; u < 8; ++u) r = gr_comb0(r, w[u]);\n"
+         "      r = gr_comb0(r, gr_comb0(gr_comb0(gr_comb0(w[0], w[1]), gr_comb0(w[2], w[3])), gr_comb0(gr_comb0(w[4], w[5]), gr_comb0(w[6], w[7]))));\n"
          "    }\n"
-         "    for (; q < ny; ++q) r = gr_comb0(r, sm[c][q * BX + tx]);\n"
+         "    " << T << " rest = " << Em::identity(ph) << ";\n"
+         "    for (; q < ny; ++q) rest = gr_comb0(rest, sm[c][q * BX + tx]);\n"
+         "    r = gr_comb0(r, rest);\n"
          "    dst[o + c] = r;\n  }\n}\n";
+}
+
+// Mode 0: the kept dimension is the contiguous one (column sums).  A workgroup of 512 lanes is BX
+// lanes across the outputs by BY = 512 / BX along the reduced range; a lane takes four consecutive
+// outputs with one dwordx4 per array and reduced element (one output where the kept dimension is
+// strided or shorter than four) and every BY-th element of its chunk, the BY partial results of an
+// output are combined in order through LDS.  BX is an argument: the planner fits it to the shape.
+// The last group of four outputs of a ragged dimension starts four from its end: it overlaps the
+// group before it, both store the same values, and no load leaves the array.
+void gen_reduce_columns(Em& e) {
+  const GroupPlan& g = e.g;
+  const int rank = g.rank, kr = g.red_kept_rank, kd = kr - 1;
+  const Phase& ph = g.phases[0];
+  const char* T = cty(ph.out_dtype);
+  const int W = g.red_vec ? 4 : 1;
+  int n_loads = 0;
+  for (const Instr& in : g.prog) if (in.kind == IKind::LOAD) ++n_loads;
+  // Two kernels, one per kind of shape.  Outputs that fill the chip by themselves (red_wide): batches of four; their workgroups walk
+  // rows far apart, and more rows at a time cost more than the loads in flight gain (512 x 2^19: 172.8 us with eight,
+  // 166.3 with four; 2048 x 65536 products of two arrays 218 / 176).  Others: batches of eight (16384 x 4096 56.1 us with four, 50.1),
+  // whose registers would halve the wavefronts of the former (3 x 2^22 14.7 us from one kernel with both, 13.3).
+  const int most = 4;
+  reduce_columns_kernel(e, false, n_loads <= 2 && g.prog.size() <= 12 ? 8 : most);
+  reduce_columns_kernel(e, true, most);
   reduce_combine(e);
 }
 

@@ -199,6 +199,7 @@ struct GroupPlan {
   int red_mode = 0;                      // REDUCE: 0 lanes across the outputs, 1 block-per-output
   int red_vec = 0;                       // REDUCE mode 0: a lane owns four consecutive outputs (dwordx4 loads)
   int red_bx = 1;                        // REDUCE mode 0: lanes of a workgroup across the outputs
+  bool red_wide = false;                 // REDUCE mode 0: one launch, and blocks enough to fill the chip
   int red_tight = 1;                     // REDUCE mode 0: splits of a request whose partial results do not fit the static scratch array
   int64_t red_out = 0, red_len = 0;      // REDUCE: outputs, reduced elements per output
   int red_kept_rank = 0;

@@ -906,23 +906,34 @@ void choose_pair_rows(GroupPlan* g) {
 // (first sum 26 us = 4 TB/s, second 20 us), 3977 x 7342 110 -> 111; column sums of 4096 x 512 19 -> 9.
 void choose_column_split(GroupPlan* g) {
   g->slabs = g->red_tight = 1;
+  g->red_wide = false;
   if (g->red_out == 0) return;   // nothing to launch
   const int64_t V = reduce_units(*g), LEN = std::max<int64_t>(1, g->red_len);
   auto even = [&](int64_t bx) { const int64_t nb = (V + bx - 1) / bx; return (V + nb - 1) / nb; };   // blocks of equal width
   // One launch where that leaves a lane at most 32 elements, or where the outputs alone fill the chip: blocks as
-  // wide as still give 512 workgroups, 16 lanes (256 bytes) at least.
+  // wide as still give 512 workgroups, 16 lanes (256 bytes) at least; 256 where a block lies within one row; 128 of rows that are no
+  // whole 128-byte lines, whose blocks share a line with each neighbour.  Long programs need the wavefronts there: 256, and 512 for few elements.
+  // (us, blocks chosen by 512 workgroups / by this: 64 x 2^18 15.6 / 13.5, 32 x 2^19 15.1 / 12.9, 256 x 2^18 51.2 / 43.1, 512 x 2^19
+  // 212 / 166, 2048 x 65536 91.5 / 84.4, 512 x 64 x 1024 over the middle 27.4 / 24.4, 700 x 70001 42.7 / 36.5 in 137 blocks and 47 in 274, of exp 46 /
+  // 42 in 274 and 55 in 137; 20 x 300001 of exp 7.6 / 8.2 in 293; 64 x 64 x 64 x 64 over the third 14.0 / 17.8, whose rows are short.)
+  bool heavy = false;
+  for (const Instr& in : g->prog)
+    if (in.dtype == GR_F32 && (in.kind == IKind::UNARY || in.kind == IKind::BINARY) && (in.op == GR_DIV || in.op == GR_EXP || in.op == GR_LOG || in.op == GR_SQRT || in.op == GR_TANH || in.op == GR_ERF)) heavy = true;
+  const int64_t D = g->dims[g->red_kept_rank - 1], fill = D < 1024 || (heavy && LEN < 64 && D % 32) ? 512 : (D % 32 == 0 || heavy ? 256 : 128);
   int64_t bx = kReduceLanes;
-  while (bx > 16 && (V + bx - 1) / bx < 512) bx /= 2;
+  while (bx > 16 && (V + bx - 1) / bx < fill) bx /= 2;
   g->red_bx = (int)even(bx);
-  if ((bx >= 64 && (V + bx - 1) / bx >= 512) || LEN <= 32 * (kReduceLanes / g->red_bx)) return;
+  const bool full = bx >= 64 && (V + bx - 1) / bx >= fill;
+  g->red_wide = full && LEN > 8 * (kReduceLanes / g->red_bx);   // (fewer elements per lane: all of them at once)
+  if (full || LEN <= 32 * (kReduceLanes / g->red_bx)) return;
   // Otherwise enough chunks for two workgroups per compute unit, of 16 elements per lane at least.  Rows of whole
   // 128-byte lines: blocks of 32 lanes (8192^2 47.5 us; 16 lanes 50.5, 64 52.3, 128 58.9, 256 62.9; 16384 x 4096 50.6, 52.4,
   // 58.3, 60.6, 73.1); ragged rows: whole rows up to 128 lanes, else 64 (100003 x 257 22.5 us with 65 lanes, 24.0 with 33,
   // 27.5 with 22; 3977 x 7342 30.1 with 32, 28.6 with 64, 29.4 with 128).  1024 or 2048 workgroups are no better.
-  const int64_t D = g->dims[g->red_kept_rank - 1];
   g->red_bx = (int)even(D % 32 == 0 ? 32 : (V <= 128 ? 128 : 64));
   const int64_t blocks = (V + g->red_bx - 1) / g->red_bx, by = kReduceLanes / g->red_bx;
-  int64_t nsplit = std::min<int64_t>((512 + blocks - 1) / blocks, std::max<int64_t>(1, LEN / (16 * by)));
+  // (and never more than 256 elements in one lane's chain of additions)
+  const int64_t nsplit = std::max<int64_t>(std::min<int64_t>((512 + blocks - 1) / blocks, std::max<int64_t>(1, LEN / (16 * by))), std::min<int64_t>((LEN + 256 * by - 1) / (256 * by), (int64_t)1 << 20));
   g->slabs = (int)nsplit;
   // Partial results of a request that must not allocate come out of the static scratch array, beside the request's
   // stored results.  Where they do not fit, it makes do with as many as chunks of 256 elements (128 where a lane owns one
@@ -1776,6 +1787,11 @@ std::string describe_plan(const Plan& plan) {
       bool f2 = true;
       for (const Node* n : g.pair->members) { if (n->is_view()) continue; s << (f2 ? "" : ",") << n->id << ':' << node_label(n); f2 = false; }
       s << "]]";
+    }
+    if (g.kind == GroupKind::REDUCE) {
+      if (g.red_mode == 0) s << " lanes=" << g.red_bx << "x" << kReduceLanes / g.red_bx << (g.red_vec ? " by four outputs" : "") << (g.red_wide ? " wide" : "");
+      else s << " workgroup per output";
+      if (g.slabs > 1) s << " splits=" << g.slabs;
     }
     if (g.kind == GroupKind::ROWRED) {
       s << " phases=" << g.phases.size() << " row_threads=" << g.row_threads << " NP=" << g.NP;

@@ -231,7 +231,7 @@ static void disk_store(const std::string& path, const std::string& key, const st
 static void kernel_entry_points(const GroupPlan& g, std::string* name, bool* combine, int* scan) {
   *name = kernel_name(g);
   *combine = (g.kind == GroupKind::GEMV && g.gemv_mode >= 1) || g.kind == GroupKind::REDUCE || g.kind == GroupKind::GEMM;
-  *scan = g.kind == GroupKind::SCAN ? (g.scan_mode == 4 ? 0 : g.scan_mode >= 2 ? 2 : 1) : 0;
+  *scan = g.kind == GroupKind::SCAN ? (g.scan_mode == 4 ? 0 : g.scan_mode >= 2 ? 2 : 1) : (g.kind == GroupKind::REDUCE && g.red_mode == 0 ? 3 : 0);
 }
 
 // Loads a code object and publishes the kernel in the in-memory cache.
@@ -250,6 +250,7 @@ static gr_status finish_kernel(gr_ctx* c, const std::string& sig, const std::str
       GR_HIP(c, hipModuleGetFunction(&k.fn3, k.module, "gr_scan_offsets"));
     }
     if (scan == 2) GR_HIP(c, hipModuleGetFunction(&k.fn2, k.module, "gr_scan_clear"));
+    if (scan == 3) GR_HIP(c, hipModuleGetFunction(&k.fn3, k.module, (k.name + "_wide").c_str()));
   }
   auto ins = c->cache.emplace(sig, std::move(k));
   if (out) *out = &ins.first->second;
@@ -624,7 +625,8 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
       }
       if (g.red_mode == 0) s[L.extra + 3] |= (uint64_t)g.red_bx << 32;
       const int64_t units = g.red_mode == 0 ? (reduce_units(g) + g.red_bx - 1) / g.red_bx : g.red_out;
-      gr_status st = launch(c, k->fn, k->name, units * slabs, s, g.red_mode == 0 ? kReduceLanes : 256);
+      gr_status st = g.red_mode == 0 && g.red_wide ? launch(c, k->fn3, k->name + "_wide", units * slabs, s, kReduceLanes)
+                                                  : launch(c, k->fn, k->name, units * slabs, s, g.red_mode == 0 ? kReduceLanes : 256);
       if (st != GR_OK || slabs <= 1) return st;
       return launch(c, k->fn2, k->name + "_combine", g.red_out >= 1024 ? (g.red_out + 255) / 256 : g.red_out, s);
     }

@@ -66,6 +66,35 @@ def test_column_reductions_keep_infinities_and_nan(env):
         assert reduction_check(got, ref)[0].all(), op
 
 
+# outputs that fill the chip by themselves: short ranges in one batch, whole batches of four and what is left of them, blocks of 64 elements
+# and beside them, ragged rows; operands of one and two arrays, strided groups of outputs
+@pytest.mark.parametrize("shape,axis", [((3, 1 << 18), 0), ((16, 1 << 17), 0), ((17, 131077), 0), ((65, 65536), 0), ((270, 32768), 0), ((515, 65536), 0), ((600, 16500), 0), ((530, 70001), 0),
+                                        ((70, 64, 1024), 1), ((40, 130, 1030), 1), ((3, 300, 30000), 1)])
+def test_wide_column_reductions(env, shape, axis):
+    a, b = positive(shape, 23), positive(shape, 24)
+    b.reshape(-1)[::7] *= -1.0
+    got, ref = both(env, lambda xp, a: xp.sum(a, axis=axis), a=a)   # positive terms: 1e-5 of every element
+    assert reduction_check(got, ref)[0].all()
+    for op in ("max", "min"):
+        got, ref = both(env, lambda xp, a, b: getattr(xp, op)(a * b, axis=axis), a=a, b=b)
+        assert np.array_equal(got, ref), op
+    i = np.random.default_rng(25).integers(-2**31, 2**31 - 1, shape, dtype=np.int64).astype(np.int32)
+    got, ref = both(env, lambda xp, i: xp.sum(i, axis=axis), i=i)
+    assert np.array_equal(got, ref)
+
+
+# Signed values summed in chains of c additions leave a relative error of u sqrt(c / 6), u = 2^-24 (an addition's error is uniform
+# in u times the partial sum).  c: blocks of 64 where the outputs fill the chip (chains of 256 to 4096 before), at most 256 elsewhere.
+@pytest.mark.parametrize("shape,c", [((2048, 65536), 64), ((1600, 100000), 64), ((700, 70001), 64), ((4096, 30000), 256), ((30000, 4000), 256), ((16384, 2048), 256), ((200000, 300), 256)])
+def test_column_sums_do_not_chain_additions(env, shape, c):
+    gr, ctx, torch = env
+    x = torch.randn(shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(26))
+    assert (" wide" in gr.sum(ctx.array(x), axis=0).plan()) == (c == 64)
+    got = gr.sum(ctx.array(x), axis=0).torch().double()
+    want = sum(part.double().sum(0) for part in x.chunk(16, 0))
+    assert float((got - want).norm() / want.norm()) < 2.0**-24 * (c / 6) ** 0.5
+
+
 # columns: ragged and whole groups of four, narrow arrays, one tile and a little more; rows: below, at and beside a patch
 @pytest.mark.parametrize("shape", [(2, 5), (3, 4), (5, 6), (17, 9), (4, 257), (63, 63), (66, 1027), (1031, 1028), (70, 1501), (4100, 1537), (3, 65, 7), (5, 130, 1030),
                                    (2, 3, 4, 5), (70001, 33)])

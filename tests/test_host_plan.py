@@ -839,6 +839,22 @@ def test_one_kernel_of_row_pairs_serves_every_length_without_allocating(ctx, d):
     assert ctx.stats()["cache_misses"] == misses + 1
 
 
+@pytest.mark.parametrize("rows", [3, 30, 64, 300, 700, 4096, 20000, 300000, 5000000])
+def test_column_sums_bound_the_chain_of_additions(ctx, rows):
+    # a lane adds up at most 256 elements in turn, or blocks of 64 of them; no output is left to fewer lanes than the chip has where rows suffice
+    for cols in (3, 17, 64, 257, 444, 1000, 2048, 8192, 16384, 32768, 65532, 65536, 70001, 131072, 1 << 18, 300001, 1 << 19, 1 << 21):
+        if rows * cols > 1 << 40:
+            continue
+        plan = gr.sum(ctx.spec((rows, cols)), axis=0).plan()
+        m = re.search(r"lanes=(\d+)x(\d+)( by four outputs)?( wide)?(?: splits=(\d+))?", plan)
+        bx, by, quads, wide, splits = int(m[1]), int(m[2]), m[3], m[4], int(m[5] or 1)
+        units = -(-cols // 4) if quads else cols
+        share = -(-rows // (splits * by))
+        assert 1 <= bx <= 512 and by == 512 // bx and (quads is not None) == (cols >= 4)
+        assert wide or share <= 256, plan
+        assert -(-units // bx) * splits >= 128 or share <= 32, plan
+
+
 def _registers(out, tmp_path):
     """(vector registers, bytes of scratch memory) per lane of the request's first kernel, compiled with the library's options."""
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
