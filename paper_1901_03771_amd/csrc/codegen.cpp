@@ -1175,7 +1175,9 @@ void gen_reduce_columns(Em& e) {
   // rows far apart, and more rows at a time cost more than the loads in flight gain (512 x 2^19: 172.8 us with eight,
   // 166.3 with four; 2048 x 65536 products of two arrays 218 / 176).  Others: batches of eight (16384 x 4096 56.1 us with four, 50.1),
   // whose registers would halve the wavefronts of the former (3 x 2^22 14.7 us from one kernel with both, 13.3).
-  const int most = 4;
+  // (registers for what a batch loads, of the 256 that 512 lanes leave each: 223 for five arrays by four, 204 for eight by two;
+  // twelve by four spilled 1 KiB per lane)
+  const int most = n_loads <= 5 ? 4 : (n_loads <= 8 ? 2 : 1);
   reduce_columns_kernel(e, false, n_loads <= 2 && g.prog.size() <= 12 ? 8 : most);
   reduce_columns_kernel(e, true, most);
   reduce_combine(e);

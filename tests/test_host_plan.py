@@ -868,6 +868,15 @@ def _registers(out, tmp_path):
     return tuple(max(int(v) for v in re.findall(key + r":\s+(\d+)", text)) for key in (r"\.vgpr_count", r"\.private_segment_fixed_size"))
 
 
+@pytest.mark.parametrize("arrays", [1, 2, 5, 6, 8, 9, 12, 16])
+def test_column_sums_of_many_arrays_keep_to_registers(ctx, tmp_path, arrays):
+    x = [ctx.spec((4096, 4096)) for _ in range(arrays)]
+    value = gr.exp(x[0])
+    for t in x[1:]:
+        value = value * t + gr.exp(t)
+    assert _registers(gr.sum(value, axis=0), tmp_path)[1] == 0
+
+
 PAIR_PROGRAMS = {   # program, dtype, longest row that the kernel for pairs takes
     "squares": (lambda a, b: gr.sum((a - b) * (a - b), axis=2), gr.GR_F32, 64),
     "products": (lambda a, b: gr.sum(a * b, axis=2), gr.GR_F32, 64),
