@@ -31,6 +31,11 @@ struct gr_program {
   std::vector<std::pair<int, int>> cur_patch;     // provenance of the argument block being filled (while recording)
 };
 
+namespace gr {
+// The static array that requests which must not allocate take stored and partial results from.
+constexpr size_t kStaticScratchBytes = (size_t)16 << 20;
+}  // namespace gr
+
 struct gr_ctx {
   int device = -1;
   hipStream_t stream = nullptr;
@@ -127,7 +132,7 @@ struct gr_ctx {
   unsigned char* static_base = nullptr;
   size_t static_cap = 0, static_used = 0;
   bool static_mode = false;
-  bool static_tight = false;    // the running request of that kind takes the fewest partial results
+  bool tight = false;           // the running request takes the fewest partial results (tight_partials)
   bool plan_static = false;     // the request being planned is one of those: the planner keeps optional partial results within the array
 
   // gr_program_create: the request being recorded instead of executed, and the programs alive

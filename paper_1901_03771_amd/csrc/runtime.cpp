@@ -506,7 +506,7 @@ static size_t workspace_need(const GroupPlan& g, bool tight) {
 // for a request that must not allocate, a piece of the static array.
 static gr_status get_workspace(gr_ctx* c, const GroupPlan& g, void** ws) {
   *ws = nullptr;
-  const size_t need = workspace_need(g, c->static_mode && c->static_tight);
+  const size_t need = workspace_need(g, c->tight);
   if (need == 0) return GR_OK;
   if (c->static_mode) {
     *ws = ctx_alloc(c, need);
@@ -616,7 +616,7 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
       if (g.red_out == 0) return GR_OK;
       s[L.extra] = (uint64_t)g.red_out;
       s[L.extra + 1] = (uint64_t)g.red_len;
-      const int slabs = reduce_slabs(g, c->static_mode && c->static_tight);
+      const int slabs = reduce_slabs(g, c->tight);
       s[L.extra + 3] = (uint64_t)slabs;
       if (slabs > 1) {
         gr_status wst = get_workspace(c, g, &ws);
@@ -776,6 +776,30 @@ static void static_unbind(gr_ctx* c, Plan* plan) {
     }
 }
 
+// Bytes of the static scratch array that the stored results of earlier sub-graphs and the partial results of two-stage kernels of
+// a request take, whose own result goes to the caller's buffer.
+static size_t scratch_need(const Plan& plan, const Node* root, bool tight) {
+  auto blocks = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
+  size_t need = 0;
+  for (const auto& gp : plan.groups) {
+    for (const Node* r : {(const Node*)gp->root, gp->pair ? (const Node*)gp->pair->root : nullptr}) {
+      if (!r || r == root) continue;
+      const size_t nb = (size_t)r->count() * itemsize(r->dtype);
+      need += blocks(nb ? nb : 256);
+    }
+    need += blocks(workspace_need(*gp, tight));
+  }
+  return need;
+}
+
+// Column sums make do with fewer partial results where the request would not fit the static scratch array otherwise: every
+// entry point decides that alike, so that a request has the same bits whether it may allocate or not.
+static bool tight_partials(const Plan& plan, const Node* root) {
+  bool fewer = false;
+  for (const auto& gp : plan.groups) fewer = fewer || (gp->kind == GroupKind::REDUCE && gp->red_mode == 0 && gp->red_tight < gp->slabs);
+  return fewer && scratch_need(plan, root, false) > kStaticScratchBytes && scratch_need(plan, root, true) <= kStaticScratchBytes;
+}
+
 gr_status execute_plan(gr_ctx* c, Plan* plan, Node* root, void* user_out, bool check_alias) {
   if (c->device < 0 && !c->opt_dry_run) return fail(c, GR_ERR_NODEVICE, "context has no device");
   if (user_out && check_alias) {
@@ -793,27 +817,17 @@ gr_status execute_plan(gr_ctx* c, Plan* plan, Node* root, void* user_out, bool c
   }
   static gr_ctx::Kernel dry_kernel;  // stands for any kernel in a dry run that does not compile
   const bool no_compile = c->device < 0 && c->opt_dry_run >= 2;
+  c->tight = tight_partials(*plan, root);
   if (c->static_mode) {
     // A request that must not allocate: checked in full before the first launch.  Every kernel
     // has to be loaded already (loading a code object allocates device memory), and the stored
     // results of earlier sub-graphs plus the partial results of two-stage kernels have to fit
     // the static array.
-    size_t need = 0, least = 0;
-    for (auto& gp : plan->groups) {
+    for (auto& gp : plan->groups)
       if (!no_compile && !c->cache.count(gp->signature) && !use_general(c, *gp))
         return fail(c, GR_ERR_UNSUPPORTED, "materialize_into_static: a kernel of this request is not loaded yet; call gr_plan_compile "
                                            "(or evaluate a request of the same structure with gr_materialize_into) once first");
-      for (const Node* r : {(const Node*)gp->root, gp->pair ? (const Node*)gp->pair->root : nullptr}) {
-        if (!r || (r == root && user_out)) continue;
-        size_t nb = (size_t)r->count() * itemsize(r->dtype);
-        need += ((nb ? nb : 256) + 255) & ~(size_t)255;
-        least += ((nb ? nb : 256) + 255) & ~(size_t)255;
-      }
-      need += (workspace_need(*gp, false) + 255) & ~(size_t)255;
-      least += (workspace_need(*gp, true) + 255) & ~(size_t)255;
-    }
-    c->static_tight = need > c->static_cap;
-    if (c->static_tight) need = least;
+    const size_t need = scratch_need(*plan, root, c->tight);
     if (need > c->static_cap)
       return fail(c, GR_ERR_OOM, "materialize_into_static: the request needs " + std::to_string(need) + " bytes for intermediate and partial results; "
                                  "the static scratch array holds " + std::to_string(c->static_cap));
@@ -962,6 +976,7 @@ gr_status execute_plan(gr_ctx* c, Plan* plan, Node* root, void* user_out, bool c
 // they were (nothing becomes materialised, no input is released).
 static gr_status record_plan(gr_ctx* c, Plan* plan, Node* root) {
   gr_program* P = c->capture;
+  c->tight = tight_partials(*plan, root);
   for (auto& gp : plan->groups) {
     gr_status pst = prepare_group(c, *gp);  // all compilations of the request start together
     if (pst != GR_OK) return pst;

@@ -10,14 +10,12 @@
 
 #include "ctx.h"
 
-#define GR_STATIC_SCRATCH_BYTES (16u << 20)
-
 // In host code this name is only a stand-in for the device symbol, never a device address:
 // host code below uses the per-device address obtained from hipGetSymbolAddress.  (The symbol
 // lookup is by name: the compiler gives a file-scope static device variable a global symbol in
 // the code object because host code refers to it; attribute "used" would keep the symbol local
 // and the lookup would fail.)
-static __device__ __align__(256) unsigned char scratch[GR_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[gr::kStaticScratchBytes];
 
 namespace gr {
 
@@ -39,7 +37,7 @@ gr_status static_scratch_attach(gr_ctx* c) {
     g_scratch_ptr[c->device] = ptr;
   }
   c->static_base = (unsigned char*)g_scratch_ptr[c->device];
-  c->static_cap = GR_STATIC_SCRATCH_BYTES;
+  c->static_cap = gr::kStaticScratchBytes;
   return GR_OK;
 }
 
@@ -49,7 +47,7 @@ using namespace gr;
 
 extern "C" gr_status gr_static_scratch_bytes(size_t* bytes) {
   if (!bytes) return GR_ERR_ARG;
-  *bytes = GR_STATIC_SCRATCH_BYTES;
+  *bytes = gr::kStaticScratchBytes;
   return GR_OK;
 }
 
@@ -66,7 +64,7 @@ extern "C" gr_status gr_materialize_into_static(gr_ctx* ctx, gr_array a, void* d
   if (ctx->device < 0) {
     // dry run on a device-less context: an address range that nothing ever dereferences
     ctx->static_base = (unsigned char*)(uintptr_t)0x7f0000000000ull;
-    ctx->static_cap = GR_STATIC_SCRATCH_BYTES;
+    ctx->static_cap = gr::kStaticScratchBytes;
   }
   if (!ctx->static_base) return fail(ctx, GR_ERR_HIP, "materialize_into_static: the static scratch array has no address on this device");
   Plan plan;  // (host memory only)

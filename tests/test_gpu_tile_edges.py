@@ -264,3 +264,24 @@ def test_static_entry_near_the_scratch_limit_takes_fewer_partial_sums(env):
     got = torch.empty(cols, device="cuda")
     assert gr.lib().gr_materialize_into_static(ctx._p, lazy.h, got.data_ptr(), cols * 4) == 0, ctx.last_error()
     assert torch.equal(got, want) and np.array_equal(got.cpu().numpy(), np.cumsum(a.astype(np.float64), 1).sum(0).astype(f32))
+
+
+@pytest.mark.parametrize("rows,cols", [(13900, 300), (13900, 299), (4080, 1024), (64, 300)])
+def test_column_sums_have_the_same_bits_from_every_entry_point(env, rows, cols):
+    # near the limit of the static scratch array, where there is room for fewer partial results, as elsewhere
+    gr, ctx, torch = env
+    t = torch.randn(rows, cols, device="cuda", generator=torch.Generator(device="cuda").manual_seed(27))
+    prog = lambda leaf: gr.sum(gr.cumsum(leaf, 1), axis=0)
+    want = prog(ctx.array(t)).torch()
+    lazy = prog(ctx.array(t))
+    lazy.compile()
+    got = torch.empty(cols, device="cuda")
+    assert gr.lib().gr_materialize_into_static(ctx._p, lazy.h, got.data_ptr(), cols * 4) == 0, ctx.last_error()
+    assert torch.equal(got, want)
+    into = torch.empty(cols, device="cuda")
+    prog(ctx.array(t)).materialize_into(into)
+    assert torch.equal(into, want)
+    leaf = ctx.array(t)
+    replayed = torch.empty(cols, device="cuda")
+    ctx.program(prog(leaf), [leaf]).run([t], replayed)
+    assert torch.equal(replayed, want)
