@@ -852,6 +852,16 @@ void gen_rowred(Em& e) {
       // (only sums and extrema exist: a sum of C equal values, an extremum of them)
       // handled below by the generic loop with the uniform name.
     }
+    // long rows: positions whose loads and temporaries are in registers at the same time
+    int n_loads = 0;
+    bool heavy = false;
+    for (int i : stage_instrs[s]) {
+      const Instr& in = g.prog[i];
+      if (in.uniform) continue;
+      if (in.kind == IKind::LOAD) ++n_loads;
+      else if (heavy_op(in)) heavy = true;
+    }
+    const int LONG_POS = n_loads <= 1 ? 4 : (n_loads <= 2 ? 2 : 1);
     // two bodies: unguarded positions 0..NP-2, guarded last position
     for (int pass = 0; pass < 2; ++pass) {
       const bool guarded = pass == 1;
@@ -884,6 +894,7 @@ void gen_rowred(Em& e) {
         }
       }
       if (final_stage && g.out_dtype != GR_I64) e.o << "    " << (g.out_dtype == GR_F32 ? "f4u" : "i4u") << " ov;\n";
+      if (ph && RT == 1024) e.o << "    " << cty(ph->out_dtype) << " c4[4];\n";
       e.o << "#pragma unroll\n    for (int j = 0; j < 4; ++j) {\n";
       for (int i : stage_instrs[s]) {
         const Instr& in = g.prog[i];
@@ -893,7 +904,9 @@ void gen_rowred(Em& e) {
         else e.o << "      const " << cty(in.dtype) << " t" << i << " = " << rhs << ";\n";
       }
       if (ph) {
-        std::string upd = "acc" + std::to_string(s) + " = " + Em::combine(*ph, "acc" + std::to_string(s), name(want, true)) + ";";
+        // (long rows: the elements of a position in pairs first, which shortens the chain of additions to a quarter)
+        std::string upd = RT == 1024 ? "c4[j] = " + name(want, true) + ";" : "acc" + std::to_string(s) + " = " + Em::combine(*ph, "acc" + std::to_string(s), name(want, true)) + ";";
+        if (guarded && RT == 1024) e.o << "      c4[j] = " << Em::identity(*ph) << ";\n";
         if (guarded) e.o << "      if (c + j < C) " << upd << "\n";
         else e.o << "      " << upd << "\n";
       } else {
@@ -901,12 +914,19 @@ void gen_rowred(Em& e) {
         else e.o << "      ov[j] = " << name(want, true) << ";\n";
       }
       e.o << "    }\n";
+      if (ph && RT == 1024) {
+        const std::string c = "gr_comb" + std::to_string(s);
+        e.o << "    acc" << s << " = " << c << "(acc" << s << ", " << c << "(" << c << "(c4[0], c4[1]), " << c << "(c4[2], c4[3])));\n";
+      }
       if (final_stage && g.out_dtype != GR_I64) {
         const char* vt = g.out_dtype == GR_F32 ? "f4u" : "i4u";
         const std::string st = (g.nt & 8) ? "__builtin_nontemporal_store(ov, (GM " + std::string(vt) + "*)(po + c))" : "*(GM " + std::string(vt) + "*)(po + c) = ov";
         if (guarded) e.o << "    if (row_ok) { if (c + 4 <= C) " << st << "; else { for (int j = 0; j < 4; ++j) if (c + j < C) po[c + j] = ov[j]; } }\n";
         else e.o << "    if (row_ok) " << st << ";\n";
       }
+      // (long rows: an empty statement that the accumulator passes through holds the loads and the temporaries of a few positions
+      // at a time in registers; the compiler would sink the arithmetic of all positions behind all loads)
+      if (RT == 1024 && !guarded && (n_loads || heavy)) e.o << "    if (" << (heavy ? "" : "p < " + std::to_string(NP - 2) + " && ") << "p % " << LONG_POS << " == " << LONG_POS - 1 << ") asm volatile(\"\" : " << (ph ? "\"+v\"(acc" + std::to_string(s) + ")" : std::string()) << " : : \"memory\");\n";
       e.o << "  }\n";
     }
     if (ph) {

@@ -210,13 +210,19 @@ __global__ __launch_bounds__(256) void gr_interp_rowred_kernel(GrInterpRowArgs A
     unsigned acc = none;
     for (int v = 0; v < VL; ++v) {
     acc = none;
-    for (int p = 0; p < NP; ++p)
+    for (int p = 0; p < NP; ++p) {
+      unsigned c4[4] = {none, none, none, none};
+#pragma unroll
       for (int j = 0; j < 4; ++j) {
         const long long c = ((long long)p * RT + v * HT + lane) * 4 + j;
         if (c >= C) continue;
         gi_run(a, A.seg_begin[s], A.seg_end[s], c, idx, my, red[rslot]);
-        acc = gi_combine(op, is_int, acc, my[A.seg_slot[s] * 256]);
+        if (RT == 1024) c4[j] = my[A.seg_slot[s] * 256];
+        else acc = gi_combine(op, is_int, acc, my[A.seg_slot[s] * 256]);
       }
+      // (pairs first, as the generated kernel combines a position of a long row)
+      if (RT == 1024) acc = gi_combine(op, is_int, acc, gi_combine(op, is_int, gi_combine(op, is_int, c4[0], c4[1]), gi_combine(op, is_int, c4[2], c4[3])));
+    }
     for (int m = (RT < 64 ? RT : 64) / 2; m > 0; m >>= 1) acc = gi_combine(op, is_int, acc, (unsigned)__shfl_xor((int)acc, m, 64));
     if (RT > 64 && (threadIdx.x & 63) == 0) part[4 * v + (threadIdx.x >> 6)] = acc;
     }

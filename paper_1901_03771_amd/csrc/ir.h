@@ -147,6 +147,12 @@ inline int64_t gemm_split_extent(int64_t K, int64_t nsplit) {
   return nsplit > 1 ? (((K + nsplit - 1) / nsplit + 31) / 32) * 32 : K;
 }
 
+// A float operation that is a sequence of instructions of its own.
+inline bool heavy_op(const Instr& in) {
+  return in.dtype == GR_F32 && ((in.kind == IKind::BINARY && in.op == GR_DIV) ||
+                                (in.kind == IKind::UNARY && (in.op == GR_EXP || in.op == GR_LOG || in.op == GR_SQRT || in.op == GR_TANH || in.op == GR_ERF)));
+}
+
 // One sub-graph of the ordered list of Algorithm 1, ready for code generation.
 struct GroupPlan {
   GroupKind kind = GroupKind::MAP;

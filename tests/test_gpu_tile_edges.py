@@ -221,6 +221,19 @@ def test_programs_over_long_rows(env, shape):
     other.close()
 
 
+# (see test_column_sums_do_not_chain_additions: a lane adds up 16 positions of four elements, pairs first: an error below that of chains
+# of 32; one chain of 64 elements was above it)
+@pytest.mark.parametrize("shape", [(512, 65536), (512, 40001), (600, 33000)])
+def test_long_row_sums_do_not_chain_additions(env, shape):
+    gr, ctx, torch = env
+    err = 0.0
+    for seed in range(4):
+        x = torch.randn(shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(seed))
+        got, want = (gr.sum(ctx.array(x), axis=1) * 0.5).torch().double(), x.double().sum(1) * 0.5
+        err += float((got - want).norm() / want.norm()) / 4
+    assert err < 2.0**-24 * (32 / 6) ** 0.5
+
+
 # small integers: every sum is exact in any order.  Extents below, at and beside the tiles of 64 x 64, 128 x 32 and 32 x 128, groups
 # of four that stick out, sums of one step, of whole steps, of steps in flight and around them, sums split over workgroups
 @pytest.mark.parametrize("m,k,n", [(4, 9, 4), (5, 11, 6), (33, 31, 35), (63, 32, 61), (64, 33, 64), (65, 64, 67), (70, 95, 130), (129, 96, 66), (100, 97, 31), (300, 128, 19),

@@ -877,6 +877,36 @@ def test_column_sums_of_many_arrays_keep_to_registers(ctx, tmp_path, arrays):
     assert _registers(gr.sum(value, axis=0), tmp_path)[1] == 0
 
 
+def _squares_to_one(t):
+    return t / gr.sum(t * t, axis=-1, keepdims=True)
+
+
+LONG_ROW_PROGRAMS = {   # values that stay in registers while others pass through them
+    "softmax": lambda x, y, z: wl.softmax(gr, x),
+    "layer norm": lambda x, y, z: (lambda d: d / gr.sqrt(gr.mean(d * d, 1, True) + 1e-5))(x - gr.mean(x, 1, True)),
+    "tanh": lambda x, y, z: _squares_to_one(gr.tanh(0.79 * x) * x),
+    "logistic": lambda x, y, z: _squares_to_one(x / (1.0 + gr.exp(-x))),
+    "erf and log": lambda x, y, z: (lambda t: _squares_to_one(t) + gr.max(t, -1, True))(gr.erf(x) * x + gr.log(abs(x) + 1.0)),
+    "two arrays": lambda x, y, z: _squares_to_one(x * y + x),
+    "three arrays": lambda x, y, z: _squares_to_one(gr.tanh(x * y) + z) * y,
+    "exp and its operand": lambda x, y, z: wl.softmax(gr, x) + x,
+    "sum of products": lambda x, y, z: gr.sum(x * y, axis=1) * 2.0,
+    "a value per row of three arrays": lambda x, y, z: gr.log(gr.sum(gr.exp(x - gr.max(x, 1, True)) * gr.tanh(y * z), axis=1) + 1.0),
+}
+
+
+@pytest.mark.parametrize("name", sorted(LONG_ROW_PROGRAMS))
+def test_long_rows_keep_their_values_in_registers(ctx, tmp_path, name):
+    seen = 0
+    for cols in (20000, 40000, 49152, 65536):
+        out = LONG_ROW_PROGRAMS[name](*(ctx.spec((4096, cols)) for _ in range(3)))
+        if "row_threads=1024" not in out.plan():
+            continue   # (cut: more than 80 registers of values between two of its reductions)
+        seen += 1
+        assert _registers(out, tmp_path)[1] == 0, cols
+    assert seen >= 1
+
+
 PAIR_PROGRAMS = {   # program, dtype, longest row that the kernel for pairs takes
     "squares": (lambda a, b: gr.sum((a - b) * (a - b), axis=2), gr.GR_F32, 64),
     "products": (lambda a, b: gr.sum(a * b, axis=2), gr.GR_F32, 64),
