@@ -514,15 +514,6 @@ void pop_output_group(GroupPlan* g) {
   g->out_unit = g->out_coef[g->rank - 1] == 1 || g->dims[g->rank - 1] == 1;
 }
 
-// Longest row of `x` that reductions with consumers may keep in registers: 64 elements of each of 1024 lanes.  Arrays of fewer than
-// 16 rows keep the partition into cuts beyond what 256 lanes hold: a handful of workgroups cannot fill the chip, though up
-// to here they are still faster than the cuts' launches (softmax of 8 x 20000: 16.5 us in cuts, 7.1 resident; of 1 x 65536
-// 16.4 and 15.3), and the tests show the paper's own partition of a softmax on such an array.
-int64_t resident_limit(const gr_ctx* c, const Node* x) {
-  const int64_t C = x->shape[x->ndim - 1];
-  return std::min<int64_t>(c->opt_rowred_max_cols, C > 0 && x->count() / C >= 16 ? 65536 : 16384);
-}
-
 struct Planner {
   gr_ctx* c;
   Node* root;
@@ -564,7 +555,7 @@ struct Planner {
         const Node* x = n->in[0];
         bool last_only = x->ndim >= 1;
         for (int d = 0; d < x->ndim; ++d) if (n->red_axis[d] != (d == x->ndim - 1)) last_only = false;
-        if (!last_only || x->shape[x->ndim - 1] > resident_limit(c, x)) cuts.insert(n);
+        if (!last_only || x->shape[x->ndim - 1] > std::min<int64_t>(c->opt_rowred_max_cols, 65536)) cuts.insert(n);   // (64 elements of each of 1024 lanes)
       }
     }
   }
@@ -706,8 +697,7 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
     const int64_t tc = (int64_t)g->BX * 4, padded = (C + tc - 1) / tc * tc;
     int64_t ops = 0;   // per element, in simple operations
     for (const Instr& in : g->prog1)
-      if (!in.uniform && (in.kind == IKind::UNARY || in.kind == IKind::BINARY))
-        ops += in.dtype == GR_F32 && (in.op == GR_DIV || in.op == GR_EXP || in.op == GR_LOG || in.op == GR_SQRT || in.op == GR_TANH || in.op == GR_ERF) ? 8 : 1;
+      if (!in.uniform && (in.kind == IKind::UNARY || in.kind == IKind::BINARY)) ops += heavy_op(in) ? 8 : 1;
     const bool heavy = ops >= 16 && C * 100 < padded * 80;
     if (heavy || (g->BX >= 128 && C > tc && C * 100 < padded * 85)) {
       g->flat = 1;
@@ -785,8 +775,8 @@ void choose_gemm_tiles(GroupPlan* g, int wanted) {
 }
 
 // Row-resident reductions: per-element values that are computed in one phase and used in a later one, the most alive
-// between any two phases.
-int rowred_live(const GroupPlan& g) {
+// between any two phases; `early`: one of them is computed, not just loaded, in the first.
+int rowred_live(const GroupPlan& g, bool* early = nullptr) {
   const int n = (int)g.prog.size(), nst = (int)g.phases.size() + 1;
   std::vector<int> made(n, -1), used(n, -1);
   for (int s = 0; s < nst; ++s) {
@@ -807,10 +797,47 @@ int rowred_live(const GroupPlan& g) {
   int most = 0;
   for (int s = 0; s + 1 < nst; ++s) {
     int live = 0;
-    for (int i = 0; i < n; ++i) if (!g.prog[i].uniform && made[i] >= 0 && made[i] <= s && used[i] > s) ++live;
+    for (int i = 0; i < n; ++i)
+      if (!g.prog[i].uniform && made[i] >= 0 && made[i] <= s && used[i] > s) {
+        ++live;
+        if (s == 0 && early && g.prog[i].kind != IKind::LOAD) *early = true;
+      }
     most = std::max(most, live);
   }
   return most;
+}
+
+// Whether rows of more than 16384 elements, which take one workgroup of 1024 lanes each, are worth keeping in registers
+// over cutting the program at its reductions: estimates of both in microseconds, fitted to measurements at 1 to 600 rows of 16400
+// to 65536 elements.  A workgroup walks its row in 0.5 per 10^4 elements and array read, 0.4 for a result per element and
+// what divisions, exp and the like take; the chip holds 256 of them at a time.  Cuts cost a launch for each reduction and for
+// the map after it (and before it, of a value that is used again), and the passes over the arrays between them at 5.5 TB/s.
+// (us, cuts / resident: softmax of 8 x 20000 16.5 / 7.1, 16 x 65536 17.9 / 17.5, 1245 x 26936 148 / 58, 512 x 65536 133 / 62; x - mean(x) of 16 x 32768
+// 8.8 / 4.0; tanh(0.79 x) x over the sum of its squares 16 x 20000 11.7 / 7.8, 16 x 65536 14.9 / 22.9, 64 x 65536 26.4 / 25.4; sum(tanh(x)) / 2 of 16 x 16400
+// 8.6 / 5.4, 64 x 65536 10.6 / 17.7, 256 x 49152 16.7 / 14.9; sum(x) / 2 of 16 x 65536 8.7 / 5.0, 600 x 65536 30.9 / 27.6.)
+bool long_rows_pay(const GroupPlan& g) {
+  const int64_t C = g.dims[g.rank - 1];
+  int64_t rows = 1;
+  for (int k = 0; k + 1 < g.rank; ++k) rows *= g.dims[k];
+  const bool full = !g.out_per_row;
+  int loads = 0;
+  double per = full ? 0.4 : 0.0;
+  for (const Instr& in : g.prog) {
+    if (in.uniform) continue;
+    if (in.kind == IKind::LOAD) { ++loads; per += 0.5; }
+    else if (heavy_op(in)) {
+      if (in.op == GR_TANH || in.op == GR_ERF) per += full ? 1.5 : 1.8;
+      else if (in.op == GR_EXP || in.op == GR_LOG) per += full ? 0.7 : 1.1;
+      else per += 0.75;
+    }
+  }
+  const int reds = (int)g.phases.size();
+  bool stored = false;   // a value that is computed for the first reduction is used again
+  rowred_live(g, &stored);
+  const double resident = 2.7 + (double)C * per * 1e-4 * std::max(1.0, (double)rows / 256);
+  const int launches = 2 * reds + (stored ? 1 : 0), passes = loads - 1 + (full ? 2 * reds + 2 + (stored ? 1 : 0) : 3 * reds - 2);
+  const double cuts = std::max(4.1 * launches, 3.4 * launches + (double)rows * (double)C * 4.0 * passes / 5.5e6);
+  return resident <= cuts;
 }
 
 // Vector instructions per element of a row's value, about; 0 for a program with an operation that is a sequence of its own
@@ -917,8 +944,7 @@ void choose_column_split(GroupPlan* g) {
   // 212 / 166, 2048 x 65536 91.5 / 84.4, 512 x 64 x 1024 over the middle 27.4 / 24.4, 700 x 70001 42.7 / 36.5 in 137 blocks and 47 in 274, of exp 46 /
   // 42 in 274 and 55 in 137; 20 x 300001 of exp 7.6 / 8.2 in 293; 64 x 64 x 64 x 64 over the third 14.0 / 17.8, whose rows are short.)
   bool heavy = false;
-  for (const Instr& in : g->prog)
-    if (in.dtype == GR_F32 && (in.kind == IKind::UNARY || in.kind == IKind::BINARY) && (in.op == GR_DIV || in.op == GR_EXP || in.op == GR_LOG || in.op == GR_SQRT || in.op == GR_TANH || in.op == GR_ERF)) heavy = true;
+  for (const Instr& in : g->prog) if (heavy_op(in)) heavy = true;
   const int64_t D = g->dims[g->red_kept_rank - 1], fill = D < 1024 || (heavy && LEN < 64 && D % 32) ? 512 : (D % 32 == 0 || heavy ? 256 : 128);
   int64_t bx = kReduceLanes;
   while (bx > 16 && (V + bx - 1) / bx < fill) bx /= 2;
@@ -1504,17 +1530,16 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
       // (measured on MI355X for 4096-float rows: 256 lanes 93 us, 128 lanes 96 us, 64 lanes 104 us)
       // lanes per row: enough for one to four dwordx4 positions per lane; very short rows share a
       // wave between many rows instead of leaving most of 16 lanes idle
-      // Rows of more than 16384 elements whose reductions feed a value per element: 1024 lanes, up to 16 positions per lane,
-      // one workgroup per row.  (A cut per reduction reads and writes the matrix four times over; softmax, cuts against
-      // resident rows, us: 2047 x 16388 149 / 54, 1245 x 26936 148 / 58, 512 x 65536 133 / 62, 500 x 40001 100 / 37, 143 x 26823
-      // 31 / 12, 1 x 65536 16.4 / 15.3.)  A sum of such rows that is a result of its own stays with the two-stage kernel.
+      // Rows of more than 16384 elements: 1024 lanes, up to 16 positions per lane, one workgroup per row, where that pays
+      // (long_rows_pay).  A sum of such rows that is a result of its own stays with the two-stage kernel.
       g->row_threads = C <= 4 ? 1 : (C <= 8 ? 2 : (C <= 16 ? 4 : (C <= 32 ? 8 : (C <= 256 ? 16 : (C <= 1024 ? 64 : (C <= 2048 ? 128 : 256))))));
       if (c->opt_rowred_threads == 16 || c->opt_rowred_threads == 64 || c->opt_rowred_threads == 128 || c->opt_rowred_threads == 256)
         if (C <= c->opt_rowred_threads * 64) g->row_threads = (int)c->opt_rowred_threads;  // at most 16 positions per lane
       if (C > 16384) g->row_threads = 1024;
       g->NP = (int)std::max<int64_t>(1, (C + (int64_t)g->row_threads * 4 - 1) / ((int64_t)g->row_threads * 4));
-      // The values that a phase leaves for later ones live in registers: of 128 per lane, 80 may hold them.
-      if (g->row_threads == 1024 && (int64_t)rowred_live(*g) * g->NP * 4 > 80) {
+      // The values that a phase leaves for later ones live in registers: of 128 per lane, 80 may hold them (the others hold
+      // the operands and temporaries of a few positions).
+      if (g->row_threads == 1024 && ((int64_t)rowred_live(*g) * g->NP * 4 > 80 || !long_rows_pay(*g))) {
         for (const Node* n : reds) if (n != r) invalid->push_back({n, "rows too long to keep their values"});
         if (!invalid->empty()) return GR_OK;
       }

@@ -191,12 +191,14 @@ def test_scans_of_short_lines(env, shape):
     assert got.dtype == np.int64 and np.array_equal(got, ref)
 
 
-# rows kept by 1024 lanes: one element more than 256 lanes keep, ragged, all 16 positions, the first length
-# beyond; the fewest rows
-@pytest.mark.parametrize("shape", [(16, 16385), (19, 20000), (15, 20000), (16, 33001), (17, 65535), (16, 65536), (16, 65537), (2, 8, 17000)])
-def test_programs_over_long_rows(env, shape):
+# rows kept by 1024 lanes: one element more than 256 lanes keep, ragged, every count of positions, the first length
+# beyond; one row and many.  `kept`: whether a softmax, a program that normalises one array and a program over two arrays stay in one kernel
+@pytest.mark.parametrize("shape,kept", [((16, 16385), "RRR"), ((19, 20000), "RRR"), ((15, 20000), "RRR"), ((1, 20479), "RRR"), ((40, 25000), "RRR"), ((16, 33001), "RRR"), ((40, 36864), "RRR"),
+                                        ((64, 40001), "RRR"), ((70, 45056), "R-R"), ((64, 49153), "R-R"), ((33, 53000), "R-R"), ((64, 57344), "R-R"), ((65, 61437), "R-R"), ((17, 65535), "R--"),
+                                        ((16, 65536), "R--"), ((64, 65536), "R-R"), ((300, 65533), "R-R"), ((16, 65537), "---"), ((2, 8, 17000), "RRR")])
+def test_programs_over_long_rows(env, shape, kept):
     gr, ctx, torch = env
-    a = positive(shape, 19) * f32(3.0)
+    a, b = positive(shape, 19) * f32(3.0), positive(shape, 20)
 
     def softmax(xp, a):
         e = xp.exp(a - xp.max(a, axis=-1, keepdims=True))
@@ -206,14 +208,22 @@ def test_programs_over_long_rows(env, shape):
         s = xp.sqrt(a) + a
         return s / xp.sqrt(xp.sum(s * s, axis=-1, keepdims=True)) + a * xp.max(s, axis=-1, keepdims=True)
 
+    def product(xp, a, b):
+        s = a * b + a
+        return s / xp.sum(s * s, axis=-1, keepdims=True)
+
     other = gr.Context()
     other.set_option("interp", 2)      # the byte-code interpreter: the same bits
-    t = torch.from_numpy(a).cuda()
-    for prog in (softmax, normal, lambda xp, a: xp.log(xp.sum(xp.exp(a), axis=-1) + 1.0)):
-        got, ref = both(env, prog, a=a)
+    routes = ""
+    for prog in (softmax, normal, product, lambda xp, a: xp.log(xp.sum(xp.exp(a), axis=-1) + 1.0)):
+        arrays = dict(a=a, b=b) if prog is product else dict(a=a)
+        got, ref = both(env, prog, **arrays)
         assert reduction_check(got, ref)[0].all()
-        if shape[-1] <= 65536 and shape[0] != 15 and prog is softmax:
-            assert np.array_equal(prog(gr, other.array(t)).numpy(), got)
+        routes += "R" if "row_threads=1024" in planned(env, prog, **arrays) else "-"
+        if routes[-1] == "R":
+            keep = {k: torch.from_numpy(v).cuda() for k, v in arrays.items()}
+            assert np.array_equal(prog(gr, **{k: other.array(t) for k, t in keep.items()}).numpy(), got)
+    assert routes[:3] == kept
     i = np.random.default_rng(20).integers(-2**31, 2**31 - 1, shape, dtype=np.int64).astype(np.int32)
     got, ref = both(env, lambda xp, i: i - xp.max(i, axis=-1, keepdims=True) + xp.min(i, axis=-1, keepdims=True), i=i)
     assert np.array_equal(got, ref)

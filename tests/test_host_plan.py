@@ -428,6 +428,7 @@ def test_leaves_and_only_leaves_are_materialised(ctx):
 
 
 def test_row_resident_limit_turns_reduction_into_a_cut(ctx):
+    ctx.set_option("rowred_max_cols", 16384)
     x = ctx.spec((8, 20000))
     out = wl.softmax(gr, x)
     # max is cut; exp(X-m) feeds both the (cut) sum and the final division, so the
@@ -905,6 +906,20 @@ def test_long_rows_keep_their_values_in_registers(ctx, tmp_path, name):
         seen += 1
         assert _registers(out, tmp_path)[1] == 0, cols
     assert seen >= 1
+
+
+def test_long_rows_are_cut_where_few_workgroups_lose(ctx):
+    def resident(prog, rows, cols):
+        return "row_threads=1024" in prog(ctx.spec((rows, cols))).plan()
+
+    softmax = lambda x: wl.softmax(gr, x)
+    heavy = lambda x: _squares_to_one(gr.tanh(0.79 * x) * x)
+    heavy_sum = lambda x: gr.sum(gr.tanh(x), axis=1) * 0.5
+    mean = lambda x: gr.mean(x, 1)
+    assert all(resident(softmax, r, 20000) for r in (1, 8, 15, 16, 2000)) and resident(softmax, 16, 65536)
+    assert resident(heavy, 16, 20000) and not resident(heavy, 16, 65536) and resident(heavy, 64, 65536) and resident(heavy, 600, 65536)
+    assert resident(heavy_sum, 16, 16400) and not resident(heavy_sum, 64, 65536) and resident(heavy_sum, 256, 49152)
+    assert all(resident(mean, r, 65536) for r in (1, 16, 600)) and not resident(mean, 600, 65537)
 
 
 PAIR_PROGRAMS = {   # program, dtype, longest row that the kernel for pairs takes
