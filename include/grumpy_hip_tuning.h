@@ -39,6 +39,10 @@ extern "C" {
  *                     compute unit, where the result fills at least 85 % (65 % if M or N is not a multiple
  *                     of 128) of its rounds over the 256 compute units, else 128 x 128 tiles; 0 = the kernel
  *                     that stages tiles through registers for every product
+ *   "gemm_clamped"    1 (default) = small or ragged matrix products use tiles of 64 x 64, 128 x 32 or 32 x 128 with
+ *                     unguarded loads from clamped positions, where an estimate of their time is no higher than that
+ *                     of the kernels above; 0 = never ("gemm_big" = 0, "gemm_bn", "gemm_kstep" and "gemm_split" switch
+ *                     them off as well)
  *   "nontemporal"     1 (default) = loads of arrays that are read once carry the non-temporal hint,
  *                     and so do the vector stores of a requested value of 192 MiB or more (not of
  *                     intermediate results of the request; except in kernels that read a transposed

@@ -714,15 +714,19 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
 
 // Small or ragged matrix products: tiles of 64 x 64 (128 x 32, 32 x 128) with clamped loads (gemm_tile_body), after the
 // choice between the kernels with tiles of 128 and 256.
-// Cost of such a product in microseconds, fitted to measurements: rounds of 256 workgroups times steps of 32 values of k at 0.62,
-// 5 for the launch and the first loads, and for a split of K 4 for the second launch and the partial tiles' traffic at 5 TB/s.
+// The split of K: cheapest by rounds of 256 workgroups times steps of 32 values of k at 0.62 us, 5 for the launch and the first
+// loads, and for a split 4 for the second launch and the partial tiles' traffic at 5 TB/s.
 // It takes over from the register-staged kernel (us, before / now: 2001^3 275 / 156, 649 x 448 x 714 26 / 15, 1792 x 74 x 213
-// 14.6 / 6.3, 11845 x 2066 x 48 78 / 48, 2066 x 11845 x 48 62 / 39, 64 x 4096 x 4096 49 / 29, 512^3 16.6 / 10.4, 30 x 5000 x 3000 56 / 23),
+// 14.6 / 6.3, 11845 x 2066 x 48 78 / 48, 2066 x 11845 x 48 62 / 39, 64 x 4096 x 4096 49 / 29, 30 x 5000 x 3000 56 / 23),
 // except for short sums with a large result, whose stores bound it and which the larger tile writes faster (11845 x 48 x 2066
 // 42 against 57, 16384 x 100 x 1000 44 / 58, 2^20 x 16 x 8 26 / 55), tall operands with few columns (65536 x 512 x 10 28 / 31)
 // and large products of two operands contiguous along k (4001^3 1082 / 1111; the other layouts 1201 / 1143 and
-// 1318 / 1152); and from the direct 128 x 128 kernel where its cost is 2 lower (4096 x 784 x 512 42 / 39; 4096 x 512 x 784 stays: 37
-// against 45).
+// 1318 / 1152); and from the direct 128 x 128 kernel where an estimate of its time is 5 % lower than that kernel's.  Both
+// estimates, in microseconds, were fitted to 446 products of 64 to 4096 values of k in four layouts (within 7 %): rounds of 256
+// workgroups times steps, the launch, and for a split the second launch and the partial tiles' traffic.  The choice misses the
+// faster kernel by 2.6 % at most (direct / this: 512^3 16.8 / 10.5, 512 x 528 x 512 18.6 / 11.3, 256 x 2048 x 256 17.5 / 11.3, 1000 x 512 x 252
+// 16.8 / 10.6, 1024 x 784 x 512 22.3 / 18.2, 4096 x 784 x 512 39.0 / 34.3, with a bias and tanh 42.1 / 40.5; 768 x 1024 x 768 stays: 22.3 / 24.3, 512 x 4096 x 512
+// 27.5 / 28.9, 4096 x 512 x 784 37.2 / 42.7, 2048^3 129 / 151).
 // `wanted`: splits of K that the larger tiles would take if they may store any number of partial tiles.  It decides
 // between the kernels, so that a request that must not allocate takes the kernel that the same request would take
 // otherwise (and that is loaded by then); g->slabs, which stays within its scratch array, bounds the splits.
@@ -758,13 +762,13 @@ void choose_gemm_tiles(GroupPlan* g, int wanted) {
   };
   const int before = g->slabs, best_ks = cheapest(before);
   if (g->VR == 2) {
-    // (long sums over small results stay with the direct kernel's division of K, whose tests hold it to that: a bound of its
-    // own, not a measured crossing; 640 x 512 x 1024 and the like may be faster here)
-    if (K >= 512 && M * N < (int64_t)1 << (K == 512 ? 18 : 20)) return;
-    cheapest(wanted);
-    const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128) * wanted, steps = (gemm_split_extent(K, wanted) + 15) / 16;
-    const double direct = (double)((wgs + 255) / 256) * (double)steps * (wgs <= 256 ? 1.1 : 0.95) + 2.0 + (wanted > 1 ? 6.0 + (double)wanted * (double)M * (double)N * 8.0 / 5e6 : 0.0);
-    if (cost + 2.0 > direct) return;
+    const int ks = cheapest(wanted);
+    auto rounds = [](int64_t workgroups) { return (double)((workgroups + 255) / 256); };
+    auto split = [&](double launch, double traffic, int n) { return n > 1 ? launch + traffic * (double)n * (double)M * (double)N * 8e-6 : 0.0; };
+    const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128) * wanted;
+    const double direct = rounds(wgs) * (double)((gemm_split_extent(K, wanted) + 15) / 16) * (wgs <= 256 ? 0.93 : 0.86) + 4.3 + split(3.4, 0.18, wanted);
+    const double clamped = rounds(tiles * ks) * (double)((gemm_split_extent(K, ks) + 31) / 32) * 0.56 + 4.0 + split(2.7, 0.22, ks);
+    if (clamped * 1.05 > direct) return;
   }
   g->VR = 3;
   g->UC = 1;
@@ -1307,7 +1311,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         g->UC = 1;
       }
     }
-    if (c->opt_gemm_bn == 0 && c->opt_gemm_kstep == 0 && c->opt_gemm_split == 0 && c->opt_gemm_big) choose_gemm_tiles(g, wanted ? wanted : g->slabs);
+    if (c->opt_gemm_bn == 0 && c->opt_gemm_kstep == 0 && c->opt_gemm_split == 0 && c->opt_gemm_big && c->opt_gemm_clamped) choose_gemm_tiles(g, wanted ? wanted : g->slabs);
   } else if (dot && !(dot == r && dot_as_reduce(dot) && c->opt_fusion)) {
     // ---- contraction with pointwise epilogue ------------------------------
     g->kind = GroupKind::GEMV;

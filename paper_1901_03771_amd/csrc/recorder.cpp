@@ -234,6 +234,7 @@ gr_status gr_ctx_set_option(gr_ctx* ctx, const char* key, int64_t value) {
   else if (k == "gemm_kstep") ctx->opt_gemm_kstep = value;
   else if (k == "gemm_split") ctx->opt_gemm_split = value;
   else if (k == "gemm_big") ctx->opt_gemm_big = value;
+  else if (k == "gemm_clamped") ctx->opt_gemm_clamped = value;
   else if (k == "map_phase") ctx->opt_map_phase = value;
   else if (k == "pool_limit") ctx->opt_pool_limit = value;
   else if (k == "stage_rows") ctx->opt_stage_rows = value;

@@ -969,6 +969,7 @@ def test_matrix_products_with_k_divided_over_direct_workgroups(env, layout, M, N
                   rowv=g.integers(-5, 6, (N,)).astype(f32), Z=g.integers(-2, 3, (M, N)).astype(f32))
     prog = lambda xp, X, Y, rowv, Z: ((X.T if layout[0] == "t" else X) @ (Y.T if layout[1] == "t" else Y) + rowv) * Z
     ctx.set_option("gemm_split", split)
+    ctx.set_option("gemm_clamped", 0)
     try:
         dev, keep = to_dev(torch, ctx, arrays)
         plan = prog(gr, **dev).plan()
@@ -979,6 +980,7 @@ def test_matrix_products_with_k_divided_over_direct_workgroups(env, layout, M, N
         ctx.sync()
     finally:
         ctx.set_option("gemm_split", 0)
+        ctx.set_option("gemm_clamped", 1)
     ref = prog(ora, **{k: ora.array(v) for k, v in arrays.items()}).numpy()
     assert np.array_equal(buf[4096:4096 + M * N].view(M, N).cpu().numpy(), ref)
     assert bool((buf[:4096] == -77.0).all()) and bool((buf[4096 + M * N:] == -77.0).all())
@@ -990,6 +992,7 @@ def test_direct_matrix_products_of_random_shapes(env, seed):
     four layouts, operands that are windows of larger arrays, a bias along either dimension; small integers, every element."""
     gr, ctx, torch = env
     g = np.random.default_rng(470 + seed)
+    ctx.set_option("gemm_clamped", 0)
     direct = 0
     for case in range(10):
         ta, tb = bool(g.integers(2)), bool(g.integers(2))
@@ -1015,6 +1018,7 @@ def test_direct_matrix_products_of_random_shapes(env, seed):
         got, ref = run_both(env, prog, arrays)
         assert got.shape == (M, N) and np.array_equal(got, ref), (seed, case, M, N, K, ta, tb)
     ctx.set_option("gemm_split", 0)
+    ctx.set_option("gemm_clamped", 1)
     assert direct >= 3, "many of these shapes go to the direct kernels (results whose last 128 columns are mostly empty take 32-wide tiles)"
 
 
@@ -1740,7 +1744,7 @@ def test_interpreter_reductions_over_any_axes(env_interp, shape, axis, keep):
         assert np.array_equal(got, ref)
         assert ctx.stats()["interp_launches"] >= n0 + 6, "the interpreter did not run"
     finally:
-        ctx.set_option("rowred_max_cols", 16384)
+        ctx.set_option("rowred_max_cols", 65536)
 
 
 @pytest.mark.parametrize("shape,axis", [c for c in SCAN_CASES if int(np.prod(c[0])) <= 1 << 21])

@@ -840,6 +840,20 @@ def test_one_kernel_of_row_pairs_serves_every_length_without_allocating(ctx, d):
     assert ctx.stats()["cache_misses"] == misses + 1
 
 
+def test_products_near_a_size_take_the_same_kernel(ctx):
+    # the choice between the direct kernel and clamped tiles is a comparison of estimates: no size stands out among its neighbours
+    def tiles(m, k, n):
+        return re.search(r"tile=(\S+ \S+)", (ctx.spec((m, k)) @ ctx.spec((k, n))).plan())[1]
+
+    for m, n in ((512, 512), (508, 512), (1000, 252), (640, 512), (256, 256), (1024, 512)):
+        assert {tiles(m, k, n) for k in (448, 480, 496, 512, 528, 544, 640)} == {"64x64 clamped"}, (m, n)
+    for m, k, n in ((768, 1024, 768), (512, 4096, 512), (4096, 512, 784), (2048, 2048, 2048)):
+        assert tiles(m, k, n) == "128x128 direct", (m, k, n)
+    assert tiles(4096, 784, 512) == "64x64 clamped"
+    ctx.set_option("gemm_clamped", 0)
+    assert tiles(512, 512, 512) == "128x128 direct"
+
+
 @pytest.mark.parametrize("rows", [3, 30, 64, 300, 700, 4096, 20000, 300000, 5000000])
 def test_column_sums_bound_the_chain_of_additions(ctx, rows):
     # a lane adds up at most 256 elements in turn, or blocks of 64 of them; no output is left to fewer lanes than the chip has where rows suffice
