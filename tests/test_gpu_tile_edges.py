@@ -246,7 +246,7 @@ def test_long_row_sums_do_not_chain_additions(env, shape):
 
 # small integers: every sum is exact in any order.  Extents below, at and beside the tiles of 64 x 64, 128 x 32 and 32 x 128, groups
 # of four that stick out, sums of one step, of whole steps, of steps in flight and around them, sums split over workgroups
-@pytest.mark.parametrize("m,k,n", [(4, 17, 4), (5, 19, 6), (724, 9, 740), (801, 4, 702), (33, 31, 35), (63, 32, 61), (64, 33, 64), (65, 64, 67), (70, 95, 130), (129, 96, 66), (100, 97, 31), (300, 128, 19),
+@pytest.mark.parametrize("m,k,n", [(4, 17, 4), (5, 19, 6), (724, 9, 740), (801, 12, 702), (33, 31, 35), (63, 32, 61), (64, 33, 64), (65, 64, 67), (70, 95, 130), (129, 96, 66), (100, 97, 31), (300, 128, 19),
                                    (131, 160, 32), (29, 129, 200), (32, 161, 129), (30, 1000, 300), (37, 4100, 41), (66, 2051, 200), (257, 515, 255), (8, 300, 5)])
 @pytest.mark.parametrize("layout", ["nn", "tn", "nt", "tt"])
 def test_products_with_clamped_tiles(env, m, k, n, layout):
