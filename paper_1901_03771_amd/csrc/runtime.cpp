@@ -364,7 +364,7 @@ static bool still_compiling(gr_ctx* c, const std::string& sig) {
 }
 
 gr_status compile_group(gr_ctx* c, GroupPlan& g, gr_ctx::Kernel** out) {
-  if (g.pair_k && c->pending.count(g.general) && (c->opt_interp != 1 || c->capture || !still_compiling(c, g.general))) {
+  if (g.pair_k && !c->pending.empty() && c->pending.count(g.general) && (c->opt_interp != 1 || c->capture || !still_compiling(c, g.general))) {
     gr_status st = prepare_group(c, g);   // (both compile at the same time)
     if (st == GR_OK && c->pending.count(g.general)) st = collect_job(c, g.general, nullptr);
     if (st != GR_OK) return st;
@@ -393,7 +393,7 @@ gr_status compile_group(gr_ctx* c, GroupPlan& g, gr_ctx::Kernel** out) {
 // Whether the lane groups' kernel runs a plan for rows over pairs: it is loaded, and that plan's own is not (nor can
 // be had at once, unless the request must not load kernels at all).
 static bool use_general(gr_ctx* c, const GroupPlan& g) {
-  return g.pair_k && !c->cache.count(g.signature) && c->cache.count(g.general) && (c->static_mode || still_compiling(c, g.signature));
+  return g.pair_k && (c->static_mode || !c->pending.empty()) && !c->cache.count(g.signature) && c->cache.count(g.general) && (c->static_mode || still_compiling(c, g.signature));
 }
 
 static gr_status launch(gr_ctx* c, hipFunction_t fn, const std::string& name, int64_t grid, std::vector<uint64_t>& args, unsigned threads = 256) {
