@@ -107,7 +107,11 @@ gr_status gr_ctx_set_allocator(gr_ctx* ctx, void* (*alloc)(size_t bytes, void* u
  *                     one kernel per recorded op, every intermediate stored
  *                     (the eager execution model the paper starts from)
  *   "rowred_max_cols" longest row (elements) a reduction may keep resident
- *                     in registers and still fuse with its consumers
+ *                     in registers and still fuse with its consumers; default
+ *                     and largest effective value 65536.  Rows of more than
+ *                     16384 elements stay resident only where an estimate
+ *                     from the row's length, the number of rows and the
+ *                     program says that it is faster than the cuts
  *   "gemv_pair"       1 (default) = a contraction A.v whose epilogue result r
  *                     feeds the contraction A^T.r runs with it in one pass
  *                     over A; 0 = two passes

@@ -1830,7 +1830,8 @@ std::string describe_plan(const Plan& plan) {
       else if (g.row_iters > 1) s << " rows_per_group=" << g.row_iters;
     }
     if (g.kind == GroupKind::SCAN) s << " mode=" << (g.scan_mode == 4 ? "lines-in-lane-groups" : g.scan_mode == 3 ? "one-pass-line-tiles" : (g.scan_mode == 2 ? "one-pass-tiles" : (g.scan_mode ? "thread-per-line" : "lanes-along-axis"))) << " lines=" << g.red_out << " length=" << g.red_len << " chunks=" << g.scan_nchunk;
-    if (g.kind == GroupKind::MAP) s << " tile=" << g.BY * g.VR << "x" << g.BX * 4 * g.UC << " patch=" << g.VR << "x" << g.UC * 4;
+    if (g.kind == GroupKind::MAP && g.flat == 1) s << " lanes over groups of columns patch=" << g.VR << "x4";
+    else if (g.kind == GroupKind::MAP) s << " tile=" << g.BY * g.VR << "x" << g.BX * 4 * g.UC << " patch=" << g.VR << "x" << g.UC * 4 << (g.flat == 2 ? " overlapping" : "");
     s << '\n';
   }
   return s.str();

@@ -33,6 +33,12 @@ def both(env, program, **arrays):
     return got, ref
 
 
+def planned(env, program, **arrays):
+    gr, ctx, torch = env
+    code = {np.dtype(f32): gr.GR_F32, np.dtype(np.int32): gr.GR_I32}
+    return program(gr, **{k: ctx.spec(v.shape, code[v.dtype]) for k, v in arrays.items()}).plan()
+
+
 def positive(shape, seed):
     return (np.random.default_rng(seed).random(shape) + 0.25).astype(f32)
 
@@ -45,6 +51,7 @@ def positive(shape, seed):
     ((40, 6, 50, 7), (0, 2)), ((50, 30, 6), (0, 1)), ((0, 300), 0)])
 def test_column_reductions(env, shape, axis):
     a = positive(shape, 7)
+    assert " lanes=" in planned(env, lambda xp, a: xp.sum(a * a, axis=axis), a=a)
     if 0 not in shape:
         a.reshape(-1)[:: max(1, a.size // 5)] = -3.5
         for op in ("max", "min"):
@@ -95,16 +102,22 @@ def test_column_sums_do_not_chain_additions(env, shape, c):
     assert float((got - want).norm() / want.norm()) < 2.0**-24 * (c / 6) ** 0.5
 
 
-# columns: ragged and whole groups of four, narrow arrays, one tile and a little more; rows: below, at and beside a patch
-@pytest.mark.parametrize("shape", [(2, 5), (3, 4), (5, 6), (17, 9), (4, 257), (63, 63), (66, 1027), (1031, 1028), (70, 1501), (4100, 1537), (3, 65, 7), (5, 130, 1030),
-                                   (2, 3, 4, 5), (70001, 33)])
-def test_maps_of_ragged_rows(env, shape):
+# columns: ragged and whole groups of four, narrow arrays, one tile and a little more; rows: below, at and beside a patch.
+# `kinds`, of a long program, a short one and a stencil: L lanes numbered over groups of columns, o tiles whose last groups overlap, - others
+@pytest.mark.parametrize("shape,kinds", [((2, 5), "Lo"), ((2, 3), "--"), ((3, 4), "--"), ((5, 6), "Lo-"), ((17, 9), "Loo"), ((4, 257), "Lo"), ((63, 63), "ooo"), ((66, 1027), "LLL"), ((1031, 1028), "LLL"),
+                                         ((70, 1501), "LLo"), ((4100, 1537), "LLo"), ((3000, 3000), "--o"), ((2001, 340), "L-o"), ((3, 65, 7), "oo"), ((5, 130, 1030), "LL"), ((2, 3, 4, 5), "Lo"), ((70001, 33), "Loo")])
+def test_maps_of_ragged_rows(env, shape, kinds):
     a, b = positive(shape, 10), positive(shape[-1:], 11)
-    got, ref = both(env, lambda xp, a, b: xp.sqrt(a * b + 1.0) / (a + b), a=a, b=b)   # operations that round once: the same bits
-    assert np.array_equal(got, ref)
-    if len(shape) == 2 and min(shape) > 4:
-        got, ref = both(env, lambda xp, a: a[2:, 2:] - a[:-2, :-2] * a[1:-1, 1:-1], a=a)
+    long, short = (lambda xp, a, b: xp.sqrt(a * b + 1.0) / (a + b)), (lambda xp, a, b: a * b + 1.0)
+    stencil = lambda xp, a: a[2:, 2:] - a[:-2, :-2] * a[1:-1, 1:-1]
+    runs = [(long, dict(a=a, b=b)), (short, dict(a=a, b=b))] + ([(stencil, dict(a=a))] if len(shape) == 2 and min(shape) > 4 else [])
+    routes = ""
+    for prog, arrays in runs:   # operations that round once: the same bits
+        plan = planned(env, prog, **arrays)
+        routes += "L" if "lanes over groups" in plan else "o" if "overlapping" in plan else "-"
+        got, ref = both(env, prog, **arrays)
         assert np.array_equal(got, ref)
+    assert routes == kinds
 
 
 @pytest.mark.parametrize("shape", [(40, 9), (66, 1027), (1031, 1030)])
@@ -118,12 +131,6 @@ def test_in_place_maps_of_ragged_rows(env, shape):
         X[:] = X * X + 0.5
         X[1:-1, 1:] = X[1:-1, 1:] * 3.0
     assert np.array_equal(A.numpy(), B.numpy()) and np.array_equal(t.cpu().numpy(), B.numpy())
-
-
-def planned(env, program, **arrays):
-    gr, ctx, torch = env
-    code = {np.dtype(f32): gr.GR_F32, np.dtype(np.int32): gr.GR_I32}
-    return program(gr, **{k: ctx.spec(v.shape, code[v.dtype]) for k, v in arrays.items()}).plan()
 
 
 # pairs of rows: a lane per row of the longer operand; row lengths around the groups of four and the lane groups of the
@@ -174,9 +181,10 @@ def test_rows_over_pairs(env, n, c, d, kernels):
 # lines of a few lane groups: positions that stick out of the line by every count, one to four positions, both widths of
 # group; lines that do not fill the last workgroup
 @pytest.mark.parametrize("shape", [(3, 4), (17, 5), (40, 63), (33, 64), (37, 65), (50, 66), (21, 67), (16, 144), (7, 255), (5, 256), (9, 257), (100, 511), (6, 513),
-                                   (1001, 703), (4, 1021), (3, 1024), (2, 9, 130)])
+                                   (1001, 703), (4, 1021), (3, 1024), (2, 9, 130), (40, 3), (5, 1025)])
 def test_scans_of_short_lines(env, shape):
     a = positive(shape, 17)
+    assert ("lines-in-lane-groups" in planned(env, lambda xp, a: xp.cumsum(a * 0.5 + 1.0, -1), a=a)) == (4 <= shape[-1] <= 1024)
     got, ref = both(env, lambda xp, a: xp.cumsum(a * 0.5 + 1.0, -1), a=a)   # positive terms: 1e-5 of every prefix
     assert reduction_check(got, ref)[0].all()
     for op in ("cummax", "cummin"):
