@@ -719,8 +719,7 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
 // It takes over from the register-staged kernel (us, before / now: 2001^3 275 / 156, 649 x 448 x 714 26 / 15, 1792 x 74 x 213
 // 14.6 / 6.3, 11845 x 2066 x 48 78 / 48, 2066 x 11845 x 48 62 / 39, 64 x 4096 x 4096 49 / 29, 30 x 5000 x 3000 56 / 23),
 // except for short sums with a large result, whose stores bound it and which the larger tile writes faster (11845 x 48 x 2066
-// 42 against 57, 16384 x 100 x 1000 44 / 58, 2^20 x 16 x 8 26 / 55), sums of at most one of its steps with a small one (16 x 16 x 96 3.5 / 4.0,
-// 512 x 16 x 176 3.7 / 4.2, 608 x 16 x 656 4.0 / 4.3; 2000 x 16 x 1000 7.5 / 6.0), tall operands with few columns (65536 x 512 x 10 28 / 31)
+// 42 against 57, 16384 x 100 x 1000 44 / 58, 2^20 x 16 x 8 26 / 55), tall operands with few columns (65536 x 512 x 10 28 / 31)
 // and large products of two operands contiguous along k (4001^3 1082 / 1111; the other layouts 1201 / 1143 and
 // 1318 / 1152); and from the direct 128 x 128 kernel where an estimate of its time is 5 % lower than that kernel's.  Both
 // estimates, in microseconds, were fitted to 446 products of 64 to 4096 values of k in four layouts (within 7 %): rounds of 256
@@ -745,7 +744,6 @@ void choose_gemm_tiles(GroupPlan* g, int wanted) {
   if (g->VR != 2) {
     const bool rows_of_k = g->groups[g->mat_group].coef[1] == 1 && g->groups[g->vec_group].coef[0] == 1;
     if (K <= 128 && M * N >= (int64_t)1 << 22) return;               // stores
-    if (K <= 16 && M * N < (int64_t)1 << 19) return;                 // one step of the larger tile
     if (tn == 32 && tiles >= 256) return;                            // one pass over a tall operand
     if (rows_of_k && M * N >= (int64_t)1 << 23) return;              // many large tiles, both operands contiguous along k
   }
