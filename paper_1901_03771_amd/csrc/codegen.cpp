@@ -852,16 +852,20 @@ void gen_rowred(Em& e) {
       // (only sums and extrema exist: a sum of C equal values, an extremum of them)
       // handled below by the generic loop with the uniform name.
     }
-    // long rows: positions whose loads and temporaries are in registers at the same time
+    // Long rows: stages whose loads would pile up in registers (values that pass through heavy operations, or that no later
+    // stage needs) or that make values to keep by heavy operations, and the positions that may be in flight there.  Where all
+    // loaded values are kept anyway, loads that wait for each other cost more (softmax of 1245 x 26936 53.9 us, 58.5 in groups
+    // of four positions).
     int n_loads = 0;
-    bool heavy = false;
+    bool heavy = false, passing = false;
     for (int i : stage_instrs[s]) {
       const Instr& in = g.prog[i];
       if (in.uniform) continue;
-      if (in.kind == IKind::LOAD) ++n_loads;
+      if (in.kind == IKind::LOAD) { ++n_loads; passing = passing || !keep[i]; }
       else if (heavy_op(in)) heavy = true;
     }
-    const int LONG_POS = n_loads <= 1 ? 4 : (n_loads <= 2 ? 2 : 1);
+    const bool in_groups = RT == 1024 && (n_loads ? heavy || passing : heavy && !final_stage);
+    const int LONG_POS = n_loads == 1 ? 4 : (n_loads == 2 ? 2 : 1);
     // two bodies: unguarded positions 0..NP-2, guarded last position
     for (int pass = 0; pass < 2; ++pass) {
       const bool guarded = pass == 1;
@@ -926,7 +930,7 @@ void gen_rowred(Em& e) {
       }
       // (long rows: an empty statement that the accumulator passes through holds the loads and the temporaries of a few positions
       // at a time in registers; the compiler would sink the arithmetic of all positions behind all loads)
-      if (RT == 1024 && !guarded && (n_loads || heavy)) e.o << "    if (" << (heavy ? "" : "p < " + std::to_string(NP - 2) + " && ") << "p % " << LONG_POS << " == " << LONG_POS - 1 << ") asm volatile(\"\" : " << (ph ? "\"+v\"(acc" + std::to_string(s) + ")" : std::string()) << " : : \"memory\");\n";
+      if (in_groups && !guarded) e.o << "    if (" << (heavy ? "" : "p < " + std::to_string(NP - 2) + " && ") << "p % " << LONG_POS << " == " << LONG_POS - 1 << ") asm volatile(\"\" : " << (ph ? "\"+v\"(acc" + std::to_string(s) + ")" : std::string()) << " : : \"memory\");\n";
       e.o << "  }\n";
     }
     if (ph) {

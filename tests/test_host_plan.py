@@ -902,6 +902,8 @@ LONG_ROW_PROGRAMS = {   # values that stay in registers while others pass throug
     "tanh": lambda x, y, z: _squares_to_one(gr.tanh(0.79 * x) * x),
     "logistic": lambda x, y, z: _squares_to_one(x / (1.0 + gr.exp(-x))),
     "erf and log": lambda x, y, z: (lambda t: _squares_to_one(t) + gr.max(t, -1, True))(gr.erf(x) * x + gr.log(abs(x) + 1.0)),
+    "erf and tanh of kept values": lambda x, y, z: (lambda d: _squares_to_one(gr.erf(d) * gr.tanh(d)))(x - gr.mean(x, 1, True)),
+    "tanh of a layer norm": lambda x, y, z: (lambda d: gr.tanh(d / gr.sqrt(gr.mean(d * d, 1, True) + 1e-5)))(x - gr.mean(x, 1, True)),
     "two arrays": lambda x, y, z: _squares_to_one(x * y + x),
     "three arrays": lambda x, y, z: _squares_to_one(gr.tanh(x * y) + z) * y,
     "exp and its operand": lambda x, y, z: wl.softmax(gr, x) + x,
