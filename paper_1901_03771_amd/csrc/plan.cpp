@@ -876,8 +876,8 @@ int simple_issue(const GroupPlan& g, const std::vector<char>& in_value) {
 //   203, of exp(a - b) tanh(a b) 136 / 936; 200000 x 8 x 8: a / b 8.3 / 9.2);
 // - long rows of several operands: their registers (three 300 x 3000 x 64 29 / 42; two 65536 x 32 x 64 55 / 35), or the
 //   scalar unit's (two 200000 x 8 x 64 35 / 37), or many instructions for each (seven, 20000 x 64 x 64 28 / 29, 20000 x 16 x 32 5.2 / 7.5);
-// - few pairs, which leave compute units idle: the cheapest programs below 2^17 (5000 x 16 x 64 4.7 / 5.6; 10000 x 16 x 64
-//   7.0 / 5.7), others below 2^18 and with rows over 24 elements below 2^20 (cheb 20000 x 16 x 32 5.7 / 6.9; 20000 x 64 x 32 16.7 / 12.1);
+// - few pairs, which leave compute units idle: the cheapest programs below 2^17 (5000 x 16 x 64 4.5 / 5.6; 10000 x 16 x 64
+//   7.0 / 5.7), 2^16 where the general kernel's lanes do not divide the row evenly (2000 x 64 x 48 6.9 / 4.2), others below 2^18 and with rows over 24 elements below 2^20 (cheb 20000 x 16 x 32 5.7 / 6.9; 20000 x 64 x 32 16.7 / 12.1);
 // - rows of four, which the general kernel reads with one load each, unless the program is short (seven instructions 20000 x 64 4.4 / 4.9);
 // - short rows whose results a lane stores, or reads, apart: 64-bit results and operands of the epilogue that follow both
 //   dimensions, where the lane's is the outer one (i32 sums 65536 x 32 of 4 6.9 / 12.6, of 8 10.3 / 13.0, of 12 25.0 / 13.1; a matrix
@@ -918,7 +918,8 @@ void choose_pair_rows(GroupPlan* g) {
   const int issue = simple_issue(*g, in_value);
   if (issue == 0 || issue > (K <= 4 ? 4 : (K <= 24 ? 8 : 5)) || held[0] * K > 128 || held[1] * K > 64) return;
   const bool cheap = issue <= 3 && held[0] == 1 && held[1] == 1;
-  if (pairs < (int64_t)1 << (cheap ? 17 : (K <= 24 ? 18 : 20))) return;
+  const bool ragged = K > 16 && K != 4 * (int64_t)g->row_threads;   // (the general kernel guards every element of such rows)
+  if (pairs < (int64_t)1 << (cheap ? (ragged ? 16 : 17) : (K <= 24 ? 18 : 20))) return;
   bool apart = g->out_dtype == GR_I64;
   const std::vector<char> in_result = value(g->results[0]);
   for (size_t i = 0; i < g->prog.size(); ++i)

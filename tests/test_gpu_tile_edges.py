@@ -139,7 +139,7 @@ def test_in_place_maps_of_ragged_rows(env, shape):
 # distances with and without a matrix added to them, of a maximum of minima and of an i32 sum: P the pairs' kernel, - the general one
 @pytest.mark.parametrize("n,c,d,kernels", [
     (256, 4, 2, "----"), (257, 5, 4, "----"), (300, 7, 5, "----"), (1000, 19, 16, "----"), (1001, 33, 17, "----"), (4099, 6, 31, "----"), (511, 64, 33, "----"), (2049, 9, 63, "----"),
-    (700, 3, 64, "----"), (5, 1030, 12, "----"), (260, 260, 54, "----"),
+    (700, 3, 64, "----"), (5, 1030, 12, "----"), (260, 260, 54, "PP--"), (260, 260, 64, "----"),
     (32768, 4, 2, "-P--"), (32768, 5, 4, "-P--"), (28001, 5, 7, "-P--"), (65536, 4, 16, "PPPP"), (20001, 14, 9, "PPPP"), (4099, 65, 24, "PPPP"), (363, 362, 64, "PP--"), (300, 1030, 17, "PPPP"),
     (1030, 300, 17, "PPPP"), (1100, 1030, 25, "PP-P"), (1030, 1100, 33, "PP-P"), (40001, 33, 63, "PP-P"), (65536, 18, 65, "----"), (400000, 3, 16, "----"), (5, 70000, 31, "PP--")])
 def test_rows_over_pairs(env, n, c, d, kernels):

@@ -977,6 +977,7 @@ def test_row_pairs_are_taken_where_they_fill_the_device(ctx):
         return "pairs:" in gr.sum(x * b, axis=2).plan()
 
     assert not squares(5000, 16, 64) and not squares(127, 1024, 16) and squares(8192, 16, 64) and squares(16, 8192, 64) and not squares(200000, 3, 64)
+    assert squares(2000, 64, 48) and squares(8192, 8, 17) and not squares(2000, 64, 64) and not squares(2000, 64, 16) and not squares(8191, 8, 48)
     assert not squares(8192, 16, 16, 2) and squares(16384, 16, 16, 2) and not squares(16384, 16, 32, 2) and squares(65536, 16, 32, 2)
     assert squares(65536, 32, 42, 3) and not squares(65536, 32, 43, 3)   # (three operands: at most 128 registers of them)
 
