@@ -43,6 +43,10 @@ extern "C" {
  *                     unguarded loads from clamped positions, where an estimate of their time is no higher than that
  *                     of the kernels above; 0 = never ("gemm_big" = 0, "gemm_bn", "gemm_kstep" and "gemm_split" switch
  *                     them off as well)
+ *   "assign_in_place" 1 (default) = a slice assignment whose value reads the destination's storage up to four rows or
+ *                     columns away, and that storage only, is evaluated in place after a launch that saves the cells around its
+ *                     tiles (two-dimensional boxes with unit steps along the rows, 32-bit elements); 0 = the
+ *                     value gets a buffer of its own and is copied back
  *   "nontemporal"     1 (default) = loads of arrays that are read once carry the non-temporal hint,
  *                     and so do the vector stores of a requested value of 192 MiB or more (not of
  *                     intermediate results of the request; except in kernels that read a transposed

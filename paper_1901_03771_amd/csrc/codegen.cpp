@@ -570,6 +570,133 @@ void gen_map(Em& e) {
          "          }\n        }\n  }\n}\n";
 }
 
+// A map that writes the array it reads at positions a few rows and columns away.  A workgroup loads all that its
+// tile needs, waits until all of its waves have, and only then stores; the cells around a tile, which other workgroups
+// write, come from copies that gr_map_save made in a launch before: whole rows above and below every row of tiles, and a few columns
+// on either side of every boundary between tiles of a row.
+// Bound by HBM or the caches: 2 rows saved, and read again, per VR rows read and written.
+void gen_map_in_place(Em& e) {
+  const GroupPlan& g = e.g;
+  const int TC = g.BX * 4, TR = g.BY * g.VR, HT = g.halo[0], HB = g.halo[1], HL = g.halo[2], HR = g.halo[3];
+  const int off = (HL + 3) / 4 * 4, offr = (HR + 3) / 4 * 4;
+  std::ostream& o = e.o;
+  const std::string T = cty(g.out_dtype), V4 = vty4(g.out_dtype), V2 = vty2(g.out_dtype);
+  auto head = [&](const char* name) {
+    kernel_head(e, name);
+    o << "  const int C = (int)" << e.dim(1) << ", R = (int)" << e.dim(0) << ", nbx = (C + " << g.cphase + TC - 1 << ") / " << TC << ", nby = (R + " << TR - 1 << ") / " << TR << ";\n"
+         "  const long long orow = " << e.S(e.L.ocoef) << ", pitch = (long long)nbx * " << TC + 0 << " + " << off + offr << ";\n"
+         "  GM " << T << "* const po = (GM " << T << "*)" << e.slot(e.L.out) << " + " << e.S(e.L.obase) << ";\n"
+         "  GM " << T << "* const rows = (GM " << T << "*)" << e.slot(e.L.extra) << ";\n"
+         "  GM " << T << "* const cols = rows + (long long)nby * " << HT + HB << " * pitch;\n  (void)cols; (void)pitch;\n";
+  };
+  prelude(e);
+  head("gr_map_save");
+  o << "  unsigned idx = blockIdx.x * 256 + threadIdx.x;\n  const unsigned quads = (unsigned)(pitch / 4), first = quads * (unsigned)nby * " << HT + HB << "u;\n"
+       "  if (idx < first) {\n"
+       "    const int i4 = (int)(idx % quads), line = (int)(idx / quads), h = line % " << std::max(1, HT + HB) << ", by = line / " << std::max(1, HT + HB) << ";\n"
+       "    const int at = h < " << HT << " ? by * " << TR << " - " << HT << " + h : by * " << TR << " + " << TR - HT << " + h, r = at < R + " << HB - 1 << " ? at : R + " << HB - 1 << ";\n"
+       "    const int c = 4 * i4 - " << off + g.cphase << ";\n"
+       "    GM " << T << "* const to = rows + (long long)line * pitch + 4 * i4;\n    const GM " << T << "* const from = po + r * orow;\n"
+       "    if (c >= " << -HL << " && c + 4 <= C + " << HR << ") *(GM " << V4 << "*)to = *(const GM " << V4 << "*)(from + c);\n"
+       "    else for (int j = 0; j < 4; ++j) { const int k = c + j; to[j] = from[k < " << -HL << " ? " << -HL << " : (k < C + " << HR << " ? k : C + " << HR - 1 << ")]; }\n"
+       "    return;\n  }\n";
+  if (HL + HR > 0)
+    o << "  idx -= first;\n  const unsigned lines = (unsigned)R + " << HT + HB << "u;\n"
+         "  if (idx >= lines * (unsigned)(nbx - 1) * " << HL + HR << "u) return;\n"
+         "  const int q = (int)(idx % " << HL + HR << "), line = (int)(idx / " << HL + HR << "), r = (int)(line % lines) - " << HT << ", b = (int)(line / lines);\n"
+         // (a boundary near the end of the rows: columns that no element reads are not there)
+         "  const int c = (b + 1) * " << TC << " - " << g.cphase << " + q - " << HL << ";\n"
+         "  cols[idx] = po[r * orow + (c < C + " << HR << " ? c : C + " << HR - 1 << ")];\n";
+  o << "}\n";
+  head("gr_map");
+  o << "  const unsigned ntiles = (unsigned)(nbx * nby), per = (ntiles + 7) / 8, tile = (blockIdx.x % 8) * per + blockIdx.x / 8;\n"
+       "  if (blockIdx.x / 8 >= per || tile >= ntiles) return;\n"
+       "  const int bx = (int)(tile % (unsigned)nbx), by = (int)(tile / (unsigned)nbx), tx = threadIdx.x % " << g.BX << ", ty = " << (g.BY > 1 ? "threadIdx.x / " + std::to_string(g.BX) : std::string("0")) << ";\n"
+       "  const int r0 = by * " << TR << " + ty * " << g.VR << ", c0 = bx * " << TC << " + tx * 4 - " << g.cphase << ", rmax = R + " << HB - 1 << ";\n"
+       "  const bool live = c0 < C, whole = c0 >= 0 && c0 + 4 <= C;\n  (void)ty;\n";
+  int self = -1;
+  for (size_t i = 0; i < g.groups.size(); ++i) if (!g.groups[i].structural_zero[0] || !g.groups[i].structural_zero[1]) self = (int)i;
+  for (size_t i = 0; i < g.groups.size(); ++i)
+    if ((int)i != self) o << "  const GM " << cty(g.groups[i].dtype) << "* const q" << i << " = (const GM " << cty(g.groups[i].dtype) << "*)" << e.slot(e.L.ptr[i]) << " + " << e.S(e.L.base[i]) << ";\n";
+  // loads of the patch: per row (relative to r0) the columns (relative to c0)
+  std::vector<char> used(g.prog.size(), 0);
+  std::vector<int> work(g.results.begin(), g.results.end());
+  while (!work.empty()) {
+    const int i = work.back();
+    work.pop_back();
+    if (i < 0 || used[i]) continue;
+    used[i] = 1;
+    work.push_back(g.prog[i].a);
+    work.push_back(g.prog[i].b);
+  }
+  std::map<int, std::map<int, int>> at;   // row -> column -> instruction
+  std::map<int, std::string> name;
+  for (size_t i = 0; i < g.prog.size(); ++i) {
+    const Instr& in = g.prog[i];
+    if (in.kind != IKind::LOAD || !used[i]) continue;
+    if (in.group != self) name[(int)i] = "q" + std::to_string(in.group) + "[0]";
+    else at[(int)in.delta[0] + g.self_row][(int)in.delta[1] + g.self_col] = (int)i;
+  }
+  auto rn = [](int s) { return s < 0 ? "m" + std::to_string(-s) : std::to_string(s); };
+  std::ostringstream fast, slow, left, right;
+  std::set<int> edge;
+  int nl = 0;
+  for (const auto& row : at) {
+    const int s = row.first;
+    const std::string grid = "po + (long long)(r0 + " + std::to_string(s) + " < rmax ? r0 + " + std::to_string(s) + " : rmax) * orow + c0";
+    const int h = s < 0 ? HT + s : HT + s - g.VR;
+    const std::string saved = "rows + (by * " + std::to_string(HT + HB) + "ll + " + std::to_string(h) + ") * pitch + (c0 + " + std::to_string(off + g.cphase) + ")";
+    const std::string w = "w" + rn(s);
+    o << "  const GM " << T << "* const " << w << " = ";
+    if (s >= 0 && s < g.VR) o << grid;
+    else if (g.BY == 1) o << saved;
+    else o << (s < 0 ? "ty == 0" : "ty == " + std::to_string(g.BY - 1)) << " ? (const GM " << T << "*)(" << saved << ") : (const GM " << T << "*)(" << grid << ")";
+    o << ";\n";
+    std::vector<std::pair<int, int>> v(row.second.begin(), row.second.end());
+    size_t i = 0;
+    while (i < v.size()) {
+      size_t run = 1;
+      while (i + run < v.size() && v[i + run].first == v[i].first + (int)run) ++run;
+      for (size_t pos = 0; pos < run;) {
+        const size_t take = run - pos >= 4 ? 4 : (run - pos >= 2 ? 2 : 1);
+        const int dc = v[i + pos].first;
+        const std::string nm = "L" + std::to_string(nl++), ty = take == 4 ? V4 : (take == 2 ? V2 : T);
+        o << "  " << ty << ' ' << nm << ";\n";
+        fast << "    " << nm << " = *(const GM " << ty << "*)(" << w << " + " << dc << ");\n";
+        for (size_t q = 0; q < take; ++q) {
+          const int c = dc + (int)q;
+          const std::string el = take == 1 ? nm : nm + "[" + std::to_string(q) + "]";
+          name[v[i + pos + q].second] = el;
+          edge.insert(c);
+          slow << "    " << el << " = " << w << "[k" << rn(c) << "];\n";
+          const std::string line = "[(r0 + " + std::to_string(s) + " < rmax ? r0 + " + std::to_string(s) + " : rmax) * " + std::to_string(HL + HR) + "ll + ";
+          if (c < 0) left << "    " << el << " = cb" << line << HL + c << "];\n";
+          if (c >= 4) right << "    " << el << " = cb" << line << HL + c - 4 << "];\n";
+        }
+        pos += take;
+      }
+      i += run;
+    }
+  }
+  o << "  if (whole) {\n" << fast.str() << "  } else if (live) {\n";
+  for (int c : edge) o << "    const int k" << rn(c) << " = (c0 + " << c << " < " << -HL << " ? " << -HL << " : (c0 + " << c << " < C + " << HR << " ? c0 + " << c << " : C + " << HR - 1 << ")) - c0;\n";
+  o << slow.str() << "  }\n";
+  const std::string cb = "    const GM " + T + "* const cb = cols + ((long long)";
+  if (HL > 0) o << "  if (tx == 0 && bx > 0) {\n" << cb << "(bx - 1) * (R + " << HT + HB << ") + " << HT << ") * " << HL + HR << ";\n" << left.str() << "  }\n";
+  if (HR > 0) o << "  if (tx == " << g.BX - 1 << " && bx + 1 < nbx && live) {\n" << cb << "bx * (R + " << HT + HB << ") + " << HT << ") * " << HL + HR << ";\n" << right.str() << "  }\n";
+  // every load of the workgroup has returned before any of its stores is issued
+  o << "  asm volatile(\"s_waitcnt vmcnt(0)\" ::: \"memory\");\n  __syncthreads();\n  if (!live) return;\n";
+  emit_scalar_program(e, g.prog, g.results, [&](const Instr&, int id) { return name[id]; }, "0", "t", "  ");
+  for (int v = 0; v < g.VR; ++v) {
+    const int* t = &g.results[(size_t)v * 4];
+    o << "  if (r0 + " << v << " < R) {\n    GM " << T << "* const to = po + (r0 + " << v << ") * orow + c0;\n"
+         "    if (whole) { " << V4 << " ov; ov[0] = t" << t[0] << "; ov[1] = t" << t[1] << "; ov[2] = t" << t[2] << "; ov[3] = t" << t[3] << "; *(GM " << V4 << "*)to = ov; }\n    else {\n";
+    for (int j = 0; j < 4; ++j) o << "      if (c0 + " << j << " >= 0 && c0 + " << j << " < C) to[" << j << "] = t" << t[j] << ";\n";
+    o << "    }\n  }\n";
+  }
+  o << "}\n";
+}
+
 // ---- ROWRED -------------------------------------------------------------------
 
 // Short rows whose elements come from pairs of operands, one that follows the first kept dimension
@@ -2809,7 +2936,7 @@ void gemm_combine(Em& e, const EpiLoad& epi_load) {
 std::string generate_source(const GroupPlan& g) {
   Em e(g);
   switch (g.kind) {
-    case GroupKind::MAP: gen_map(e); break;
+    case GroupKind::MAP: if (g.in_place) gen_map_in_place(e); else gen_map(e); break;
     case GroupKind::ROWRED: gen_rowred(e); break;
     case GroupKind::REDUCE: gen_reduce(e); break;
     case GroupKind::SCAN: gen_scan(e); break;

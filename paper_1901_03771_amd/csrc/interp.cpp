@@ -39,7 +39,7 @@ static int opcode(const Instr& in) {
 // Fills `A` and `grid` for sub-graph `g` writing to `out_ptr`; false if the sub-graph is outside
 // what the interpreter covers (then the caller waits for the compiler as usual).
 bool interp_encode(const GroupPlan& g, void* out_ptr, GrInterpArgs* A, unsigned* grid) {
-  if (g.kind != GroupKind::MAP || g.rank < 1 || g.rank > GR_INTERP_RANK || g.out_dtype == GR_I64 || g.result1 < 0) return false;
+  if (g.kind != GroupKind::MAP || g.in_place || g.rank < 1 || g.rank > GR_INTERP_RANK || g.out_dtype == GR_I64 || g.result1 < 0) return false;
   if (g.groups.size() > GR_INTERP_GROUPS || g.consts.size() > GR_INTERP_CONSTS) return false;
   const std::vector<Instr>& p = g.prog1;
   const int n = (int)p.size();

@@ -197,6 +197,9 @@ struct GroupPlan {
   bool xcd_remap = false;
   int cphase = 0;     // map: lanes own columns 4k - cphase .. 4k - cphase + 3, so that their vector stores are 16-byte aligned in the output
   int stage_mask = 0;                    // MAP: access groups (bit per group) read through a transposing LDS tile
+  bool in_place = false;                 // MAP: writes the array that it reads at shifted positions (see gen_map_in_place)
+  int self_row = 0, self_col = 0;        // in_place: rows and columns from the element written to the one read with shift 0
+  int halo[4] = {0};                     // in_place: rows read above and below a tile, columns left and right of it
   int flat = 0;                          // MAP: every patch lies inside the array, the last ones overlap: 1 lanes numbered over
                                          // row and column groups, 2 in tiles
   int diag = 0;                          // MAP with staged operands: tile rows are taken diagonally (row block + column block)
@@ -245,7 +248,26 @@ inline int64_t reduce_units(const GroupPlan& g) {
 struct OutSpec {
   int64_t base = 0;
   int64_t strides[MAXD] = {0};
+  bool in_place = false;  // the value may read the destination's storage at shifted positions
 };
+
+// In-place maps: the cells around the tiles, saved before any tile is written.  Per row of tiles `halo[0]` + `halo[1]`
+// rows of `pitch` elements (column c at index c + cphase + `off`), then per boundary between two columns of tiles
+// `halo[2]` + `halo[3]` elements of every row.
+struct SavedCells {
+  int64_t nbx, nby, off, pitch, rows, cols;   // rows, cols: elements of the two parts
+};
+inline SavedCells saved_cells(const GroupPlan& g) {
+  SavedCells s;
+  const int64_t R = g.dims[0], C = g.dims[1], TR = (int64_t)g.BY * g.VR, TC = (int64_t)g.BX * 4;
+  s.nbx = (C + g.cphase + TC - 1) / TC;
+  s.nby = (R + TR - 1) / TR;
+  s.off = (g.halo[2] + 3) / 4 * 4;
+  s.pitch = s.nbx * TC + s.off + (g.halo[3] + 3) / 4 * 4;
+  s.rows = s.nby * (g.halo[0] + g.halo[1]) * s.pitch;
+  s.cols = (s.nbx - 1) * (R + g.halo[0] + g.halo[1]) * (g.halo[2] + g.halo[3]);
+  return s;
+}
 
 struct PlanEntry;
 

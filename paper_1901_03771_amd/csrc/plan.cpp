@@ -473,7 +473,7 @@ void make_signature(GroupPlan* g) {
   std::string s;
   s.reserve(256 + 32 * (g->prog.size() + g->prog1.size()));
   for (int64_t v : {(int64_t)g->kind, (int64_t)g->rank, (int64_t)g->out_dtype, (int64_t)g->out_per_row, (int64_t)g->BX, (int64_t)g->BY,
-                    (int64_t)g->VR + (g->kind == GroupKind::GEMM && g->VR == 2 && g->slabs > 1 ? 1024 : 0) /* (the direct-to-LDS product kernels compile the split of K in or out) */, (int64_t)g->UC, (int64_t)g->NP, (int64_t)g->row_threads + 1024 * (int64_t)g->row_iters + (((int64_t)g->pair_k) << 32) + (((int64_t)g->pair_lane) << 40) /* (a pair kernel compiles its row length in) */, (int64_t)g->xcd_remap + 2 * (int64_t)g->stage_mask + (((int64_t)g->tail) << 40) + (((int64_t)g->diag) << 44) + (((int64_t)g->cphase) << 48) + (((int64_t)g->flat) << 52), (int64_t)g->red_mode + 16 * (int64_t)g->red_vec,
+                    (int64_t)g->VR + (g->kind == GroupKind::GEMM && g->VR == 2 && g->slabs > 1 ? 1024 : 0) /* (the direct-to-LDS product kernels compile the split of K in or out) */, (int64_t)g->UC, (int64_t)g->NP, (int64_t)g->row_threads + 1024 * (int64_t)g->row_iters + (((int64_t)g->pair_k) << 32) + (((int64_t)g->pair_lane) << 40) /* (a pair kernel compiles its row length in) */, (int64_t)g->xcd_remap + 2 * (int64_t)g->stage_mask + (((int64_t)g->tail) << 40) + (((int64_t)g->diag) << 44) + (((int64_t)g->cphase) << 48) + (((int64_t)g->flat) << 52) + (((int64_t)g->in_place) << 56), (int64_t)g->red_mode + 16 * (int64_t)g->red_vec,
                     (int64_t)g->red_kept_rank, (int64_t)g->gemv_mode, (int64_t)g->LPR, (int64_t)g->KV, (int64_t)g->mat_group,
                     (int64_t)g->vec_group, (int64_t)g->nt, (int64_t)g->unroll, (int64_t)g->scan_mode + 16 * (int64_t)g->scan_vec + (g->scan_mode >= 2 ? 256 * g->scan_chunk : 0) /* (a one-pass scan's tile size is compiled in) */, (int64_t)g->out_unit, (int64_t)g->groups.size()})
     put(s, v);
@@ -484,6 +484,7 @@ void make_signature(GroupPlan* g) {
     for (int k = 0; k < nd; ++k) cls = cls * 4 + (ag.structural_zero[k] ? 0 : (ag.coef[k] == 1 ? 1 : 2));
     put(s, cls);
   }
+  if (g->in_place) put(s, (int64_t)g->self_row * 256 + g->self_col);
   put(s, (int64_t)g->consts.size());
   for (const ConstSlot& c : g->consts) put(s, (int64_t)c.dtype);
   put(s, (int64_t)g->phases.size());
@@ -710,6 +711,46 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
   // (rows shorter than 256 bytes share cache lines with other waves as well: 3145728 x 8 52.6 -> 42.6 us without the hint)
   if (c->opt_nontemporal == 1 && g->rank >= 2 && R > 1 && C < 64) g->nt &= ~7;
   g->tail = (g->rank >= 2 && !g->flat && C < 64 && (C & 3) && g->UC == 1 && !g->stage_mask) ? (int)(C & 3) : 0;
+}
+
+// A map that is to write the array it reads at shifted positions, element (r, c) from elements a few rows and columns
+// away (a sweep of a stencil over a grid with a single buffer): every array read is a scalar or lies over the output with its strides.
+// Tiles of 256 columns (the narrowest power of two that holds shorter rows) by eight rows per lane: taller patches save and
+// read fewer rows around them, and their registers leave fewer waves (4096^2, us per sweep by 256 columns: 4 rows 28.7, 8 27.9, 16 29.7; by
+// 1024: 37.0, 31.2, 29.0, of 32 rows 36.0; 8192^2 by 256, 512 and 1024 columns, 8 rows: 102, 107, 115).  Four rows where eight
+// would leave compute units without a tile (1000^2: 7.8 against 8.5).
+// (us per sweep, value in a buffer of its own and copied back / in place: 1000^2 9.1 / 7.8, 2000^2 20.0 / 11.8, 4096 x 1024 23.1 / 11.8,
+// 100000 x 130 34.8 / 20.5, 4096^2 49.6 / 27.9, 1024 x 16384 49.1 / 26.9, 8192^2 185 / 102; both are two launches, grids
+// below 512^2 take the host's time for them either way.)
+static void choose_in_place(GroupPlan* g) {
+  if (g->rank != 2 || g->orig_rank != 2 || !g->out_unit || g->out_dtype == GR_I64 || g->stage_mask) return;
+  const int64_t R = g->dims[0], C = g->dims[1], row = g->out_coef[0];
+  if (C < 16 || R < 2 || row < C || R > 1 << 30 || C > 1 << 30) return;
+  const AccessGroup* self = nullptr;
+  for (const AccessGroup& ag : g->groups) {
+    if (ag.structural_zero[0] && ag.structural_zero[1]) continue;
+    if (self || ag.leaf->ndim != 2 || ag.dtype != g->out_dtype || ag.coef[0] != row || ag.coef[1] != 1) return;
+    self = &ag;
+  }
+  if (!self) return;
+  const int64_t d = self->base - g->out_base, dr = d >= 0 ? (d + row / 2) / row : -((row / 2 - d) / row), dc = d - dr * row;
+  int64_t lo[2] = {0, 0}, hi[2] = {0, 0};
+  for (const auto& s : self->deltas) {
+    lo[0] = std::min(lo[0], dr + s[0]); hi[0] = std::max(hi[0], dr + s[0]);
+    lo[1] = std::min(lo[1], dc + s[1]); hi[1] = std::max(hi[1], dc + s[1]);
+  }
+  if (lo[0] < -4 || hi[0] > 4 || lo[1] < -4 || hi[1] > 4 || row < C + hi[1] - lo[1]) return;
+  g->in_place = true;
+  g->self_row = (int)dr; g->self_col = (int)dc;
+  g->halo[0] = (int)-lo[0]; g->halo[1] = (int)hi[0]; g->halo[2] = (int)-lo[1]; g->halo[3] = (int)hi[1];
+  g->flat = 0; g->tail = 0; g->UC = 1; g->nt = 0; g->diag = 0;
+  g->cphase = row % 4 == 0 ? (int)(((g->out_base % 4) + 4) % 4) : 0;
+  g->xcd_remap = true;
+  g->BX = std::min(64, std::max(4, next_pow2((C + g->cphase + 3) / 4)));
+  g->BY = 256 / g->BX;
+  const int64_t across = (C + g->cphase + 4 * g->BX - 1) / (4 * g->BX);
+  g->VR = across * (R / (8 * (int64_t)g->BY)) >= 256 ? 8 : 4;
+  if (saved_cells(*g).rows + saved_cells(*g).cols > (int64_t)1 << 30) g->in_place = false;
 }
 
 // Small or ragged matrix products: tiles of 64 x 64 (128 x 32, 32 x 128) with clamped loads (gemm_tile_body), after the
@@ -1614,6 +1655,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
     collapse_dims(g, barrier, ps, 1);
     pop_output_group(g);
     choose_map_schedule(c, g, !(r == pl.root && pl.out));
+    if (r == pl.root && pl.out && pl.out->in_place && src == r && r->ndim > 0) choose_in_place(g);
     g->owned = owned;
   }
 
@@ -1830,7 +1872,7 @@ std::string describe_plan(const Plan& plan) {
     }
     if (g.kind == GroupKind::SCAN) s << " mode=" << (g.scan_mode == 4 ? "lines-in-lane-groups" : g.scan_mode == 3 ? "one-pass-line-tiles" : (g.scan_mode == 2 ? "one-pass-tiles" : (g.scan_mode ? "thread-per-line" : "lanes-along-axis"))) << " lines=" << g.red_out << " length=" << g.red_len << " chunks=" << g.scan_nchunk;
     if (g.kind == GroupKind::MAP && g.flat == 1) s << " lanes over groups of columns patch=" << g.VR << "x4";
-    else if (g.kind == GroupKind::MAP) s << " tile=" << g.BY * g.VR << "x" << g.BX * 4 * g.UC << " patch=" << g.VR << "x" << g.UC * 4 << (g.flat == 2 ? " overlapping" : "");
+    else if (g.kind == GroupKind::MAP) s << " tile=" << g.BY * g.VR << "x" << g.BX * 4 * g.UC << " patch=" << g.VR << "x" << g.UC * 4 << (g.flat == 2 ? " overlapping" : "") << (g.in_place ? " in place" : "");
     s << '\n';
   }
   return s.str();

@@ -231,7 +231,7 @@ static void disk_store(const std::string& path, const std::string& key, const st
 static void kernel_entry_points(const GroupPlan& g, std::string* name, bool* combine, int* scan) {
   *name = kernel_name(g);
   *combine = (g.kind == GroupKind::GEMV && g.gemv_mode >= 1) || g.kind == GroupKind::REDUCE || g.kind == GroupKind::GEMM;
-  *scan = g.kind == GroupKind::SCAN ? (g.scan_mode == 4 ? 0 : g.scan_mode >= 2 ? 2 : 1) : (g.kind == GroupKind::REDUCE && g.red_mode == 0 ? 3 : 0);
+  *scan = g.kind == GroupKind::SCAN ? (g.scan_mode == 4 ? 0 : g.scan_mode >= 2 ? 2 : 1) : (g.kind == GroupKind::REDUCE && g.red_mode == 0 ? 3 : (g.kind == GroupKind::MAP && g.in_place ? 4 : 0));
 }
 
 // Loads a code object and publishes the kernel in the in-memory cache.
@@ -250,6 +250,7 @@ static gr_status finish_kernel(gr_ctx* c, const std::string& sig, const std::str
       GR_HIP(c, hipModuleGetFunction(&k.fn3, k.module, "gr_scan_offsets"));
     }
     if (scan == 2) GR_HIP(c, hipModuleGetFunction(&k.fn2, k.module, "gr_scan_clear"));
+    if (scan == 4) GR_HIP(c, hipModuleGetFunction(&k.fn2, k.module, "gr_map_save"));
     if (scan == 3) GR_HIP(c, hipModuleGetFunction(&k.fn3, k.module, (k.name + "_wide").c_str()));
   }
   auto ins = c->cache.emplace(sig, std::move(k));
@@ -483,6 +484,7 @@ static int64_t scan_line_tile_cells(const GroupPlan& g) {
 static int reduce_slabs(const GroupPlan& g, bool tight) { return tight && g.red_mode == 0 ? g.red_tight : g.slabs; }
 static size_t workspace_need(const GroupPlan& g, bool tight) {
   switch (g.kind) {
+    case GroupKind::MAP: return g.in_place ? (size_t)(saved_cells(g).rows + saved_cells(g).cols) * 4 : 0;
     case GroupKind::REDUCE: return reduce_slabs(g, tight) > 1 && g.red_out > 0 ? (size_t)reduce_slabs(g, tight) * (size_t)g.red_out * itemsize(g.out_dtype) : 0;
     case GroupKind::SCAN: {
       int64_t total = 1;
@@ -594,6 +596,14 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
       int64_t ntiles = outer * ((C + g.cphase + TC - 1) / TC) * ((R + TR - 1) / TR);
       if (g.flat == 1) ntiles = (outer * ((C + 3) / 4) * ((R + g.VR - 1) / g.VR) + 255) / 256;
       int64_t grid = g.xcd_remap ? 8 * ((ntiles + 7) / 8) : ntiles;
+      if (g.in_place) {
+        gr_status wst = get_workspace(c, g, &ws);
+        if (wst != GR_OK) return wst;
+        s[L.extra] = (uint64_t)(uintptr_t)ws;
+        const SavedCells sv = saved_cells(g);
+        gr_status st = launch(c, k->fn2, "gr_map_save", (sv.rows / 4 + sv.cols + 255) / 256, s);
+        if (st != GR_OK) return st;
+      }
       return launch(c, k->fn, k->name, grid, s);
     }
     case GroupKind::ROWRED: {
@@ -1315,6 +1325,41 @@ static bool swap_candidate(const Node* base, const Node* d, const OutSpec& spec,
   return box > 0 && (all - box) * 4 <= box;
 }
 
+// A value that reads the destination's storage at shifted positions, without a second buffer: one kernel saves the cells around
+// its tiles, the next one evaluates it in place.  While that kernel is still in the compiler the caller's general way serves
+// (the interpreter writes elements as it goes).
+static gr_status assign_in_place(gr_ctx* ctx, Node* v, const Node* base, const OutSpec& spec, uintptr_t lo, uintptr_t hi, bool* done) {
+  OutSpec in = spec;
+  in.in_place = true;
+  Plan plan;
+  plan.out = &in;
+  gr_status st = make_plan(ctx, v, &plan);
+  if (st != GR_OK) return st;
+  GroupPlan& g = *plan.groups.back();
+  bool ok = plan.out_honoured && g.kind == GroupKind::MAP && g.in_place;
+  for (const AccessGroup& ag : g.groups) {
+    if (!ok) break;
+    const bool scalar = ag.structural_zero[0] && ag.structural_zero[1];
+    uintptr_t a = 0, b = 0;
+    if (ag.leaf->materialized) extent_of(ag.leaf, &a, &b);
+    ok = scalar ? !(a < hi && lo < b) : ag.leaf->materialized && ag.leaf->data == base->data;
+  }
+  if (ok && !(ctx->device < 0 && ctx->opt_dry_run >= 2)) {
+    if (ctx->opt_interp >= 2) ok = false;
+    else {
+      st = prepare_group(ctx, g);
+      if (st == GR_OK && ctx->opt_interp == 1 && still_compiling(ctx, g.signature)) ok = false;
+    }
+  }
+  if (st == GR_OK && ok) {
+    drop_shadow(ctx, const_cast<Node*>(base));
+    st = execute_plan(ctx, &plan, v, base->data, false);
+    *done = st == GR_OK;
+  }
+  clear_planned(&plan);
+  return st;
+}
+
 }  // namespace gr
 
 extern "C" gr_status gr_array_lend_buffer(gr_ctx* ctx, gr_array a, void* dptr2, size_t bytes) {
@@ -1476,7 +1521,12 @@ extern "C" gr_status gr_assign(gr_ctx* ctx, gr_array dst, gr_array value) {
       ctx->stats.assign_swaps++;
       direct = true;
     } else {
+      const bool honoured = plan.out_honoured;
       clear_planned(&plan);
+      if (honoured && ctx->opt_assign_in_place) {
+        st = assign_in_place(ctx, v, base, spec, lo, hi, &direct);
+        if (st != GR_OK) return st;
+      }
     }
   }
   if (direct) return GR_OK;

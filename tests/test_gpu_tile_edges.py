@@ -316,3 +316,79 @@ def test_column_sums_have_the_same_bits_from_every_entry_point(env, rows, cols):
     replayed = torch.empty(cols, device="cuda")
     ctx.program(prog(leaf), [leaf]).run([t], replayed)
     assert torch.equal(replayed, want)
+
+
+IN_PLACE = {   # destination and value of a slice assignment that reads its own destination elsewhere
+    "five points": lambda u: (np.s_[1:-1, 1:-1], 3 * (u[1:-1, 1:-1] + u[:-2, 1:-1] + u[1:-1, 2:] + u[1:-1, :-2] + u[2:, 1:-1])),
+    "corners": lambda u: (np.s_[1:-1, 1:-1], u[:-2, :-2] + u[2:, 2:] - u[:-2, 2:] + u[2:, :-2]),
+    "from below": lambda u: (np.s_[:-1, :], u[1:, :] + u[:-1, :]),
+    "from the left": lambda u: (np.s_[:, 3:], u[:, :-3] - u[:, 3:]),
+    "from the right": lambda u: (np.s_[:, :-4], u[:, 4:] * 1),
+    "far corner": lambda u: (np.s_[4:, 4:], u[:-4, :-4] * 2),
+    "two corners": lambda u: (np.s_[2:-3, 3:-1], u[:-5, 4:] - u[5:, :-4]),
+    "twice": lambda u: (np.s_[1:-1, 1:-1], 2 * u[:-2, 1:-1] - abs(u[2:, 2:])),
+}
+
+
+# one tile, tiles that end at, before and behind the box, rows shorter than a tile (several tile rows of lanes), one column of the last tile
+@pytest.mark.parametrize("rows,cols", [(8, 20), (17, 66), (33, 257), (34, 258), (35, 259), (64, 263), (66, 514), (131, 300), (1030, 1282), (2500, 600), (4000, 24)])
+@pytest.mark.parametrize("dtype", [f32, np.int32])
+def test_assignments_evaluated_in_place(env, rows, cols, dtype):
+    gr, ctx, torch = env
+    for name, program in IN_PLACE.items():
+        for window in (0, 1):   # the whole array, or a window that starts off a 16-byte boundary, whose surroundings stay
+            a = np.random.default_rng(31).integers(-50, 50, (rows + 5 * window, cols + 6 * window)).astype(dtype)
+            t = torch.from_numpy(a).cuda()
+            cut = np.s_[2 * window:2 * window + rows, 3 * window:3 * window + cols]
+            u, ref = ctx.array(t[cut]), a[cut]
+            ctx.set_option("profile", 1)
+            ctx.profile_reset()
+            for _ in range(2):
+                box, value = program(u)
+                u[box] = value
+                box, value = program(ref)
+                ref[box] = value.copy()
+            ctx.sync()
+            saved = ctx.profile_read("gr_map_save")[0]
+            ctx.set_option("profile", 0)
+            # (along the rows only, in one column of tiles: nothing around a tile to save)
+            assert saved == 2 or (name.startswith("from the") and cols < 260), (name, window)
+            assert np.array_equal(t.cpu().numpy(), a), (name, window)
+
+
+def test_assignments_not_evaluated_in_place(env):
+    # values that read another array as well, other strides, a destination read further away: copied back as before
+    gr, ctx, torch = env
+    a = np.random.default_rng(32).integers(-50, 50, (70, 300)).astype(f32)
+    b = np.random.default_rng(33).integers(-50, 50, (70, 300)).astype(f32)
+
+    def other(u, w):
+        u[1:-1, 1:-1] = u[2:, 1:-1] + w[1:-1, 1:-1]
+
+    def wide(u, w):
+        u[:, 5:] = u[:, :-5] * 2
+
+    def stepped(u, w):
+        u[2:, ::2] = u[:-2, ::2] + 1
+
+    def turned(u, w):
+        u[1:, 1:] = u.T[:-1, :-1] if u.shape[0] == u.shape[1] else u[:-1, :-1].T.T * 3
+
+    def overwritten_scalar(u, w):
+        u[:, :] = u[3:4, 4:5] + u * 1
+
+    ctx.set_option("profile", 1)
+    for f in (other, wide, stepped, overwritten_scalar, turned):
+        x, y = a.copy(), a.copy()
+        t, w = torch.from_numpy(x).cuda(), torch.from_numpy(b).cuda()
+        ctx.profile_reset()
+        f(ctx.array(t), ctx.array(w))
+        ctx.sync()
+        saved = ctx.profile_read("gr_map_save")[0]
+        class Copy(np.ndarray):
+            def __setitem__(self, key, value):
+                np.ndarray.__setitem__(self, key, np.array(value))
+        f(y.view(Copy), b)
+        assert np.array_equal(t.cpu().numpy(), y), f.__name__
+        assert saved == (1 if f is turned else 0), f.__name__   # (transposed twice is not turned)
+    ctx.set_option("profile", 0)
