@@ -43,6 +43,8 @@ extern "C" {
  *                     unguarded loads from clamped positions, where an estimate of their time is no higher than that
  *                     of the kernels above; 0 = never ("gemm_big" = 0, "gemm_bn", "gemm_kstep" and "gemm_split" switch
  *                     them off as well)
+ *   "moments"         1 (default) = sums over an axis that is not the contiguous one and the sums of squared deviations
+ *                     from their mean (var, std) come out of one pass; 0 = a pass each
  *   "assign_in_place" 1 (default) = a slice assignment whose value reads the destination's storage up to four rows or
  *                     columns away, and that storage only, is evaluated in place after a launch that saves the cells around its
  *                     tiles (two-dimensional boxes with unit steps along the rows, 32-bit elements); 0 = the

@@ -1118,7 +1118,7 @@ void gen_rowred(Em& e) {
 
 // ---- REDUCE (generic reduction root) --------------------------------------------
 
-void reduce_combine(Em& e) {
+void reduce_combine(Em& e, const std::string& squares = "") {
   const GroupPlan& g = e.g;
   const Phase& ph = g.phases[0];
   const char* T = cty(ph.out_dtype);
@@ -1129,6 +1129,29 @@ void reduce_combine(Em& e) {
   e.o << "  const GM " << T << "* const ws = (const GM " << T << "*)" << e.slot(e.L.extra + 2) << ";\n";
   e.o << "  GM " << T << "* const out = (GM " << T << "*)" << e.slot(e.L.out) << ";\n";
   e.o << "  __shared__ long long gr_sm[4];\n";
+  if (!squares.empty())
+    // means and sums of squares about them follow the sums, one per split and output each; the elements per split are known
+    e.o << "  const long long LEN = " << e.S(e.L.extra + 1) << ", chunk = (LEN + NSPLIT - 1) / NSPLIT;\n"
+           "  const GM float* const wu = ws + NSPLIT * NOUT; const GM float* const wm = wu + NSPLIT * NOUT;\n"
+           "  GM float* const sq = (GM float*)" << squares << ";\n"
+           "  auto count = [&](long long s) { const long long left = LEN - s * chunk; return (float)(left < 0 ? 0 : (left < chunk ? left : chunk)); };\n"
+           "  if (NOUT >= 1024) {\n"
+           "    const long long o = (long long)blockIdx.x * 256 + threadIdx.x;\n    if (o < NOUT) {\n"
+           "      float a[8] = {0, 0, 0, 0, 0, 0, 0, 0};\n"
+           "      for (long long s = 0; s < NSPLIT; s += 8)\n"
+           "#pragma unroll\n        for (int i = 0; i < 8; ++i) { const bool in = s + i < NSPLIT; const long long p = in ? s + i : 0; const float w = count(p) * wu[p * NOUT + o]; a[i] += in ? w : 0.0f; }\n"
+           "      const float t = (((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]))) / (float)LEN;\n"
+           "#pragma unroll\n      for (int i = 0; i < 8; ++i) a[i] = 0.0f;\n"
+           "      for (long long s = 0; s < NSPLIT; s += 8)\n"
+           "#pragma unroll\n        for (int i = 0; i < 8; ++i) { const bool in = s + i < NSPLIT; const long long p = in ? s + i : 0; const float d = wu[p * NOUT + o] - t, w = wm[p * NOUT + o] + count(p) * d * d; a[i] += in ? w : 0.0f; }\n"
+           "      sq[o] = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));\n    }\n  } else {\n"
+           "    const long long o = blockIdx.x;\n    float* const sm = (float*)gr_sm;\n    float t = 0.0f, m = 0.0f;\n"
+           "    for (long long s = threadIdx.x; s < NSPLIT; s += 256) t += count(s) * wu[s * NOUT + o];\n"
+           "    t = gr_lanes0(t);\n    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = t;\n    __syncthreads();\n"
+           "    t = ((sm[0] + sm[1]) + (sm[2] + sm[3])) / (float)LEN;\n    __syncthreads();\n"
+           "    for (long long s = threadIdx.x; s < NSPLIT; s += 256) { const float d = wu[s * NOUT + o] - t; m += wm[s * NOUT + o] + count(s) * d * d; }\n"
+           "    m = gr_lanes0(m);\n    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;\n    __syncthreads();\n"
+           "    if (threadIdx.x == 0) sq[o] = (sm[0] + sm[1]) + (sm[2] + sm[3]);\n    __syncthreads();\n  }\n";
   e.o << "  if (NOUT >= 1024) {\n"
          "    const long long o = (long long)blockIdx.x * 256 + threadIdx.x;\n"
          "    if (o < NOUT) {\n      " << T << " acc = ws[o];\n"
@@ -1139,7 +1162,8 @@ void reduce_combine(Em& e) {
          "        acc = gr_comb0(acc, gr_comb0(gr_comb0(gr_comb0(v0, v1), gr_comb0(v2, v3)), gr_comb0(gr_comb0(v4, v5), gr_comb0(v6, v7))));\n"
          "      }\n"
          "      for (; s < NSPLIT; ++s) acc = gr_comb0(acc, ws[s * NOUT + o]);\n"
-         "      out[o] = acc;\n    }\n"
+      << (squares.empty() ? "" : "      sq[o] = gr_squares(acc, sq[o]);\n")
+      << "      out[o] = acc;\n    }\n"
          "  } else {\n"
          "    const long long o = blockIdx.x;\n    " << T << " acc = " << Em::identity(ph) << ";\n"
          "    for (long long s = threadIdx.x; s < NSPLIT; s += 256) acc = gr_comb0(acc, ws[s * NOUT + o]);\n"
@@ -1147,14 +1171,22 @@ void reduce_combine(Em& e) {
          "    " << T << "* sm = (" << T << "*)gr_sm;\n"
          "    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = acc;\n"
          "    __syncthreads();\n"
-         "    if (threadIdx.x == 0) out[o] = gr_comb0(gr_comb0(sm[0], sm[1]), gr_comb0(sm[2], sm[3]));\n"
-         "  }\n}\n";
+         "    if (threadIdx.x == 0) {\n      acc = gr_comb0(gr_comb0(sm[0], sm[1]), gr_comb0(sm[2], sm[3]));\n      out[o] = acc;\n"
+      << (squares.empty() ? "" : "      sq[o] = gr_squares(acc, sq[o]);\n")
+      << "    }\n  }\n}\n";
 }
 
 // One kernel of mode 0 (see gen_reduce_columns).  Loads in flight per lane and array: U, written out, all first (a wave-wide
 // vote in the body keeps the compiler from unrolling a loop with a remainder); what is left of a lane's share is loaded together
 // with clamped positions, whose surplus values are not combined.
-void reduce_columns_kernel(Em& e, bool wide, int U) {
+// `squares` (an expression for the output pointer): the sums of squared deviations from the mean come out of the same pass, the sums
+// being what they are without.  A lane takes a batch's mean and squares about it and joins them to its running mean and
+// squares (n1 n2 / (n1 + n2) times the squared difference of the means is what a join adds), which loses no digits however
+// far the mean is from zero, because means are relative to the median of three of the column's values (no outlier) and a
+// value is subtracted from once, as in the second of two passes.  Partial results of
+// lanes and of splits are joined the same way, all at once about their common mean.
+void reduce_columns_kernel(Em& e, bool wide, int U, const std::string& squares = "") {
+  const bool moments = !squares.empty();
   const GroupPlan& g = e.g;
   const int rank = g.rank, kr = g.red_kept_rank, kd = kr - 1;
   const Phase& ph = g.phases[0];
@@ -1188,6 +1220,10 @@ void reduce_columns_kernel(Em& e, bool wide, int U) {
     e.o << ";\n";
   }
   for (int c = 0; c < W; ++c) e.o << "  " << T << " acc" << c << " = " << Em::identity(ph) << ";\n";
+  if (moments) {
+    e.o << "  float count = 0.0f;\n";
+    for (int c = 0; c < W; ++c) e.o << "  float mu" << c << " = 0.0f, m2" << c << " = 0.0f, pv" << c << " = 0.0f;\n";
+  }
   auto loads = [&](int u, const std::string& jx, const char* ind) {
     const std::string su = "_" + std::to_string(u);
     if (rank > kr) {
@@ -1237,6 +1273,18 @@ void reduce_columns_kernel(Em& e, bool wide, int U) {
   const bool blocked = wide && ph.op == GR_SUM && ph.out_dtype == GR_F32;
   const char* const to = blocked ? "b" : "acc";
   e.o << "  if (ok) {\n    long long j = jbeg + ty;\n";
+  if (moments) {
+    e.o << "    {\n";
+    loads(U, "0ll", "      ");
+    loads(U + 1, "LEN / 2", "      ");
+    loads(U + 2, "LEN - 1", "      ");
+    for (int u = U; u < U + 3; ++u) values(u);
+    for (int c = 0; c < W; ++c) {
+      e.o << "      pv" << c << " = __builtin_amdgcn_fmed3f(";
+      for (int u = U; u < U + 3; ++u) e.o << "v" << u << "_" << c << (u < U + 2 ? ", " : ");\n");
+    }
+    e.o << "    }\n";
+  }
   if (blocked) {
     e.o << "    while (" << more << ") {\n";
     for (int c = 0; c < W; ++c) e.o << "      " << T << " b" << c << " = " << Em::identity(ph) << ";\n";
@@ -1253,6 +1301,18 @@ void reduce_columns_kernel(Em& e, bool wide, int U) {
     };
     tree(0, U);
     join(to, 0);
+  } else if (moments) {
+    for (int u = 0; u < U; ++u) { values(u); join(to, u); }
+    e.o << "      count += " << U << ".0f;\n      const float share = " << U << ".0f / count, rest = count - " << U << ".0f;\n";
+    for (int c = 0; c < W; ++c) {
+      const std::string C = std::to_string(c);
+      auto v = [&](int u) { return "v" + std::to_string(u) + "_" + C; };
+      e.o << "      {\n";
+      std::function<std::string(int, int, bool)> sum = [&](int lo, int n, bool rel) { return n == 1 ? (rel ? "(" + v(lo) + " - pv" + C + ")" : v(lo)) : "(" + sum(lo, n / 2, rel) + " + " + sum(lo + n / 2, n - n / 2, rel) + ")"; };
+      e.o << "        const float m = " << sum(0, U, true) << " * " << 1.0 / U << "f, d = m - mu" << C << ", at = pv" << C << " + m;\n";
+      for (int u = 0; u < U; ++u) e.o << "        " << v(u) << " -= at; " << v(u) << " *= " << v(u) << ";\n";
+      e.o << "        mu" << C << " = __builtin_fmaf(d, share, mu" << C << "); m2" << C << " += " << sum(0, U, false) << " + d * (rest * share) * d;\n      }\n";
+    }
   } else
     for (int u = 0; u < U; ++u) { e.o << "      {\n"; values(u); join(to, u); e.o << "      }\n"; }
   e.o << "    }\n";
@@ -1268,14 +1328,45 @@ void reduce_columns_kernel(Em& e, bool wide, int U) {
       e.o << "      " << (u ? "if (j + " + std::to_string(u) + "ll * BY < jend) " : std::string()) << "{\n";
       values(u);
       join("acc", u);
+      if (moments) {
+        e.o << "      count += 1.0f;\n      const float share = 1.0f / count;\n";
+        for (int c = 0; c < W; ++c) e.o << "      { const float d = v" << u << "_" << c << " - pv" << c << " - mu" << c << "; mu" << c << " = __builtin_fmaf(d, share, mu" << c << "); m2" << c << " += d * ((count - 1.0f) * share) * d; }\n";
+      }
       e.o << "      }\n";
     }
     e.o << "    }\n";
   }
   e.o << "  }\n";
   e.o << "  GM " << T << "* const dst = NSPLIT > 1 ? (GM " << T << "*)" << e.slot(e.L.extra + 2) << " + split * NOUT : (GM " << T << "*)" << e.slot(e.L.out) << ";\n";
+  if (moments) {
+    // the lanes of an output: their common mean, then their squares and those of their means about it
+    e.o << "  GM float* const wsu = (GM float*)" << e.slot(e.L.extra + 2) << " + (NSPLIT + split) * NOUT;\n"
+           "  GM float* const dst2 = NSPLIT > 1 ? wsu + NSPLIT * NOUT : (GM float*)" << squares << ";\n"
+           "  {\n    __shared__ float sn[" << kReduceLanes << "], su[" << W << "][" << kReduceLanes << "], sq[" << W << "][" << kReduceLanes << "];\n"
+           "    sn[threadIdx.x] = ok ? count : 0.0f;\n";
+    for (int c = 0; c < W; ++c) e.o << "    su[" << c << "][threadIdx.x] = mu" << c << "; sq[" << c << "][threadIdx.x] = m2" << c << ";\n";
+    e.o << "    __syncthreads();\n"
+           "    auto meet = [&](int c, unsigned first, unsigned step, unsigned end, float& n, float& u, float& m) {\n"
+           "      n = 0.0f;\n      float a[8] = {0, 0, 0, 0, 0, 0, 0, 0};\n"   // (eight chains: no long one)
+           "      for (unsigned q = first; q < end; q += 8 * step)\n"
+           "#pragma unroll\n        for (int i = 0; i < 8; ++i) { const bool in = q + i * step < end; const unsigned at = (in ? q + i * step : first) * BX + tx; const float k = in ? sn[at] : 0.0f, w = su[c][at]; n += k; a[i] += in ? k * w : 0.0f; }\n"
+           "      u = n > 0.0f ? (((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]))) / n : 0.0f;\n"
+           "#pragma unroll\n      for (int i = 0; i < 8; ++i) a[i] = 0.0f;\n"
+           "      for (unsigned q = first; q < end; q += 8 * step)\n"
+           "#pragma unroll\n        for (int i = 0; i < 8; ++i) { const bool in = q + i * step < end; const unsigned at = (in ? q + i * step : first) * BX + tx; const float d = su[c][at] - u, w = sq[c][at] + sn[at] * d * d; a[i] += in ? w : 0.0f; }\n"
+           "      m = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));\n    };\n"
+           // (lanes past the rows of a short range have nothing; many lanes meet in groups first, a lane per group and column)
+           "    const unsigned have = jend - jbeg < BY ? (unsigned)(jend > jbeg ? jend - jbeg : 0) : BY;\n"
+           "    unsigned nl = have;\n"
+           "    if (have > 16) {\n      const unsigned G = have >= 64 ? 16 : have / 4, c = ty % 4, g = ty / 4;\n      float n = 0.0f, u = 0.0f, m = 0.0f;\n"
+           "      const bool here = ok && g < G && c < " << W << "u;\n      if (here) meet((int)c, g, G, have, n, u, m);\n"
+           "      __syncthreads();\n"
+           "      if (here) { if (c == 0) sn[g * BX + tx] = n; su[c][g * BX + tx] = u; sq[c][g * BX + tx] = m; }\n"
+           "      __syncthreads();\n      nl = G;\n    }\n"
+           "    if (ok) for (unsigned c = ty; c < " << W << "u; c += BY) {\n      float n, u, m;\n      meet((int)c, 0, 1, nl, n, u, m);\n      if (NSPLIT > 1) wsu[o + c] = u;\n      dst2[o + c] = m;\n    }\n  }\n";
+  }
   e.o << "  if (BY == 1) {\n    if (ok) { ";
-  for (int c = 0; c < W; ++c) e.o << "dst[o + " << c << "] = acc" << c << "; ";
+  for (int c = 0; c < W; ++c) e.o << "dst[o + " << c << "] = acc" << c << "; " << (moments ? "if (NSPLIT == 1) dst2[o + " + std::to_string(c) + "] = gr_squares(acc" + std::to_string(c) + ", dst2[o + " + std::to_string(c) + "]); " : "");
   e.o << "}\n    return;\n  }\n"
          "  __shared__ " << T << " sm[" << W << "][" << kReduceLanes << "];\n";
   for (int c = 0; c < W; ++c) e.o << "  sm[" << c << "][threadIdx.x] = acc" << c << ";\n";
@@ -1304,7 +1395,8 @@ void reduce_columns_kernel(Em& e, bool wide, int U) {
          "    " << T << " rest = " << Em::identity(ph) << ";\n"
          "    for (; q < ny; ++q) rest = gr_comb0(rest, sm[c][q * BX + tx]);\n"
          "    r = gr_comb0(r, rest);\n"
-         "    dst[o + c] = r;\n  }\n}\n";
+         "    dst[o + c] = r;\n"
+      << (moments ? "    if (NSPLIT == 1) dst2[o + c] = gr_squares(r, dst2[o + c]);\n" : "") << "  }\n}\n";
 }
 
 // Mode 0: the kept dimension is the contiguous one (column sums).  A workgroup of 512 lanes is BX
@@ -1314,7 +1406,7 @@ void reduce_columns_kernel(Em& e, bool wide, int U) {
 // output are combined in order through LDS.  BX is an argument: the planner fits it to the shape.
 // The last group of four outputs of a ragged dimension starts four from its end: it overlaps the
 // group before it, both store the same values, and no load leaves the array.
-void gen_reduce_columns(Em& e) {
+void gen_reduce_columns(Em& e, const std::string& squares) {
   const GroupPlan& g = e.g;
   const int rank = g.rank, kr = g.red_kept_rank, kd = kr - 1;
   const Phase& ph = g.phases[0];
@@ -1328,13 +1420,16 @@ void gen_reduce_columns(Em& e) {
   // whose registers would halve the wavefronts of the former (3 x 2^22 14.7 us from one kernel with both, 13.3).
   // (registers for what a batch loads, of the 256 that 512 lanes leave each: 223 for five arrays by four, 204 for eight by two;
   // twelve by four spilled 1 KiB per lane)
+  // (squares about a mean as the second of two passes gives them where differences from the first value or the sum overflow)
+  if (!squares.empty())
+    e.o << "static __device__ __forceinline__ float gr_squares(float s, float m) { const bool f = __builtin_fabsf(s) < __builtin_inff(); return (f ? m != m : m == m && s == s) ? __builtin_inff() : m; }\n";
   const int most = n_loads <= 5 ? 4 : (n_loads <= 8 ? 2 : 1);
-  reduce_columns_kernel(e, false, n_loads <= 2 && g.prog.size() <= 12 ? 8 : most);
-  reduce_columns_kernel(e, true, most);
-  reduce_combine(e);
+  reduce_columns_kernel(e, false, n_loads <= 2 && g.prog.size() <= 12 ? 8 : most, squares);
+  if (squares.empty()) reduce_columns_kernel(e, true, most);
+  reduce_combine(e, squares);
 }
 
-void gen_reduce(Em& e) {
+void gen_reduce(Em& e, const std::string& squares = "") {
   const GroupPlan& g = e.g;
   const int rank = g.rank, kr = g.red_kept_rank;
   const Phase& ph = g.phases[0];
@@ -1343,7 +1438,7 @@ void gen_reduce(Em& e) {
   phase_helpers(e, 0, 64);
   // Stage 1 (Section 3.2: map fused with a per-block combine): every output's reduced range is
   // cut into NSPLIT chunks; a column of lanes (mode 0) or a workgroup (mode 1) combines one chunk.
-  if (g.red_mode == 0) { gen_reduce_columns(e); return; }
+  if (g.red_mode == 0) { gen_reduce_columns(e, squares); return; }
   kernel_head(e, kernel_name(g));
   e.o << "  const long long NOUT = " << e.S(e.L.extra) << ", LEN = " << e.S(e.L.extra + 1) << ", NSPLIT = " << e.S(e.L.extra + 3) << ";\n";
   e.o << "  const long long o = blockIdx.x % NOUT, split = blockIdx.x / NOUT;\n  __shared__ long long gr_sm[4];\n";
@@ -2938,7 +3033,14 @@ std::string generate_source(const GroupPlan& g) {
   switch (g.kind) {
     case GroupKind::MAP: if (g.in_place) gen_map_in_place(e); else gen_map(e); break;
     case GroupKind::ROWRED: gen_rowred(e); break;
-    case GroupKind::REDUCE: gen_reduce(e); break;
+    case GroupKind::REDUCE:
+      if (g.pair) {
+        Em e2(*g.pair);
+        e2.slot_base = e.L.total;
+        e.total_slots = e.L.total + e2.L.total;
+        gen_reduce(e, e2.slot(e2.L.out));
+      } else gen_reduce(e);
+      break;
     case GroupKind::SCAN: gen_scan(e); break;
     case GroupKind::GEMM: gen_gemm(e); break;
     case GroupKind::GEMV:

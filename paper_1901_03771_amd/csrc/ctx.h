@@ -73,6 +73,7 @@ struct gr_ctx {
   int64_t opt_plan_cache = 1;
   int64_t opt_scan_threads = 0, opt_scan_min_threads = 0;
   int64_t opt_scan_one_pass = 1;
+  int64_t opt_moments = 1;           // column sums and the squared deviations from their mean in one pass
   int64_t opt_assign_in_place = 1;   // slice assignments that read their destination at shifted positions: evaluated in place where they can be
   int64_t opt_gemm_kstep = 0;
   int64_t opt_gemm_split = 0;   // matrix product: workgroups per output tile along K (0 = chosen by the planner)

@@ -267,7 +267,7 @@ bool interp_encode_gen(const GroupPlan& g, void* out_ptr, GrInterpGenArgs* G, un
     if (g.phases.size() != 1) return false;
     const Phase& ph = g.phases[0];
     if (ph.in_dtype == GR_I64 || (ph.out_dtype == GR_I64 && !(ph.in_dtype == GR_I32 && ph.op == GR_SUM))) return false;
-    if (!encode_operands(g, &G->m)) return false;
+    if (!encode_operands(g, &G->m, fresh, fresh_ptr)) return false;
     G->op = ph.op == GR_SUM ? 0 : (ph.op == GR_MAX ? 1 : 2);
     G->is_int = ph.in_dtype == GR_I32;
     G->out_i64 = ph.out_dtype == GR_I64;

@@ -1773,6 +1773,73 @@ static void fuse_gemv_pairs(gr_ctx* c, Plan* plan) {
   }
 }
 
+// Do instruction `a` of A's program and `b` of B's compute the same value?
+static bool same_value(const GroupPlan& A, int a, const GroupPlan& B, int b) {
+  if (a < 0 || b < 0) return a == b;
+  const Instr& x = A.prog[a];
+  const Instr& y = B.prog[b];
+  if (x.kind != y.kind || x.op != y.op || x.dtype != y.dtype) return false;
+  if (x.kind == IKind::LOAD) {
+    const AccessGroup& p = A.groups[x.group];
+    const AccessGroup& q = B.groups[y.group];
+    int64_t off = p.base - q.base;
+    if (p.leaf != q.leaf) return false;
+    for (int k = 0; k < A.rank; ++k) {
+      if (p.coef[k] != q.coef[k]) return false;
+      off += p.coef[k] * (x.delta[k] - y.delta[k]);
+    }
+    return off == 0;
+  }
+  if (x.kind == IKind::CONST) return A.consts[x.cslot].value == B.consts[y.cslot].value;
+  return same_value(A, x.a, B, y.a) && same_value(A, x.b, B, y.b);
+}
+
+// Column sums S of v whose mean is what the next sub-graph takes v's squared deviations from (var, std and what divides by
+// them): sums of (v - S / n)^2 with n the reduced elements.  One pass over the operands gives both; the sub-graph list, the
+// materialised nodes and the sums are the same.  Bound by HBM like the sums alone; a launch or two less for small arrays.
+// (us for a variance, two passes / one: 100003 x 257 44.2 / 27.3, 8192^2 93 / 51, 3977 x 7342 55 / 36, 16384 x 512 18.3 / 14.1, 768 x 444 14.6 / 10.5,
+// 64 x 8192 9.9 / 8.5, 1000003 x 4 20.5 / 16.5, 100 x 30 8.8 / 8.7; column standardisation of 100003 x 257 88 / 72.)
+// Where the sums take the wide kernel (outputs enough to fill the chip in one launch each) they stay apart, and where the partial results,
+// three per split instead of one, could crowd the static scratch array.
+static void fuse_moments(gr_ctx* c, Plan* plan) {
+  if (!c->opt_moments || !c->opt_fusion) return;
+  for (size_t i = 0; i + 1 < plan->groups.size(); ++i) {
+    GroupPlan& A = *plan->groups[i];
+    GroupPlan& B = *plan->groups[i + 1];
+    if (A.kind != GroupKind::REDUCE || B.kind != GroupKind::REDUCE || A.pair || B.pair || A.red_mode != 0 || B.red_mode != 0 || A.red_wide || A.red_vec != B.red_vec) continue;
+    if (A.rank != B.rank || A.red_kept_rank != B.red_kept_rank || A.red_len < 2 || A.red_len >= (int64_t)1 << 24 || A.red_out < 1 || A.red_out != B.red_out) continue;
+    bool same = true;
+    for (int k = 0; k < A.rank; ++k) same = same && A.dims[k] == B.dims[k];
+    if (!same || (A.slabs > 1 && (int64_t)A.red_tight * A.red_out * 12 > (int64_t)4 << 20)) continue;
+    const Phase& pa = A.phases[0];
+    const Phase& pb = B.phases[0];
+    if (pa.op != GR_SUM || pb.op != GR_SUM || pa.out_dtype != GR_F32 || pb.out_dtype != GR_F32 || pa.in_dtype != GR_F32 || pb.in_dtype != GR_F32) continue;
+    const Instr& q = B.prog[pb.value];
+    int d = -1;
+    if (q.kind == IKind::UNARY && q.op == GR_SQUARE) d = q.a;
+    else if (q.kind == IKind::BINARY && q.op == GR_MUL && q.a == q.b) d = q.a;
+    if (d < 0 || B.prog[d].kind != IKind::BINARY || B.prog[d].op != GR_SUB) continue;
+    const Instr& m = B.prog[B.prog[d].b];
+    if (m.kind != IKind::BINARY || m.op != GR_DIV || B.prog[m.b].kind != IKind::CONST || B.consts[B.prog[m.b].cslot].value != (double)A.red_len) continue;
+    const Instr& s = B.prog[m.a];
+    if (s.kind != IKind::LOAD || B.groups[s.group].leaf != A.root) continue;
+    // S is read at the output's own position
+    const AccessGroup& sg = B.groups[s.group];
+    int64_t at = sg.base, st = 1;
+    bool own = true;
+    for (int k = A.rank - 1; k >= 0; --k) {
+      at += sg.coef[k] * s.delta[k];
+      if (k >= A.red_kept_rank) { own = own && (sg.coef[k] == 0 || A.dims[k] == 1); continue; }
+      own = own && (sg.coef[k] == st || A.dims[k] == 1);
+      st *= A.dims[k];
+    }
+    if (!own || at != 0 || !same_value(A, pa.value, B, B.prog[d].a)) continue;
+    A.pair = std::move(plan->groups[i + 1]);
+    plan->groups.erase(plan->groups.begin() + i + 1);
+    make_signature(&A);
+  }
+}
+
 gr_status make_plan_uncached(gr_ctx* c, Node* root, Plan* plan) {
   if (root->kind == Kind::SCALAR) return fail(c, GR_ERR_UNSUPPORTED, "a bare scalar cannot be materialised");
   Planner pl;
@@ -1817,6 +1884,7 @@ gr_status make_plan_uncached(gr_ctx* c, Node* root, Plan* plan) {
       plan->out_honoured = !plan->out || (!plan->groups.empty() && plan->groups.back()->root == root && plan->groups.back()->kind == GroupKind::MAP &&
                                           map_source(root) == root);
       fuse_gemv_pairs(c, plan);
+      fuse_moments(c, plan);
       return GR_OK;
     }
   }

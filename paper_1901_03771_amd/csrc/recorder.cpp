@@ -230,6 +230,7 @@ gr_status gr_ctx_set_option(gr_ctx* ctx, const char* key, int64_t value) {
   else if (k == "map_bx") ctx->opt_map_bx = value;
   else if (k == "rowred_threads") ctx->opt_rowred_threads = value;
   else if (k == "rowred_rows") ctx->opt_rowred_rows = value;
+  else if (k == "moments") ctx->opt_moments = value;
   else if (k == "assign_in_place") ctx->opt_assign_in_place = value;
   else if (k == "gemm_bn") ctx->opt_gemm_bn = value;
   else if (k == "gemm_kstep") ctx->opt_gemm_kstep = value;

@@ -231,7 +231,7 @@ static void disk_store(const std::string& path, const std::string& key, const st
 static void kernel_entry_points(const GroupPlan& g, std::string* name, bool* combine, int* scan) {
   *name = kernel_name(g);
   *combine = (g.kind == GroupKind::GEMV && g.gemv_mode >= 1) || g.kind == GroupKind::REDUCE || g.kind == GroupKind::GEMM;
-  *scan = g.kind == GroupKind::SCAN ? (g.scan_mode == 4 ? 0 : g.scan_mode >= 2 ? 2 : 1) : (g.kind == GroupKind::REDUCE && g.red_mode == 0 ? 3 : (g.kind == GroupKind::MAP && g.in_place ? 4 : 0));
+  *scan = g.kind == GroupKind::SCAN ? (g.scan_mode == 4 ? 0 : g.scan_mode >= 2 ? 2 : 1) : (g.kind == GroupKind::REDUCE && g.red_mode == 0 && !g.pair ? 3 : (g.kind == GroupKind::MAP && g.in_place ? 4 : 0));
 }
 
 // Loads a code object and publishes the kernel in the in-memory cache.
@@ -485,7 +485,7 @@ static int reduce_slabs(const GroupPlan& g, bool tight) { return tight && g.red_
 static size_t workspace_need(const GroupPlan& g, bool tight) {
   switch (g.kind) {
     case GroupKind::MAP: return g.in_place ? (size_t)(saved_cells(g).rows + saved_cells(g).cols) * 4 : 0;
-    case GroupKind::REDUCE: return reduce_slabs(g, tight) > 1 && g.red_out > 0 ? (size_t)reduce_slabs(g, tight) * (size_t)g.red_out * itemsize(g.out_dtype) : 0;
+    case GroupKind::REDUCE: return reduce_slabs(g, tight) > 1 && g.red_out > 0 ? (size_t)reduce_slabs(g, tight) * (size_t)g.red_out * itemsize(g.out_dtype) * (g.pair ? 3 : 1) : 0;
     case GroupKind::SCAN: {
       int64_t total = 1;
       for (int k2 = 0; k2 < g.rank; ++k2) total *= g.dims[k2];
@@ -626,6 +626,10 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
       if (g.red_out == 0) return GR_OK;
       s[L.extra] = (uint64_t)g.red_out;
       s[L.extra + 1] = (uint64_t)g.red_len;
+      if (g.pair) {   // (one pass for both sums; the second block of arguments names the second one's output)
+        fst = fill_args(c, *g.pair, L2, pair_out_ptr, s.data() + L.total, g.root, out_ptr, L.total);
+        if (fst != GR_OK) return fst;
+      }
       const int slabs = reduce_slabs(g, c->tight);
       s[L.extra + 3] = (uint64_t)slabs;
       if (slabs > 1) {
@@ -889,6 +893,20 @@ gr_status execute_plan(gr_ctx* c, Plan* plan, Node* root, void* user_out, bool c
       }
     }
     bool interpreted = false;
+    auto run_interp_gen = [&](GrInterpGenArgs& ga, unsigned grid) {
+      void* part = nullptr;
+      const size_t part_bytes = ga.nsplit > 1 ? (size_t)grid * 8 : 0;
+      if (part_bytes) part = ctx_alloc(c, part_bytes);
+      if (part_bytes && !part) ga.nsplit = 1, grid = (unsigned)ga.nout;   // no room for partial results: one workgroup per output
+      ga.partial = (unsigned long long)(uintptr_t)part;
+      gr_status ist = interp_launch_gen(c, ga, grid);
+      if (ist == GR_OK && ga.nsplit > 1) {
+        ga.kind = GI_KIND_COMBINE;
+        ist = interp_launch_gen(c, ga, (unsigned)ga.nout);
+      }
+      if (part) ctx_free(c, part, part_bytes);   // (the pool hands blocks out again in stream order)
+      return ist;
+    };
     if (try_interp) {
       GrInterpArgs ia;
       unsigned igrid = 0;
@@ -899,8 +917,8 @@ gr_status execute_plan(gr_ctx* c, Plan* plan, Node* root, void* user_out, bool c
         GrInterpGenArgs ga, gb;
         unsigned grid_b = 0;
         if (total > 0 && interp_encode_gen(g, outs[0], &ga, &igrid, true) && interp_encode_gen(*g.pair, outs[1], &gb, &grid_b, true, g.root, outs[0])) {
-          st = interp_launch_gen(c, ga, igrid);
-          if (st == GR_OK) st = interp_launch_gen(c, gb, grid_b);
+          st = run_interp_gen(ga, igrid);
+          if (st == GR_OK) st = run_interp_gen(gb, grid_b);
           interpreted = true;
         }
       } else if (total == 0 && g.kind == GroupKind::MAP) interpreted = true;  // nothing to compute
@@ -917,17 +935,7 @@ gr_status execute_plan(gr_ctx* c, Plan* plan, Node* root, void* user_out, bool c
         // reductions over any axes, scans, contractions with their epilogues
         GrInterpGenArgs ga;
         if (interp_encode_gen(g, outs[0], &ga, &igrid)) {
-          void* part = nullptr;
-          const size_t part_bytes = ga.nsplit > 1 ? (size_t)igrid * 8 : 0;
-          if (part_bytes) part = ctx_alloc(c, part_bytes);
-          if (part_bytes && !part) ga.nsplit = 1, igrid = (unsigned)ga.nout;   // no room for partial results: one workgroup per output
-          ga.partial = (unsigned long long)(uintptr_t)part;
-          st = interp_launch_gen(c, ga, igrid);
-          if (st == GR_OK && ga.nsplit > 1) {
-            ga.kind = GI_KIND_COMBINE;
-            st = interp_launch_gen(c, ga, (unsigned)ga.nout);
-          }
-          if (part) ctx_free(c, part, part_bytes);   // (the pool hands blocks out again in stream order)
+          st = run_interp_gen(ga, igrid);
           interpreted = true;
         }
       }

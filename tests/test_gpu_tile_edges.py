@@ -392,3 +392,63 @@ def test_assignments_not_evaluated_in_place(env):
         assert np.array_equal(t.cpu().numpy(), y), f.__name__
         assert saved == (1 if f is turned else 0), f.__name__   # (transposed twice is not turned)
     ctx.set_option("profile", 0)
+
+
+# sums of a column and of its squared deviations from one pass: rows below, at and beside a batch of eight per lane, lanes that meet in
+# one step and in groups, several launches' worth of splits, one output per lane (fewer than four columns), several reduced dimensions.
+# Bound: a lane joins at most 32 batches, each a tree of three levels, groups and splits of at most 64 each in eight chains:
+# 32 + 3 + 2 * (8 + 3) roundings, and three in a term itself, 60 of 2^-24.
+@pytest.mark.parametrize("shape,axis", [((2, 5), 0), ((3, 3), 0), ((8, 4), 0), ((9, 30), 0), ((33, 1027), 0), ((100, 17), 0), ((257, 2), 0), ((515, 64), 0), ((4099, 257), 0),
+                                        ((70001, 90), 0), ((200003, 5), 0), ((40, 70, 33), 1), ((30, 20, 50), (0, 1))])
+def test_columns_with_their_squared_deviations(env, shape, axis):
+    gr, ctx, torch = env
+    rng = np.random.default_rng(41)
+    far = rng.standard_normal(shape).astype(f32) + f32(300)          # a mean far from zero
+    out = rng.standard_normal(shape).astype(f32)
+    out[(0,) * len(shape)] = 5000                                    # an outlier
+    assert "fused-with" in planned(env, lambda xp, a: gr.var(a, axis), a=out)
+    for a in (rng.random(shape).astype(f32), far, out, np.full(shape, 2.7, f32)):
+        t = torch.from_numpy(a).cuda()
+        got = gr.var(ctx.array(t), axis).numpy()
+        want = a.astype(np.float64).var(axis)
+        assert got.shape == want.shape and (np.abs(got - want) <= 60 * 2.0 ** -24 * want + 1e-12).all()
+        # the sums keep their bits, and every entry point gives the same ones
+        x = ctx.array(t)
+        both_used = (x - gr.mean(x, axis, True)) / gr.sqrt(gr.var(x, axis, True) + 1e-5)
+        ctx.set_option("moments", 0)
+        apart = gr.sum(x, axis).numpy()
+        ctx.set_option("moments", 1)
+        m = gr.sum(x, axis)
+        v = gr.var(x, axis)
+        v.materialize()
+        assert np.array_equal(m.numpy(), apart)
+        lazy = gr.var(ctx.array(t), axis)
+        lazy.compile()
+        into = torch.empty(want.shape, device="cuda")
+        assert gr.lib().gr_materialize_into_static(ctx._p, lazy.h, into.data_ptr(), into.numel() * 4) == 0, ctx.last_error()
+        assert np.array_equal(into.cpu().numpy(), got)
+        ctx.program(gr.var(x, axis), [x]).run([t], into)
+        assert np.array_equal(into.cpu().numpy(), got)
+        full = a.astype(np.float64)
+        scale = np.sqrt(full.var(axis, keepdims=True) + 1e-5)
+        want = (full - full.mean(axis, keepdims=True)) / scale
+        # (the mean is a sum of the same depth: its rounding, over the deviation)
+        assert (np.abs(both_used.numpy() - want) <= 60 * 2.0 ** -24 * (np.abs(full).max() / scale + np.abs(want))).all()
+
+
+def test_squared_deviations_of_values_that_are_not_finite_or_overflow(env):
+    gr, ctx, torch = env
+    for rows in (3, 1000):
+        a = np.ones((rows, 9), f32)
+        a[1, 0], a[2, 1], a[0, 2] = np.inf, np.nan, -np.inf
+        a[:, 3] = 1e38                                # the sum overflows, the values are equal
+        a[::2, 4], a[1::2, 4] = 3e38, -3e38           # differences overflow
+        a[0, 5] = 0.0
+        a[1:, 5] = 1e25                               # squares overflow
+        t = torch.from_numpy(a).cuda()
+        x = ctx.array(t)
+        got = gr.var(x, 0).numpy()
+        ctx.set_option("moments", 0)
+        want = gr.var(x, 0).numpy()
+        ctx.set_option("moments", 1)
+        assert np.array_equal(got, want, equal_nan=True), rows
