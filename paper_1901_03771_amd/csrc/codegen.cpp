@@ -2433,31 +2433,56 @@ void emit_unrolled(std::ostream& o, const std::vector<std::pair<const char*, int
 using EpiLoad = std::function<std::string(const Instr&, int)>;
 void gemm_combine(Em& e, const EpiLoad& epi_load);
 
+// Three bfloat16 pieces of a float32 value, x = h + m + l exactly, for the matrix products below: h takes x's first eight
+// bits, m the rest rounded to nearest, l what is left, eight bits at most.  The matrix cores multiply bfloat16
+// pairs exactly and add them in float32 at sixteen times the float32 rate, so a product of two split operands, six of
+// their instructions (the three terms below 2^-23 of a product, of either sign, are left out), takes 3/8 of the time, and its sum is
+// rounded six times per sixteen values of k where float32 instructions round eight times (32 x 32 blocks, relative error against
+// 64 bits of float32 instructions / these: normal values, K = 784 4.7e-7 / 4.0e-7, 16384 2.2e-6 / 2.1e-6; uniform ones 4.1e-7 / 2.9e-7).
+// What the pieces cannot hold is noticed, and the tile is computed again in float32 instructions (gemm_big_body): infinities leave a
+// not-finite sum, and of a value whose last piece would reach below the smallest denormal bfloat16 (a nonzero value
+// below 2^-110 can be one) the low half of that piece, which is zero otherwise, is collected in `low`.
+// The splitting competes with the matrix instructions: about 6 vector instructions per value.  They overlap with other waves' matrix
+// instructions; the two-term dot product instruction, which could take off a piece without unpacking it, does not (one wave with matrix
+// instructions beside one with as many cycles of these: their sum; of the others a fifth more than the longer of the two).
+void split_helpers(Em& e) {
+  e.o << "typedef __bf16 gr_b2 __attribute__((ext_vector_type(2)));\n"
+         "typedef __bf16 gr_b8 __attribute__((ext_vector_type(8)));\n"
+         "typedef float gr_p2 __attribute__((ext_vector_type(2)));\n"
+         "typedef unsigned gr_u4 __attribute__((ext_vector_type(4)));\n"
+         "static __device__ __forceinline__ void gr_split2(float x0, float x1, unsigned& h, unsigned& m, unsigned& l, unsigned& low) {\n"
+         "  const unsigned u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);\n"
+         "  const float r0 = x0 - __uint_as_float(u0 & 0xffff0000u), r1 = x1 - __uint_as_float(u1 & 0xffff0000u);\n"
+         "  h = __builtin_amdgcn_perm(u1, u0, 0x07060302u);\n"
+         "  m = __builtin_bit_cast(unsigned, __builtin_convertvector((gr_p2{r0, r1}), gr_b2));\n"
+         "  const unsigned l0 = __float_as_uint(r0 - __uint_as_float(m << 16)), l1 = __float_as_uint(r1 - __uint_as_float(m & 0xffff0000u));\n"
+         "  l = __builtin_amdgcn_perm(l1, l0, 0x07060302u);\n"
+         // (in place: left to the compiler, the collecting is put off and the pieces are kept in scratch memory for it)
+         "  asm(\"v_or3_b32 %0, %0, %1, %2\" : \"+v\"(low) : \"v\"(l0), \"v\"(l1));\n}\n";
+}
+
 // Matrix product of large operands, each contiguous along one of its dimensions (K a multiple of 16; M and N need
-// not be multiples of 256: edge tiles load clamped rows and store only what exists): one workgroup per 256 x 256 tile of the result and
-// per compute unit, four waves with a 128 x 128 quarter each as 4 x 4 matrix-core blocks (256 accumulator
-// registers per lane).
+// not be multiples of the tile: edge tiles load clamped rows and store only what exists): one workgroup per tile of the result
+// and compute unit, tiles of 256 x 256 (four waves with a 128 x 128 quarter each as 4 x 4 matrix-core blocks, 256
+// accumulator registers per lane) or 128 x 128 (two groups of four waves, 2 x 2 blocks each).
 //   * Tiles of 16 values of k go from global memory straight into LDS (global_load_lds_dwordx4: lane L of a
 //     wave deposits its 16 bytes at M0 + 16 L, whatever address it loaded them from), two steps ahead, into a
 //     ring of three stages, so a step has one barrier, no staging registers and no LDS write instructions.
-//   * Left tile: 256 rows of 16 floats; the four 16-byte chunks of row m sit at chunk position c ^ (m / 4 % 4),
+//   * A tile contiguous along k: rows of 16 floats; the four 16-byte chunks of row m sit at chunk position c ^ (m / 4 % 4),
 //     which lets both the depositing wave (16 lanes = 4 rows x 4 chunks) and the reading one (16 lanes = 16
-//     rows, one chunk) touch every bank once.  A lane reads the four k values of a chunk with one ds_read_b128
-//     and feeds them to four matrix instructions: the instruction for element t of the chunks takes k = 4 h + t
-//     (+ 8 in the second half of the step) in half-wave h instead of k = 2 s + h.  Both operands use the same
-//     assignment, so every product is formed once; only the order of the additions differs.
-//   * Right tile: 16 rows of 256 floats with a pitch of 264 (rows 4 apart lie 32 banks apart).  Block j of a
-//     lane's four column blocks is column 4 r + j of the wave's 128 (r = lane % 32), so the four operands of a
+//     rows, one chunk) touch every bank once.
+//   * A tile contiguous along its other dimension: 16 rows of 256 floats with a pitch of 264 (rows 4 apart lie 32 banks apart).
+//     Block j of a lane's four column blocks is column 4 r + j of the wave's 128 (r = lane % 32), so the four operands of a
 //     k come with one ds_read_b128 and a lane's results are four neighbouring columns (16-byte stores).
-//   * Per step and wave: 128 matrix instructions, 16 LDS reads, 8 direct loads, one barrier, each placed
-//     behind a fixed matrix instruction (scheduling barriers pin the order): with one wave per SIMD every
-//     instruction between two matrix instructions delays the second one, which is what bounds this kernel
-//     (measured on 4096^3, one variant each: staging through registers 137 TFLOP/s, direct loads 143, the
-//     same with addresses precomputed and 16-byte reads of the right operand 151; a loop of nothing but
-//     matrix instructions 154).
+//   * Half-wave h takes k = 4 h .. 4 h + 3 and 8 + 4 h .. of a step for both operands, eight values per lane and block, which
+//     it splits into three pieces (split_helpers) and multiplies with six matrix instructions per pair of blocks.
+// Bound by vector issue (176 instructions per wave and step for the pieces of 128 x 64 x 16 products, 704 cycles) and the matrix
+// cores (768); measured against float32 matrix instructions with the same tiles and loads (us, before / now): 2048^3 143 / 113,
+// 4096 x 512 x 784 42 / 31, 784 x 4096 x 512 43 / 35, 1536^3 79 / 67, 512 x 2848 x 2352 74 / 54, 4096^3 932 / 697
+// (197 TFLOP/s); relative error 4.1e-7 / 2.4e-7 (4096 x 512 x 784), 1.15e-6 / 1.0e-6 (4096^3).
 // The direct loads are written as assembly: the compiler's own form of them makes it wait for every outstanding
 // LDS read before each use (it counts them as LDS traffic that may return out of order).  Their completion is
-// tracked by hand: vmcnt(8) before a step's barrier leaves only the eight loads of the newest tile in flight.
+// tracked by hand: the wait before a step's barrier leaves only the loads of the newest tile in flight.
 void gemm_big_body(Em& e, const EpiLoad& epi_load) {
   const GroupPlan& g = e.g;
   const int NB = g.BX / 64;          // matrix-core blocks per wave along each dimension: 4 (256 x 256 tiles) or 2 (128 x 128)
@@ -2476,14 +2501,16 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
   const char* RV = NB == 4 ? "f4" : "gr_f2";      // what a lane reads of a row-contiguous tile per k
   std::ostream& o = e.o;
   const bool split = g.slabs > 1;
-  o << "  __shared__ __attribute__((aligned(16))) float gr_lds[" << 3 * STAGE << "];\n"
+  const bool two = NB == 2;
+  o << "  __shared__ __attribute__((aligned(16))) float gr_lds[" << (two ? 6 : 3) * STAGE << "];\n"
        "  typedef __attribute__((address_space(3))) float lfloat;\n"
        "  typedef __attribute__((address_space(3))) f4 lf4;\n"
        "  typedef float gr_f2 __attribute__((ext_vector_type(2)));\n"
        "  typedef gr_f2 gr_f2u __attribute__((aligned(4)));\n"
        "  typedef __attribute__((address_space(3))) gr_f2 lgr_f2;\n"
-       "  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, lh = lane >> 5;\n"
-       "  const int wm = (wave >> 1) * " << 32 * NB << ", wn = (wave & 1) * " << 32 * NB << ";\n"
+       "  const int tid = threadIdx.x, lane = tid & 63, wave = " << (two ? "(tid >> 6) & 3" : "tid >> 6") << ", l32 = lane & 31, lh = lane >> 5;\n"
+    << (two ? "  const int group = __builtin_amdgcn_readfirstlane(tid >> 8);\n" : "  const int group = 0;\n")
+    << "  const int wm = (wave >> 1) * " << 32 * NB << ", wn = (wave & 1) * " << 32 * NB << ";\n"
        "  const long long tiles_n = (N + " << T - 1 << ") / " << T << ";\n";
   // split K (few output tiles, a long contraction): workgroup (tile, split) accumulates the steps of k in [kbeg, KE),
   // a whole number of steps and at least two by the planner's choice, and leaves its partial tile in a workspace
@@ -2494,7 +2521,9 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
        "  f16v acc[" << NB << "][" << NB << "];\n"
        "  for (int i = 0; i < " << NB << "; ++i) for (int j = 0; j < " << NB << "; ++j) for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;\n"
        "  const unsigned wv = __builtin_amdgcn_readfirstlane(wave);\n"
-       "  const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) void*)gr_lds;\n";
+       "  const lfloat* const ring = (const lfloat*)gr_lds + group * " << 3 * STAGE << ";\n"
+       "  const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) void*)gr_lds + " << 12 * STAGE << "u * (unsigned)group;\n"
+       "  const long long kfirst = kbeg + 16 * group;\n";
   for (const Op& x : ops) {
     const std::string n = x.n, w0 = x.n[0] == 'a' ? "wm" : "wn", X = x.n[0] == 'a' ? "A" : "B";
     // direct loads: a uniform base (advanced every step; made visibly uniform, the operands of the loads must be scalar
@@ -2504,14 +2533,14 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
       // (rows beyond the operand's edge read its last row: their results are never stored)
       o << "  for (int p = 0; p < " << NB << "; ++p) { const int m = 16 * (" << NB << " * wave + p) + lane / 4, c = (lane % 4) ^ ((m >> 2) & 3); const long long last = " << x.lim << " - 1 - " << x.org
         << "; " << n << "off[p] = 4u * (unsigned)((m < last ? m : last) * " << x.ld << " + 4 * c); }\n"
-           "  const unsigned long long " << n << "64 = (unsigned long long)(" << X << " + " << x.org << " * " << x.ld << " + kbeg);\n"
-           "  const unsigned long long " << n << "step = 64ull;\n";
+           "  const unsigned long long " << n << "64 = (unsigned long long)(" << X << " + " << x.org << " * " << x.ld << " + kfirst);\n"
+           "  const unsigned long long " << n << "step = " << (two ? 128 : 64) << "ull;\n";
     else {
       // (groups of four beyond the operand's edge, whose extent is a multiple of four, read its last group)
       if (NB == 4) o << "  for (int p = 0; p < 4; ++p) { const long long last = " << x.lim << " - 4 - " << x.org << "; " << n << "off[p] = 4u * (unsigned)((4 * wave + p) * " << x.ld << " + (4 * lane < last ? 4 * lane : last)); }\n";
       else o << "  for (int p = 0; p < 2; ++p) { const long long last = " << x.lim << " - 4 - " << x.org << "; " << n << "off[p] = 4u * (unsigned)((2 * (2 * wave + p) + lane / 32) * " << x.ld << " + (4 * l32 < last ? 4 * l32 : last)); }\n";
-      o << "  const unsigned long long " << n << "64 = (unsigned long long)(" << X << " + " << x.org << " + kbeg * " << x.ld << ");\n"
-           "  const unsigned long long " << n << "step = 64ull * (unsigned long long)__builtin_amdgcn_readfirstlane((int)" << x.ld << ");\n";
+      o << "  const unsigned long long " << n << "64 = (unsigned long long)(" << X << " + " << x.org << " + kfirst * " << x.ld << ");\n"
+           "  const unsigned long long " << n << "step = " << (two ? 128 : 64) << "ull * (unsigned long long)__builtin_amdgcn_readfirstlane((int)" << x.ld << ");\n";
     }
     const int wave_bytes = x.kc ? 1024 * NB : (NB == 4 ? 4 * 264 * 4 : 4 * 272 * 2);
     o << "  unsigned long long " << n << "base = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(" << n << "64 >> 32)) << 32) | (unsigned)__builtin_amdgcn_readfirstlane((int)" << n << "64);\n"
@@ -2519,11 +2548,11 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
     // LDS read bases of this lane, per stage
     if (x.kc)
       o << "  const lfloat* " << n << "p[3][2];\n#pragma unroll\n  for (int st = 0; st < 3; ++st)\n#pragma unroll\n"
-           "    for (int hf = 0; hf < 2; ++hf) " << n << "p[st][hf] = (const lfloat*)gr_lds + st * " << STAGE << " + " << x.part << " + (" << w0 << " + l32) * 16 + 4 * ((2 * hf + lh) ^ ((l32 >> 2) & 3));\n"
-           "  f4 " << n << "F[2][" << NB << "];\n";
+           "    for (int hf = 0; hf < 2; ++hf) " << n << "p[st][hf] = ring + st * " << STAGE << " + " << x.part << " + (" << w0 << " + l32) * 16 + 4 * ((2 * hf + lh) ^ ((l32 >> 2) & 3));\n"
+           "";
     else
-      o << "  const lfloat* " << n << "p[3];\n#pragma unroll\n  for (int st = 0; st < 3; ++st) " << n << "p[st] = (const lfloat*)gr_lds + st * " << STAGE << " + " << x.part << " + " << rc_row(4) << " * lh + " << w0 << " + " << NB << " * l32;\n"
-           "  " << RV << " " << n << "F[2];\n";
+      o << "  const lfloat* " << n << "p[3];\n#pragma unroll\n  for (int st = 0; st < 3; ++st) " << n << "p[st] = ring + st * " << STAGE << " + " << x.part << " + " << rc_row(4) << " * lh + " << w0 << " + " << NB << " * l32;\n"
+           "";
   }
   o << "  const long long nkt = (KE - kbeg) / 16;\n";
   // piece p (0 .. NB - 1: the left tile, NB .. 2 NB - 1: the right tile) of the tile at the bases into the stage in role st
@@ -2542,60 +2571,7 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
   // different columns, was measured on 2048^3, whose rows of 8 KiB cost the 128 x 128-tile kernel a tenth against rows
   // padded by 64 bytes: no change, so the walk starts at zero everywhere.)
   const char* ADV = "abase += astep; bbase += bstep;\n";
-  const char* SB = "__builtin_amdgcn_sched_barrier(0);\n";
-  // operand of a matrix instruction (group s of the step, block blk) and the LDS reads that provide it
-  auto val = [&](const Op& x, int s, int blk) {
-    std::ostringstream v;
-    if (x.kc) v << x.n << "F[" << (s >> 2) << "][" << blk << "][" << (s & 3) << "]";
-    else v << x.n << "F[" << (s & 1) << "][" << blk << "]";
-    return v.str();
-  };
-  auto read_kc = [&](const Op& x, int st, int hf, int blk, const char* ind) {
-    o << ind << x.n << "F[" << hf << "][" << blk << "] = *(const lf4*)(" << x.n << "p[" << st << "][" << hf << "] + " << blk * 512 << ");\n";
-  };
-  auto read_rc = [&](const Op& x, int st, int s, const char* ind) {
-    o << ind << x.n << "F[" << (s & 1) << "] = *(const l" << RV << "*)(" << x.n << "p[" << st << "] + " << rc_row(8 * (s >> 2) + (s & 3)) << ");\n";
-  };
-  // One step.  Role 0 is the stage that holds the current tile; the tile two steps on goes to the stage in role 2 if more2;
-  // the first operands of the next step are read (from role 1) behind the barrier if more1.  Every load and LDS read
-  // sits behind a fixed matrix instruction of a fixed group.
-  auto step = [&](bool more2, bool more1, const char* ind) {
-    for (int s = 0; s < 8; ++s) {
-      if (s == 7)
-        // the next tile has landed (all but the newest P loads are complete) and this wave's reads of the current one are done
-        o << ind << "__builtin_amdgcn_s_waitcnt(" << (more2 ? 0x0070 | P : 0x0070) << ");\n" << ind << "__builtin_amdgcn_s_barrier();\n";
-      for (int q = 0; q < G; ++q) {
-        const int i = q / NB, j = q % NB;
-        o << ind << SB << ind << "acc[" << i << "][" << j << "] = __builtin_amdgcn_mfma_f32_32x32x2f32(" << val(ops[0], s, i) << ", " << val(ops[1], s, j)
-          << ", acc[" << i << "][" << j << "], 0, 0, 0);\n" << ind << SB;
-        if (more2 && q == 1 && s < P && s < 7) piece(2, s, ind);
-        if (more2 && NB == 4 && s == 6 && q == 9) piece(2, 7, ind);
-        if (more2 && s == (NB == 4 ? 6 : 3) && q == (NB == 4 ? 9 : 1)) o << ind << ADV;
-        for (int k = 0; k < 2; ++k) {
-          const Op& x = ops[k];
-          if (x.kc) {
-            // second half of the step: behind the last NB matrix instructions of group 1 (left) / 2 (right);
-            // first half of the next step: behind the first 2 NB of group 7
-            if (s == 1 + k && q >= G - NB) read_kc(x, 0, 1, q - (G - NB), ind);
-            if (s == 7 && more1 && q >= NB * k && q < NB + NB * k) read_kc(x, 1, 0, q - NB * k, ind);
-          } else {
-            if (s < 7 && q == NB + k) read_rc(x, 0, s + 1, ind);
-            if (s == 7 && more1 && q == NB + k) read_rc(x, 1, 0, ind);
-          }
-        }
-      }
-    }
-  };
-  // prologue: tiles 0 and 1 (K >= 32)
-  for (int t = 0; t < 2; ++t) {
-    for (int p = 0; p < P; ++p) piece(t, p, "  ");
-    o << "  " << ADV;
-  }
-  o << "  __builtin_amdgcn_s_waitcnt(" << (0x0F70 | P) << ");\n  __builtin_amdgcn_s_barrier();\n";
-  for (const Op& x : ops) {
-    if (x.kc) for (int blk = 0; blk < NB; ++blk) read_kc(x, 0, 0, blk, "  ");
-    else read_rc(x, 0, 0, "  ");
-  }
+
   // the stages rotate through three roles (0: the tile of this step, 1: of the next one, 2: the target of this step's
   // loads): the addresses are exchanged after every step, a handful of register moves per step
   std::ostringstream rot;
@@ -2606,14 +2582,167 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
     else rot << "    { const lfloat* const t0 = " << x.n << "p[0]; " << x.n << "p[0] = " << x.n << "p[1]; " << x.n << "p[1] = " << x.n << "p[2]; " << x.n << "p[2] = t0; }\n";
     if (&x == &ops[0]) rot << "    ";
   }
-  o << "  long long kt = 0;\n"
-       "  for (; kt + 2 < nkt; ++kt) {\n";
-  step(true, true, "    ");
-  o << "    " << rot.str() << "  }\n"
-       "  // the last two steps load nothing\n";
-  step(false, true, "  ");
-  o << "  " << rot.str();
-  step(false, false, "  ");
+  const std::string rot_text = rot.str();
+  // Values t (t < 4) and 4 + t of a lane's eight are k = 4 h + t and 8 + 4 h + t in half-wave h, for both operands.
+  // Block blk of an operand in stage `role`, split into set `set`; a statement per element so that they can be placed apart.
+  auto raw = [&](const Op& x, int role, int blk, const char* ind) {
+    const std::string n = x.n;
+    for (int hf = 0; hf < 2; ++hf)
+      o << ind << "{ const f4 w = *(const lf4*)(" << n << "p[" << role << "][" << hf << "] + " << blk * 512 << "); " << n << "r[" << blk << "][" << 4 * hf << "] = w[0]; " << n << "r[" << blk << "][" << 4 * hf + 1 << "] = w[1]; " << n << "r[" << blk << "][" << 4 * hf + 2 << "] = w[2]; " << n << "r[" << blk << "][" << 4 * hf + 3 << "] = w[3]; }\n";
+  };
+  auto raw_all = [&](const Op& x, int role, const char* ind) {
+    const std::string n = x.n;
+    for (int blk = 0; x.kc && blk < NB; ++blk) raw(x, role, blk, ind);
+    for (int v = 0; !x.kc && v < 8; ++v) {
+      o << ind << "{ const " << RV << " w = *(const l" << RV << "*)(" << n << "p[" << role << "] + " << rc_row(8 * (v >> 2) + (v & 3)) << ");";
+      for (int blk = 0; blk < NB; ++blk) o << ' ' << n << "r[" << blk << "][" << v << "] = w[" << blk << "];";
+      o << " }\n";
+    }
+  };
+  auto pieces_of = [&](const Op& x, int set, int blk, int p, const char* ind) {
+    const std::string n = x.n, to = n + "s" + std::to_string(set) + "[" + std::to_string(blk) + "]";
+    o << ind << "{ unsigned h, m, l; gr_split2(" << n << "r[" << blk << "][" << 2 * p << "], " << n << "r[" << blk << "][" << 2 * p + 1 << "], h, m, l, low); " << to << "[0][" << p << "] = h; " << to << "[1][" << p << "] = m; " << to << "[2][" << p << "] = l; }\n";
+  };
+  static const int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+  auto mfma = [&](int set, int t, int i, int j, const char* ind) {
+    o << ind << "acc[" << i << "][" << j << "] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(gr_b8, as" << set << "[" << i << "][" << order[t][0] << "]), __builtin_bit_cast(gr_b8, bs" << set << "[" << j << "][" << order[t][1] << "]), acc[" << i << "][" << j << "], 0, 0, 0);\n";
+  };
+  const char* SB = "__builtin_amdgcn_sched_barrier(0);\n";
+  for (const Op& x : ops) o << "  gr_u4 " << x.n << "s0[" << NB << "][3];\n";
+  o << "  unsigned low = 0u;\n";
+  auto wait = [&](int left, const char* ind) { o << ind << "__builtin_amdgcn_s_waitcnt(" << (0x0070 | left) << ");\n" << ind << "__builtin_amdgcn_s_barrier();\n"; };
+  if (two) {
+    // Group g of four waves takes every second step from step g on, its tiles in a ring of its own.  Vector and matrix instructions
+    // of one wave hardly overlap, those of two waves of a SIMD do: between two barriers group 0 splits a tile and
+    // multiplies it while group 1 multiplies the tile that it split before and splits the next.
+    o << "  const int n0 = (int)((nkt + 1) / 2), mine = (int)((nkt + 1 - group) / 2);\n";
+    // (a group with one step less than the other repeats its last tile and leaves it out)
+    auto fetch = [&](int role, const char* tile, const char* ind) {
+      for (int p = 0; p < P; ++p) piece(role, p, ind);
+      o << ind << "if (" << tile << " + 1 < mine) { " << "abase += astep; bbase += bstep; }\n";
+    };
+    auto split_tile = [&](const char* ind) {
+      for (const Op& x : ops) {
+        o << ind << "float " << x.n << "r[" << NB << "][8];\n";
+        raw_all(x, 0, ind);
+      }
+      for (const Op& x : ops) for (int blk = 0; blk < NB; ++blk) for (int p = 0; p < 4; ++p) pieces_of(x, 0, blk, p, ind);
+    };
+    auto products = [&](const char* ind) {
+      for (int t = 0; t < 6; ++t) for (int i = 0; i < NB; ++i) for (int j = 0; j < NB; ++j) mfma(0, t, i, j, ind);
+    };
+    // (each group has loops of its own, with as many barriers: the compiler moves sums about where paths of a loop meet)
+    auto step = [&](int group, bool more, bool first, const char* ind) {
+      o << ind << "{\n";
+      if (more) fetch(2, "t + 2", ind);
+      if (group == 1 && !first) {
+        products(ind);
+        o << ind << SB;
+      }
+      split_tile(ind);
+      if (group == 0) {
+        o << ind << SB;
+        products(ind);
+      }
+      wait(more ? P : 0, ind);
+      o << ind << rot_text << ind << "}\n";
+    };
+    fetch(0, "0", "  ");
+    o << "  if (n0 > 1) {\n";
+    fetch(1, "1", "    ");
+    o << "    __builtin_amdgcn_s_waitcnt(" << (0x0F70 | P) << ");\n  } else __builtin_amdgcn_s_waitcnt(" << 0x0F70 << ");\n  __builtin_amdgcn_s_barrier();\n  int t = 0;\n";
+    o << "  if (group == 0) {\n    for (; t + 2 < n0; ++t)\n";
+    step(0, true, false, "    ");
+    o << "    for (; t < n0; ++t)\n";
+    step(0, false, false, "    ");
+    o << "  } else {\n    if (n0 > 2)\n";
+    step(1, true, true, "    ");
+    o << "    else\n";
+    step(1, false, true, "    ");
+    o << "    for (t = 1; t + 2 < n0; ++t)\n";
+    step(1, true, false, "    ");
+    o << "    for (; t < n0; ++t)\n";
+    step(1, false, false, "    ");
+    o << "    if (mine == n0) {\n";
+    products("    ");
+    o << "    }\n  }\n";
+    // the groups add up their sums: each takes one row of blocks
+    o << "  f16v own[2];\n"
+         "  { f4* const area = (f4*)gr_lds + (wave * 8) * 64 + lane;   // 32 KiB per group: what it leaves to the other one\n"
+         "    unsigned* const flags = (unsigned*)gr_lds + 16384;\n"
+         "    bool odd = (low & 0xffffu) != 0u;\n"
+         "#pragma unroll\n    for (int j = 0; j < 2; ++j)\n#pragma unroll\n      for (int q = 0; q < 16; ++q) { const float a = acc[0][j][q], b = acc[1][j][q]; own[j][q] = group ? b : a; acc[0][j][q] = group ? a : b; }\n"
+         "#pragma unroll\n    for (int j = 0; j < 2; ++j)\n#pragma unroll\n      for (int q = 0; q < 4; ++q) area[group * 2048 + (j * 4 + q) * 64] = f4{acc[0][j][4 * q], acc[0][j][4 * q + 1], acc[0][j][4 * q + 2], acc[0][j][4 * q + 3]};\n"
+         "    if (lane == 0) flags[group * 4 + wave] = 0u;\n"
+         "    if (odd) flags[group * 4 + wave] = 1u;\n"
+         "    __syncthreads();\n"
+         "#pragma unroll\n    for (int j = 0; j < 2; ++j)\n#pragma unroll\n      for (int q = 0; q < 4; ++q) { const f4 v = area[(1 - group) * 2048 + (j * 4 + q) * 64]; own[j][4 * q] += v[0]; own[j][4 * q + 1] += v[1]; own[j][4 * q + 2] += v[2]; own[j][4 * q + 3] += v[3]; }\n"
+         "    odd = (flags[wave] | flags[4 + wave]) != 0u;\n"
+         "#pragma unroll\n    for (int j = 0; j < 2; ++j)\n#pragma unroll\n      for (int q = 0; q < 16; ++q) odd = odd || !(__builtin_fabsf(own[j][q]) < __builtin_inff());\n"
+         "    if (__builtin_amdgcn_ballot_w64(odd) != 0ull) {\n";
+    o << "      const long long row = bm0 + wm + " << (ops[0].kc ? "32 * group + l32" : "2 * l32 + group") << ";\n"
+         "      const GM float* const pa = A + (row < M ? row : M - 1) * am;\n      const GM float* pb[2];\n"
+         "#pragma unroll\n      for (int j = 0; j < 2; ++j) {\n        const long long col = bn0 + wn + " << (ops[1].kc ? "32 * j + l32" : "2 * l32 + j") << ";\n        pb[j] = B + (col < N ? col : N - 1) * bn;\n"
+         "#pragma unroll\n        for (int q = 0; q < 16; ++q) own[j][q] = 0.0f;\n      }\n"
+         "      for (long long k = kbeg; k < KE; k += 2) {\n        const float va = pa[(k + lh) * ak];\n"
+         "#pragma unroll\n        for (int j = 0; j < 2; ++j) own[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va, pb[j][(k + lh) * bk], own[j], 0, 0, 0);\n      }\n";
+    o << "    }\n  }\n";
+  } else {
+    // 256 accumulators per lane leave no room for two sets of pieces: the right operand's are made first, a
+    // row of blocks of the left one's while the one before is multiplied.
+    auto step = [&](bool more2, const char* ind) {
+      o << ind << "{\n";
+      if (more2) {
+        for (int p = 0; p < P; ++p) piece(2, p, ind);
+        o << ind << ADV;
+      }
+      for (const Op& x : ops) {
+        o << ind << "float " << x.n << "r[" << NB << "][8];\n";
+        if (!x.kc) raw_all(x, 0, ind);
+      }
+      auto block = [&](const Op& x, int blk) {
+        if (x.kc) raw(x, 0, blk, ind);
+        for (int p = 0; p < 4; ++p) pieces_of(x, 0, blk, p, ind);
+        o << ind << SB;
+      };
+      for (int blk = 0; blk < NB; ++blk) block(ops[1], blk);
+      for (int i = 0; i < NB; ++i) {
+        block(ops[0], i);
+        for (int t = 0; t < 6; ++t) for (int j = 0; j < NB; ++j) mfma(0, t, i, j, ind);
+        o << ind << SB;
+      }
+      wait(more2 ? P : 0, ind);
+      o << ind << "}\n";
+    };
+    // prologue: tiles 0 and 1 (K >= 32)
+    for (int t = 0; t < 2; ++t) {
+      for (int p = 0; p < P; ++p) piece(t, p, "  ");
+      o << "  " << ADV;
+    }
+    o << "  __builtin_amdgcn_s_waitcnt(" << (0x0F70 | P) << ");\n  __builtin_amdgcn_s_barrier();\n";
+    o << "  long long kt = 0;\n"
+         "  for (; kt + 2 < nkt; ++kt) {\n";
+    step(true, "    ");
+    o << "    " << rot_text << "  }\n"
+         "  // the last two steps load nothing\n";
+    step(false, "  ");
+    o << "  " << rot_text;
+    step(false, "  ");
+  }
+  if (!two) {
+  // a wave whose pieces or sums are not what they should be computes its blocks again
+  o << "  bool again = (low & 0xffffu) != 0u;\n"
+       "  float most = 0.0f;\n";
+  emit_unrolled(o, {{"i", NB}, {"j", NB}, {"h", 2}}, std::string("    __builtin_amdgcn_sched_barrier(0);\n#pragma unroll\n    for (int q = 0; q < 8; ++q) most += acc[i][j][8 * h + q] * 0.0f;   // (not a number for what is not finite)\n    asm(\"\" : \"+v\"(most));\n"), "  ");
+  o << "  again = again || !(most == 0.0f);\n"
+       "  const bool bad = __builtin_amdgcn_ballot_w64(again) != 0ull;\n";
+  // (a block at a time: where the two ways meet, few registers change places)
+  emit_unrolled(o, {{"i", NB}, {"j", NB}}, std::string("    __builtin_amdgcn_sched_barrier(0);\n    if (bad) {\n      const long long row = bm0 + wm + ") + (ops[0].kc ? "32 * i + l32" : std::to_string(NB) + " * l32 + i") + ", col = bn0 + wn + " + (ops[1].kc ? "32 * j + l32" : std::to_string(NB) + " * l32 + j") + ";\n"
+         "      const GM float* const pa = A + (row < M ? row : M - 1) * am; const GM float* const pb = B + (col < N ? col : N - 1) * bn;\n"
+         "#pragma unroll\n      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;\n"
+         "#pragma unroll 1\n      for (long long k = kbeg + lh; k < KE; k += 2) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[k * ak], pb[k * bk], acc[i][j], 0, 0, 0);\n    }\n", "  ");   // (whole steps: an even number of values)
+  o << "  __builtin_amdgcn_sched_barrier(0);\n";
+  }
   // epilogue on the accumulators: element q of a block is its row rr = 8 (q / 4) + 4 (lane / 32) + q % 4 and column lane % 32;
   // block i of a k-contiguous left operand holds rows wm + 32 i + rr, of a row-contiguous one rows wm + NB rr + i; block j
   // of a row-contiguous right operand holds column wn + NB (lane % 32) + j (a lane's NB results are neighbours: one
@@ -2625,18 +2754,19 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
   else o << "  GM float* const out = (GM float*)" << e.slot(e.L.out) << ";\n";
   const std::string body = captured(e, [&] {
     o << "      const int rr = 8 * (q / 4) + 4 * lh + (q % 4);\n"
-         "      const long long row_at = bm0 + wm + " << (ops[0].kc ? "32 * i + rr" : std::to_string(NB) + " * rr + i") << ", row = row_at < M ? row_at : M - 1;\n"
+         "      const long long row_at = bm0 + wm + " << (two ? (ops[0].kc ? "32 * group + rr" : "2 * rr + group") : (ops[0].kc ? "32 * i + rr" : std::to_string(NB) + " * rr + i")) << ", row = row_at < M ? row_at : M - 1;\n"
          "      " << RV << " ov;\n"
          "#pragma unroll\n      for (int j = 0; j < " << NB << "; ++j) {\n"
          "        const long long col_at = bn0 + wn + " << (ops[1].kc ? "32 * j + l32" : std::to_string(NB) + " * l32 + j") << ", col = col_at < N ? col_at : N - 1;\n"
-         "        const float cacc = acc[i][j][q];\n";
+         "        const float cacc = " << (two ? "own[j][q]" : "acc[i][j][q]") << ";\n";
     std::string res = "cacc";
     if (!split) { emit_scalar_program(e, g.prog, g.results, epi_load, "cacc", "t", "        "); res = "t" + std::to_string(g.results[0]); }
     if (ops[1].kc) o << "        if (row_at < M && col_at < N) out[row * N + col] = " << res << ";\n      }\n      (void)ov;\n";
     else o << "        ov[j] = " << res << ";\n      }\n"
               "      if (row_at < M && bn0 + wn + " << NB << " * l32 < N) *(GM " << RV << "u*)(out + row * N + bn0 + wn + " << NB << " * l32) = ov;\n";
   });
-  emit_unrolled(o, {{"i", NB}, {"q", 16}}, body, "    ");
+  if (two) emit_unrolled(o, {{"q", 16}}, body, "    ");
+  else emit_unrolled(o, {{"i", NB}, {"q", 16}}, body, "    ");
   o << "}\n";
 }
 
@@ -2822,7 +2952,10 @@ void gen_gemm(Em& e) {
   const int BP = BN == 128 && b_mode == 1 ? (KS == 32 ? 129 : 130) : BN + 4;
   prelude(e);
   e.o << "typedef float f16v __attribute__((ext_vector_type(16)));\n";
-  kernel_head(e, "gr_gemm");
+  if (g.VR == 2) {
+    split_helpers(e);
+  }
+  kernel_head(e, "gr_gemm", g.VR == 2 && g.BX == 128 ? 512 : 256);
   e.o << "  const long long M = " << e.S(e.L.extra) << ", N = " << e.S(e.L.extra + 1) << ", K = " << e.S(e.L.extra + 2) << ";\n";
   group_pointers(e, "  ");
   e.o << "  const GM float* const A = q" << g.mat_group << "; const GM float* const B = q" << g.vec_group << ";\n";

@@ -762,12 +762,13 @@ static void choose_in_place(GroupPlan* g) {
 // except for short sums with a large result, whose stores bound it and which the larger tile writes faster (11845 x 48 x 2066
 // 42 against 57, 16384 x 100 x 1000 44 / 58, 2^20 x 16 x 8 26 / 55), tall operands with few columns (65536 x 512 x 10 28 / 31)
 // and large products of two operands contiguous along k (4001^3 1082 / 1111; the other layouts 1201 / 1143 and
-// 1318 / 1152); and from the direct 128 x 128 kernel where an estimate of its time is 5 % lower than that kernel's.  Both
-// estimates, in microseconds, were fitted to 446 products of 64 to 4096 values of k in four layouts (within 7 %): rounds of 256
-// workgroups times steps, the launch, and for a split the second launch and the partial tiles' traffic.  The choice misses the
-// faster kernel by 2.6 % at most (direct / this: 512^3 16.8 / 10.5, 512 x 528 x 512 18.6 / 11.3, 256 x 2048 x 256 17.5 / 11.3, 1000 x 512 x 252
-// 16.8 / 10.6, 1024 x 784 x 512 22.3 / 18.2, 4096 x 784 x 512 39.0 / 34.3, with a bias and tanh 42.1 / 40.5; 768 x 1024 x 768 stays: 22.3 / 24.3, 512 x 4096 x 512
-// 27.5 / 28.9, 4096 x 512 x 784 37.2 / 42.7, 2048^3 129 / 151).
+// 1318 / 1152); and from the direct 128 x 128 kernel where an estimate of its time is lower than that kernel's.  Both
+// estimates, in microseconds: rounds of 256 workgroups times steps (fitted to 446 products of 64 to 4096 values of k in four layouts,
+// that of the direct kernel again to 36 when its arithmetic changed), the launch, and for a split the second launch and the partial tiles' traffic; without a
+// split the epilogue, which runs when the products are done (a second launch hides it behind its traffic): 4096 x 784 x 512 with a bias and
+// tanh 40.5 clamped, 35 direct in two parts.  (us, direct / this: 512^3 14.6 / 10.8, 1024 x 512 x 512 16.9 / 14.0, 224 x 192 x 1856 12.1 / 8.3,
+// 528 x 208 x 2320 14.1 / 14.2, 448 x 768 x 1456 22.2 / 22.4; stay: 368 x 2160 x 1296 26.1 / 32.5, 1296 x 3264 x 208 25.7 / 30.0, 3056 x 448 x 896 25.4 / 31.8,
+// 2048^3 113 / 151.  The choice missed the faster one of 36 products by 10 % at most, 4096 x 784 x 512 plain 34.9 / 38.7.)
 // `wanted`: splits of K that the larger tiles would take if they may store any number of partial tiles.  It decides
 // between the kernels, so that a request that must not allocate takes the kernel that the same request would take
 // otherwise (and that is loaded by then); g->slabs, which stays within its scratch array, bounds the splits.
@@ -807,9 +808,13 @@ void choose_gemm_tiles(GroupPlan* g, int wanted) {
     auto rounds = [](int64_t workgroups) { return (double)((workgroups + 255) / 256); };
     auto split = [&](double launch, double traffic, int n) { return n > 1 ? launch + traffic * (double)n * (double)M * (double)N * 8e-6 : 0.0; };
     const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128) * wanted;
-    const double direct = rounds(wgs) * (double)((gemm_split_extent(K, wanted) + 15) / 16) * (wgs <= 256 ? 0.93 : 0.86) + 4.3 + split(3.4, 0.18, wanted);
+    const double direct = rounds(wgs) * (double)((gemm_split_extent(K, wanted) + 15) / 16) * 0.75 + 4.5 + split(3.4, 0.18, wanted);
     const double clamped = rounds(tiles * ks) * (double)((gemm_split_extent(K, ks) + 31) / 32) * 0.56 + 4.0 + split(2.7, 0.22, ks);
-    if (clamped * 1.05 > direct) return;
+    double epilogue = 0.0;   // vector instructions per result, at 39 of a lane per picosecond
+    for (const Instr& in : g->prog)
+      if (in.kind == IKind::UNARY || in.kind == IKind::BINARY) epilogue += heavy_op(in) ? 40.0 : 1.0;
+    epilogue *= (double)M * (double)N / 3.9e7;
+    if (clamped + (ks > 1 ? 0.0 : epilogue) > direct + (wanted > 1 ? 0.0 : epilogue)) return;
   }
   g->VR = 3;
   g->UC = 1;
@@ -1318,33 +1323,32 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         g->VR = 2;   // (marks the kernels whose tiles go straight into LDS)
         g->UC = 1;
       } else if (direct && g->BX == 128 && g->M >= 128 && g->N >= 128 && c->opt_gemm_split == 0) {
-        // The same kernel with 128 x 128 tiles, up to three workgroups per compute unit, and K divided over `slabs`
+        // The same kernel with 128 x 128 tiles, one workgroup per compute unit, and K divided over `slabs`
         // workgroups per tile where that fills the compute units more evenly or at all.  The count is the one with the
-        // lowest cost in a model fitted to measurements (microseconds): rounds of 256 workgroups times the steps of one
-        // workgroup at 0.95 per step (1.1 where compute units hold a single workgroup, which has nobody to overlap its
-        // barriers with), plus, for a split product, 6 for the second launch and the traffic of the partial tiles at
+        // lowest cost in a model fitted to measurements (microseconds): rounds of 256 workgroups (one per compute unit) times the
+        // steps of one workgroup at 0.75 per step, plus, for a split product, 6 for the second launch and the traffic of the partial tiles at
         // 5 TB/s.  A larger count has to beat a smaller one by 3 %.  Every split holds at least 128 values of k, the last
         // one at least two steps; the partial tiles stay below 1 GiB (within the static scratch array for a request that must not
         // allocate).
-        // (measured, split chosen / one workgroup per tile / the kernel that stages through registers with its own
-        // split: 1024^3 30 / 68 / 38 us, 1536^3 77 / 98 / 90, 3072^3 442 / 525 / 598, 8192 x 256 x 8192 273 / 499 / 306,
-        // 1024 x 1024 x 8192 139 / 493 / 159, 512 x 512 x 16384 80 / 976 / 89)
+        // (measured, us: 784 x 4096 x 512 by 8 splits 35.7, by 9 34.3; 2080 x 2368 x 512 by 3 45; 512 x 4096 x 512 by 16 25.6;
+        // 3072^3 by 3 396, 442 with float32 instructions)
         const int64_t tiles128 = ((g->M + 127) / 128) * ((g->N + 127) / 128);
-        auto cheapest = [&](int64_t room) {   // room: floats of partial tiles
+        auto cheapest = [&](int64_t room, int least) {   // room: floats of partial tiles
           double best = 0;
           int best_ks = 0;
-          for (int ks = 1; ks <= 64; ++ks) {
+          for (int ks = least; ks <= 64; ++ks) {
             const int64_t kch = gemm_split_extent(g->K, ks);
             if (ks > 1 && (kch < 128 || g->K - (ks - 1) * kch < 32 || (int64_t)ks * g->M * g->N > room)) continue;
             const int64_t wgs = tiles128 * ks, rnd = (wgs + 255) / 256, steps = (kch + 15) / 16;
-            const double cost = (double)rnd * (double)steps * (wgs <= 256 ? 1.1 : 0.95) + (ks > 1 ? 6.0 + (double)ks * (double)g->M * (double)g->N * 8.0 / 5e6 : 0.0);
+            const double cost = (double)rnd * (double)steps * 0.75 + (ks > 1 ? 6.0 + (double)ks * (double)g->M * (double)g->N * 8.0 / 5e6 : 0.0);
             if (best_ks == 0 || cost < best * 0.97) { best = cost; best_ks = ks; }
           }
           return best_ks;
         };
-        wanted = cheapest((int64_t)1 << 28);
-        const int best_ks = c->plan_static ? cheapest((int64_t)(c->static_cap / sizeof(float))) : wanted;
-        g->slabs = best_ks;
+        wanted = cheapest((int64_t)1 << 28, 1);
+        // (a request that must not allocate splits as well where the same request otherwise does: the kernel has it compiled in)
+        const int best_ks = c->plan_static ? cheapest((int64_t)(c->static_cap / sizeof(float)), wanted > 1 ? 2 : 1) : wanted;
+        g->slabs = std::max(1, best_ks);
         g->VR = 2;
         g->UC = 1;
       } else if (direct && split_ok && g->BX == 128 && g->M >= 128 && g->N >= 128) {

@@ -452,3 +452,42 @@ def test_squared_deviations_of_values_that_are_not_finite_or_overflow(env):
         want = gr.var(x, 0).numpy()
         ctx.set_option("moments", 1)
         assert np.array_equal(got, want, equal_nan=True), rows
+
+
+# operands in three pieces: the smallest contraction, odd and even numbers of steps for the two groups of waves, edge tiles, several
+# workgroups per tile; and what the pieces cannot hold.  The bound: K roundings at most per sum, over the sum of magnitudes.
+@pytest.mark.parametrize("m,n,k", [(128, 128, 32), (128, 252, 48), (260, 128, 64), (300, 380, 80), (132, 248, 1040), (4096, 3584, 48)])
+@pytest.mark.parametrize("layout", ["nn", "tn", "nt", "tt"])
+def test_products_loaded_straight_into_lds(env, m, n, k, layout):
+    gr, ctx, torch = env
+    rng = np.random.default_rng(51)
+    a, b = rng.standard_normal((m, k)).astype(f32), rng.standard_normal((k, n)).astype(f32)
+    ctx.set_option("gemm_clamped", 0)
+    try:
+        for kind in ("ordinary", "infinities", "small", "denormal", "largest"):
+            x, y = a.copy(), b.copy()
+            if kind == "infinities":
+                x[m // 2, k // 2], y[k // 3, n // 3], y[0, n - 1] = np.inf, -np.inf, np.nan
+            elif kind == "small":
+                x *= f32(2.0 ** -118)          # products stay ordinary, last pieces do not
+                y *= f32(2.0 ** 110)
+            elif kind == "denormal":
+                x *= f32(2.0 ** -130)
+                x[::3] = 0
+                y *= f32(2.0 ** 120)
+            elif kind == "largest":
+                x[1, 2], y[2, 1] = np.finfo(f32).max, 0.0
+            ta, tb = (torch.from_numpy(np.ascontiguousarray(v.T if t == "t" else v)).cuda() for v, t in ((x, layout[0]), (y, layout[1])))
+            A, B = ctx.array(ta), ctx.array(tb)
+            out = (gr.transpose(A) if layout[0] == "t" else A) @ (gr.transpose(B) if layout[1] == "t" else B)
+            assert "direct" in out.plan()
+            got = out.numpy()
+            with np.errstate(all="ignore"):
+                want = x.astype(np.float64) @ y.astype(np.float64)
+                bound = (np.abs(x).astype(np.float64) @ np.abs(y).astype(np.float64)) * (k * 2.0 ** -24) + 2.0 ** -149 * k
+            fits = np.isfinite(want) & (np.abs(want) < 3e38)
+            assert (np.abs(got - want)[fits] <= bound[fits]).all(), kind
+            odd = ~np.isfinite(want)
+            assert np.array_equal(got[odd], want[odd].astype(f32), equal_nan=True), kind
+    finally:
+        ctx.set_option("gemm_clamped", 1)
