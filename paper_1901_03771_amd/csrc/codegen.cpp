@@ -2477,8 +2477,8 @@ void split_helpers(Em& e) {
 //   * Half-wave h takes k = 4 h .. 4 h + 3 and 8 + 4 h .. of a step for both operands, eight values per lane and block, which
 //     it splits into three pieces (split_helpers) and multiplies with six matrix instructions per pair of blocks.
 // Bound by vector issue (176 instructions per wave and step for the pieces of 128 x 64 x 16 products, 704 cycles) and the matrix
-// cores (768); measured against float32 matrix instructions with the same tiles and loads (us, before / now): 2048^3 143 / 113,
-// 4096 x 512 x 784 42 / 31, 784 x 4096 x 512 43 / 35, 1536^3 79 / 67, 512 x 2848 x 2352 74 / 54, 4096^3 932 / 697
+// cores (768); measured against float32 matrix instructions with the same tiles and loads (us, before / now): 2048^3 143 / 108,
+// 4096 x 512 x 784 42 / 31, 784 x 4096 x 512 43 / 35, 1536^3 79 / 64, 512 x 2848 x 2352 74 / 54, 3072^3 442 / 363, 4096^3 932 / 697
 // (197 TFLOP/s); relative error 4.1e-7 / 2.4e-7 (4096 x 512 x 784), 1.15e-6 / 1.0e-6 (4096^3).
 // The direct loads are written as assembly: the compiler's own form of them makes it wait for every outstanding
 // LDS read before each use (it counts them as LDS traffic that may return out of order).  Their completion is
@@ -2614,7 +2614,8 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
   if (two) {
     // Group g of four waves takes every second step from step g on, its tiles in a ring of its own.  Vector and matrix instructions
     // of one wave hardly overlap, those of two waves of a SIMD do: between two barriers group 0 splits a tile and
-    // multiplies it while group 1 multiplies the tile that it split before and splits the next.
+    // multiplies it while group 1 multiplies the tile that it split before and splits the next (2048^3, us: one group of four waves 133,
+    // two in step 120, these 110).
     o << "  const int n0 = (int)((nkt + 1) / 2), mine = (int)((nkt + 1 - group) / 2);\n";
     // (a group with one step less than the other repeats its last tile and leaves it out)
     auto fetch = [&](int role, const char* tile, const char* ind) {
@@ -2632,40 +2633,43 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
       for (int t = 0; t < 6; ++t) for (int i = 0; i < NB; ++i) for (int j = 0; j < NB; ++j) mfma(0, t, i, j, ind);
     };
     // (each group has loops of its own, with as many barriers: the compiler moves sums about where paths of a loop meet)
-    auto step = [&](int group, bool more, bool first, const char* ind) {
+    auto step = [&](bool more, const char* ind) {   // of group 0
       o << ind << "{\n";
       if (more) fetch(2, "t + 2", ind);
-      if (group == 1 && !first) {
-        products(ind);
-        o << ind << SB;
-      }
       split_tile(ind);
-      if (group == 0) {
-        o << ind << SB;
-        products(ind);
-      }
+      o << ind << SB;
+      products(ind);
       wait(more ? P : 0, ind);
       o << ind << rot_text << ind << "}\n";
+    };
+    auto late = [&](bool flying, bool more, bool sure, const char* ind) {   // of group 1: multiplies behind the barrier, with the next tile's loads before
+      o << ind << "{\n";
+      split_tile(ind);
+      wait(flying ? P : 0, ind);
+      o << ind << rot_text;
+      if (more) fetch(2, "t + 3", ind);
+      if (!sure) o << ind << "if (t < mine) {\n";
+      products(ind);
+      if (!sure) o << ind << "}\n";
+      o << ind << SB << ind << "}\n";
     };
     fetch(0, "0", "  ");
     o << "  if (n0 > 1) {\n";
     fetch(1, "1", "    ");
     o << "    __builtin_amdgcn_s_waitcnt(" << (0x0F70 | P) << ");\n  } else __builtin_amdgcn_s_waitcnt(" << 0x0F70 << ");\n  __builtin_amdgcn_s_barrier();\n  int t = 0;\n";
     o << "  if (group == 0) {\n    for (; t + 2 < n0; ++t)\n";
-    step(0, true, false, "    ");
+    step(true, "    ");
     o << "    for (; t < n0; ++t)\n";
-    step(0, false, false, "    ");
-    o << "  } else {\n    if (n0 > 2)\n";
-    step(1, true, true, "    ");
-    o << "    else\n";
-    step(1, false, true, "    ");
-    o << "    for (t = 1; t + 2 < n0; ++t)\n";
-    step(1, true, false, "    ");
-    o << "    for (; t < n0; ++t)\n";
-    step(1, false, false, "    ");
-    o << "    if (mine == n0) {\n";
-    products("    ");
-    o << "    }\n  }\n";
+    step(false, "    ");
+    o << "  } else {\n    if (n0 > 2) {\n";
+    fetch(2, "2", "      ");
+    o << "    }\n    for (; t + 3 < n0; ++t)\n";
+    late(true, true, true, "    ");
+    o << "    if (t + 2 < n0) {\n";
+    late(true, false, true, "    ");
+    o << "    ++t;\n    }\n    for (; t < n0; ++t)\n";
+    late(false, false, false, "    ");
+    o << "  }\n";
     // the groups add up their sums: each takes one row of blocks
     o << "  f16v own[2];\n"
          "  { f4* const area = (f4*)gr_lds + (wave * 8) * 64 + lane;   // 32 KiB per group: what it leaves to the other one\n"

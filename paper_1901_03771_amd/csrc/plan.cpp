@@ -768,7 +768,7 @@ static void choose_in_place(GroupPlan* g) {
 // split the epilogue, which runs when the products are done (a second launch hides it behind its traffic): 4096 x 784 x 512 with a bias and
 // tanh 40.5 clamped, 35 direct in two parts.  (us, direct / this: 512^3 14.6 / 10.8, 1024 x 512 x 512 16.9 / 14.0, 224 x 192 x 1856 12.1 / 8.3,
 // 528 x 208 x 2320 14.1 / 14.2, 448 x 768 x 1456 22.2 / 22.4; stay: 368 x 2160 x 1296 26.1 / 32.5, 1296 x 3264 x 208 25.7 / 30.0, 3056 x 448 x 896 25.4 / 31.8,
-// 2048^3 113 / 151.  The choice missed the faster one of 36 products by 10 % at most, 4096 x 784 x 512 plain 34.9 / 38.7.)
+// 2048^3 108 / 151.  The choice missed the faster one of 36 products by 10 % at most, 4096 x 784 x 512 plain 34.9 / 38.7.)
 // `wanted`: splits of K that the larger tiles would take if they may store any number of partial tiles.  It decides
 // between the kernels, so that a request that must not allocate takes the kernel that the same request would take
 // otherwise (and that is loaded by then); g->slabs, which stays within its scratch array, bounds the splits.
@@ -1331,7 +1331,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         // one at least two steps; the partial tiles stay below 1 GiB (within the static scratch array for a request that must not
         // allocate).
         // (measured, us: 784 x 4096 x 512 by 8 splits 35.7, by 9 34.3; 2080 x 2368 x 512 by 3 45; 512 x 4096 x 512 by 16 25.6;
-        // 3072^3 by 3 396, 442 with float32 instructions)
+        // 3072^3 by 2 363, 442 with float32 instructions)
         const int64_t tiles128 = ((g->M + 127) / 128) * ((g->N + 127) / 128);
         auto cheapest = [&](int64_t room, int least) {   // room: floats of partial tiles
           double best = 0;
