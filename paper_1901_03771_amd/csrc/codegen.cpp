@@ -2462,9 +2462,9 @@ void split_helpers(Em& e) {
 }
 
 // Matrix product of large operands, each contiguous along one of its dimensions (K a multiple of 16; M and N need
-// not be multiples of the tile: edge tiles load clamped rows and store only what exists): one workgroup per tile of the result
-// and compute unit, tiles of 256 x 256 (four waves with a 128 x 128 quarter each as 4 x 4 matrix-core blocks, 256
-// accumulator registers per lane) or 128 x 128 (two groups of four waves, 2 x 2 blocks each).
+// not be multiples of the tile: edge tiles load clamped rows and store only what exists): one workgroup per tile of the
+// result, tiles of 256 x 256 (four waves with a 128 x 128 quarter each as 4 x 4 matrix-core blocks, 256
+// accumulator registers per lane) or 128 x 128 (one or two groups of four waves, 2 x 2 blocks per wave).
 //   * Tiles of 16 values of k go from global memory straight into LDS (global_load_lds_dwordx4: lane L of a
 //     wave deposits its 16 bytes at M0 + 16 L, whatever address it loaded them from), two steps ahead, into a
 //     ring of three stages, so a step has one barrier, no staging registers and no LDS write instructions.
@@ -2501,7 +2501,7 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
   const char* RV = NB == 4 ? "f4" : "gr_f2";      // what a lane reads of a row-contiguous tile per k
   std::ostream& o = e.o;
   const bool split = g.slabs > 1;
-  const bool two = NB == 2;
+  const bool two = g.UC == 2;        // two groups of four waves
   o << "  __shared__ __attribute__((aligned(16))) float gr_lds[" << (two ? 6 : 3) * STAGE << "];\n"
        "  typedef __attribute__((address_space(3))) float lfloat;\n"
        "  typedef __attribute__((address_space(3))) f4 lf4;\n"
@@ -2692,8 +2692,8 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
          "#pragma unroll\n        for (int j = 0; j < 2; ++j) own[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va, pb[j][(k + lh) * bk], own[j], 0, 0, 0);\n      }\n";
     o << "    }\n  }\n";
   } else {
-    // 256 accumulators per lane leave no room for two sets of pieces: the right operand's are made first, a
-    // row of blocks of the left one's while the one before is multiplied.
+    // One group: the right operand's pieces first, then a row of blocks at a time the left one's and its products.  Workgroups on the
+    // same compute unit overlap; 256 accumulators per lane leave no room for more pieces (without the scheduling barriers they spill).
     auto step = [&](bool more2, const char* ind) {
       o << ind << "{\n";
       if (more2) {
@@ -2959,7 +2959,7 @@ void gen_gemm(Em& e) {
   if (g.VR == 2) {
     split_helpers(e);
   }
-  kernel_head(e, "gr_gemm", g.VR == 2 && g.BX == 128 ? 512 : 256);
+  kernel_head(e, "gr_gemm", g.VR == 2 && g.UC == 2 ? 512 : 256);
   e.o << "  const long long M = " << e.S(e.L.extra) << ", N = " << e.S(e.L.extra + 1) << ", K = " << e.S(e.L.extra + 2) << ";\n";
   group_pointers(e, "  ");
   e.o << "  const GM float* const A = q" << g.mat_group << "; const GM float* const B = q" << g.vec_group << ";\n";

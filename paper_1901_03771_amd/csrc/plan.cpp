@@ -1323,9 +1323,9 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         g->VR = 2;   // (marks the kernels whose tiles go straight into LDS)
         g->UC = 1;
       } else if (direct && g->BX == 128 && g->M >= 128 && g->N >= 128 && c->opt_gemm_split == 0) {
-        // The same kernel with 128 x 128 tiles, one workgroup per compute unit, and K divided over `slabs`
+        // The same kernel with 128 x 128 tiles and K divided over `slabs`
         // workgroups per tile where that fills the compute units more evenly or at all.  The count is the one with the
-        // lowest cost in a model fitted to measurements (microseconds): rounds of 256 workgroups (one per compute unit) times the
+        // lowest cost in a model fitted to measurements (microseconds): rounds of 256 workgroups times the
         // steps of one workgroup at 0.75 per step, plus, for a split product, 6 for the second launch and the traffic of the partial tiles at
         // 5 TB/s.  A larger count has to beat a smaller one by 3 %.  Every split holds at least 128 values of k, the last
         // one at least two steps; the partial tiles stay below 1 GiB (within the static scratch array for a request that must not
@@ -1358,6 +1358,12 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
       }
     }
     if (c->opt_gemm_bn == 0 && c->opt_gemm_kstep == 0 && c->opt_gemm_split == 0 && c->opt_gemm_big && c->opt_gemm_clamped) choose_gemm_tiles(g, wanted ? wanted : g->slabs);
+    // The direct kernel with 128 x 128 tiles (UC: groups of four waves in a workgroup): two groups divide a tile's steps where compute units have
+    // one workgroup each, one group where they hold several at a time, which overlap each other's loads, epilogues and arithmetic.
+    // (us, float32 instructions before / one group / two: 256 workgroups or fewer: 4096 x 512 x 784 37.2 / 36.7 / 29.6, 4096 x 512 x 1024 39.4 /
+    // 38.7 / 33.0, 2048 x 128 x 2048 with tanh 28.1 / 28.3 / 20.5; more: 12800 x 64 x 768 22.6 / 19.4 / 26.1, 6000 x 128 x 1500 32.7 / 26.6 / 33.9,
+    // 12800 x 256 x 768 57.6 / 44.4 / 50.7, 3000 x 512 x 2048 65.6 / 52.7 / 54.0, 5120 x 384 x 2560 98.9 / 82.2 / 86.8.)
+    if (g->VR == 2 && g->BX == 128) g->UC = ((g->M + 127) / 128) * ((g->N + 127) / 128) * (wanted ? wanted : g->slabs) <= 256 ? 2 : 1;
   } else if (dot && !(dot == r && dot_as_reduce(dot) && c->opt_fusion)) {
     // ---- contraction with pointwise epilogue ------------------------------
     g->kind = GroupKind::GEMV;

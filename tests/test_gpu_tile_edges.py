@@ -456,7 +456,7 @@ def test_squared_deviations_of_values_that_are_not_finite_or_overflow(env):
 
 # operands in three pieces: the smallest contraction, odd and even numbers of steps for the two groups of waves, edge tiles, several
 # workgroups per tile; and what the pieces cannot hold.  The bound: K roundings at most per sum, over the sum of magnitudes.
-@pytest.mark.parametrize("m,n,k", [(128, 128, 32), (128, 252, 48), (260, 128, 64), (300, 380, 80), (132, 248, 1040), (4096, 3584, 48)])
+@pytest.mark.parametrize("m,n,k", [(128, 128, 32), (128, 252, 48), (260, 128, 64), (300, 380, 80), (132, 248, 1040), (2100, 2300, 32), (2100, 2300, 48), (4096, 3584, 48)])
 @pytest.mark.parametrize("layout", ["nn", "tn", "nt", "tt"])
 def test_products_loaded_straight_into_lds(env, m, n, k, layout):
     gr, ctx, torch = env
