@@ -1309,7 +1309,7 @@ void reduce_columns_kernel(Em& e, bool wide, int U, const std::string& squares =
       auto v = [&](int u) { return "v" + std::to_string(u) + "_" + C; };
       e.o << "      {\n";
       std::function<std::string(int, int, bool)> sum = [&](int lo, int n, bool rel) { return n == 1 ? (rel ? "(" + v(lo) + " - pv" + C + ")" : v(lo)) : "(" + sum(lo, n / 2, rel) + " + " + sum(lo + n / 2, n - n / 2, rel) + ")"; };
-      e.o << "        const float m = " << sum(0, U, true) << " * " << 1.0 / U << "f, d = m - mu" << C << ", at = pv" << C << " + m;\n";
+      e.o << "        const float m = " << sum(0, U, true) << " * " << std::to_string(1.0 / U) << "f, d = m - mu" << C << ", at = pv" << C << " + m;\n";
       for (int u = 0; u < U; ++u) e.o << "        " << v(u) << " -= at; " << v(u) << " *= " << v(u) << ";\n";
       e.o << "        mu" << C << " = __builtin_fmaf(d, share, mu" << C << "); m2" << C << " += " << sum(0, U, false) << " + d * (rest * share) * d;\n      }\n";
     }

@@ -436,6 +436,33 @@ def test_columns_with_their_squared_deviations(env, shape, axis):
         assert (np.abs(both_used.numpy() - want) <= 60 * 2.0 ** -24 * (np.abs(full).max() / scale + np.abs(want))).all()
 
 
+@pytest.mark.parametrize("arrays", [9, 12])
+def test_columns_of_many_loads_with_their_squared_deviations(env, arrays):
+    # one row at a time: against two passes
+    gr, ctx, torch = env
+    rng = np.random.default_rng(42)
+    x = [ctx.array(torch.from_numpy(rng.random((1001, 130)).astype(f32)).cuda()) for _ in range(arrays)]
+
+    def squares():
+        def value():
+            v = x[0] * 1
+            for t in x[1:]:
+                v = v + t * 0.5
+            return v
+        return gr.sum(gr.square(value() - gr.sum(value(), 0, True) / 1001), 0)
+
+    one = squares()
+    assert "fused-with" in one.plan()
+    one = one.numpy()
+    ctx.set_option("moments", 0)
+    two = squares()
+    assert "fused-with" not in two.plan()
+    two = two.numpy()
+    ctx.set_option("moments", 1)
+    # (each within 60 roundings of the sum, as in test_columns_with_their_squared_deviations)
+    assert (np.abs(one - two) <= 2 * 60 * 2.0 ** -24 * np.abs(two)).all()
+
+
 def test_squared_deviations_of_values_that_are_not_finite_or_overflow(env):
     gr, ctx, torch = env
     for rows in (3, 1000):

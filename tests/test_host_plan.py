@@ -892,6 +892,38 @@ def test_column_sums_of_many_arrays_keep_to_registers(ctx, tmp_path, arrays):
     assert _registers(gr.sum(value, axis=0), tmp_path)[1] == 0
 
 
+@pytest.mark.parametrize("arrays", [1, 2, 3, 5, 6, 8, 9, 12])
+def test_columns_with_their_squared_deviations_compile_for_any_number_of_loads(ctx, tmp_path, arrays):
+    # eight, four, two rows at a time, or one (whose share of a batch is a whole number)
+    x = [ctx.spec((4096, 512)) for _ in range(arrays)]
+
+    def value():
+        v = gr.exp(x[0])
+        for t in x[1:]:
+            v = v + t * 0.5
+        return v
+
+    out = gr.sum(gr.square(value() - gr.sum(value(), 0, True) / 4096), 0)
+    assert "fused-with" in out.plan()
+    assert _registers(out, tmp_path)[1] == 0
+
+
+def test_columns_of_a_neighbourhood_with_their_squared_deviations_compile(ctx):
+    x = ctx.spec((1002, 514))
+
+    def mean():
+        v = x[:-2, :-2]
+        for i in range(3):
+            for j in range(3):
+                if i or j:
+                    v = v + x[i:1000 + i, j:512 + j]
+        return v / 9
+
+    out = gr.sum(gr.square(mean() - gr.sum(mean(), 0, True) / 1000), 0)
+    assert "fused-with" in out.plan()
+    out.compile()
+
+
 def _squares_to_one(t):
     return t / gr.sum(t * t, axis=-1, keepdims=True)
 
