@@ -1783,25 +1783,32 @@ static void fuse_gemv_pairs(gr_ctx* c, Plan* plan) {
   }
 }
 
-// Do instruction `a` of A's program and `b` of B's compute the same value?
-static bool same_value(const GroupPlan& A, int a, const GroupPlan& B, int b) {
+// Do instruction `a` of A's program and `b` of B's compute the same value?  `known`: pairs compared before (values used more than
+// once are reached over many paths, twice as many per level of a chain of squares).
+static bool same_value(const GroupPlan& A, int a, const GroupPlan& B, int b, std::map<std::pair<int, int>, bool>* known) {
   if (a < 0 || b < 0) return a == b;
+  const auto at = known->find({a, b});
+  if (at != known->end()) return at->second;
   const Instr& x = A.prog[a];
   const Instr& y = B.prog[b];
-  if (x.kind != y.kind || x.op != y.op || x.dtype != y.dtype) return false;
-  if (x.kind == IKind::LOAD) {
+  bool same = x.kind == y.kind && x.op == y.op && x.dtype == y.dtype;
+  if (same && x.kind == IKind::LOAD) {
     const AccessGroup& p = A.groups[x.group];
     const AccessGroup& q = B.groups[y.group];
     int64_t off = p.base - q.base;
-    if (p.leaf != q.leaf) return false;
-    for (int k = 0; k < A.rank; ++k) {
-      if (p.coef[k] != q.coef[k]) return false;
+    same = p.leaf == q.leaf;
+    for (int k = 0; same && k < A.rank; ++k) {
+      same = p.coef[k] == q.coef[k];
       off += p.coef[k] * (x.delta[k] - y.delta[k]);
     }
-    return off == 0;
+    same = same && off == 0;
+  } else if (same && x.kind == IKind::CONST) {
+    same = std::memcmp(&A.consts[x.cslot].value, &B.consts[y.cslot].value, sizeof(double)) == 0;
+  } else if (same) {
+    same = same_value(A, x.a, B, y.a, known) && same_value(A, x.b, B, y.b, known);
   }
-  if (x.kind == IKind::CONST) return A.consts[x.cslot].value == B.consts[y.cslot].value;
-  return same_value(A, x.a, B, y.a) && same_value(A, x.b, B, y.b);
+  (*known)[{a, b}] = same;
+  return same;
 }
 
 // Column sums S of v whose mean is what the next sub-graph takes v's squared deviations from (var, std and what divides by
@@ -1843,7 +1850,8 @@ static void fuse_moments(gr_ctx* c, Plan* plan) {
       own = own && (sg.coef[k] == st || A.dims[k] == 1);
       st *= A.dims[k];
     }
-    if (!own || at != 0 || !same_value(A, pa.value, B, B.prog[d].a)) continue;
+    std::map<std::pair<int, int>, bool> known;
+    if (!own || at != 0 || !same_value(A, pa.value, B, B.prog[d].a, &known)) continue;
     A.pair = std::move(plan->groups[i + 1]);
     plan->groups.erase(plan->groups.begin() + i + 1);
     make_signature(&A);

@@ -10,6 +10,7 @@ import re
 import shutil
 import subprocess
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -922,6 +923,29 @@ def test_columns_of_a_neighbourhood_with_their_squared_deviations_compile(ctx):
     out = gr.sum(gr.square(mean() - gr.sum(mean(), 0, True) / 1000), 0)
     assert "fused-with" in out.plan()
     out.compile()
+
+
+@pytest.mark.parametrize("depth", [26, 40, 300])
+def test_planning_squared_deviations_of_a_value_shared_at_every_level(ctx, depth):
+    # 2^depth paths lead through the value, which is compared with its second recording (28 levels took 7 seconds once)
+    if depth > 26:
+        test_planning_squared_deviations_of_a_value_shared_at_every_level(ctx, 26)
+    x = ctx.spec((4096, 512))
+
+    def value():
+        y = x
+        for k in range(depth):
+            y = (y + 0.125 * k) * y
+        return y
+
+    out = gr.sum(gr.square(value() - gr.sum(value(), 0, True) / 4096), 0)
+    start = time.perf_counter()
+    plan = out.plan()
+    assert time.perf_counter() - start < 0.5
+    assert "fused-with" in plan
+    # one operation of the second recording differs: two passes
+    other = gr.sum(gr.square((x + value()) - gr.sum((x - value()), 0, True) / 4096), 0)
+    assert "fused-with" not in other.plan()
 
 
 def _squares_to_one(t):
