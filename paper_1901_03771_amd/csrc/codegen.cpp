@@ -1140,18 +1140,19 @@ void reduce_combine(Em& e, const std::string& squares = "") {
            "      float a[8] = {0, 0, 0, 0, 0, 0, 0, 0};\n"
            "      for (long long s = 0; s < NSPLIT; s += 8)\n"
            "#pragma unroll\n        for (int i = 0; i < 8; ++i) { const bool in = s + i < NSPLIT; const long long p = in ? s + i : 0; const float w = count(p) * wu[p * NOUT + o]; a[i] += in ? w : 0.0f; }\n"
-           "      const float t = (((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]))) / (float)LEN;\n"
+           "      float t = (((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]))) / (float)LEN;\n"
+           "      const float over = gr_overflow(t);\n"
            "#pragma unroll\n      for (int i = 0; i < 8; ++i) a[i] = 0.0f;\n"
            "      for (long long s = 0; s < NSPLIT; s += 8)\n"
            "#pragma unroll\n        for (int i = 0; i < 8; ++i) { const bool in = s + i < NSPLIT; const long long p = in ? s + i : 0; const float d = wu[p * NOUT + o] - t, w = wm[p * NOUT + o] + count(p) * d * d; a[i] += in ? w : 0.0f; }\n"
-           "      sq[o] = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));\n    }\n  } else {\n"
+           "      sq[o] = (((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]))) + over;\n    }\n  } else {\n"
            "    const long long o = blockIdx.x;\n    float* const sm = (float*)gr_sm;\n    float t = 0.0f, m = 0.0f;\n"
            "    for (long long s = threadIdx.x; s < NSPLIT; s += 256) t += count(s) * wu[s * NOUT + o];\n"
            "    t = gr_lanes0(t);\n    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = t;\n    __syncthreads();\n"
-           "    t = ((sm[0] + sm[1]) + (sm[2] + sm[3])) / (float)LEN;\n    __syncthreads();\n"
+           "    t = ((sm[0] + sm[1]) + (sm[2] + sm[3])) / (float)LEN;\n    __syncthreads();\n    const float over = gr_overflow(t);\n"
            "    for (long long s = threadIdx.x; s < NSPLIT; s += 256) { const float d = wu[s * NOUT + o] - t; m += wm[s * NOUT + o] + count(s) * d * d; }\n"
            "    m = gr_lanes0(m);\n    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;\n    __syncthreads();\n"
-           "    if (threadIdx.x == 0) sq[o] = (sm[0] + sm[1]) + (sm[2] + sm[3]);\n    __syncthreads();\n  }\n";
+           "    if (threadIdx.x == 0) sq[o] = ((sm[0] + sm[1]) + (sm[2] + sm[3])) + over;\n    __syncthreads();\n  }\n";
   e.o << "  if (NOUT >= 1024) {\n"
          "    const long long o = (long long)blockIdx.x * 256 + threadIdx.x;\n"
          "    if (o < NOUT) {\n      " << T << " acc = ws[o];\n"
@@ -1185,6 +1186,8 @@ void reduce_combine(Em& e, const std::string& squares = "") {
 // far the mean is from zero, because means are relative to the median of three of the column's values (no outlier) and a
 // value is subtracted from once, as in the second of two passes.  Partial results of
 // lanes and of splits are joined the same way, all at once about their common mean.
+// Means stay finite: values so far apart that a difference of means overflows (or a sum of them below) have infinite squares, and a
+// batch that holds a value that is not finite has squares that are not a number; neither enters the mean.
 void reduce_columns_kernel(Em& e, bool wide, int U, const std::string& squares = "") {
   const bool moments = !squares.empty();
   const GroupPlan& g = e.g;
@@ -1304,15 +1307,31 @@ void reduce_columns_kernel(Em& e, bool wide, int U, const std::string& squares =
   } else if (moments) {
     for (int u = 0; u < U; ++u) { values(u); join(to, u); }
     e.o << "      count += " << U << ".0f;\n      const float share = " << U << ".0f / count, rest = count - " << U << ".0f;\n";
-    for (int c = 0; c < W; ++c) {
+    auto v = [](int u, int c) { return "v" + std::to_string(u) + "_" + std::to_string(c); };
+    std::function<std::string(int, int, int, bool)> sum = [&](int c, int lo, int n, bool rel) {
+      if (n == 1) return rel ? "(" + v(lo, c) + " - pv" + std::to_string(c) + ")" : v(lo, c);
+      return "(" + sum(c, lo, n / 2, rel) + " + " + sum(c, lo + n / 2, n - n / 2, rel) + ")";
+    };
+    auto join_batch = [&](int c) {
       const std::string C = std::to_string(c);
-      auto v = [&](int u) { return "v" + std::to_string(u) + "_" + C; };
-      e.o << "      {\n";
-      std::function<std::string(int, int, bool)> sum = [&](int lo, int n, bool rel) { return n == 1 ? (rel ? "(" + v(lo) + " - pv" + C + ")" : v(lo)) : "(" + sum(lo, n / 2, rel) + " + " + sum(lo + n / 2, n - n / 2, rel) + ")"; };
-      e.o << "        const float m = " << sum(0, U, true) << " * " << std::to_string(1.0 / U) << "f, d = m - mu" << C << ", at = pv" << C << " + m;\n";
-      for (int u = 0; u < U; ++u) e.o << "        " << v(u) << " -= at; " << v(u) << " *= " << v(u) << ";\n";
-      e.o << "        mu" << C << " = __builtin_fmaf(d, share, mu" << C << "); m2" << C << " += " << sum(0, U, false) << " + d * (rest * share) * d;\n      }\n";
+      e.o << "        { const float at = pv" << C << " + m" << C << ";\n";
+      for (int u = 0; u < U; ++u) e.o << "        " << v(u, c) << " -= at; " << v(u, c) << " *= " << v(u, c) << ";\n";
+      e.o << "        mu" << C << " = __builtin_fmaf(d" << C << ", share, mu" << C << "); m2" << C << " += " << sum(c, 0, U, false) << " + d" << C << " * (rest * share) * d" << C << "; }\n";
+    };
+    for (int c = 0; c < W; ++c) e.o << "      const float m" << c << " = " << sum(c, 0, U, true) << " * " << std::to_string(1.0 / U) << "f, d" << c << " = m" << c << " - mu" << c << ";\n";
+    e.o << "      if (";
+    for (int c = 0; c < W; ++c) e.o << (c ? " & " : "") << "(__builtin_fabsf(d" << c << ") < __builtin_inff())";
+    e.o << ") {\n";   // (one branch for all columns: the compiler interleaves their arithmetic)
+    for (int c = 0; c < W; ++c) join_batch(c);
+    e.o << "      } else {\n";
+    for (int c = 0; c < W; ++c) {
+      e.o << "        if (__builtin_fabsf(d" << c << ") < __builtin_inff())\n";
+      join_batch(c);
+      e.o << "        else m2" << c << " += ";
+      for (int u = 0; u < U; ++u) e.o << (u ? " && " : "") << "__builtin_fabsf(" << v(u, c) << ") < __builtin_inff()";
+      e.o << " ? __builtin_inff() : __builtin_nanf(\"\");\n";
     }
+    e.o << "      }\n";
   } else
     for (int u = 0; u < U; ++u) { e.o << "      {\n"; values(u); join(to, u); e.o << "      }\n"; }
   e.o << "    }\n";
@@ -1330,7 +1349,19 @@ void reduce_columns_kernel(Em& e, bool wide, int U, const std::string& squares =
       join("acc", u);
       if (moments) {
         e.o << "      count += 1.0f;\n      const float share = 1.0f / count;\n";
-        for (int c = 0; c < W; ++c) e.o << "      { const float d = v" << u << "_" << c << " - pv" << c << " - mu" << c << "; mu" << c << " = __builtin_fmaf(d, share, mu" << c << "); m2" << c << " += d * ((count - 1.0f) * share) * d; }\n";
+        auto join_one = [&](int c) { e.o << "        { mu" << c << " = __builtin_fmaf(d" << c << ", share, mu" << c << "); m2" << c << " += d" << c << " * ((count - 1.0f) * share) * d" << c << "; }\n"; };
+        for (int c = 0; c < W; ++c) e.o << "      const float d" << c << " = v" << u << "_" << c << " - pv" << c << " - mu" << c << ";\n";
+        e.o << "      if (";
+        for (int c = 0; c < W; ++c) e.o << (c ? " & " : "") << "(__builtin_fabsf(d" << c << ") < __builtin_inff())";
+        e.o << ") {\n";
+        for (int c = 0; c < W; ++c) join_one(c);
+        e.o << "      } else {\n";
+        for (int c = 0; c < W; ++c) {
+          e.o << "        if (__builtin_fabsf(d" << c << ") < __builtin_inff())\n";
+          join_one(c);
+          e.o << "        else m2" << c << " += __builtin_fabsf(v" << u << "_" << c << ") < __builtin_inff() ? __builtin_inff() : __builtin_nanf(\"\");\n";
+        }
+        e.o << "      }\n";
       }
       e.o << "      }\n";
     }
@@ -1350,11 +1381,11 @@ void reduce_columns_kernel(Em& e, bool wide, int U, const std::string& squares =
            "      n = 0.0f;\n      float a[8] = {0, 0, 0, 0, 0, 0, 0, 0};\n"   // (eight chains: no long one)
            "      for (unsigned q = first; q < end; q += 8 * step)\n"
            "#pragma unroll\n        for (int i = 0; i < 8; ++i) { const bool in = q + i * step < end; const unsigned at = (in ? q + i * step : first) * BX + tx; const float k = in ? sn[at] : 0.0f, w = su[c][at]; n += k; a[i] += in ? k * w : 0.0f; }\n"
-           "      u = n > 0.0f ? (((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]))) / n : 0.0f;\n"
+           "      u = n > 0.0f ? (((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]))) / n : 0.0f;\n      const float over = gr_overflow(u);\n"
            "#pragma unroll\n      for (int i = 0; i < 8; ++i) a[i] = 0.0f;\n"
            "      for (unsigned q = first; q < end; q += 8 * step)\n"
            "#pragma unroll\n        for (int i = 0; i < 8; ++i) { const bool in = q + i * step < end; const unsigned at = (in ? q + i * step : first) * BX + tx; const float d = su[c][at] - u, w = sq[c][at] + sn[at] * d * d; a[i] += in ? w : 0.0f; }\n"
-           "      m = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));\n    };\n"
+           "      m = (((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]))) + over;\n    };\n"
            // (lanes past the rows of a short range have nothing; many lanes meet in groups first, a lane per group and column)
            "    const unsigned have = jend - jbeg < BY ? (unsigned)(jend > jbeg ? jend - jbeg : 0) : BY;\n"
            "    unsigned nl = have;\n"
@@ -1420,9 +1451,12 @@ void gen_reduce_columns(Em& e, const std::string& squares) {
   // whose registers would halve the wavefronts of the former (3 x 2^22 14.7 us from one kernel with both, 13.3).
   // (registers for what a batch loads, of the 256 that 512 lanes leave each: 223 for five arrays by four, 204 for eight by two;
   // twelve by four spilled 1 KiB per lane)
-  // (squares about a mean as the second of two passes gives them where differences from the first value or the sum overflow)
+  // Squares about a mean as the second of two passes gives them: about a mean that is not a number, not a number; about an infinite
+  // one (the sum overflows, or a value is infinite), infinite for finite values.  gr_overflow: what a mean of means adds to
+  // the squares, and zero in its place where it overflows, which only values with infinite squares can make it do.
   if (!squares.empty())
-    e.o << "static __device__ __forceinline__ float gr_squares(float s, float m) { const bool f = __builtin_fabsf(s) < __builtin_inff(); return (f ? m != m : m == m && s == s) ? __builtin_inff() : m; }\n";
+    e.o << "static __device__ __forceinline__ float gr_squares(float s, float m) { return __builtin_fabsf(s) < __builtin_inff() ? m : (s != s ? s : (m == m ? __builtin_inff() : m)); }\n"
+           "static __device__ __forceinline__ float gr_overflow(float& mean) { if (__builtin_fabsf(mean) < __builtin_inff()) return 0.0f; mean = 0.0f; return __builtin_inff(); }\n";
   const int most = n_loads <= 5 ? 4 : (n_loads <= 8 ? 2 : 1);
   reduce_columns_kernel(e, false, n_loads <= 2 && g.prog.size() <= 12 ? 8 : most, squares);
   if (squares.empty()) reduce_columns_kernel(e, true, most);

@@ -465,20 +465,31 @@ def test_columns_of_many_loads_with_their_squared_deviations(env, arrays):
 
 def test_squared_deviations_of_values_that_are_not_finite_or_overflow(env):
     gr, ctx, torch = env
-    for rows in (3, 1000):
-        a = np.ones((rows, 9), f32)
+    for rows, cols in ((3, 9), (4, 13), (5, 2), (64, 13), (1000, 13), (1001, 3), (70001, 13), (300, 2050)):
+        a = np.ones((rows, max(cols, 13)), f32)
         a[1, 0], a[2, 1], a[0, 2] = np.inf, np.nan, -np.inf
         a[:, 3] = 1e38                                # the sum overflows, the values are equal
         a[::2, 4], a[1::2, 4] = 3e38, -3e38           # differences overflow
         a[0, 5] = 0.0
         a[1:, 5] = 1e25                               # squares overflow
+        a[:, 6], a[rows - 1, 6] = 3e38, -3e38         # the sum overflows, and differences do
+        a[:, 7], a[1, 7] = -3e38, 3e38
+        a[:, 8], a[rows // 2:, 8] = 3e38, -3e38       # parts of the sum are infinite, of either sign
+        a[:, 9], a[1, 9], a[2, 9] = 3e38, -3e38, np.inf
+        a[:, 10], a[0, 10], a[1, 10] = 2e38, -np.inf, -2e38
+        a[:, 11], a[rows - 1, 11] = 1e37, -1e37
+        a[:, 12], a[0, 12], a[rows - 1, 12], a[rows // 2, 12] = 3e38, np.inf, np.inf, np.inf
+        if cols < 13:
+            a = np.ascontiguousarray(np.roll(a, -6, 1)[:, :cols])
+        else:
+            a = np.tile(a, (1, cols // 13 + 1))[:, :cols].copy()
         t = torch.from_numpy(a).cuda()
         x = ctx.array(t)
         got = gr.var(x, 0).numpy()
         ctx.set_option("moments", 0)
         want = gr.var(x, 0).numpy()
         ctx.set_option("moments", 1)
-        assert np.array_equal(got, want, equal_nan=True), rows
+        assert np.array_equal(got, want, equal_nan=True), (rows, cols, got[:13], want[:13])
 
 
 # operands in three pieces: the smallest contraction, odd and even numbers of steps for the two groups of waves, edge tiles, several
