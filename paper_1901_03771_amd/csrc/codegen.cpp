@@ -2473,9 +2473,13 @@ void gemm_combine(Em& e, const EpiLoad& epi_load);
 // their instructions (the three terms below 2^-23 of a product, of either sign, are left out), takes 3/8 of the time, and its sum is
 // rounded six times per sixteen values of k where float32 instructions round eight times (32 x 32 blocks, relative error against
 // 64 bits of float32 instructions / these: normal values, K = 784 4.7e-7 / 4.0e-7, 16384 2.2e-6 / 2.1e-6; uniform ones 4.1e-7 / 2.9e-7).
-// What the pieces cannot hold is noticed, and the tile is computed again in float32 instructions (gemm_big_body): infinities leave a
-// not-finite sum, and of a value whose last piece would reach below the smallest denormal bfloat16 (a nonzero value
-// below 2^-110 can be one) the low half of that piece, which is zero otherwise, is collected in `low`.
+// What the pieces cannot hold is noticed as they are made, and the wave multiplies these sixteen values of k with float32 instructions
+// (gemm_big_body): of a value whose last piece would reach below the smallest denormal bfloat16 (a nonzero value below 2^-110 can
+// be one) the low half of that piece, which is zero otherwise, is collected in `low`; of infinities, and of values whose products with
+// one another could overflow piece by piece with other signs than their own, `big` keeps the largest magnitude (2^62 and more: gr_odd).
+// (What is not a number is one in all of its products either way.)
+// (us with 1e-35 at every 41st position of every 37th row, the wave's whole share of K again at the end, from global memory / change to a
+// loop of float32 instructions where it is met / without such values: 2048^3 457 / 145 / 104, 4096 x 512 x 784 119 / 40 / 31, 4096^3 9890 / 1045 / 712.)
 // The splitting competes with the matrix instructions: about 6 vector instructions per value.  They overlap with other waves' matrix
 // instructions; the two-term dot product instruction, which could take off a piece without unpacking it, does not (one wave with matrix
 // instructions beside one with as many cycles of these: their sum; of the others a fifth more than the longer of the two).
@@ -2484,7 +2488,7 @@ void split_helpers(Em& e) {
          "typedef __bf16 gr_b8 __attribute__((ext_vector_type(8)));\n"
          "typedef float gr_p2 __attribute__((ext_vector_type(2)));\n"
          "typedef unsigned gr_u4 __attribute__((ext_vector_type(4)));\n"
-         "static __device__ __forceinline__ void gr_split2(float x0, float x1, unsigned& h, unsigned& m, unsigned& l, unsigned& low) {\n"
+         "static __device__ __forceinline__ void gr_split2(float x0, float x1, unsigned& h, unsigned& m, unsigned& l, unsigned& low, float& big) {\n"
          "  const unsigned u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);\n"
          "  const float r0 = x0 - __uint_as_float(u0 & 0xffff0000u), r1 = x1 - __uint_as_float(u1 & 0xffff0000u);\n"
          "  h = __builtin_amdgcn_perm(u1, u0, 0x07060302u);\n"
@@ -2492,7 +2496,9 @@ void split_helpers(Em& e) {
          "  const unsigned l0 = __float_as_uint(r0 - __uint_as_float(m << 16)), l1 = __float_as_uint(r1 - __uint_as_float(m & 0xffff0000u));\n"
          "  l = __builtin_amdgcn_perm(l1, l0, 0x07060302u);\n"
          // (in place: left to the compiler, the collecting is put off and the pieces are kept in scratch memory for it)
-         "  asm(\"v_or3_b32 %0, %0, %1, %2\" : \"+v\"(low) : \"v\"(l0), \"v\"(l1));\n}\n";
+         "  asm(\"v_or3_b32 %0, %0, %1, %2\" : \"+v\"(low) : \"v\"(l0), \"v\"(l1));\n"
+         "  asm(\"v_max3_f32 %0, |%1|, |%2|, %0\" : \"+v\"(big) : \"v\"(x0), \"v\"(x1));\n}\n"
+         "static __device__ __forceinline__ bool gr_odd(unsigned low, float big) { return __builtin_amdgcn_ballot_w64((low & 0xffffu) != 0u || big >= 0x1p62f) != 0ull; }\n";
 }
 
 // Matrix product of large operands, each contiguous along one of its dimensions (K a multiple of 16; M and N need
@@ -2635,7 +2641,7 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
   };
   auto pieces_of = [&](const Op& x, int set, int blk, int p, const char* ind) {
     const std::string n = x.n, to = n + "s" + std::to_string(set) + "[" + std::to_string(blk) + "]";
-    o << ind << "{ unsigned h, m, l; gr_split2(" << n << "r[" << blk << "][" << 2 * p << "], " << n << "r[" << blk << "][" << 2 * p + 1 << "], h, m, l, low); " << to << "[0][" << p << "] = h; " << to << "[1][" << p << "] = m; " << to << "[2][" << p << "] = l; }\n";
+    o << ind << "{ unsigned h, m, l; gr_split2(" << n << "r[" << blk << "][" << 2 * p << "], " << n << "r[" << blk << "][" << 2 * p + 1 << "], h, m, l, low, big); " << to << "[0][" << p << "] = h; " << to << "[1][" << p << "] = m; " << to << "[2][" << p << "] = l; }\n";
   };
   static const int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
   auto mfma = [&](int set, int t, int i, int j, const char* ind) {
@@ -2643,114 +2649,95 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
   };
   const char* SB = "__builtin_amdgcn_sched_barrier(0);\n";
   for (const Op& x : ops) o << "  gr_u4 " << x.n << "s0[" << NB << "][3];\n";
-  o << "  unsigned low = 0u;\n";
-  auto wait = [&](int left, const char* ind) { o << ind << "__builtin_amdgcn_s_waitcnt(" << (0x0070 | left) << ");\n" << ind << "__builtin_amdgcn_s_barrier();\n"; };
+  const char* NONE_ODD = "unsigned low = 0u; float big = 0.0f;\n";
+  // blocks [i0, i1) x [j0, j1) of the tile in role 0 with float32 instructions, from LDS again (the values are not kept for it)
+  auto exact = [&](int i0, int i1, int j0, int j1, const char* ind) {
+    o << ind << "{ __atomic_signal_fence(__ATOMIC_SEQ_CST);\n" << ind << "float ar[" << NB << "][8], br[" << NB << "][8];\n";
+    for (const Op& x : ops)
+      for (int b = &x == ops ? i0 : j0; b < (&x == ops ? i1 : j1); ++b) {
+        if (x.kc) raw(x, 0, b, ind);
+        else for (int v = 0; v < 8; ++v) o << ind << x.n << "r[" << b << "][" << v << "] = " << x.n << "p[0][" << rc_row(8 * (v >> 2) + (v & 3)) + b << "];\n";
+      }
+    for (int v = 0; v < 8; ++v) for (int i = i0; i < i1; ++i) for (int j = j0; j < j1; ++j)
+      o << ind << "acc[" << i << "][" << j << "] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[" << i << "][" << v << "], br[" << j << "][" << v << "], acc[" << i << "][" << j << "], 0, 0, 0);\n";
+    o << ind << "}\n";
+  };
   if (two) {
     // Group g of four waves takes every second step from step g on, its tiles in a ring of its own.  Vector and matrix instructions
     // of one wave hardly overlap, those of two waves of a SIMD do: between two barriers group 0 splits a tile and
     // multiplies it while group 1 multiplies the tile that it split before and splits the next (2048^3, us: one group of four waves 133,
     // two in step 120, these 110).
     o << "  const int n0 = (int)((nkt + 1) / 2), mine = (int)((nkt + 1 - group) / 2);\n";
-    // (a group with one step less than the other repeats its last tile and leaves it out)
     auto fetch = [&](int role, const char* tile, const char* ind) {
+      o << ind << "if (" << tile << " < mine) {\n";
       for (int p = 0; p < P; ++p) piece(role, p, ind);
-      o << ind << "if (" << tile << " + 1 < mine) { " << "abase += astep; bbase += bstep; }\n";
+      o << ind << ADV << ind << "}\n";
     };
     auto split_tile = [&](const char* ind) {
+      o << ind << NONE_ODD;
       for (const Op& x : ops) {
         o << ind << "float " << x.n << "r[" << NB << "][8];\n";
         raw_all(x, 0, ind);
       }
       for (const Op& x : ops) for (int blk = 0; blk < NB; ++blk) for (int p = 0; p < 4; ++p) pieces_of(x, 0, blk, p, ind);
+      o << ind << "if (gr_odd(low, big)) break;\n" << ind << SB;
     };
     auto products = [&](const char* ind) {
       for (int t = 0; t < 6; ++t) for (int i = 0; i < NB; ++i) for (int j = 0; j < NB; ++j) mfma(0, t, i, j, ind);
-    };
-    // (each group has loops of its own, with as many barriers: the compiler moves sums about where paths of a loop meet)
-    auto step = [&](bool more, const char* ind) {   // of group 0
-      o << ind << "{\n";
-      if (more) fetch(2, "t + 2", ind);
-      split_tile(ind);
       o << ind << SB;
-      products(ind);
-      wait(more ? P : 0, ind);
-      o << ind << rot_text << ind << "}\n";
     };
-    auto late = [&](bool flying, bool more, bool sure, const char* ind) {   // of group 1: multiplies behind the barrier, with the next tile's loads before
-      o << ind << "{\n";
-      split_tile(ind);
-      wait(flying ? P : 0, ind);
-      o << ind << rot_text;
-      if (more) fetch(2, "t + 3", ind);
-      if (!sure) o << ind << "if (t < mine) {\n";
-      products(ind);
-      if (!sure) o << ind << "}\n";
-      o << ind << SB << ind << "}\n";
+    auto advance = [&](const char* ind) {   // the next tile has landed, all of this one's reads are done
+      o << ind << "if (t + 2 < mine) __builtin_amdgcn_s_waitcnt(" << (0x0070 | P) << "); else __builtin_amdgcn_s_waitcnt(" << 0x0070 << ");\n" << ind << "__builtin_amdgcn_s_barrier();\n" << ind << rot_text;
     };
+    // (each group, and a wave that meets a value the pieces cannot hold for what is left of its steps, has a loop of its own, with as many
+    // barriers: where two ways to the same sums meet within a step, the compiler moves them about)
     fetch(0, "0", "  ");
-    o << "  if (n0 > 1) {\n";
-    fetch(1, "1", "    ");
-    o << "    __builtin_amdgcn_s_waitcnt(" << (0x0F70 | P) << ");\n  } else __builtin_amdgcn_s_waitcnt(" << 0x0F70 << ");\n  __builtin_amdgcn_s_barrier();\n  int t = 0;\n";
-    o << "  if (group == 0) {\n    for (; t + 2 < n0; ++t)\n";
-    step(true, "    ");
-    o << "    for (; t < n0; ++t)\n";
-    step(false, "    ");
-    o << "  } else {\n    if (n0 > 2) {\n";
-    fetch(2, "2", "      ");
-    o << "    }\n    for (; t + 3 < n0; ++t)\n";
-    late(true, true, true, "    ");
-    o << "    if (t + 2 < n0) {\n";
-    late(true, false, true, "    ");
-    o << "    ++t;\n    }\n    for (; t < n0; ++t)\n";
-    late(false, false, false, "    ");
-    o << "  }\n";
+    fetch(1, "1", "  ");
+    o << "  if (mine > 1) __builtin_amdgcn_s_waitcnt(" << (0x0F70 | P) << "); else __builtin_amdgcn_s_waitcnt(" << 0x0F70 << ");\n  __builtin_amdgcn_s_barrier();\n  int t = 0;\n"
+         "  if (group == 0) {\n    for (; t < mine; ++t) {\n";
+    const char* ind = "      ";
+    fetch(2, "t + 2", ind);
+    split_tile(ind);
+    products(ind);
+    advance(ind);
+    o << "    }\n    while (t < mine) {\n";
+    exact(0, NB, 0, NB, ind);
+    advance(ind);
+    o << ind << "++t;\n";
+    fetch(2, "t + 2", ind);
+    o << "    }\n  } else {\n";
+    fetch(2, "2", "    ");
+    o << "    for (; t < mine; ++t) {\n";
+    split_tile(ind);
+    advance(ind);
+    fetch(2, "t + 3", ind);
+    products(ind);
+    o << "    }\n    while (t < mine) {\n";
+    exact(0, NB, 0, NB, ind);
+    advance(ind);
+    fetch(2, "t + 3", ind);
+    o << ind << "++t;\n    }\n"
+         "    if (mine < n0) __builtin_amdgcn_s_barrier();\n  }\n";
     // the groups add up their sums: each takes one row of blocks
     o << "  f16v own[2];\n"
          "  { f4* const area = (f4*)gr_lds + (wave * 8) * 64 + lane;   // 32 KiB per group: what it leaves to the other one\n"
-         "    unsigned* const flags = (unsigned*)gr_lds + 16384;\n"
-         "    bool odd = (low & 0xffffu) != 0u;\n"
          "#pragma unroll\n    for (int j = 0; j < 2; ++j)\n#pragma unroll\n      for (int q = 0; q < 16; ++q) { const float a = acc[0][j][q], b = acc[1][j][q]; own[j][q] = group ? b : a; acc[0][j][q] = group ? a : b; }\n"
          "#pragma unroll\n    for (int j = 0; j < 2; ++j)\n#pragma unroll\n      for (int q = 0; q < 4; ++q) area[group * 2048 + (j * 4 + q) * 64] = f4{acc[0][j][4 * q], acc[0][j][4 * q + 1], acc[0][j][4 * q + 2], acc[0][j][4 * q + 3]};\n"
-         "    if (lane == 0) flags[group * 4 + wave] = 0u;\n"
-         "    if (odd) flags[group * 4 + wave] = 1u;\n"
          "    __syncthreads();\n"
          "#pragma unroll\n    for (int j = 0; j < 2; ++j)\n#pragma unroll\n      for (int q = 0; q < 4; ++q) { const f4 v = area[(1 - group) * 2048 + (j * 4 + q) * 64]; own[j][4 * q] += v[0]; own[j][4 * q + 1] += v[1]; own[j][4 * q + 2] += v[2]; own[j][4 * q + 3] += v[3]; }\n"
-         "    odd = (flags[wave] | flags[4 + wave]) != 0u;\n"
-         "#pragma unroll\n    for (int j = 0; j < 2; ++j)\n#pragma unroll\n      for (int q = 0; q < 16; ++q) odd = odd || !(__builtin_fabsf(own[j][q]) < __builtin_inff());\n"
-         "    if (__builtin_amdgcn_ballot_w64(odd) != 0ull) {\n";
-    o << "      const long long row = bm0 + wm + " << (ops[0].kc ? "32 * group + l32" : "2 * l32 + group") << ";\n"
-         "      const GM float* const pa = A + (row < M ? row : M - 1) * am;\n      const GM float* pb[2];\n"
-         "#pragma unroll\n      for (int j = 0; j < 2; ++j) {\n        const long long col = bn0 + wn + " << (ops[1].kc ? "32 * j + l32" : "2 * l32 + j") << ";\n        pb[j] = B + (col < N ? col : N - 1) * bn;\n"
-         "#pragma unroll\n        for (int q = 0; q < 16; ++q) own[j][q] = 0.0f;\n      }\n"
-         "      for (long long k = kbeg; k < KE; k += 2) {\n        const float va = pa[(k + lh) * ak];\n"
-         "#pragma unroll\n        for (int j = 0; j < 2; ++j) own[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va, pb[j][(k + lh) * bk], own[j], 0, 0, 0);\n      }\n";
-    o << "    }\n  }\n";
+         "  }\n";
   } else {
     // One group: the right operand's pieces first, then a row of blocks at a time the left one's and its products.  Workgroups on the
     // same compute unit overlap; 256 accumulators per lane leave no room for more pieces (without the scheduling barriers they spill).
-    auto step = [&](bool more2, const char* ind) {
-      o << ind << "{\n";
-      if (more2) {
-        for (int p = 0; p < P; ++p) piece(2, p, ind);
-        o << ind << ADV;
-      }
-      for (const Op& x : ops) {
-        o << ind << "float " << x.n << "r[" << NB << "][8];\n";
-        if (!x.kc) raw_all(x, 0, ind);
-      }
-      auto block = [&](const Op& x, int blk) {
-        if (x.kc) raw(x, 0, blk, ind);
-        for (int p = 0; p < 4; ++p) pieces_of(x, 0, blk, p, ind);
-        o << ind << SB;
-      };
-      for (int blk = 0; blk < NB; ++blk) block(ops[1], blk);
-      for (int i = 0; i < NB; ++i) {
-        block(ops[0], i);
-        for (int t = 0; t < 6; ++t) for (int j = 0; j < NB; ++j) mfma(0, t, i, j, ind);
-        o << ind << SB;
-      }
-      wait(more2 ? P : 0, ind);
-      o << ind << "}\n";
+    // (A wave that meets a value the pieces cannot hold does what is left of its steps in a loop of its own, with as many barriers: where two
+    // ways to the same sums meet within a step, the compiler keeps them twice.)
+    auto fetch = [&](const char* ind) {
+      o << ind << "if (kt + 2 < nkt) {\n";
+      for (int p = 0; p < P; ++p) piece(2, p, ind);
+      o << ind << ADV << ind << "}\n";
+    };
+    auto advance = [&](const char* ind) {   // the next tile has landed, all of this one's reads are done
+      o << ind << "if (kt + 2 < nkt) __builtin_amdgcn_s_waitcnt(" << (0x0070 | P) << "); else __builtin_amdgcn_s_waitcnt(" << 0x0070 << ");\n" << ind << "__builtin_amdgcn_s_barrier();\n" << ind << rot_text;
     };
     // prologue: tiles 0 and 1 (K >= 32)
     for (int t = 0; t < 2; ++t) {
@@ -2758,28 +2745,43 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
       o << "  " << ADV;
     }
     o << "  __builtin_amdgcn_s_waitcnt(" << (0x0F70 | P) << ");\n  __builtin_amdgcn_s_barrier();\n";
-    o << "  long long kt = 0;\n"
-         "  for (; kt + 2 < nkt; ++kt) {\n";
-    step(true, "    ");
-    o << "    " << rot_text << "  }\n"
-         "  // the last two steps load nothing\n";
-    step(false, "  ");
-    o << "  " << rot_text;
-    step(false, "  ");
-  }
-  if (!two) {
-  // a wave whose pieces or sums are not what they should be computes its blocks again
-  o << "  bool again = (low & 0xffffu) != 0u;\n"
-       "  float most = 0.0f;\n";
-  emit_unrolled(o, {{"i", NB}, {"j", NB}, {"h", 2}}, std::string("    __builtin_amdgcn_sched_barrier(0);\n#pragma unroll\n    for (int q = 0; q < 8; ++q) most += acc[i][j][8 * h + q] * 0.0f;   // (not a number for what is not finite)\n    asm(\"\" : \"+v\"(most));\n"), "  ");
-  o << "  again = again || !(most == 0.0f);\n"
-       "  const bool bad = __builtin_amdgcn_ballot_w64(again) != 0ull;\n";
-  // (a block at a time: where the two ways meet, few registers change places)
-  emit_unrolled(o, {{"i", NB}, {"j", NB}}, std::string("    __builtin_amdgcn_sched_barrier(0);\n    if (bad) {\n      const long long row = bm0 + wm + ") + (ops[0].kc ? "32 * i + l32" : std::to_string(NB) + " * l32 + i") + ", col = bn0 + wn + " + (ops[1].kc ? "32 * j + l32" : std::to_string(NB) + " * l32 + j") + ";\n"
-         "      const GM float* const pa = A + (row < M ? row : M - 1) * am; const GM float* const pb = B + (col < N ? col : N - 1) * bn;\n"
-         "#pragma unroll\n      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;\n"
-         "#pragma unroll 1\n      for (long long k = kbeg + lh; k < KE; k += 2) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[k * ak], pb[k * bk], acc[i][j], 0, 0, 0);\n    }\n", "  ");   // (whole steps: an even number of values)
-  o << "  __builtin_amdgcn_sched_barrier(0);\n";
+    o << "  long long kt = 0;\n  int first = 0;\n"
+         "  for (; kt < nkt; ++kt) {\n    " << NONE_ODD;
+    const char* ind = "    ";
+    fetch(ind);
+    for (const Op& x : ops) {
+      o << ind << "float " << x.n << "r[" << NB << "][8];\n";
+      if (!x.kc) raw_all(x, 0, ind);
+    }
+    auto block = [&](const Op& x, int blk) {
+      if (x.kc) raw(x, 0, blk, ind);
+      for (int p = 0; p < 4; ++p) pieces_of(x, 0, blk, p, ind);
+      o << ind << SB;
+    };
+    for (int blk = 0; blk < NB; ++blk) block(ops[1], blk);
+    for (int i = 0; i < NB; ++i) {
+      block(ops[0], i);
+      o << ind << "if (gr_odd(low, big)) { first = " << i << "; break; }\n";
+      for (int t = 0; t < 6; ++t) for (int j = 0; j < NB; ++j) mfma(0, t, i, j, ind);
+      o << ind << SB;
+    }
+    advance(ind);
+    o << "  }\n"
+         "  while (kt < nkt) {\n";
+    for (int i = 0; i < NB; ++i) {
+      o << ind << "if (first <= " << i << ") {\n";
+      for (int j = 0; j < NB; ++j) {
+        exact(i, i + 1, j, j + 1, ind);
+        o << ind << SB;
+      }
+      o << ind << "}\n";
+    }
+    o << ind << "first = 0;\n";
+    advance(ind);
+    o << ind << "++kt;\n";
+    fetch(ind);
+    o << "  }\n";
+    if (NB == 4) for (int i = 0; i < NB; ++i) for (int j = 0; j < NB; ++j) o << "  asm(\"\" : \"+a\"(acc[" << i << "][" << j << "]));\n";   // (the sums of either loop in the same registers)
   }
   // epilogue on the accumulators: element q of a block is its row rr = 8 (q / 4) + 4 (lane / 32) + q % 4 and column lane % 32;
   // block i of a k-contiguous left operand holds rows wm + 32 i + rr, of a row-contiguous one rows wm + NB rr + i; block j

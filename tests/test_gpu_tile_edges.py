@@ -529,3 +529,58 @@ def test_products_loaded_straight_into_lds(env, m, n, k, layout):
             assert np.array_equal(got[odd], want[odd].astype(f32), equal_nan=True), kind
     finally:
         ctx.set_option("gemm_clamped", 1)
+
+
+# a wave that meets a value the pieces cannot hold changes to float32 instructions: in the first step, in the last rows of blocks of the
+# last but one step, in the last step of either group; sums that overflow keep their signs
+@pytest.mark.parametrize("m,n,k", [(300, 380, 64), (300, 380, 400), (300, 380, 416), (2100, 2300, 176), (4096, 3584, 112)])
+@pytest.mark.parametrize("layout", ["nn", "tn", "nt", "tt"])
+def test_products_change_to_float32_instructions_at_any_step(env, m, n, k, layout):
+    gr, ctx, torch = env
+    rng = np.random.default_rng(52)
+    x, y = rng.standard_normal((m, k)).astype(f32), rng.standard_normal((k, n)).astype(f32)
+    x[127::128], y[:, 127::128] = 0, 0
+    x[127::128, k - 20] = f32(1.2345678e-35)
+    y[k - 5, 127::128] = f32(1.7654321e30)
+    x[5, 3], x[6, 3], y[3, 9] = 1e30, -1e30, 1e30
+    ta, tb = (torch.from_numpy(np.ascontiguousarray(v.T if t == "t" else v)).cuda() for v, t in ((x, layout[0]), (y, layout[1])))
+    A, B = ctx.array(ta), ctx.array(tb)
+    ctx.set_option("gemm_clamped", 0)
+    out = (gr.transpose(A) if layout[0] == "t" else A) @ (gr.transpose(B) if layout[1] == "t" else B)
+    assert "direct" in out.plan()
+    got = out.numpy()
+    ctx.set_option("gemm_clamped", 1)
+    X, Y = (torch.from_numpy(v).cuda().double() for v in (x, y))
+    want, bound = (X @ Y).cpu().numpy(), (X.abs() @ Y.abs()).cpu().numpy() * (k * 2.0 ** -24)
+    assert got[5, 9] == np.inf and got[6, 9] == -np.inf
+    got[5:7, 9] = 0
+    want[5:7, 9] = 0
+    assert (np.abs(got - want) <= bound).all()
+    # one product per sum: within a rounding of it
+    assert (np.abs(got - want)[127::128] <= 2.0 ** -23 * np.abs(want[127::128])).all()
+
+
+@pytest.mark.parametrize("m,k,n", [(2048, 2048, 2048), (3000, 1024, 2048), (4096, 1024, 4096)])
+def test_products_with_a_few_values_the_pieces_cannot_hold_take_no_more_than_twice_the_time(env, m, k, n):
+    import time
+    gr, ctx, torch = env
+    a, b, out = torch.randn(m, k, device="cuda"), torch.randn(k, n, device="cuda"), torch.empty(m, n, device="cuda")
+    A, B = ctx.array(a), ctx.array(b)
+    assert "direct" in (A @ B).plan()
+    program = ctx.program(A @ B, [A, B])
+
+    def best():
+        times = []
+        for _ in range(6):
+            torch.cuda.synchronize()
+            start = time.perf_counter()
+            for _ in range(10):
+                program.run([a, b], out)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - start)
+        return min(times)
+
+    ordinary = best()
+    for value in (1e-35, float("inf"), 1e30):
+        a[::37, ::41] = value
+        assert best() <= 2 * ordinary, value
