@@ -2467,19 +2467,22 @@ void emit_unrolled(std::ostream& o, const std::vector<std::pair<const char*, int
 using EpiLoad = std::function<std::string(const Instr&, int)>;
 void gemm_combine(Em& e, const EpiLoad& epi_load);
 
-// Three bfloat16 pieces of a float32 value, x = h + m + l exactly, for the matrix products below: h takes x's first eight
-// bits, m the rest rounded to nearest, l what is left, eight bits at most.  The matrix cores multiply bfloat16
-// pairs exactly and add them in float32 at sixteen times the float32 rate, so a product of two split operands, six of
-// their instructions (the three terms below 2^-23 of a product, of either sign, are left out), takes 3/8 of the time, and its sum is
-// rounded six times per sixteen values of k where float32 instructions round eight times (32 x 32 blocks, relative error against
-// 64 bits of float32 instructions / these: normal values, K = 784 4.7e-7 / 4.0e-7, 16384 2.2e-6 / 2.1e-6; uniform ones 4.1e-7 / 2.9e-7).
-// What the pieces cannot hold is noticed as they are made, and the wave multiplies these sixteen values of k with float32 instructions
-// (gemm_big_body): of a value whose last piece would reach below the smallest denormal bfloat16 (a nonzero value below 2^-110 can
-// be one) the low half of that piece, which is zero otherwise, is collected in `low`; of infinities, and of values whose products with
-// one another could overflow piece by piece with other signs than their own, `big` keeps the largest magnitude (2^62 and more: gr_odd).
+// Three bfloat16 pieces of a float32 value, x = h + m + l exactly, for the matrix products of gemm_big_body: each the rest rounded to
+// nearest (eight bits, so that the last one is exact).  The matrix cores multiply bfloat16 pairs exactly and add them
+// in float32 at sixteen times the float32 rate; eight of the nine products of pieces, all but l l, which is below 2^-34 of the
+// product, take half of the time of float32 instructions.  Two things keep the sums at least as near 64 bits as those instructions'
+// for any operands: the pieces lean to neither side (with a first piece that is cut off the small products of positive operands
+// are all positive, and are lost where the sum has outgrown them: uniform values, K = 4096, 3.6e-6 for 8.4e-7), and the products below h h have
+// sums of their own, because these matrix instructions do not round to nearest as float32 ones do (a single product per sum, 2048^3
+// times a diagonal matrix: largest relative error of an element 6.0e-8 with float32 instructions, 1.2e-7 with all
+// products in one sum, 2.9e-7 with six of them, 6.0e-8 so).
+// What the pieces cannot hold is noticed as they are made, and the wave multiplies these and all further values of k with float32 instructions:
+// of a value whose last piece would reach below the smallest denormal bfloat16 (a nonzero value below 2^-110 can
+// be one) the low half of that piece, which is zero otherwise, is collected in `low`; of infinities, and of values whose products could make
+// a sum of pieces overflow where the sum of the values does not, `big` keeps the largest magnitude (2^48 and more: gr_odd).
 // (What is not a number is one in all of its products either way.)
-// (us with 1e-35 at every 41st position of every 37th row, the wave's whole share of K again at the end, from global memory / change to a
-// loop of float32 instructions where it is met / without such values: 2048^3 457 / 145 / 104, 4096 x 512 x 784 119 / 40 / 31, 4096^3 9890 / 1045 / 712.)
+// (us with 1e-35 at every 41st position of every 37th row / without such values / float32 instructions for all: 2048^3 147 / 120 / 134,
+// 4096 x 512 x 784 40 / 34 / 42.)
 // The splitting competes with the matrix instructions: about 6 vector instructions per value.  They overlap with other waves' matrix
 // instructions; the two-term dot product instruction, which could take off a piece without unpacking it, does not (one wave with matrix
 // instructions beside one with as many cycles of these: their sum; of the others a fifth more than the longer of the two).
@@ -2489,16 +2492,15 @@ void split_helpers(Em& e) {
          "typedef float gr_p2 __attribute__((ext_vector_type(2)));\n"
          "typedef unsigned gr_u4 __attribute__((ext_vector_type(4)));\n"
          "static __device__ __forceinline__ void gr_split2(float x0, float x1, unsigned& h, unsigned& m, unsigned& l, unsigned& low, float& big) {\n"
-         "  const unsigned u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);\n"
-         "  const float r0 = x0 - __uint_as_float(u0 & 0xffff0000u), r1 = x1 - __uint_as_float(u1 & 0xffff0000u);\n"
-         "  h = __builtin_amdgcn_perm(u1, u0, 0x07060302u);\n"
+         "  h = __builtin_bit_cast(unsigned, __builtin_convertvector((gr_p2{x0, x1}), gr_b2));\n"
+         "  const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);\n"
          "  m = __builtin_bit_cast(unsigned, __builtin_convertvector((gr_p2{r0, r1}), gr_b2));\n"
          "  const unsigned l0 = __float_as_uint(r0 - __uint_as_float(m << 16)), l1 = __float_as_uint(r1 - __uint_as_float(m & 0xffff0000u));\n"
          "  l = __builtin_amdgcn_perm(l1, l0, 0x07060302u);\n"
          // (in place: left to the compiler, the collecting is put off and the pieces are kept in scratch memory for it)
          "  asm(\"v_or3_b32 %0, %0, %1, %2\" : \"+v\"(low) : \"v\"(l0), \"v\"(l1));\n"
          "  asm(\"v_max3_f32 %0, |%1|, |%2|, %0\" : \"+v\"(big) : \"v\"(x0), \"v\"(x1));\n}\n"
-         "static __device__ __forceinline__ bool gr_odd(unsigned low, float big) { return __builtin_amdgcn_ballot_w64((low & 0xffffu) != 0u || big >= 0x1p62f) != 0ull; }\n";
+         "static __device__ __forceinline__ bool gr_odd(unsigned low, float big) { return __builtin_amdgcn_ballot_w64((low & 0xffffu) != 0u || big >= 0x1p48f) != 0ull; }\n";
 }
 
 // Matrix product of large operands, each contiguous along one of its dimensions (K a multiple of 16; M and N need
@@ -2510,16 +2512,26 @@ void split_helpers(Em& e) {
 //     ring of three stages, so a step has one barrier, no staging registers and no LDS write instructions.
 //   * A tile contiguous along k: rows of 16 floats; the four 16-byte chunks of row m sit at chunk position c ^ (m / 4 % 4),
 //     which lets both the depositing wave (16 lanes = 4 rows x 4 chunks) and the reading one (16 lanes = 16
-//     rows, one chunk) touch every bank once.
+//     rows, one chunk) touch every bank once.  A lane reads the four k values of a chunk with one ds_read_b128
+//     and feeds them to four matrix instructions: the instruction for element t of the chunks takes k = 4 h + t
+//     (+ 8 in the second half of the step) in half-wave h instead of k = 2 s + h.  Both operands use the same
+//     assignment, so every product is formed once; only the order of the additions differs.
 //   * A tile contiguous along its other dimension: 16 rows of 256 floats with a pitch of 264 (rows 4 apart lie 32 banks apart).
 //     Block j of a lane's four column blocks is column 4 r + j of the wave's 128 (r = lane % 32), so the four operands of a
 //     k come with one ds_read_b128 and a lane's results are four neighbouring columns (16-byte stores).
-//   * Half-wave h takes k = 4 h .. 4 h + 3 and 8 + 4 h .. of a step for both operands, eight values per lane and block, which
-//     it splits into three pieces (split_helpers) and multiplies with six matrix instructions per pair of blocks.
-// Bound by vector issue (176 instructions per wave and step for the pieces of 128 x 64 x 16 products, 704 cycles) and the matrix
-// cores (768); measured against float32 matrix instructions with the same tiles and loads (us, before / now): 2048^3 143 / 108,
-// 4096 x 512 x 784 42 / 31, 784 x 4096 x 512 43 / 35, 1536^3 79 / 64, 512 x 2848 x 2352 74 / 54, 3072^3 442 / 363, 4096^3 932 / 697
-// (197 TFLOP/s); relative error 4.1e-7 / 2.4e-7 (4096 x 512 x 784), 1.15e-6 / 1.0e-6 (4096^3).
+//   * One group: float32 matrix instructions.  Per step and wave of the 256 x 256 tiles 128 of them, 16 LDS reads, 8 direct loads, one
+//     barrier, each placed behind a fixed matrix instruction (scheduling barriers pin the order): with one wave per SIMD every
+//     instruction between two matrix instructions delays the second one, which is what bounds this kernel
+//     (measured on 4096^3, one variant each: staging through registers 137 TFLOP/s, direct loads 143, the
+//     same with addresses precomputed and 16-byte reads of the right operand 151; a loop of nothing but
+//     matrix instructions 154).
+//   * Two groups: bfloat16 matrix instructions over three pieces of every value (split_helpers), which one wave per SIMD could not
+//     both make and multiply in time.  A second set of sums fits here only (256 x 256 tiles have no registers for it; three workgroups of one
+//     group per compute unit would be two: 3000 x 512 x 2048 72 us for 65 with float32 instructions).
+//     (us, float32 instructions / pieces; relative error against 64 bits: 2048^3 132 / 119.5, 8.1e-7 / 1.9e-7; 4096 x 512 x 784 41.8 / 34.7,
+//     4.1e-7 / 9.3e-8; 784 x 4096 x 512 44.4 / 38.8; 512 x 2848 x 2352 70 / 60.  With six products and one sum 101, 31.3, 35.4 and 52.)
+//     Per wave and step 221 vector instructions, 32 of them conversions at half rate, 1010 cycles, and 32 matrix instructions, 1024: of 119.5 us
+//     the matrix cores of 2048^3 work 55, the vector units as long, mostly one after the other.
 // The direct loads are written as assembly: the compiler's own form of them makes it wait for every outstanding
 // LDS read before each use (it counts them as LDS traffic that may return out of order).  Their completion is
 // tracked by hand: the wait before a step's barrier leaves only the loads of the newest tile in flight.
@@ -2623,50 +2635,48 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
     if (&x == &ops[0]) rot << "    ";
   }
   const std::string rot_text = rot.str();
-  // Values t (t < 4) and 4 + t of a lane's eight are k = 4 h + t and 8 + 4 h + t in half-wave h, for both operands.
-  // Block blk of an operand in stage `role`, split into set `set`; a statement per element so that they can be placed apart.
-  auto raw = [&](const Op& x, int role, int blk, const char* ind) {
-    const std::string n = x.n;
-    for (int hf = 0; hf < 2; ++hf)
-      o << ind << "{ const f4 w = *(const lf4*)(" << n << "p[" << role << "][" << hf << "] + " << blk * 512 << "); " << n << "r[" << blk << "][" << 4 * hf << "] = w[0]; " << n << "r[" << blk << "][" << 4 * hf + 1 << "] = w[1]; " << n << "r[" << blk << "][" << 4 * hf + 2 << "] = w[2]; " << n << "r[" << blk << "][" << 4 * hf + 3 << "] = w[3]; }\n";
-  };
-  auto raw_all = [&](const Op& x, int role, const char* ind) {
-    const std::string n = x.n;
-    for (int blk = 0; x.kc && blk < NB; ++blk) raw(x, role, blk, ind);
-    for (int v = 0; !x.kc && v < 8; ++v) {
-      o << ind << "{ const " << RV << " w = *(const l" << RV << "*)(" << n << "p[" << role << "] + " << rc_row(8 * (v >> 2) + (v & 3)) << ");";
-      for (int blk = 0; blk < NB; ++blk) o << ' ' << n << "r[" << blk << "][" << v << "] = w[" << blk << "];";
-      o << " }\n";
-    }
-  };
-  auto pieces_of = [&](const Op& x, int set, int blk, int p, const char* ind) {
-    const std::string n = x.n, to = n + "s" + std::to_string(set) + "[" + std::to_string(blk) + "]";
-    o << ind << "{ unsigned h, m, l; gr_split2(" << n << "r[" << blk << "][" << 2 * p << "], " << n << "r[" << blk << "][" << 2 * p + 1 << "], h, m, l, low, big); " << to << "[0][" << p << "] = h; " << to << "[1][" << p << "] = m; " << to << "[2][" << p << "] = l; }\n";
-  };
-  static const int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
-  auto mfma = [&](int set, int t, int i, int j, const char* ind) {
-    o << ind << "acc[" << i << "][" << j << "] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(gr_b8, as" << set << "[" << i << "][" << order[t][0] << "]), __builtin_bit_cast(gr_b8, bs" << set << "[" << j << "][" << order[t][1] << "]), acc[" << i << "][" << j << "], 0, 0, 0);\n";
-  };
-  const char* SB = "__builtin_amdgcn_sched_barrier(0);\n";
-  for (const Op& x : ops) o << "  gr_u4 " << x.n << "s0[" << NB << "][3];\n";
-  const char* NONE_ODD = "unsigned low = 0u; float big = 0.0f;\n";
-  // blocks [i0, i1) x [j0, j1) of the tile in role 0 with float32 instructions, from LDS again (the values are not kept for it)
-  auto exact = [&](int i0, int i1, int j0, int j1, const char* ind) {
-    o << ind << "{ __atomic_signal_fence(__ATOMIC_SEQ_CST);\n" << ind << "float ar[" << NB << "][8], br[" << NB << "][8];\n";
-    for (const Op& x : ops)
-      for (int b = &x == ops ? i0 : j0; b < (&x == ops ? i1 : j1); ++b) {
-        if (x.kc) raw(x, 0, b, ind);
-        else for (int v = 0; v < 8; ++v) o << ind << x.n << "r[" << b << "][" << v << "] = " << x.n << "p[0][" << rc_row(8 * (v >> 2) + (v & 3)) + b << "];\n";
-      }
-    for (int v = 0; v < 8; ++v) for (int i = i0; i < i1; ++i) for (int j = j0; j < j1; ++j)
-      o << ind << "acc[" << i << "][" << j << "] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[" << i << "][" << v << "], br[" << j << "][" << v << "], acc[" << i << "][" << j << "], 0, 0, 0);\n";
-    o << ind << "}\n";
-  };
   if (two) {
+    // Values t (t < 4) and 4 + t of a lane's eight are k = 4 h + t and 8 + 4 h + t in half-wave h, for both operands.
+    // Block blk of an operand's tile in role 0.
+    auto raw = [&](const Op& x, int blk, const char* ind) {
+      const std::string n = x.n;
+      for (int hf = 0; hf < 2; ++hf)
+        o << ind << "{ const f4 w = *(const lf4*)(" << n << "p[0][" << hf << "] + " << blk * 512 << "); " << n << "r[" << blk << "][" << 4 * hf << "] = w[0]; " << n << "r[" << blk << "][" << 4 * hf + 1 << "] = w[1]; " << n << "r[" << blk << "][" << 4 * hf + 2 << "] = w[2]; " << n << "r[" << blk << "][" << 4 * hf + 3 << "] = w[3]; }\n";
+    };
+    auto raw_all = [&](const Op& x, const char* ind) {
+      const std::string n = x.n;
+      for (int blk = 0; x.kc && blk < NB; ++blk) raw(x, blk, ind);
+      for (int v = 0; !x.kc && v < 8; ++v) {
+        o << ind << "{ const " << RV << " w = *(const l" << RV << "*)(" << n << "p[0] + " << rc_row(8 * (v >> 2) + (v & 3)) << ");";
+        for (int blk = 0; blk < NB; ++blk) o << ' ' << n << "r[" << blk << "][" << v << "] = w[" << blk << "];";
+        o << " }\n";
+      }
+    };
+    auto pieces_of = [&](const Op& x, int blk, int p, const char* ind) {
+      const std::string n = x.n, to = n + "s[" + std::to_string(blk) + "]";
+      o << ind << "{ unsigned h, m, l; gr_split2(" << n << "r[" << blk << "][" << 2 * p << "], " << n << "r[" << blk << "][" << 2 * p + 1 << "], h, m, l, low, big); " << to << "[0][" << p << "] = h; " << to << "[1][" << p << "] = m; " << to << "[2][" << p << "] = l; }\n";
+    };
+    static const int order[8][2] = {{2, 1}, {1, 2}, {2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+    auto mfma = [&](int t, int i, int j, const char* ind) {
+      const std::string to = std::string(t < 7 ? "tail[" : "acc[") + std::to_string(i) + "][" + std::to_string(j) + "]";
+      o << ind << to << " = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(gr_b8, as[" << i << "][" << order[t][0] << "]), __builtin_bit_cast(gr_b8, bs[" << j << "][" << order[t][1] << "]), " << to << ", 0, 0, 0);\n";
+    };
+    const char* SB = "__builtin_amdgcn_sched_barrier(0);\n";
+    for (const Op& x : ops) o << "  gr_u4 " << x.n << "s[" << NB << "][3];\n";
+    const char* NONE_ODD = "unsigned low = 0u; float big = 0.0f;\n";
+    // the tile in role 0 with float32 instructions, from LDS again (the values are not kept for it)
+    auto exact = [&](const char* ind) {
+      o << ind << "{ __atomic_signal_fence(__ATOMIC_SEQ_CST);\n" << ind << "float ar[" << NB << "][8], br[" << NB << "][8];\n";
+      for (const Op& x : ops) raw_all(x, ind);
+      for (int v = 0; v < 8; ++v) for (int i = 0; i < NB; ++i) for (int j = 0; j < NB; ++j)
+        o << ind << "acc[" << i << "][" << j << "] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[" << i << "][" << v << "], br[" << j << "][" << v << "], acc[" << i << "][" << j << "], 0, 0, 0);\n";
+      o << ind << "}\n";
+    };
     // Group g of four waves takes every second step from step g on, its tiles in a ring of its own.  Vector and matrix instructions
     // of one wave hardly overlap, those of two waves of a SIMD do: between two barriers group 0 splits a tile and
-    // multiplies it while group 1 multiplies the tile that it split before and splits the next (2048^3, us: one group of four waves 133,
-    // two in step 120, these 110).
+    // multiplies it while group 1 multiplies the tile that it split before and splits the next (2048^3 with six products and
+    // one sum, us: one group of four waves 133, two in step 120, these 108).
+    o << "  f16v tail[2][2];\n  for (int i = 0; i < 2; ++i) for (int j = 0; j < 2; ++j) for (int q = 0; q < 16; ++q) tail[i][j][q] = 0.0f;\n";
     o << "  const int n0 = (int)((nkt + 1) / 2), mine = (int)((nkt + 1 - group) / 2);\n";
     auto fetch = [&](int role, const char* tile, const char* ind) {
       o << ind << "if (" << tile << " < mine) {\n";
@@ -2677,13 +2687,13 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
       o << ind << NONE_ODD;
       for (const Op& x : ops) {
         o << ind << "float " << x.n << "r[" << NB << "][8];\n";
-        raw_all(x, 0, ind);
+        raw_all(x, ind);
       }
-      for (const Op& x : ops) for (int blk = 0; blk < NB; ++blk) for (int p = 0; p < 4; ++p) pieces_of(x, 0, blk, p, ind);
+      for (const Op& x : ops) for (int blk = 0; blk < NB; ++blk) for (int p = 0; p < 4; ++p) pieces_of(x, blk, p, ind);
       o << ind << "if (gr_odd(low, big)) break;\n" << ind << SB;
     };
     auto products = [&](const char* ind) {
-      for (int t = 0; t < 6; ++t) for (int i = 0; i < NB; ++i) for (int j = 0; j < NB; ++j) mfma(0, t, i, j, ind);
+      for (int t = 0; t < 8; ++t) for (int i = 0; i < NB; ++i) for (int j = 0; j < NB; ++j) mfma(t, i, j, ind);
       o << ind << SB;
     };
     auto advance = [&](const char* ind) {   // the next tile has landed, all of this one's reads are done
@@ -2701,7 +2711,7 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
     products(ind);
     advance(ind);
     o << "    }\n    while (t < mine) {\n";
-    exact(0, NB, 0, NB, ind);
+    exact(ind);
     advance(ind);
     o << ind << "++t;\n";
     fetch(2, "t + 2", ind);
@@ -2713,11 +2723,12 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
     fetch(2, "t + 3", ind);
     products(ind);
     o << "    }\n    while (t < mine) {\n";
-    exact(0, NB, 0, NB, ind);
+    exact(ind);
     advance(ind);
     fetch(2, "t + 3", ind);
     o << ind << "++t;\n    }\n"
          "    if (mine < n0) __builtin_amdgcn_s_barrier();\n  }\n";
+    o << "#pragma unroll\n  for (int i = 0; i < 2; ++i)\n#pragma unroll\n    for (int j = 0; j < 2; ++j)\n#pragma unroll\n      for (int q = 0; q < 16; ++q) acc[i][j][q] += tail[i][j][q];\n";
     // the groups add up their sums: each takes one row of blocks
     o << "  f16v own[2];\n"
          "  { f4* const area = (f4*)gr_lds + (wave * 8) * 64 + lane;   // 32 KiB per group: what it leaves to the other one\n"
@@ -2727,17 +2738,52 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
          "#pragma unroll\n    for (int j = 0; j < 2; ++j)\n#pragma unroll\n      for (int q = 0; q < 4; ++q) { const f4 v = area[(1 - group) * 2048 + (j * 4 + q) * 64]; own[j][4 * q] += v[0]; own[j][4 * q + 1] += v[1]; own[j][4 * q + 2] += v[2]; own[j][4 * q + 3] += v[3]; }\n"
          "  }\n";
   } else {
-    // One group: the right operand's pieces first, then a row of blocks at a time the left one's and its products.  Workgroups on the
-    // same compute unit overlap; 256 accumulators per lane leave no room for more pieces (without the scheduling barriers they spill).
-    // (A wave that meets a value the pieces cannot hold does what is left of its steps in a loop of its own, with as many barriers: where two
-    // ways to the same sums meet within a step, the compiler keeps them twice.)
-    auto fetch = [&](const char* ind) {
-      o << ind << "if (kt + 2 < nkt) {\n";
-      for (int p = 0; p < P; ++p) piece(2, p, ind);
-      o << ind << ADV << ind << "}\n";
+    const char* SB = "__builtin_amdgcn_sched_barrier(0);\n";
+    for (const Op& x : ops)
+      if (x.kc) o << "  f4 " << x.n << "F[2][" << NB << "];\n";
+      else o << "  " << RV << " " << x.n << "F[2];\n";
+    // operand of a matrix instruction (group s of the step, block blk) and the LDS reads that provide it
+    auto val = [&](const Op& x, int s, int blk) {
+      std::ostringstream v;
+      if (x.kc) v << x.n << "F[" << (s >> 2) << "][" << blk << "][" << (s & 3) << "]";
+      else v << x.n << "F[" << (s & 1) << "][" << blk << "]";
+      return v.str();
     };
-    auto advance = [&](const char* ind) {   // the next tile has landed, all of this one's reads are done
-      o << ind << "if (kt + 2 < nkt) __builtin_amdgcn_s_waitcnt(" << (0x0070 | P) << "); else __builtin_amdgcn_s_waitcnt(" << 0x0070 << ");\n" << ind << "__builtin_amdgcn_s_barrier();\n" << ind << rot_text;
+    auto read_kc = [&](const Op& x, int st, int hf, int blk, const char* ind) {
+      o << ind << x.n << "F[" << hf << "][" << blk << "] = *(const lf4*)(" << x.n << "p[" << st << "][" << hf << "] + " << blk * 512 << ");\n";
+    };
+    auto read_rc = [&](const Op& x, int st, int s, const char* ind) {
+      o << ind << x.n << "F[" << (s & 1) << "] = *(const l" << RV << "*)(" << x.n << "p[" << st << "] + " << rc_row(8 * (s >> 2) + (s & 3)) << ");\n";
+    };
+    // One step.  Role 0 is the stage that holds the current tile; the tile two steps on goes to the stage in role 2 if more2;
+    // the first operands of the next step are read (from role 1) behind the barrier if more1.  Every load and LDS read
+    // sits behind a fixed matrix instruction of a fixed group.
+    auto step = [&](bool more2, bool more1, const char* ind) {
+      for (int s = 0; s < 8; ++s) {
+        if (s == 7)
+          // the next tile has landed (all but the newest P loads are complete) and this wave's reads of the current one are done
+          o << ind << "__builtin_amdgcn_s_waitcnt(" << (more2 ? 0x0070 | P : 0x0070) << ");\n" << ind << "__builtin_amdgcn_s_barrier();\n";
+        for (int q = 0; q < G; ++q) {
+          const int i = q / NB, j = q % NB;
+          o << ind << SB << ind << "acc[" << i << "][" << j << "] = __builtin_amdgcn_mfma_f32_32x32x2f32(" << val(ops[0], s, i) << ", " << val(ops[1], s, j)
+            << ", acc[" << i << "][" << j << "], 0, 0, 0);\n" << ind << SB;
+          if (more2 && q == 1 && s < P && s < 7) piece(2, s, ind);
+          if (more2 && NB == 4 && s == 6 && q == 9) piece(2, 7, ind);
+          if (more2 && s == (NB == 4 ? 6 : 3) && q == (NB == 4 ? 9 : 1)) o << ind << ADV;
+          for (int k = 0; k < 2; ++k) {
+            const Op& x = ops[k];
+            if (x.kc) {
+              // second half of the step: behind the last NB matrix instructions of group 1 (left) / 2 (right);
+              // first half of the next step: behind the first 2 NB of group 7
+              if (s == 1 + k && q >= G - NB) read_kc(x, 0, 1, q - (G - NB), ind);
+              if (s == 7 && more1 && q >= NB * k && q < NB + NB * k) read_kc(x, 1, 0, q - NB * k, ind);
+            } else {
+              if (s < 7 && q == NB + k) read_rc(x, 0, s + 1, ind);
+              if (s == 7 && more1 && q == NB + k) read_rc(x, 1, 0, ind);
+            }
+          }
+        }
+      }
     };
     // prologue: tiles 0 and 1 (K >= 32)
     for (int t = 0; t < 2; ++t) {
@@ -2745,43 +2791,18 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
       o << "  " << ADV;
     }
     o << "  __builtin_amdgcn_s_waitcnt(" << (0x0F70 | P) << ");\n  __builtin_amdgcn_s_barrier();\n";
-    o << "  long long kt = 0;\n  int first = 0;\n"
-         "  for (; kt < nkt; ++kt) {\n    " << NONE_ODD;
-    const char* ind = "    ";
-    fetch(ind);
     for (const Op& x : ops) {
-      o << ind << "float " << x.n << "r[" << NB << "][8];\n";
-      if (!x.kc) raw_all(x, 0, ind);
+      if (x.kc) for (int blk = 0; blk < NB; ++blk) read_kc(x, 0, 0, blk, "  ");
+      else read_rc(x, 0, 0, "  ");
     }
-    auto block = [&](const Op& x, int blk) {
-      if (x.kc) raw(x, 0, blk, ind);
-      for (int p = 0; p < 4; ++p) pieces_of(x, 0, blk, p, ind);
-      o << ind << SB;
-    };
-    for (int blk = 0; blk < NB; ++blk) block(ops[1], blk);
-    for (int i = 0; i < NB; ++i) {
-      block(ops[0], i);
-      o << ind << "if (gr_odd(low, big)) { first = " << i << "; break; }\n";
-      for (int t = 0; t < 6; ++t) for (int j = 0; j < NB; ++j) mfma(0, t, i, j, ind);
-      o << ind << SB;
-    }
-    advance(ind);
-    o << "  }\n"
-         "  while (kt < nkt) {\n";
-    for (int i = 0; i < NB; ++i) {
-      o << ind << "if (first <= " << i << ") {\n";
-      for (int j = 0; j < NB; ++j) {
-        exact(i, i + 1, j, j + 1, ind);
-        o << ind << SB;
-      }
-      o << ind << "}\n";
-    }
-    o << ind << "first = 0;\n";
-    advance(ind);
-    o << ind << "++kt;\n";
-    fetch(ind);
-    o << "  }\n";
-    if (NB == 4) for (int i = 0; i < NB; ++i) for (int j = 0; j < NB; ++j) o << "  asm(\"\" : \"+a\"(acc[" << i << "][" << j << "]));\n";   // (the sums of either loop in the same registers)
+    o << "  long long kt = 0;\n"
+         "  for (; kt + 2 < nkt; ++kt) {\n";
+    step(true, true, "    ");
+    o << "    " << rot_text << "  }\n"
+         "  // the last two steps load nothing\n";
+    step(false, true, "  ");
+    o << "  " << rot_text;
+    step(false, false, "  ");
   }
   // epilogue on the accumulators: element q of a block is its row rr = 8 (q / 4) + 4 (lane / 32) + q % 4 and column lane % 32;
   // block i of a k-contiguous left operand holds rows wm + 32 i + rr, of a row-contiguous one rows wm + NB rr + i; block j
@@ -2992,9 +3013,7 @@ void gen_gemm(Em& e) {
   const int BP = BN == 128 && b_mode == 1 ? (KS == 32 ? 129 : 130) : BN + 4;
   prelude(e);
   e.o << "typedef float f16v __attribute__((ext_vector_type(16)));\n";
-  if (g.VR == 2) {
-    split_helpers(e);
-  }
+  if (g.VR == 2 && g.UC == 2) split_helpers(e);
   kernel_head(e, "gr_gemm", g.VR == 2 && g.UC == 2 ? 512 : 256);
   e.o << "  const long long M = " << e.S(e.L.extra) << ", N = " << e.S(e.L.extra + 1) << ", K = " << e.S(e.L.extra + 2) << ";\n";
   group_pointers(e, "  ");

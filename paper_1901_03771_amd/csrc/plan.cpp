@@ -762,13 +762,13 @@ static void choose_in_place(GroupPlan* g) {
 // except for short sums with a large result, whose stores bound it and which the larger tile writes faster (11845 x 48 x 2066
 // 42 against 57, 16384 x 100 x 1000 44 / 58, 2^20 x 16 x 8 26 / 55), tall operands with few columns (65536 x 512 x 10 28 / 31)
 // and large products of two operands contiguous along k (4001^3 1082 / 1111; the other layouts 1201 / 1143 and
-// 1318 / 1152); and from the direct 128 x 128 kernel where an estimate of its time is lower than that kernel's.  Both
-// estimates, in microseconds: rounds of 256 workgroups times steps (fitted to 446 products of 64 to 4096 values of k in four layouts,
-// that of the direct kernel again to 36 when its arithmetic changed), the launch, and for a split the second launch and the partial tiles' traffic; without a
+// 1318 / 1152); and from the direct 128 x 128 kernel where an estimate of its time is lower than that kernel's (by 5 % where that one has one group of waves).  Both
+// estimates, in microseconds: rounds of 256 workgroups times steps (fitted to 446 products of 64 to 4096 values of k in four layouts;
+// that of the direct kernel where it multiplies pieces to 36), the launch, and for a split the second launch and the partial tiles' traffic; without a
 // split the epilogue, which runs when the products are done (a second launch hides it behind its traffic): 4096 x 784 x 512 with a bias and
-// tanh 40.5 clamped, 35 direct in two parts.  (us, direct / this: 512^3 14.6 / 10.8, 1024 x 512 x 512 16.9 / 14.0, 224 x 192 x 1856 12.1 / 8.3,
-// 528 x 208 x 2320 14.1 / 14.2, 448 x 768 x 1456 22.2 / 22.4; stay: 368 x 2160 x 1296 26.1 / 32.5, 1296 x 3264 x 208 25.7 / 30.0, 3056 x 448 x 896 25.4 / 31.8,
-// 2048^3 108 / 151.  The choice missed the faster one of 36 products by 10 % at most, 4096 x 784 x 512 plain 34.9 / 38.7.)
+// tanh 40.5 clamped, 38 direct in two parts.  (us, direct / this: 512^3 15.5 / 11.3, 1024 x 512 x 512 17.5 / 14.2, 224 x 192 x 1856 12.8 / 8.5,
+// 528 x 208 x 2320 14.7 / 14.7, 448 x 768 x 1456 23.0 / 22.8; stay: 368 x 2160 x 1296 28.3 / 32.8, 1296 x 3264 x 208 26.8 / 35.2, 3056 x 448 x 896 27.7 / 31.8,
+// 2048^3 119 / 151.  The choice missed the faster one of 45 products by 5 % at most, 4096 x 784 x 512 plain 37.8 / 39.6.)
 // `wanted`: splits of K that the larger tiles would take if they may store any number of partial tiles.  It decides
 // between the kernels, so that a request that must not allocate takes the kernel that the same request would take
 // otherwise (and that is loaded by then); g->slabs, which stays within its scratch array, bounds the splits.
@@ -808,13 +808,14 @@ void choose_gemm_tiles(GroupPlan* g, int wanted) {
     auto rounds = [](int64_t workgroups) { return (double)((workgroups + 255) / 256); };
     auto split = [&](double launch, double traffic, int n) { return n > 1 ? launch + traffic * (double)n * (double)M * (double)N * 8e-6 : 0.0; };
     const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128) * wanted;
-    const double direct = rounds(wgs) * (double)((gemm_split_extent(K, wanted) + 15) / 16) * 0.75 + 4.5 + split(3.4, 0.18, wanted);
+    const bool pieces = wgs <= 256;   // (two groups of waves per workgroup, see gemm_big_body)
+    const double direct = rounds(wgs) * (double)((gemm_split_extent(K, wanted) + 15) / 16) * (pieces ? 0.75 : 0.86) + 4.5 + split(3.4, 0.18, wanted);
     const double clamped = rounds(tiles * ks) * (double)((gemm_split_extent(K, ks) + 31) / 32) * 0.56 + 4.0 + split(2.7, 0.22, ks);
     double epilogue = 0.0;   // vector instructions per result, at 39 of a lane per picosecond
     for (const Instr& in : g->prog)
       if (in.kind == IKind::UNARY || in.kind == IKind::BINARY) epilogue += heavy_op(in) ? 40.0 : 1.0;
     epilogue *= (double)M * (double)N / 3.9e7;
-    if (clamped + (ks > 1 ? 0.0 : epilogue) > direct + (wanted > 1 ? 0.0 : epilogue)) return;
+    if ((clamped + (ks > 1 ? 0.0 : epilogue)) * (pieces ? 1.0 : 1.05) > direct + (wanted > 1 ? 0.0 : epilogue)) return;
   }
   g->VR = 3;
   g->UC = 1;
@@ -1326,12 +1327,12 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         // The same kernel with 128 x 128 tiles and K divided over `slabs`
         // workgroups per tile where that fills the compute units more evenly or at all.  The count is the one with the
         // lowest cost in a model fitted to measurements (microseconds): rounds of 256 workgroups times the
-        // steps of one workgroup at 0.75 per step, plus, for a split product, 6 for the second launch and the traffic of the partial tiles at
-        // 5 TB/s.  A larger count has to beat a smaller one by 3 %.  Every split holds at least 128 values of k, the last
+        // steps of one workgroup at 0.75 per step (two groups of waves, pieces; 0.6 to 0.9 measured) or 0.95 (one group, float32), plus, for a
+        // split product, 6 for the second launch and the traffic of the partial tiles at 5 TB/s.  A larger count has to beat a smaller one by 3 %.  Every split holds at least 128 values of k, the last
         // one at least two steps; the partial tiles stay below 1 GiB (within the static scratch array for a request that must not
         // allocate).
-        // (measured, us: 784 x 4096 x 512 by 8 splits 35.7, by 9 34.3; 2080 x 2368 x 512 by 3 45; 512 x 4096 x 512 by 16 25.6;
-        // 3072^3 by 2 363, 442 with float32 instructions)
+        // (measured, us: 784 x 4096 x 512 by 8 splits 38.8, 44.4 with float32 instructions by 9; 2080 x 2368 x 512 by 3 50, 57 by 7;
+        // 512 x 4096 x 512 by 16 27.2, 29.8; 1536^3 in one 78, with float32 instructions by 3 75; 3072^3 by 3 444, in one 525, float32 instructions both)
         const int64_t tiles128 = ((g->M + 127) / 128) * ((g->N + 127) / 128);
         auto cheapest = [&](int64_t room, int least) {   // room: floats of partial tiles
           double best = 0;
@@ -1340,7 +1341,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
             const int64_t kch = gemm_split_extent(g->K, ks);
             if (ks > 1 && (kch < 128 || g->K - (ks - 1) * kch < 32 || (int64_t)ks * g->M * g->N > room)) continue;
             const int64_t wgs = tiles128 * ks, rnd = (wgs + 255) / 256, steps = (kch + 15) / 16;
-            const double cost = (double)rnd * (double)steps * 0.75 + (ks > 1 ? 6.0 + (double)ks * (double)g->M * (double)g->N * 8.0 / 5e6 : 0.0);
+            const double cost = (double)rnd * (double)steps * (wgs <= 256 ? 0.75 : 0.95) + (ks > 1 ? 6.0 + (double)ks * (double)g->M * (double)g->N * 8.0 / 5e6 : 0.0);
             if (best_ks == 0 || cost < best * 0.97) { best = cost; best_ks = ks; }
           }
           return best_ks;
@@ -1358,11 +1359,12 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
       }
     }
     if (c->opt_gemm_bn == 0 && c->opt_gemm_kstep == 0 && c->opt_gemm_split == 0 && c->opt_gemm_big && c->opt_gemm_clamped) choose_gemm_tiles(g, wanted ? wanted : g->slabs);
-    // The direct kernel with 128 x 128 tiles (UC: groups of four waves in a workgroup): two groups divide a tile's steps where compute units have
-    // one workgroup each, one group where they hold several at a time, which overlap each other's loads, epilogues and arithmetic.
-    // (us, float32 instructions before / one group / two: 256 workgroups or fewer: 4096 x 512 x 784 37.2 / 36.7 / 29.6, 4096 x 512 x 1024 39.4 /
-    // 38.7 / 33.0, 2048 x 128 x 2048 with tanh 28.1 / 28.3 / 20.5; more: 12800 x 64 x 768 22.6 / 19.4 / 26.1, 6000 x 128 x 1500 32.7 / 26.6 / 33.9,
-    // 12800 x 256 x 768 57.6 / 44.4 / 50.7, 3000 x 512 x 2048 65.6 / 52.7 / 54.0, 5120 x 384 x 2560 98.9 / 82.2 / 86.8.)
+    // The direct kernel with 128 x 128 tiles (UC: groups of four waves in a workgroup): two groups divide a tile's steps and multiply pieces
+    // where compute units have one workgroup each, one group with float32 instructions where they hold several at a time, which overlap
+    // each other's loads, epilogues and arithmetic.
+    // (us, one group / two: 256 workgroups or fewer: 4096 x 512 x 784 41.8 / 34.7, 2048^3 132 / 119.5, 512 x 2848 x 2352 70 / 60, 2048 x 128 x 2048
+    // 14.8 / 13.3; more: 12800 x 64 x 768 22.1 / 26.1, 6000 x 128 x 1500 32.2 / 35.1, 12800 x 256 x 768 53.1 / 54.7,
+    // 5120 x 384 x 2560 97 / 97, 3000 x 512 x 2048 66 to 71 / 62.)
     if (g->VR == 2 && g->BX == 128) g->UC = ((g->M + 127) / 128) * ((g->N + 127) / 128) * (wanted ? wanted : g->slabs) <= 256 ? 2 : 1;
   } else if (dot && !(dot == r && dot_as_reduce(dot) && c->opt_fusion)) {
     // ---- contraction with pointwise epilogue ------------------------------

@@ -584,3 +584,45 @@ def test_products_with_a_few_values_the_pieces_cannot_hold_take_no_more_than_twi
     for value in (1e-35, float("inf"), 1e30):
         a[::37, ::41] = value
         assert best() <= 2 * ordinary, value
+
+
+# one nonzero product per sum leaves nothing for errors to hide in: within one rounding of it, also where last pieces are denormal
+# bfloat16 values, at the ends of what the pieces hold, and beyond; denormal products within three units of the last place (the small products
+# of pieces are rounded to it one by one)
+@pytest.mark.parametrize("m,n,k", [(300, 380, 64), (300, 380, 416), (2100, 2300, 176), (4096, 3584, 112)])
+@pytest.mark.parametrize("layout", ["nn", "tn", "nt", "tt"])
+def test_products_of_one_term_are_rounded_once(env, m, n, k, layout):
+    gr, ctx, torch = env
+    rng = np.random.default_rng(53)
+
+    def full(shape, low, high):   # all 24 bits, magnitudes from 2^low to 2^(high + 1)
+        return (rng.choice([-1.0, 1.0], shape) * np.ldexp(1 + rng.integers(0, 1 << 23, shape) / 2.0 ** 23, rng.integers(low, high + 1, shape))).astype(f32)
+
+    ctx.set_option("gemm_clamped", 0)
+    for kind, a, b in (("ordinary", (-3, 3), (-3, 3)), ("denormal last pieces", (-110, -103), (100, 105)), ("just too small", (-112, -111), (100, 105)), ("small", (-51, -49), (-60, -50)),
+                       ("almost denormal", (-64, -62), (-62, -60)), ("denormal products", (-66, -64), (-68, -64)), ("large", (46, 47), (46, 47)), ("just too large", (48, 49), (48, 49))):
+        x, y = full((m, k), *a), np.zeros((k, n), f32)
+        y[np.arange(n) * 7 % k, np.arange(n)] = full(n, *b)
+        ta, tb = (torch.from_numpy(np.ascontiguousarray(v.T if t == "t" else v)).cuda() for v, t in ((x, layout[0]), (y, layout[1])))
+        A, B = ctx.array(ta), ctx.array(tb)
+        out = (gr.transpose(A) if layout[0] == "t" else A) @ (gr.transpose(B) if layout[1] == "t" else B)
+        assert "direct" in out.plan()
+        got = out.numpy()
+        want = x[:, np.arange(n) * 7 % k].astype(np.float64) * y.sum(0, dtype=np.float64)
+        assert (np.abs(got - want) <= 2.0 ** -24 * (1 + 2.0 ** -6) * np.abs(want) + (3 * 2.0 ** -149 if a[0] + b[0] < -120 else 0)).all(), kind
+    ctx.set_option("gemm_clamped", 1)
+
+
+@pytest.mark.parametrize("m,n,k", [(512, 640, 4096), (2100, 2300, 2048), (4096, 4096, 4096)])
+def test_products_of_positive_operands_do_not_lean_to_one_side(env, m, n, k):
+    # K / 2 roundings of a sum that grows evenly: 2^-24 / sqrt(3) times the root of K / 2 / 3, half as much again allowed
+    gr, ctx, torch = env
+    torch.manual_seed(54)
+    a, b = torch.rand(m, k, device="cuda"), torch.rand(k, n, device="cuda")
+    ctx.set_option("gemm_clamped", 0)
+    out = ctx.array(a) @ ctx.array(b)
+    assert "direct" in out.plan()
+    got = torch.from_numpy(out.numpy()).cuda().double()
+    ctx.set_option("gemm_clamped", 1)
+    want = a.double() @ b.double()
+    assert float((got - want).norm() / want.norm()) <= 1.5 * 2.0 ** -24 / 3 * (k / 2) ** 0.5
