@@ -171,6 +171,7 @@ gr_status make_plan_uncached(gr_ctx* c, Node* root, Plan* plan);  // plan.cpp
 void clear_planned(Plan* plan);
 gr_status expand_patch(gr_ctx* c, GroupPlan* g);
 std::string describe_plan(const Plan& plan);
+size_t scratch_need(const Plan& plan, const Node* root, bool tight);  // runtime.cpp: bytes of the static scratch array
 
 // codegen.cpp
 std::string generate_source(const GroupPlan& g);

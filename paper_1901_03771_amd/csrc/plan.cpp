@@ -1819,8 +1819,9 @@ static bool same_value(const GroupPlan& A, int a, const GroupPlan& B, int b, std
 // (us for a variance, two passes / one: 100003 x 257 44.2 / 27.3, 8192^2 93 / 51, 3977 x 7342 55 / 36, 16384 x 512 18.3 / 14.1, 768 x 444 14.6 / 10.5,
 // 64 x 8192 9.9 / 8.5, 1000003 x 4 20.5 / 16.5, 100 x 30 8.8 / 8.7; column standardisation of 100003 x 257 88 / 72.)
 // Where the sums take the wide kernel (outputs enough to fill the chip in one launch each) they stay apart, and where the partial results,
-// three per split instead of one, could crowd the static scratch array.
-static void fuse_moments(gr_ctx* c, Plan* plan) {
+// three per split instead of one for each sum, could crowd the static scratch array: where they are large, and where the request
+// fits it with the sums apart and not with them together.
+static void fuse_moments(gr_ctx* c, Plan* plan, const Node* root) {
   if (!c->opt_moments || !c->opt_fusion) return;
   for (size_t i = 0; i + 1 < plan->groups.size(); ++i) {
     GroupPlan& A = *plan->groups[i];
@@ -1854,9 +1855,13 @@ static void fuse_moments(gr_ctx* c, Plan* plan) {
     }
     std::map<std::pair<int, int>, bool> known;
     if (!own || at != 0 || !same_value(A, pa.value, B, B.prog[d].a, &known)) continue;
+    const size_t apart[2] = {scratch_need(*plan, root, false), scratch_need(*plan, root, true)};
     A.pair = std::move(plan->groups[i + 1]);
     plan->groups.erase(plan->groups.begin() + i + 1);
-    make_signature(&A);
+    bool crowded = false;
+    for (int tight = 0; tight < 2; ++tight) crowded = crowded || (apart[tight] <= kStaticScratchBytes && scratch_need(*plan, root, tight != 0) > kStaticScratchBytes);
+    if (crowded) plan->groups.insert(plan->groups.begin() + i + 1, std::move(A.pair));   // (A stays where it is: the list has had this length)
+    else make_signature(&A);
   }
 }
 
@@ -1904,7 +1909,7 @@ gr_status make_plan_uncached(gr_ctx* c, Node* root, Plan* plan) {
       plan->out_honoured = !plan->out || (!plan->groups.empty() && plan->groups.back()->root == root && plan->groups.back()->kind == GroupKind::MAP &&
                                           map_source(root) == root);
       fuse_gemv_pairs(c, plan);
-      fuse_moments(c, plan);
+      fuse_moments(c, plan, root);
       return GR_OK;
     }
   }

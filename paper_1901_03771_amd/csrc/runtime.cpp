@@ -792,7 +792,7 @@ static void static_unbind(gr_ctx* c, Plan* plan) {
 
 // Bytes of the static scratch array that the stored results of earlier sub-graphs and the partial results of two-stage kernels of
 // a request take, whose own result goes to the caller's buffer.
-static size_t scratch_need(const Plan& plan, const Node* root, bool tight) {
+size_t scratch_need(const Plan& plan, const Node* root, bool tight) {
   auto blocks = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
   size_t need = 0;
   for (const auto& gp : plan.groups) {

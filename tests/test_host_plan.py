@@ -474,6 +474,20 @@ def test_products_take_the_same_kernel_within_the_static_scratch(ctx, m, k, n, l
     assert _served_without_allocating(ctx, prog, prog) == "GR_OK", ctx.last_error()
 
 
+def test_column_variances_need_no_more_static_scratch_than_two_passes(ctx):
+    # beside a stored result of 12 to 16 MiB: what is served without allocating with the sums apart is served with them together
+    ctx.set_option("dry_run", 2)
+    served = {}
+    for moments in (0, 1):
+        ctx.set_option("moments", moments)
+        for rows in range(12000, 16600, 50):
+            x, z = ctx.spec((100003, 257)), ctx.spec((rows, 257))
+            y = gr.var(x, 0) + gr.sum(gr.cumsum(z, 0), 0)
+            served[moments, rows] = gr.STATUS[gr.lib().gr_materialize_into_static(ctx._p, y.h, ctypes.c_void_p(0x500000000000), 257 * 4)]
+    assert {s for s in served.values()} == {"GR_OK", "GR_ERR_OOM"}
+    assert all(served[1, rows] == served[0, rows] for rows in range(12000, 16600, 50))
+
+
 # ------------------------------------------------- code generation on the host ----
 def _specs(ctx, arrays):
     code = {np.dtype(np.float32): gr.GR_F32, np.dtype(np.int32): gr.GR_I32}
