@@ -768,7 +768,7 @@ static void choose_in_place(GroupPlan* g) {
 // split the epilogue, which runs when the products are done (a second launch hides it behind its traffic): 4096 x 784 x 512 with a bias and
 // tanh 40.5 clamped, 38 direct in two parts.  (us, direct / this: 512^3 15.5 / 11.3, 1024 x 512 x 512 17.5 / 14.2, 224 x 192 x 1856 12.8 / 8.5,
 // 528 x 208 x 2320 14.7 / 14.7, 448 x 768 x 1456 23.0 / 22.8; stay: 368 x 2160 x 1296 28.3 / 32.8, 1296 x 3264 x 208 26.8 / 35.2, 3056 x 448 x 896 27.7 / 31.8,
-// 2048^3 119 / 151.  The choice missed the faster one of 45 products by 5 % at most, 4096 x 784 x 512 plain 37.8 / 39.6.)
+// 2048^3 119 / 151.  The choice missed the faster one of 45 products by 7 % at most, 4096 x 784 x 512 plain 36.3 / 38.9.)
 // `wanted`: splits of K that the larger tiles would take if they may store any number of partial tiles.  It decides
 // between the kernels, so that a request that must not allocate takes the kernel that the same request would take
 // otherwise (and that is loaded by then); g->slabs, which stays within its scratch array, bounds the splits.
@@ -1327,12 +1327,12 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         // The same kernel with 128 x 128 tiles and K divided over `slabs`
         // workgroups per tile where that fills the compute units more evenly or at all.  The count is the one with the
         // lowest cost in a model fitted to measurements (microseconds): rounds of 256 workgroups times the
-        // steps of one workgroup at 0.75 per step (two groups of waves, pieces; 0.6 to 0.9 measured) or 0.95 (one group, float32), plus, for a
+        // steps of one workgroup at 0.85 per step (two groups of waves, pieces) or 0.95 (one group, float32), plus, for a
         // split product, 6 for the second launch and the traffic of the partial tiles at 5 TB/s.  A larger count has to beat a smaller one by 3 %.  Every split holds at least 128 values of k, the last
         // one at least two steps; the partial tiles stay below 1 GiB (within the static scratch array for a request that must not
         // allocate).
         // (measured, us: 784 x 4096 x 512 by 8 splits 38.8, 44.4 with float32 instructions by 9; 2080 x 2368 x 512 by 3 50, 57 by 7;
-        // 512 x 4096 x 512 by 16 27.2, 29.8; 1536^3 in one 78, with float32 instructions by 3 75; 3072^3 by 3 444, in one 525, float32 instructions both)
+        // 512 x 4096 x 512 by 16 27.2, 29.8; 1536^3 in one 78, by 3 (float32 instructions) 76; 3072^3 by 3 444, in one 525, float32 instructions both)
         const int64_t tiles128 = ((g->M + 127) / 128) * ((g->N + 127) / 128);
         auto cheapest = [&](int64_t room, int least) {   // room: floats of partial tiles
           double best = 0;
@@ -1341,7 +1341,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
             const int64_t kch = gemm_split_extent(g->K, ks);
             if (ks > 1 && (kch < 128 || g->K - (ks - 1) * kch < 32 || (int64_t)ks * g->M * g->N > room)) continue;
             const int64_t wgs = tiles128 * ks, rnd = (wgs + 255) / 256, steps = (kch + 15) / 16;
-            const double cost = (double)rnd * (double)steps * (wgs <= 256 ? 0.75 : 0.95) + (ks > 1 ? 6.0 + (double)ks * (double)g->M * (double)g->N * 8.0 / 5e6 : 0.0);
+            const double cost = (double)rnd * (double)steps * (wgs <= 256 ? 0.85 : 0.95) + (ks > 1 ? 6.0 + (double)ks * (double)g->M * (double)g->N * 8.0 / 5e6 : 0.0);
             if (best_ks == 0 || cost < best * 0.97) { best = cost; best_ks = ks; }
           }
           return best_ks;
