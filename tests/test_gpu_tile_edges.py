@@ -371,14 +371,14 @@ def test_assignments_not_evaluated_in_place(env):
     def stepped(u, w):
         u[2:, ::2] = u[:-2, ::2] + 1
 
-    def turned(u, w):
-        u[1:, 1:] = u.T[:-1, :-1] if u.shape[0] == u.shape[1] else u[:-1, :-1].T.T * 3
+    def twice_turned(u, w):
+        u[1:, 1:] = u[:-1, :-1].T.T * 3
 
     def overwritten_scalar(u, w):
         u[:, :] = u[3:4, 4:5] + u * 1
 
     ctx.set_option("profile", 1)
-    for f in (other, wide, stepped, overwritten_scalar, turned):
+    for f in (other, wide, stepped, overwritten_scalar, twice_turned):
         x, y = a.copy(), a.copy()
         t, w = torch.from_numpy(x).cuda(), torch.from_numpy(b).cuda()
         ctx.profile_reset()
@@ -390,7 +390,32 @@ def test_assignments_not_evaluated_in_place(env):
                 np.ndarray.__setitem__(self, key, np.array(value))
         f(y.view(Copy), b)
         assert np.array_equal(t.cpu().numpy(), y), f.__name__
-        assert saved == (1 if f is turned else 0), f.__name__   # (transposed twice is not turned)
+        assert saved == (1 if f is twice_turned else 0), f.__name__   # (transposed twice is not turned)
+    ctx.set_option("profile", 0)
+
+
+@pytest.mark.parametrize("n", [20, 64, 300])
+def test_assignments_of_turned_values_and_to_turned_arrays(env, n):
+    # the destination read across: copied back; a transposed view written from positions beside: the value is written
+    # with the view's strides, its elements are not contiguous along its rows
+    gr, ctx, torch = env
+    programs = {
+        "turned": lambda u, xp: (u, np.s_[1:, 1:], (u.T if xp is np else gr.transpose(u))[:-1, :-1] * 3),
+        "turned onto itself": lambda u, xp: (u, np.s_[:, :], (u.T if xp is np else gr.transpose(u)) - u),
+        "to a transposed view": lambda u, xp: ((u.T if xp is np else gr.transpose(u)), np.s_[1:, :], (u.T if xp is np else gr.transpose(u))[:-1, :] * 2),
+    }
+    ctx.set_option("profile", 1)
+    for name, program in programs.items():
+        a = np.random.default_rng(34).integers(-50, 50, (n, n)).astype(f32)
+        t = torch.from_numpy(a.copy()).cuda()
+        ctx.profile_reset()
+        to, box, value = program(ctx.array(t), gr)
+        to[box] = value
+        ctx.sync()
+        to, box, value = program(a, np)
+        to[box] = value.copy()
+        assert np.array_equal(t.cpu().numpy(), a), name
+        assert ctx.profile_read("gr_map_save")[0] == 0, name
     ctx.set_option("profile", 0)
 
 

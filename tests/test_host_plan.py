@@ -887,11 +887,15 @@ def test_column_sums_bound_the_chain_of_additions(ctx, rows):
 
 def _registers(out, tmp_path):
     """(vector registers, bytes of scratch memory) per lane of the request's first kernel, compiled with the library's options."""
+    return _registers_of(out.source(0), tmp_path)
+
+
+def _registers_of(source, tmp_path):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not found")
     src, asm = tmp_path / "k.hip", tmp_path / "k.s"
-    src.write_text("#include <hip/hip_runtime.h>\n" + out.source(0))
+    src.write_text("#include <hip/hip_runtime.h>\n" + source)
     subprocess.run([hipcc, "--offload-arch=gfx950", "-O3", "-ffp-contract=off", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                     "-S", "--cuda-device-only", "-o", str(asm), str(src)], check=True, capture_output=True, timeout=600)
     text = asm.read_text()
@@ -905,6 +909,46 @@ def test_column_sums_of_many_arrays_keep_to_registers(ctx, tmp_path, arrays):
     for t in x[1:]:
         value = value * t + gr.exp(t)
     assert _registers(gr.sum(value, axis=0), tmp_path)[1] == 0
+
+
+@pytest.mark.parametrize("layout", ["nn", "tn", "nt", "tt"])
+@pytest.mark.parametrize("m,k,n,lanes", [(2048, 1024, 2048, 512), (3000, 512, 2048, 256), (4096, 1024, 4096, 256)])
+def test_direct_products_keep_their_sums_in_registers(ctx, tmp_path, layout, m, k, n, lanes):
+    # two groups of waves (two waves per SIMD: 256 registers each), one (three workgroups per compute unit: 168), and tiles of 256 x 256
+    def product():
+        a, b = ctx.spec((m, k) if layout[0] == "n" else (k, m)), ctx.spec((k, n) if layout[1] == "n" else (n, k))
+        return (a if layout[0] == "n" else a.T) @ (b if layout[1] == "n" else b.T)
+
+    long = product()
+    for _ in range(2):
+        long = gr.erf(gr.tanh(long) * 0.5) + gr.exp(-abs(long)) * gr.log(abs(long) + 1.0)
+    for out in (product(), long + ctx.spec((n,))):
+        assert "direct" in out.plan() and f"__launch_bounds__({lanes}" in out.source(0)
+        vgprs, scratch = _registers(out, tmp_path)
+        assert scratch == 0 and vgprs <= {512: 256, 256: 168 if m == 3000 else 512}[lanes]
+
+
+IN_PLACE_VALUES = {
+    "five points": lambda u: (np.s_[1:-1, 1:-1], 0.2 * (u[1:-1, 1:-1] + u[:-2, 1:-1] + u[1:-1, 2:] + u[1:-1, :-2] + u[2:, 1:-1])),
+    "nine by nine points": lambda u: (np.s_[4:-4, 4:-4], sum((u[i:u.shape[0] - 8 + i, j:u.shape[1] - 8 + j] * (0.01 * (i + 1)) for i in range(9) for j in range(9)), u[4:-4, 4:-4])),
+    "a long point function": lambda u: (np.s_[1:, :], gr.erf(gr.tanh(u[:-1]) * 0.5) + gr.exp(-abs(u[1:])) * gr.log(abs(u[:-1]) + 1.0)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(IN_PLACE_VALUES))
+def test_assignments_in_place_keep_their_values_in_registers(ctx, tmp_path, capfd, monkeypatch, name):
+    monkeypatch.setenv("GR_LOG", "1")
+    monkeypatch.setenv("GR_CACHE_DIR", str(tmp_path / "kernels"))
+    monkeypatch.setenv("GR_KERNEL_PACK", "")
+    ctx.set_option("dry_run", 1)
+    ctx.set_option("interp", 0)
+    u = ctx.spec((4096, 4096))
+    box, value = IN_PLACE_VALUES[name](u)
+    capfd.readouterr()
+    u[box] = value
+    source = capfd.readouterr().err.split("---- generated kernel ----\n")[-1]
+    assert "gr_map_save" in source
+    assert _registers_of(source, tmp_path)[1] == 0
 
 
 @pytest.mark.parametrize("arrays", [1, 2, 3, 5, 6, 8, 9, 12])
