@@ -1820,7 +1820,9 @@ static bool same_value(const GroupPlan& A, int a, const GroupPlan& B, int b, std
 // 64 x 8192 9.9 / 8.5, 1000003 x 4 20.5 / 16.5, 100 x 30 8.8 / 8.7; column standardisation of 100003 x 257 88 / 72.)
 // Where the sums take the wide kernel (outputs enough to fill the chip in one launch each) they stay apart, and where the partial results,
 // three per split instead of one for each sum, could crowd the static scratch array: where they are large, and where the request
-// fits it with the sums apart and not with them together.
+// fits it with the sums apart and not with them together.  So do those of many arrays, whose values the registers of 512 lanes do not hold beside
+// the means and squares (us, two passes / one, 20011 x 514 by arrays: of exp 12 241 / 192, 16 311 / 303, 20 382 / 403, 24 485 / 580; of
+// sums 16 293 / 162, 32 623 / 453, 40 888 / 792).
 static void fuse_moments(gr_ctx* c, Plan* plan, const Node* root) {
   if (!c->opt_moments || !c->opt_fusion) return;
   for (size_t i = 0; i + 1 < plan->groups.size(); ++i) {
@@ -1834,6 +1836,13 @@ static void fuse_moments(gr_ctx* c, Plan* plan, const Node* root) {
     const Phase& pa = A.phases[0];
     const Phase& pb = B.phases[0];
     if (pa.op != GR_SUM || pb.op != GR_SUM || pa.out_dtype != GR_F32 || pb.out_dtype != GR_F32 || pa.in_dtype != GR_F32 || pb.in_dtype != GR_F32) continue;
+    int loads = 0;
+    bool heavy = false;
+    for (const Instr& in : A.prog) {
+      loads += in.kind == IKind::LOAD;
+      heavy = heavy || heavy_op(in);
+    }
+    if (loads > (heavy ? 16 : 40)) continue;
     const Instr& q = B.prog[pb.value];
     int d = -1;
     if (q.kind == IKind::UNARY && q.op == GR_SQUARE) d = q.a;

@@ -967,6 +967,21 @@ def test_columns_with_their_squared_deviations_compile_for_any_number_of_loads(c
     assert _registers(out, tmp_path)[1] == 0
 
 
+def test_columns_of_many_arrays_and_their_squared_deviations_stay_apart(ctx):
+    def fused(arrays, f):
+        x = [ctx.spec((4096, 512)) for _ in range(arrays)]
+
+        def value():
+            v = f(x[0])
+            for t in x[1:]:
+                v = v + t * 0.5
+            return v
+        return "fused-with" in gr.sum(gr.square(value() - gr.sum(value(), 0, True) / 4096), 0).plan()
+
+    assert [fused(n, gr.exp) for n in (1, 16, 17, 40)] == [True, True, False, False]
+    assert [fused(n, abs) for n in (1, 17, 40, 41, 150)] == [True, True, True, False, False]
+
+
 def test_columns_of_a_neighbourhood_with_their_squared_deviations_compile(ctx):
     x = ctx.spec((1002, 514))
 
