@@ -2530,8 +2530,9 @@ void split_helpers(Em& e) {
 //     group per compute unit would be two: 3000 x 512 x 2048 72 us for 65 with float32 instructions).
 //     (us, float32 instructions / pieces; relative error against 64 bits: 2048^3 132 / 119.5, 8.1e-7 / 1.9e-7; 4096 x 512 x 784 41.8 / 34.7,
 //     4.1e-7 / 9.3e-8; 784 x 4096 x 512 44.4 / 38.8; 512 x 2848 x 2352 70 / 60.  With six products and one sum 101, 31.3, 35.4 and 52.)
-//     Per wave and step 221 vector instructions, 32 of them conversions at half rate, 1010 cycles, and 32 matrix instructions, 1024: of 119.5 us
-//     the matrix cores of 2048^3 work 55, the vector units as long, mostly one after the other.
+//     Per wave and step 221 vector instructions, 32 of them conversions at half rate, 1010 cycles, and 32 matrix instructions, 1024. Bound by
+//     both and by the clock that this load leaves (counters, 2048^3: of 200 thousand cycles the matrix cores work 66 %, the vector
+//     units 69 %, both at once 40 %; 200 thousand cycles in 118 us are 1.7 GHz, where the float32 kernel runs at 2.3).
 // The direct loads are written as assembly: the compiler's own form of them makes it wait for every outstanding
 // LDS read before each use (it counts them as LDS traffic that may return out of order).  Their completion is
 // tracked by hand: the wait before a step's barrier leaves only the loads of the newest tile in flight.
