@@ -1328,9 +1328,9 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         // workgroups per tile where that fills the compute units more evenly or at all.  The count is the one with the
         // lowest cost in a model fitted to measurements (microseconds): rounds of 256 workgroups times the
         // steps of one workgroup at 0.85 per step (two groups of waves, pieces) or 0.95 (one group, float32), plus, for a
-        // split product, 6 for the second launch and the traffic of the partial tiles at 5 TB/s.  A larger count has to beat a smaller one by 3 %.  Every split holds at least 128 values of k, the last
-        // one at least two steps; the partial tiles stay below 1 GiB (within the static scratch array for a request that must not
-        // allocate).
+        // split product, 6 for the second launch and the traffic of the partial tiles at 5 TB/s.  A larger count has to beat a smaller one
+        // by 3 %.  Every split holds at least 128 values of k, the last one at least two steps; the partial tiles stay below 1 GiB
+        // (within the static scratch array for a request that must not allocate).
         // (measured, us: 784 x 4096 x 512 by 8 splits 38.8, 44.4 with float32 instructions by 9; 2080 x 2368 x 512 by 3 50, 57 by 7;
         // 512 x 4096 x 512 by 16 27.2, 29.8; 1536^3 in one 78, by 3 (float32 instructions) 76; 3072^3 by 3 444, in one 525, float32 instructions both)
         const int64_t tiles128 = ((g->M + 127) / 128) * ((g->N + 127) / 128);
