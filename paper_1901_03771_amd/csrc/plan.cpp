@@ -1816,8 +1816,8 @@ static bool same_value(const GroupPlan& A, int a, const GroupPlan& B, int b, std
 // Column sums S of v whose mean is what the next sub-graph takes v's squared deviations from (var, std and what divides by
 // them): sums of (v - S / n)^2 with n the reduced elements.  One pass over the operands gives both; the sub-graph list, the
 // materialised nodes and the sums are the same.  Bound by HBM like the sums alone; a launch or two less for small arrays.
-// (us for a variance, two passes / one: 100003 x 257 44.2 / 27.3, 8192^2 93 / 51, 3977 x 7342 55 / 36, 16384 x 512 18.3 / 14.1, 768 x 444 14.6 / 10.5,
-// 64 x 8192 9.9 / 8.5, 1000003 x 4 20.5 / 16.5, 100 x 30 8.8 / 8.7; column standardisation of 100003 x 257 88 / 72.)
+// (us for a variance, two passes / one: 100003 x 257 44.4 / 28.6, 8192^2 93.6 / 51.5, 3977 x 7342 55 / 36, 16384 x 512 18.3 / 14.1, 3000 x 1000 18.6 / 14.1,
+// 768 x 444 14.8 / 10.3, 64 x 8192 9.9 / 8.5, 1000003 x 4 20.3 / 17.1, 100 x 30 8.8 / 8.7; column standardisation of 100003 x 257 88 / 73.)
 // Where the sums take the wide kernel (outputs enough to fill the chip in one launch each) they stay apart, and where the partial results,
 // three per split instead of one for each sum, could crowd the static scratch array: where they are large, and where the request
 // fits it with the sums apart and not with them together.  So do those of many arrays, whose values the registers of 512 lanes do not hold beside
