@@ -2471,7 +2471,7 @@ void gemm_combine(Em& e, const EpiLoad& epi_load);
 // nearest (eight bits, so that the last one is exact).  The matrix cores multiply bfloat16 pairs exactly and add them
 // in float32 at sixteen times the float32 rate; eight of the nine products of pieces, all but l l, which is below 2^-34 of the
 // product, take half of the time of float32 instructions.  Two things keep the sums at least as near 64 bits as those instructions'
-// for any operands: the pieces lean to neither side (with a first piece that is cut off the small products of positive operands
+// for any operands (results below 2^-122 apart, three units of the smallest denormal at most): the pieces lean to neither side (with a first piece that is cut off the small products of positive operands
 // are all positive, and are lost where the sum has outgrown them: uniform values, K = 4096, 3.6e-6 for 8.4e-7), and the products below h h have
 // sums of their own, because these matrix instructions do not round to nearest as float32 ones do (a single product per sum, 2048^3
 // times a diagonal matrix: largest relative error of an element 6.0e-8 with float32 instructions, 1.2e-7 with all
