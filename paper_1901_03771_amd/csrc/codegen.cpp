@@ -175,6 +175,14 @@ struct Em {
     if (p.in_dtype == GR_F32) return std::string(p.op == GR_MAX ? "gr_maxf(" : "gr_minf(") + acc + ", " + x + ")";
     return "(" + acc + (p.op == GR_MAX ? " >= " : " <= ") + x + " ? " + acc + " : " + x + ")";
   }
+  // acc combined with the value of phase `s`, whose name (or, of a sum of squares, its root's) `name` gives
+  template <class F>
+  static std::string accumulate(const GroupPlan& g, int s, const std::string& acc, const F& name) {
+    const Phase& p = g.phases[s];
+    const int root = square_root_of(g, s);
+    if (root >= 0) return "__builtin_fmaf(" + name(root) + ", " + name(root) + ", " + acc + ")";
+    return combine(p, acc, name(p.value));
+  }
   static std::string identity(const Phase& p) {
     if (p.op == GR_SUM) return p.out_dtype == GR_F32 ? "0.0f" : (p.out_dtype == GR_I64 ? "0ll" : "0");
     if (p.in_dtype == GR_F32) return p.op == GR_MAX ? "(-__builtin_inff())" : "__builtin_inff()";
@@ -778,6 +786,7 @@ void gen_rowred_pairs(Em& e) {
       e.o << "));\n";
     }
   }
+  const int summed = square_root_of(g, 0) >= 0 ? square_root_of(g, 0) : ph.value;
   // leaves of the butterfly in the order in which lane 0 meets them, the rows of UJ results side by side
   int next = 0;
   std::function<int(int, int)> tree = [&](int off, int stride) -> int {
@@ -789,14 +798,14 @@ void gen_rowred_pairs(Em& e) {
         for (int q = 0; q < 4 && 4 * off + q < K; ++q) {
           const int k = 4 * off + q;
           e.o << "    {\n";
-          emit_scalar_program(e, g.prog, {ph.value},
+          emit_scalar_program(e, g.prog, {summed},
                               [&](const Instr& in, int id) -> std::string {
                                 const AccessGroup& ag = g.groups[in.group];
                                 if (!ag.structural_zero[ld]) return "x" + std::to_string(id) + "_" + std::to_string(ag.structural_zero[2] ? 0 : k);
                                 return "pu" + std::to_string(id) + "_" + std::to_string(j) + "[" + kexpr(in, k) + "]";
                               },
                               "0.0f", "v", "      ");
-          e.o << "      " << acc << " = " << Em::combine(ph, acc, "v" + std::to_string(ph.value)) << ";\n    }\n";
+          e.o << "      " << acc << " = " << Em::accumulate(g, 0, acc, [](int i) { return "v" + std::to_string(i); }) << ";\n    }\n";
         }
       }
       return me;
@@ -1036,7 +1045,7 @@ void gen_rowred(Em& e) {
       }
       if (ph) {
         // (long rows: the elements of a position in pairs first, which shortens the chain of additions to a quarter)
-        std::string upd = RT == 1024 ? "c4[j] = " + name(want, true) + ";" : "acc" + std::to_string(s) + " = " + Em::combine(*ph, "acc" + std::to_string(s), name(want, true)) + ";";
+        std::string upd = RT == 1024 ? "c4[j] = " + name(want, true) + ";" : "acc" + std::to_string(s) + " = " + Em::accumulate(g, s, "acc" + std::to_string(s), [&](int i) { return name(i, true); }) + ";";
         if (guarded && RT == 1024) e.o << "      c4[j] = " << Em::identity(*ph) << ";\n";
         if (guarded) e.o << "      if (c + j < C) " << upd << "\n";
         else e.o << "      " << upd << "\n";

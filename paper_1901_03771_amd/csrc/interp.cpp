@@ -4,6 +4,7 @@
 // over the values' live ranges, and launches the precompiled kernels.
 #include <algorithm>
 
+#include "codegen.h"
 #include "ctx.h"
 #include "interp.h"
 
@@ -240,8 +241,10 @@ bool interp_encode_rowred(const GroupPlan& g, void* out_ptr, GrInterpRowArgs* R,
       R->phase_op[s] = ph.op == GR_SUM ? 0 : (ph.op == GR_MAX ? 1 : 2);
       R->phase_int[s] = ph.in_dtype == GR_I32;
     }
+    const int root = final ? -1 : square_root_of(g, s);
+    if (!final) R->phase_square[s] = root >= 0;
     R->seg_begin[s] = ni;
-    R->seg_slot[s] = encode_segment(g, g.prog, final ? g.results[0] : g.phases[s].value, &R->m, &ni, &nl);
+    R->seg_slot[s] = encode_segment(g, g.prog, final ? g.results[0] : (root >= 0 ? root : g.phases[s].value), &R->m, &ni, &nl);
     R->seg_end[s] = ni;
     if (R->seg_slot[s] < 0) return false;
   }

@@ -47,6 +47,7 @@ struct GrInterpRowArgs {
   int seg_end[GR_INTERP_PHASES + 1];
   int seg_slot[GR_INTERP_PHASES + 1];
   int phase_op[GR_INTERP_PHASES];            // 0 sum, 1 max, 2 min
+  int phase_square[GR_INTERP_PHASES];        // the phase sums the squares of the segment's values, with fused multiply-adds
   int phase_int[GR_INTERP_PHASES];           // the phase combines i32 values (else f32)
   int per_row;                               // one output value per row (else one per element)
   int lanes;                                 // lanes per row and vec4 positions per lane: those of the generated kernel

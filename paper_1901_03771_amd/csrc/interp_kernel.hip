@@ -218,6 +218,7 @@ __global__ __launch_bounds__(256) void gr_interp_rowred_kernel(GrInterpRowArgs A
         if (c >= C) continue;
         gi_run(a, A.seg_begin[s], A.seg_end[s], c, idx, my, red[rslot]);
         if (RT == 1024) c4[j] = my[A.seg_slot[s] * 256];
+        else if (A.phase_square[s]) { const float x = __uint_as_float(my[A.seg_slot[s] * 256]); acc = __float_as_uint(__builtin_fmaf(x, x, __uint_as_float(acc))); }
         else acc = gi_combine(op, is_int, acc, my[A.seg_slot[s] * 256]);
       }
       // (pairs first, as the generated kernel combines a position of a long row)

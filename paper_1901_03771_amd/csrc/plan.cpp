@@ -1980,4 +1980,24 @@ std::string describe_plan(const Plan& plan) {
   return s.str();
 }
 
+int square_root_of(const GroupPlan& g, int s) {
+  const Phase& ph = g.phases[s];
+  if (g.kind != GroupKind::ROWRED || g.row_threads == 1024 || ph.op != GR_SUM || ph.in_dtype != GR_F32 || ph.out_dtype != GR_F32 || ph.value < 0) return -1;
+  const Instr& v = g.prog[ph.value];
+  if (!(v.kind == IKind::UNARY && v.op == GR_SQUARE) && !(v.kind == IKind::BINARY && v.op == GR_MUL && v.a == v.b)) return -1;
+  // (a square that an earlier phase has computed is kept, its root may not be)
+  std::vector<char> seen(g.prog.size(), 0);
+  std::vector<int> work;
+  for (int q = 0; q < s; ++q) work.push_back(g.phases[q].value);
+  while (!work.empty()) {
+    const int i = work.back();
+    work.pop_back();
+    if (i < 0 || seen[i]) continue;
+    seen[i] = 1;
+    work.push_back(g.prog[i].a);
+    work.push_back(g.prog[i].b);
+  }
+  return seen[ph.value] ? -1 : v.a;
+}
+
 }  // namespace gr

@@ -178,6 +178,24 @@ def test_rows_over_pairs(env, n, c, d, kernels):
     assert np.array_equal(got, ref)
 
 
+# sums of squares over rows: every count of lanes, rows that do not fill them, short of one position and over several
+@pytest.mark.parametrize("shape", [(700, 1), (500, 3), (300, 7), (1000, 30), (65, 64), (33, 250), (40, 1027), (9, 5000), (5, 16384)])
+def test_row_sums_of_squares(env, shape):
+    gr, ctx, torch = env
+    a = positive(shape, 21)
+    a[0, -1], a[1, 0], a[2, 0], a[3, 0], a[4, 0] = np.inf, np.nan, 2e19, -1e-30, -np.inf   # (a square that overflows, one that underflows)
+    other = gr.Context()
+    other.set_option("interp", 2)
+    t = torch.from_numpy(a).cuda()
+    for program in (lambda xp, a: xp.sum(a * a, axis=1), lambda xp, a: xp.sum(xp.square(a), axis=1) + 0.5, lambda xp, a: a * a / xp.sum(a * a, axis=1, keepdims=True),
+                    lambda xp, a: xp.sum((a - 0.25) ** 2, axis=1) / (xp.sum(a, axis=1) + 1.0)):
+        got, ref = both(env, program, a=a)
+        assert reduction_check(got, ref)[0].all()
+        assert np.array_equal(program(gr, other.array(t)).numpy(), got, equal_nan=True)    # the interpreter: the same bits
+    other.sync()
+    other.close()
+
+
 # lines of a few lane groups: positions that stick out of the line by every count, one to four positions, both widths of
 # group; lines that do not fill the last workgroup
 @pytest.mark.parametrize("shape", [(3, 4), (17, 5), (40, 63), (33, 64), (37, 65), (50, 66), (21, 67), (16, 144), (7, 255), (5, 256), (9, 257), (100, 511), (6, 513),
