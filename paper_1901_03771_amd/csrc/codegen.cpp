@@ -1137,14 +1137,45 @@ void reduce_combine(Em& e, const std::string& squares = "") {
   e.o << "  const long long NOUT = " << e.S(e.L.extra) << ", NSPLIT = " << e.S(e.L.extra + 3) << " & 0xffffffffll;\n";
   e.o << "  const GM " << T << "* const ws = (const GM " << T << "*)" << e.slot(e.L.extra + 2) << ";\n";
   e.o << "  GM " << T << "* const out = (GM " << T << "*)" << e.slot(e.L.out) << ";\n";
-  e.o << "  __shared__ long long gr_sm[4];\n";
-  if (!squares.empty())
+  const bool moments = !squares.empty();
+  if (moments)
     // means and sums of squares about them follow the sums, one per split and output each; the elements per split are known
     e.o << "  const long long LEN = " << e.S(e.L.extra + 1) << ", chunk = (LEN + NSPLIT - 1) / NSPLIT;\n"
            "  const GM float* const wu = ws + NSPLIT * NOUT; const GM float* const wm = wu + NSPLIT * NOUT;\n"
            "  GM float* const sq = (GM float*)" << squares << ";\n"
-           "  auto count = [&](long long s) { const long long left = LEN - s * chunk; return (float)(left < 0 ? 0 : (left < chunk ? left : chunk)); };\n"
-           "  if (NOUT >= 1024) {\n"
+           "  auto count = [&](long long s) { const long long left = LEN - s * chunk; return (float)(left < 0 ? 0 : (left < chunk ? left : chunk)); };\n";
+  // Bound by latency.  Many outputs and many splits: 16 lanes across neighbouring outputs (64 bytes of a split's results) by 16 along
+  // the splits, a lane's loads in flight four at a time (a lane per output took all splits in turn, three times over with squares: 25000 x
+  // 1024 variances 45.8 -> 28.1 us, sums 24.9 -> 21.3).
+  e.o << "  if (NOUT >= 1024 && NSPLIT >= " << kCombineSplits << ") {\n"
+         "    const unsigned tx = threadIdx.x % 16, ty = threadIdx.x / 16;\n"
+         "    const long long oraw = (long long)blockIdx.x * 16 + tx, o = oraw < NOUT ? oraw : NOUT - 1;\n"
+         "    __shared__ " << T << " part[16][17];\n"
+         "    auto fold = [&](" << T << " v) {\n      part[ty][tx] = v;\n      __syncthreads();\n      " << T << " w[16];\n"
+         "#pragma unroll\n      for (int q = 0; q < 16; ++q) w[q] = part[q][tx];\n"
+         "#pragma unroll\n      for (int d = 1; d < 16; d *= 2)\n"
+         "#pragma unroll\n        for (int q = 0; q < 16; q += 2 * d) w[q] = gr_comb0(w[q], w[q + d]);\n"
+         "      __syncthreads();\n      return w[0];\n    };\n"
+         "    " << T << " acc = " << Em::identity(ph) << ";\n";
+  if (moments)
+    // (a lane's first four splits stay in registers for the second look)
+    e.o << "    float u[4], m2[4], t = 0.0f, m = 0.0f;\n"
+           "    for (long long s0 = ty; s0 < NSPLIT; s0 += 64) {\n      float x[4], y[4], z[4];\n"
+           "#pragma unroll\n      for (int i = 0; i < 4; ++i) { const long long s = s0 + 16 * i, p = s < NSPLIT ? s : s0; x[i] = ws[p * NOUT + o]; y[i] = wu[p * NOUT + o]; z[i] = wm[p * NOUT + o]; }\n"
+           "#pragma unroll\n      for (int i = 0; i < 4; ++i) { if (s0 + 16 * i < NSPLIT) { acc += x[i]; t += count(s0 + 16 * i) * y[i]; } if (s0 == ty) { u[i] = y[i]; m2[i] = z[i]; } }\n    }\n"
+           "    t = fold(t) / (float)LEN;\n    const float over = gr_overflow(t);\n"
+           "    for (long long s0 = ty; s0 < NSPLIT; s0 += 64) {\n      if (s0 != ty) {\n"
+           "#pragma unroll\n        for (int i = 0; i < 4; ++i) { const long long s = s0 + 16 * i, p = s < NSPLIT ? s : s0; u[i] = wu[p * NOUT + o]; m2[i] = wm[p * NOUT + o]; }\n      }\n"
+           "#pragma unroll\n      for (int i = 0; i < 4; ++i) { const long long s = s0 + 16 * i; const float d = u[i] - t, w = m2[i] + count(s) * d * d; m += s < NSPLIT ? w : 0.0f; }\n    }\n"
+           "    m = fold(m) + over;\n";
+  else
+    e.o << "    for (long long s0 = ty; s0 < NSPLIT; s0 += 64) {\n      " << T << " x[4];\n"
+           "#pragma unroll\n      for (int i = 0; i < 4; ++i) { const long long s = s0 + 16 * i; x[i] = ws[(s < NSPLIT ? s : s0) * NOUT + o]; }\n"
+           "#pragma unroll\n      for (int i = 0; i < 4; ++i) if (s0 + 16 * i < NSPLIT) acc = gr_comb0(acc, x[i]);\n    }\n";
+  e.o << "    acc = fold(acc);\n    if (ty == 0 && oraw < NOUT) {\n" << (moments ? "      sq[o] = gr_squares(acc, m);\n" : "") << "      out[o] = acc;\n    }\n    return;\n  }\n"
+         "  __shared__ long long gr_sm[4];\n";
+  if (moments)
+    e.o << "  if (NOUT >= 1024) {\n"
            "    const long long o = (long long)blockIdx.x * 256 + threadIdx.x;\n    if (o < NOUT) {\n"
            "      float a[8] = {0, 0, 0, 0, 0, 0, 0, 0};\n"
            "      for (long long s = 0; s < NSPLIT; s += 8)\n"
@@ -1155,13 +1186,19 @@ void reduce_combine(Em& e, const std::string& squares = "") {
            "      for (long long s = 0; s < NSPLIT; s += 8)\n"
            "#pragma unroll\n        for (int i = 0; i < 8; ++i) { const bool in = s + i < NSPLIT; const long long p = in ? s + i : 0; const float d = wu[p * NOUT + o] - t, w = wm[p * NOUT + o] + count(p) * d * d; a[i] += in ? w : 0.0f; }\n"
            "      sq[o] = (((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]))) + over;\n    }\n  } else {\n"
-           "    const long long o = blockIdx.x;\n    float* const sm = (float*)gr_sm;\n    float t = 0.0f, m = 0.0f;\n"
-           "    for (long long s = threadIdx.x; s < NSPLIT; s += 256) t += count(s) * wu[s * NOUT + o];\n"
-           "    t = gr_lanes0(t);\n    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = t;\n    __syncthreads();\n"
-           "    t = ((sm[0] + sm[1]) + (sm[2] + sm[3])) / (float)LEN;\n    __syncthreads();\n    const float over = gr_overflow(t);\n"
-           "    for (long long s = threadIdx.x; s < NSPLIT; s += 256) { const float d = wu[s * NOUT + o] - t; m += wm[s * NOUT + o] + count(s) * d * d; }\n"
+           // (a lane's first two splits, all of them as a rule, loaded at once and kept for the second look: three round trips to memory
+           // of 2 us each were one after the other)
+           "    const long long o = blockIdx.x;\n    float* const sm = (float*)gr_sm;\n    float acc = 0.0f, t = 0.0f, m = 0.0f, u[2], m2[2];\n"
+           "    for (long long s0 = threadIdx.x; s0 < NSPLIT; s0 += 512) {\n      float x[2], y[2], z[2];\n"
+           "#pragma unroll\n      for (int i = 0; i < 2; ++i) { const long long s = s0 + 256 * i, p = s < NSPLIT ? s : s0; x[i] = ws[p * NOUT + o]; y[i] = wu[p * NOUT + o]; z[i] = wm[p * NOUT + o]; }\n"
+           "#pragma unroll\n      for (int i = 0; i < 2; ++i) { if (s0 + 256 * i < NSPLIT) { acc += x[i]; t += count(s0 + 256 * i) * y[i]; } if (s0 == threadIdx.x) { u[i] = y[i]; m2[i] = z[i]; } }\n    }\n"
+           "    t = gr_lanes0(t);\n    acc = gr_lanes0(acc);\n    if ((threadIdx.x & 63) == 0) { sm[threadIdx.x >> 6] = t; sm[4 + (threadIdx.x >> 6)] = acc; }\n    __syncthreads();\n"
+           "    t = ((sm[0] + sm[1]) + (sm[2] + sm[3])) / (float)LEN;\n    acc = (sm[4] + sm[5]) + (sm[6] + sm[7]);\n    __syncthreads();\n    const float over = gr_overflow(t);\n"
+           "    for (long long s0 = threadIdx.x; s0 < NSPLIT; s0 += 512) {\n      if (s0 != threadIdx.x) {\n"
+           "#pragma unroll\n        for (int i = 0; i < 2; ++i) { const long long s = s0 + 256 * i, p = s < NSPLIT ? s : s0; u[i] = wu[p * NOUT + o]; m2[i] = wm[p * NOUT + o]; }\n      }\n"
+           "#pragma unroll\n      for (int i = 0; i < 2; ++i) { const long long s = s0 + 256 * i; const float d = u[i] - t, w = m2[i] + count(s) * d * d; m += s < NSPLIT ? w : 0.0f; }\n    }\n"
            "    m = gr_lanes0(m);\n    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;\n    __syncthreads();\n"
-           "    if (threadIdx.x == 0) sq[o] = ((sm[0] + sm[1]) + (sm[2] + sm[3])) + over;\n    __syncthreads();\n  }\n";
+           "    if (threadIdx.x == 0) { sq[o] = gr_squares(acc, ((sm[0] + sm[1]) + (sm[2] + sm[3])) + over); out[o] = acc; }\n    return;\n  }\n";
   e.o << "  if (NOUT >= 1024) {\n"
          "    const long long o = (long long)blockIdx.x * 256 + threadIdx.x;\n"
          "    if (o < NOUT) {\n      " << T << " acc = ws[o];\n"
@@ -1174,16 +1211,16 @@ void reduce_combine(Em& e, const std::string& squares = "") {
          "      for (; s < NSPLIT; ++s) acc = gr_comb0(acc, ws[s * NOUT + o]);\n"
       << (squares.empty() ? "" : "      sq[o] = gr_squares(acc, sq[o]);\n")
       << "      out[o] = acc;\n    }\n"
-         "  } else {\n"
-         "    const long long o = blockIdx.x;\n    " << T << " acc = " << Em::identity(ph) << ";\n"
-         "    for (long long s = threadIdx.x; s < NSPLIT; s += 256) acc = gr_comb0(acc, ws[s * NOUT + o]);\n"
-         "    acc = gr_lanes0(acc);\n"
-         "    " << T << "* sm = (" << T << "*)gr_sm;\n"
-         "    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = acc;\n"
-         "    __syncthreads();\n"
-         "    if (threadIdx.x == 0) {\n      acc = gr_comb0(gr_comb0(sm[0], sm[1]), gr_comb0(sm[2], sm[3]));\n      out[o] = acc;\n"
-      << (squares.empty() ? "" : "      sq[o] = gr_squares(acc, sq[o]);\n")
-      << "    }\n  }\n}\n";
+         "    return;\n  }\n";
+  if (!moments)
+    e.o << "  const long long o = blockIdx.x;\n  " << T << " acc = " << Em::identity(ph) << ";\n"
+           "  for (long long s = threadIdx.x; s < NSPLIT; s += 256) acc = gr_comb0(acc, ws[s * NOUT + o]);\n"
+           "  acc = gr_lanes0(acc);\n"
+           "  " << T << "* sm = (" << T << "*)gr_sm;\n"
+           "  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = acc;\n"
+           "  __syncthreads();\n"
+           "  if (threadIdx.x == 0) out[o] = gr_comb0(gr_comb0(sm[0], sm[1]), gr_comb0(sm[2], sm[3]));\n";
+  e.o << "}\n";
 }
 
 // One kernel of mode 0 (see gen_reduce_columns).  Loads in flight per lane and array: U, written out, all first (a wave-wide

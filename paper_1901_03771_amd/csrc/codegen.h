@@ -36,6 +36,9 @@ constexpr int kPairSpread = 16;
 // Lanes of a workgroup of the column reductions (REDUCE mode 0).
 constexpr int kReduceLanes = 512;
 
+// Splits of a reduction from which on the kernel that combines the partial results of 1024 outputs and more takes several lanes per output.
+constexpr int kCombineSplits = 16;
+
 // 'Z': no leaf dimension follows this iteration dimension; '1': unit stride; 'G': anything else.
 char access_class(const AccessGroup& ag, int dim);
 

@@ -642,7 +642,9 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
       gr_status st = g.red_mode == 0 && g.red_wide ? launch(c, k->fn3, k->name + "_wide", units * slabs, s, kReduceLanes)
                                                   : launch(c, k->fn, k->name, units * slabs, s, g.red_mode == 0 ? kReduceLanes : 256);
       if (st != GR_OK || slabs <= 1) return st;
-      return launch(c, k->fn2, k->name + "_combine", g.red_out >= 1024 ? (g.red_out + 255) / 256 : g.red_out, s);
+      // (a workgroup per output, 16 outputs or 256: see reduce_combine)
+      const int64_t outputs = g.red_out < 1024 ? 1 : (slabs >= kCombineSplits ? 16 : 256);
+      return launch(c, k->fn2, k->name + "_combine", (g.red_out + outputs - 1) / outputs, s);
     }
     case GroupKind::SCAN: {
       if (total == 0) return GR_OK;

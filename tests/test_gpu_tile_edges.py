@@ -196,6 +196,31 @@ def test_row_sums_of_squares(env, shape):
     other.close()
 
 
+# partial results of 1024 outputs and more: splits just below the several lanes per output and at them, one round of them and more, a last
+# workgroup of one output
+@pytest.mark.parametrize("shape,splits", [((3840, 1024), 15), ((4096, 1024), 16), ((40000, 1024), 64), ((30000, 1025), 103), ((5000, 2049), 39)])
+def test_partial_results_of_many_columns(env, shape, splits):
+    a = positive(shape, 22)
+    assert f"splits={splits} " in planned(env, lambda xp, a: xp.sum(a, axis=0), a=a).replace("\n", " ") + " "
+    got, ref = both(env, lambda xp, a: xp.sum(a, axis=0), a=a)
+    assert reduction_check(got, ref)[0].all()
+    a[7::11, 3::5] *= -1
+    got, ref = both(env, lambda xp, a: xp.min(a, axis=0), a=a)
+    assert np.array_equal(got, ref)
+    i = np.random.default_rng(23).integers(-2**31, 2**31 - 1, shape, dtype=np.int64).astype(np.int32)
+    got, ref = both(env, lambda xp, i: xp.sum(i, axis=0), i=i)
+    assert np.array_equal(got, ref)
+    gr, ctx, torch = env
+    got = gr.var(ctx.array(torch.from_numpy(a).cuda()), 0).numpy()
+    want = a.astype(np.float64).var(0)
+    assert (np.abs(got - want) <= 60 * 2.0 ** -24 * want).all()   # (the bound of test_columns_with_their_squared_deviations)
+    a[5, 0], a[shape[0] - 1, shape[1] - 1], a[17, 33], a[18, 33] = np.inf, np.nan, np.inf, -np.inf
+    got, ref = both(env, lambda xp, a: xp.sum(a, axis=0), a=a)
+    assert reduction_check(got, ref)[0].all()
+    got = gr.var(ctx.array(torch.from_numpy(a).cuda()), 0).numpy()
+    assert np.isnan(got[[0, 33, shape[1] - 1]]).all() and np.isfinite(got[1:33]).all()
+
+
 # lines of a few lane groups: positions that stick out of the line by every count, one to four positions, both widths of
 # group; lines that do not fill the last workgroup
 @pytest.mark.parametrize("shape", [(3, 4), (17, 5), (40, 63), (33, 64), (37, 65), (50, 66), (21, 67), (16, 144), (7, 255), (5, 256), (9, 257), (100, 511), (6, 513),
