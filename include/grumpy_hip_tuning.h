@@ -46,9 +46,11 @@ extern "C" {
  *   "moments"         1 (default) = sums over an axis that is not the contiguous one and the sums of squared deviations
  *                     from their mean (var, std) come out of one pass; 0 = a pass each
  *   "assign_in_place" 1 (default) = a slice assignment whose value reads the destination's storage up to four rows or
- *                     columns away, and that storage only, is evaluated in place after a launch that saves the cells around its
- *                     tiles (two-dimensional boxes with unit steps along the rows, 32-bit elements); 0 = the
+ *                     columns away, and that storage only, is evaluated in place, after a launch that saves the cells around its
+ *                     tiles where these are many (two-dimensional boxes with unit steps along the rows, 32-bit elements); 0 = the
  *                     value gets a buffer of its own and is copied back
+ *   "assign_polls"    how often a workgroup of such an assignment of few tiles looks whether the tiles around its own have been loaded
+ *                     before it saves the cells that they read and goes on (default 16; 0 to 2^24; results do not depend on it)
  *   "nontemporal"     1 (default) = loads of arrays that are read once carry the non-temporal hint,
  *                     and so do the vector stores of a requested value of 192 MiB or more (not of
  *                     intermediate results of the request; except in kernels that read a transposed

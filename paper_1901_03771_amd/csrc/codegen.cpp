@@ -86,7 +86,7 @@ ArgLayout arg_layout(const GroupPlan& g) {
 
 std::string kernel_name(const GroupPlan& g) {
   switch (g.kind) {
-    case GroupKind::MAP: return "gr_map";
+    case GroupKind::MAP: return g.in_place_once ? "gr_map_save_store" : "gr_map";
     case GroupKind::ROWRED: return "gr_rowred";
     case GroupKind::REDUCE: return "gr_reduce";
     case GroupKind::SCAN: return "gr_scan";
@@ -579,44 +579,71 @@ void gen_map(Em& e) {
 }
 
 // A map that writes the array it reads at positions a few rows and columns away.  A workgroup loads all that its
-// tile needs, waits until all of its waves have, and only then stores; the cells around a tile, which other workgroups
-// write, come from copies that gr_map_save made in a launch before: whole rows above and below every row of tiles, and a few columns
-// on either side of every boundary between tiles of a row.
-// Bound by HBM or the caches: 2 rows saved, and read again, per VR rows read and written.
+// tile needs, waits until all of its waves have, and only then stores.  The cells around a tile, which other workgroups write:
+//
+// - Many tiles: they come from copies that gr_map_save made in a launch before: whole rows above and below every row of tiles, and a
+//   few columns on either side of every boundary between tiles of a row.  Bound by HBM or the caches: 2 rows saved, and read again, per VR
+//   rows read and written.
+//
+// - Few tiles (in_place_once): one launch.  A workgroup marks its tile as loaded and looks at the marks of the tiles around it until they
+//   are loaded too.  It does not look more often than `polls` times, because a tile that it waits for may not have been started: then it
+//   saves the cells of its own tile that others read (while they are still the old ones), marks the tile as saved, and stores.  A workgroup
+//   that finds a tile beside it saved takes the cells there from what was saved; whatever it loaded itself, before it looked, from a tile
+//   that was not marked so is old, since marks precede stores.  So no workgroup depends on another one's progress.  Marks carry the number
+//   of the launch; they and saved cells are written with relaxed agent-scope atomics that have completed (vmcnt) before what they precede
+//   is issued.  Bound by launches: ten sweeps of 760 x 1536 96 -> 69 us, 100 x 300 97 -> 60, 4535 x 400 102 -> 90 by one launch instead of two;
+//   with the memory busy the marks' two round trips take 10 us and hold the chip's workgroups meanwhile: 4096^2 278 -> 345, 8000^2 1030 -> 1960.
 void gen_map_in_place(Em& e) {
   const GroupPlan& g = e.g;
   const int TC = g.BX * 4, TR = g.BY * g.VR, HT = g.halo[0], HB = g.halo[1], HL = g.halo[2], HR = g.halo[3];
   const int off = (HL + 3) / 4 * 4, offr = (HR + 3) / 4 * 4;
   std::ostream& o = e.o;
   const std::string T = cty(g.out_dtype), V4 = vty4(g.out_dtype), V2 = vty2(g.out_dtype);
-  auto head = [&](const char* name) {
-    kernel_head(e, name);
-    o << "  const int C = (int)" << e.dim(1) << ", R = (int)" << e.dim(0) << ", nbx = (C + " << g.cphase + TC - 1 << ") / " << TC << ", nby = (R + " << TR - 1 << ") / " << TR << ";\n"
-         "  const long long orow = " << e.S(e.L.ocoef) << ", pitch = (long long)nbx * " << TC + 0 << " + " << off + offr << ";\n"
-         "  GM " << T << "* const po = (GM " << T << "*)" << e.slot(e.L.out) << " + " << e.S(e.L.obase) << ";\n"
-         "  GM " << T << "* const rows = (GM " << T << "*)" << e.slot(e.L.extra) << ";\n"
-         "  GM " << T << "* const cols = rows + (long long)nby * " << HT + HB << " * pitch;\n  (void)cols; (void)pitch;\n";
-  };
+  const bool once = g.in_place_once;
+  const int PT = in_place_saved(g);   // saved cells per tile
   prelude(e);
-  head("gr_map_save");
-  o << "  unsigned idx = blockIdx.x * 256 + threadIdx.x;\n  const unsigned quads = (unsigned)(pitch / 4), first = quads * (unsigned)nby * " << HT + HB << "u;\n"
-       "  if (idx < first) {\n"
-       "    const int i4 = (int)(idx % quads), line = (int)(idx / quads), h = line % " << std::max(1, HT + HB) << ", by = line / " << std::max(1, HT + HB) << ";\n"
-       "    const int at = h < " << HT << " ? by * " << TR << " - " << HT << " + h : by * " << TR << " + " << TR - HT << " + h, r = at < R + " << HB - 1 << " ? at : R + " << HB - 1 << ";\n"
-       "    const int c = 4 * i4 - " << off + g.cphase << ";\n"
-       "    GM " << T << "* const to = rows + (long long)line * pitch + 4 * i4;\n    const GM " << T << "* const from = po + r * orow;\n"
-       "    if (c >= " << -HL << " && c + 4 <= C + " << HR << ") *(GM " << V4 << "*)to = *(const GM " << V4 << "*)(from + c);\n"
-       "    else for (int j = 0; j < 4; ++j) { const int k = c + j; to[j] = from[k < " << -HL << " ? " << -HL << " : (k < C + " << HR << " ? k : C + " << HR - 1 << ")]; }\n"
-       "    return;\n  }\n";
-  if (HL + HR > 0)
-    o << "  idx -= first;\n  const unsigned lines = (unsigned)R + " << HT + HB << "u;\n"
-         "  if (idx >= lines * (unsigned)(nbx - 1) * " << HL + HR << "u) return;\n"
-         "  const int q = (int)(idx % " << HL + HR << "), line = (int)(idx / " << HL + HR << "), r = (int)(line % lines) - " << HT << ", b = (int)(line / lines);\n"
-         // (a boundary near the end of the rows: columns that no element reads are not there)
-         "  const int c = (b + 1) * " << TC << " - " << g.cphase << " + q - " << HL << ";\n"
-         "  cols[idx] = po[r * orow + (c < C + " << HR << " ? c : C + " << HR - 1 << ")];\n";
-  o << "}\n";
-  head("gr_map");
+  if (once) {
+    auto head = [&](const char* name) {
+      kernel_head(e, name);
+      o << "  const int C = (int)" << e.dim(1) << ", R = (int)" << e.dim(0) << ", nbx = (C + " << g.cphase + TC - 1 << ") / " << TC << ", nby = (R + " << TR - 1 << ") / " << TR << ";\n"
+           "  GM unsigned long long* const marks = (GM unsigned long long*)" << e.slot(e.L.extra + 1) << ";\n";
+    };
+    head("gr_map_clear");
+    o << "  const unsigned i = blockIdx.x * 256 + threadIdx.x;\n  if (i < (unsigned)(nbx * nby)) marks[i] = 0ull;\n}\n";
+    head(kernel_name(g).c_str());
+    o << "  const long long orow = " << e.S(e.L.ocoef) << ";\n"
+         "  GM " << T << "* const po = (GM " << T << "*)" << e.slot(e.L.out) << " + " << e.S(e.L.obase) << ";\n"
+         "  GM " << T << "* const saved = (GM " << T << "*)" << e.slot(e.L.extra) << ";\n"
+         "  const unsigned long long TAG = " << e.slot(e.L.extra + 2) << " << 32;\n  unsigned polls = (unsigned)(" << e.slot(e.L.extra + 2) << " >> 32);\n";
+  } else {
+    auto head = [&](const char* name) {
+      kernel_head(e, name);
+      o << "  const int C = (int)" << e.dim(1) << ", R = (int)" << e.dim(0) << ", nbx = (C + " << g.cphase + TC - 1 << ") / " << TC << ", nby = (R + " << TR - 1 << ") / " << TR << ";\n"
+           "  const long long orow = " << e.S(e.L.ocoef) << ", pitch = (long long)nbx * " << TC + 0 << " + " << off + offr << ";\n"
+           "  GM " << T << "* const po = (GM " << T << "*)" << e.slot(e.L.out) << " + " << e.S(e.L.obase) << ";\n"
+           "  GM " << T << "* const rows = (GM " << T << "*)" << e.slot(e.L.extra) << ";\n"
+           "  GM " << T << "* const cols = rows + (long long)nby * " << HT + HB << " * pitch;\n  (void)cols; (void)pitch;\n";
+    };
+    head("gr_map_save");
+    o << "  unsigned idx = blockIdx.x * 256 + threadIdx.x;\n  const unsigned quads = (unsigned)(pitch / 4), first = quads * (unsigned)nby * " << HT + HB << "u;\n"
+         "  if (idx < first) {\n"
+         "    const int i4 = (int)(idx % quads), line = (int)(idx / quads), h = line % " << std::max(1, HT + HB) << ", by = line / " << std::max(1, HT + HB) << ";\n"
+         "    const int at = h < " << HT << " ? by * " << TR << " - " << HT << " + h : by * " << TR << " + " << TR - HT << " + h, r = at < R + " << HB - 1 << " ? at : R + " << HB - 1 << ";\n"
+         "    const int c = 4 * i4 - " << off + g.cphase << ";\n"
+         "    GM " << T << "* const to = rows + (long long)line * pitch + 4 * i4;\n    const GM " << T << "* const from = po + r * orow;\n"
+         "    if (c >= " << -HL << " && c + 4 <= C + " << HR << ") *(GM " << V4 << "*)to = *(const GM " << V4 << "*)(from + c);\n"
+         "    else for (int j = 0; j < 4; ++j) { const int k = c + j; to[j] = from[k < " << -HL << " ? " << -HL << " : (k < C + " << HR << " ? k : C + " << HR - 1 << ")]; }\n"
+         "    return;\n  }\n";
+    if (HL + HR > 0)
+      o << "  idx -= first;\n  const unsigned lines = (unsigned)R + " << HT + HB << "u;\n"
+           "  if (idx >= lines * (unsigned)(nbx - 1) * " << HL + HR << "u) return;\n"
+           "  const int q = (int)(idx % " << HL + HR << "), line = (int)(idx / " << HL + HR << "), r = (int)(line % lines) - " << HT << ", b = (int)(line / lines);\n"
+           // (a boundary near the end of the rows: columns that no element reads are not there)
+           "  const int c = (b + 1) * " << TC << " - " << g.cphase << " + q - " << HL << ";\n"
+           "  cols[idx] = po[r * orow + (c < C + " << HR << " ? c : C + " << HR - 1 << ")];\n";
+    o << "}\n";
+    head(kernel_name(g).c_str());
+  }
   o << "  const unsigned ntiles = (unsigned)(nbx * nby), per = (ntiles + 7) / 8, tile = (blockIdx.x % 8) * per + blockIdx.x / 8;\n"
        "  if (blockIdx.x / 8 >= per || tile >= ntiles) return;\n"
        "  const int bx = (int)(tile % (unsigned)nbx), by = (int)(tile / (unsigned)nbx), tx = threadIdx.x % " << g.BX << ", ty = " << (g.BY > 1 ? "threadIdx.x / " + std::to_string(g.BX) : std::string("0")) << ";\n"
@@ -646,8 +673,9 @@ void gen_map_in_place(Em& e) {
     else at[(int)in.delta[0] + g.self_row][(int)in.delta[1] + g.self_col] = (int)i;
   }
   auto rn = [](int s) { return s < 0 ? "m" + std::to_string(-s) : std::to_string(s); };
-  std::ostringstream fast, slow, left, right;
+  std::ostringstream fast, slow, left, right, again;
   std::set<int> edge;
+  bool reads[3][3] = {};   // tiles around it that a tile reads
   int nl = 0;
   for (const auto& row : at) {
     const int s = row.first;
@@ -656,7 +684,7 @@ void gen_map_in_place(Em& e) {
     const std::string saved = "rows + (by * " + std::to_string(HT + HB) + "ll + " + std::to_string(h) + ") * pitch + (c0 + " + std::to_string(off + g.cphase) + ")";
     const std::string w = "w" + rn(s);
     o << "  const GM " << T << "* const " << w << " = ";
-    if (s >= 0 && s < g.VR) o << grid;
+    if (once || (s >= 0 && s < g.VR)) o << grid;
     else if (g.BY == 1) o << saved;
     else o << (s < 0 ? "ty == 0" : "ty == " + std::to_string(g.BY - 1)) << " ? (const GM " << T << "*)(" << saved << ") : (const GM " << T << "*)(" << grid << ")";
     o << ";\n";
@@ -677,6 +705,13 @@ void gen_map_in_place(Em& e) {
           name[v[i + pos + q].second] = el;
           edge.insert(c);
           slow << "    " << el << " = " << w << "[k" << rn(c) << "];\n";
+          const int dy = s < 0 ? 0 : (s >= g.VR ? 2 : 1), dx = c < 0 ? 0 : (c >= 4 ? 2 : 1);
+          if (dy != 1 || dx != 1) {
+            reads[dy][1] = reads[dy][1] || dy != 1;
+            reads[1][dx] = reads[1][dx] || dx != 1;
+            reads[dy][dx] = true;
+            again << "    " << el << " = fetch(r0 + " << s << ", c0 + " << c << ", " << el << ");\n";
+          }
           const std::string line = "[(r0 + " + std::to_string(s) + " < rmax ? r0 + " + std::to_string(s) + " : rmax) * " + std::to_string(HL + HR) + "ll + ";
           if (c < 0) left << "    " << el << " = cb" << line << HL + c << "];\n";
           if (c >= 4) right << "    " << el << " = cb" << line << HL + c - 4 << "];\n";
@@ -690,10 +725,48 @@ void gen_map_in_place(Em& e) {
   for (int c : edge) o << "    const int k" << rn(c) << " = (c0 + " << c << " < " << -HL << " ? " << -HL << " : (c0 + " << c << " < C + " << HR << " ? c0 + " << c << " : C + " << HR - 1 << ")) - c0;\n";
   o << slow.str() << "  }\n";
   const std::string cb = "    const GM " + T + "* const cb = cols + ((long long)";
-  if (HL > 0) o << "  if (tx == 0 && bx > 0) {\n" << cb << "(bx - 1) * (R + " << HT + HB << ") + " << HT << ") * " << HL + HR << ";\n" << left.str() << "  }\n";
-  if (HR > 0) o << "  if (tx == " << g.BX - 1 << " && bx + 1 < nbx && live) {\n" << cb << "bx * (R + " << HT + HB << ") + " << HT << ") * " << HL + HR << ";\n" << right.str() << "  }\n";
+  if (HL > 0 && !once) o << "  if (tx == 0 && bx > 0) {\n" << cb << "(bx - 1) * (R + " << HT + HB << ") + " << HT << ") * " << HL + HR << ";\n" << left.str() << "  }\n";
+  if (HR > 0 && !once) o << "  if (tx == " << g.BX - 1 << " && bx + 1 < nbx && live) {\n" << cb << "bx * (R + " << HT + HB << ") + " << HT << ") * " << HL + HR << ";\n" << right.str() << "  }\n";
   // every load of the workgroup has returned before any of its stores is issued
-  o << "  asm volatile(\"s_waitcnt vmcnt(0)\" ::: \"memory\");\n  __syncthreads();\n  if (!live) return;\n";
+  o << "  asm volatile(\"s_waitcnt vmcnt(0)\" ::: \"memory\");\n  __syncthreads();\n";
+  if (once) {
+    o << "  __shared__ unsigned near[9];\n"
+         "  if (threadIdx.x == 0) __hip_atomic_store((unsigned long long*)&marks[tile], TAG | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n"
+         "  if (threadIdx.x < 9) {\n"
+         "    const int y = by + (int)threadIdx.x / 3 - 1, x = bx + (int)threadIdx.x % 3 - 1;\n    unsigned state = 1;\n    constexpr unsigned around = ";
+    unsigned around = 0;   // tiles that it reads, or that read it
+    for (int dy = 0; dy < 3; ++dy) for (int dx = 0; dx < 3; ++dx) if (reads[dy][dx]) around |= 1u << (dy * 3 + dx) | 1u << (8 - dy * 3 - dx);
+    o << around << "u;\n"
+         "    if ((around >> threadIdx.x & 1) && x >= 0 && x < nbx && y >= 0 && y < nby)\n"
+         "      for (;;) {\n        const unsigned long long w = __hip_atomic_load((unsigned long long*)&marks[y * nbx + x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n"
+         "        state = (w ^ TAG) >> 32 ? 0u : (unsigned)w;\n        if (state || !polls) break;\n        --polls;\n        __builtin_amdgcn_s_sleep(1);\n      }\n"
+         "    near[threadIdx.x] = state;\n  }\n  __syncthreads();\n"
+         "  bool waited = true, old = false;\n"
+         "#pragma unroll\n  for (int q = 0; q < 9; ++q) { waited = waited && near[q] != 0; old = old || near[q] == 2; }\n"
+         "  if (!waited) {\n"
+         "    GM unsigned* const to = (GM unsigned*)saved + (long long)tile * " << PT << ";\n"
+         "    for (int i = threadIdx.x; i < " << (HT + HB) * TC << "; i += 256) {\n"
+         "      const int h = i / " << TC << ", r = by * " << TR << " + (h < " << HT << " ? " << TR - HT << " + h : h - " << HT << "), c = bx * " << TC << " - " << g.cphase << " + i % " << TC << ";\n"
+         "      if (r < R && c >= 0 && c < C) __hip_atomic_store((unsigned*)(to + i), *(const GM unsigned*)(po + r * orow + c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n    }\n";
+    if (HL + HR > 0)
+      o << "    for (int i = threadIdx.x; i < " << (HL + HR) * TR << "; i += 256) {\n"
+           "      const int q = i % " << HL + HR << ", r = by * " << TR << " + i / " << HL + HR << ", c = bx * " << TC << " - " << g.cphase << " + (q < " << HL << " ? " << TC - HL << " + q : q - " << HL << ");\n"
+           "      if (r < R && c >= 0 && c < C) __hip_atomic_store((unsigned*)(to + " << (HT + HB) * TC << " + i), *(const GM unsigned*)(po + r * orow + c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n    }\n";
+    o << "    asm volatile(\"s_waitcnt vmcnt(0)\" ::: \"memory\");\n    __syncthreads();\n"
+         "    if (threadIdx.x == 0) {\n      __hip_atomic_store((unsigned long long*)&marks[tile], TAG | 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n"
+         "      asm volatile(\"s_waitcnt vmcnt(0)\" ::: \"memory\");\n    }\n    __syncthreads();\n  }\n"
+         "  if (!live) return;\n"
+         "  if (old) {\n"
+         "    auto fetch = [&](int r, int c, " << T << " v) -> " << T << " {\n"
+         "      if (r < 0 || r >= R || c < 0 || c >= C) return v;\n"
+         "      const int y = r / " << TR << ", x = (c + " << g.cphase << ") / " << TC << ", dy = y - by, dx = x - bx;\n"
+         "      if (near[4 + 3 * dy + dx] != 2) return v;\n"
+         "      const int lr = r - y * " << TR << ", lc = c + " << g.cphase << " - x * " << TC << ";\n"
+         "      const int at = dy != 0 ? (dy < 0 ? lr - " << TR - HT << " : " << HT << " + lr) * " << TC << " + lc : " << (HT + HB) * TC << " + lr * " << HL + HR << " + (dx < 0 ? lc - " << TC - HL << " : " << HL << " + lc);\n"
+         "      const unsigned w = __hip_atomic_load((unsigned*)saved + (long long)(y * nbx + x) * " << PT << " + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);\n"
+         "      return " << (g.out_dtype == GR_F32 ? "__uint_as_float(w)" : "(int)w") << ";\n    };\n"
+      << again.str() << "  }\n";
+  } else o << "  if (!live) return;\n";
   emit_scalar_program(e, g.prog, g.results, [&](const Instr&, int id) { return name[id]; }, "0", "t", "  ");
   for (int v = 0; v < g.VR; ++v) {
     const int* t = &g.results[(size_t)v * 4];

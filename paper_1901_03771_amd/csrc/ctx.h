@@ -80,6 +80,7 @@ struct gr_ctx {
   int64_t opt_gemm_big = 1;     // matrix products of operands contiguous along one dimension: tiles loaded straight into LDS
   int64_t opt_gemm_clamped = 1; // small or ragged matrix products: tiles of 64 x 64 with clamped loads
   int64_t opt_map_phase = 1;
+  int64_t opt_assign_polls = 16;     // looks of an in-place assignment's workgroup at the marks of the tiles around it before it saves the cells they read
   int64_t opt_scan_polls = 1 << 20;   // polls a tile of a one-pass scan spends on each wait before it recomputes its offset
   uint64_t options_epoch = 0;  // bumped by every gr_ctx_set_option: part of a request's fingerprint
   uintptr_t dry_next = 0x100000;  // fake device addresses handed out by a dry run

@@ -198,6 +198,7 @@ struct GroupPlan {
   int cphase = 0;     // map: lanes own columns 4k - cphase .. 4k - cphase + 3, so that their vector stores are 16-byte aligned in the output
   int stage_mask = 0;                    // MAP: access groups (bit per group) read through a transposing LDS tile
   bool in_place = false;                 // MAP: writes the array that it reads at shifted positions (see gen_map_in_place)
+  bool in_place_once = false;            // in_place: in one launch
   int self_row = 0, self_col = 0;        // in_place: rows and columns from the element written to the one read with shift 0
   int halo[4] = {0};                     // in_place: rows read above and below a tile, columns left and right of it
   int flat = 0;                          // MAP: every patch lies inside the array, the last ones overlap: 1 lanes numbered over
@@ -267,6 +268,15 @@ inline SavedCells saved_cells(const GroupPlan& g) {
   s.rows = s.nby * (g.halo[0] + g.halo[1]) * s.pitch;
   s.cols = (s.nbx - 1) * (R + g.halo[0] + g.halo[1]) * (g.halo[2] + g.halo[3]);
   return s;
+}
+
+// In-place maps in one launch: cells of a tile that others read (rows at its top and bottom, columns at its sides), and tiles.
+inline int in_place_saved(const GroupPlan& g) {
+  return (g.halo[0] + g.halo[1]) * 4 * g.BX + (g.halo[2] + g.halo[3]) * g.BY * g.VR;
+}
+inline int64_t in_place_tiles(const GroupPlan& g) {
+  const int64_t TC = 4 * (int64_t)g.BX, TR = (int64_t)g.BY * g.VR;
+  return ((g.dims[1] + g.cphase + TC - 1) / TC) * ((g.dims[0] + TR - 1) / TR);
 }
 
 struct PlanEntry;

@@ -473,7 +473,7 @@ void make_signature(GroupPlan* g) {
   std::string s;
   s.reserve(256 + 32 * (g->prog.size() + g->prog1.size()));
   for (int64_t v : {(int64_t)g->kind, (int64_t)g->rank, (int64_t)g->out_dtype, (int64_t)g->out_per_row, (int64_t)g->BX, (int64_t)g->BY,
-                    (int64_t)g->VR + (g->kind == GroupKind::GEMM && g->VR == 2 && g->slabs > 1 ? 1024 : 0) /* (the direct-to-LDS product kernels compile the split of K in or out) */, (int64_t)g->UC, (int64_t)g->NP, (int64_t)g->row_threads + 1024 * (int64_t)g->row_iters + (((int64_t)g->pair_k) << 32) + (((int64_t)g->pair_lane) << 40) /* (a pair kernel compiles its row length in) */, (int64_t)g->xcd_remap + 2 * (int64_t)g->stage_mask + (((int64_t)g->tail) << 40) + (((int64_t)g->diag) << 44) + (((int64_t)g->cphase) << 48) + (((int64_t)g->flat) << 52) + (((int64_t)g->in_place) << 56), (int64_t)g->red_mode + 16 * (int64_t)g->red_vec,
+                    (int64_t)g->VR + (g->kind == GroupKind::GEMM && g->VR == 2 && g->slabs > 1 ? 1024 : 0) /* (the direct-to-LDS product kernels compile the split of K in or out) */, (int64_t)g->UC, (int64_t)g->NP, (int64_t)g->row_threads + 1024 * (int64_t)g->row_iters + (((int64_t)g->pair_k) << 32) + (((int64_t)g->pair_lane) << 40) /* (a pair kernel compiles its row length in) */, (int64_t)g->xcd_remap + 2 * (int64_t)g->stage_mask + (((int64_t)g->tail) << 40) + (((int64_t)g->diag) << 44) + (((int64_t)g->cphase) << 48) + (((int64_t)g->flat) << 52) + (((int64_t)g->in_place) << 56) + (((int64_t)g->in_place_once) << 57), (int64_t)g->red_mode + 16 * (int64_t)g->red_vec,
                     (int64_t)g->red_kept_rank, (int64_t)g->gemv_mode, (int64_t)g->LPR, (int64_t)g->KV, (int64_t)g->mat_group,
                     (int64_t)g->vec_group, (int64_t)g->nt, (int64_t)g->unroll, (int64_t)g->scan_mode + 16 * (int64_t)g->scan_vec + (g->scan_mode >= 2 ? 256 * g->scan_chunk : 0) /* (a one-pass scan's tile size is compiled in) */, (int64_t)g->out_unit, (int64_t)g->groups.size()})
     put(s, v);
@@ -713,6 +713,10 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
   g->tail = (g->rank >= 2 && !g->flat && C < 64 && (C & 3) && g->UC == 1 && !g->stage_mask) ? (int)(C & 3) : 0;
 }
 
+// Tiles up to which such a map is one launch: three per compute unit (ten sweeps, us, two launches / one: 252 tiles of 1000^2 96 / 68, 568 of
+// 4535 x 400 102 / 90, 752 of 1500 x 1900 108.5 / 106, 1000 of 2000^2 117 / 116, 2048 of 4096^2 278 / 345).
+constexpr int64_t kOnceTiles = 768;
+
 // A map that is to write the array it reads at shifted positions, element (r, c) from elements a few rows and columns
 // away (a sweep of a stencil over a grid with a single buffer): every array read is a scalar or lies over the output with its strides.
 // Tiles of 256 columns (the narrowest power of two that holds shorter rows) by eight rows per lane: taller patches save and
@@ -720,8 +724,7 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
 // 1024: 37.0, 31.2, 29.0, of 32 rows 36.0; 8192^2 by 256, 512 and 1024 columns, 8 rows: 102, 107, 115).  Four rows where eight
 // would leave compute units without a tile (1000^2: 7.8 against 8.5).
 // (us per sweep, value in a buffer of its own and copied back / in place: 1000^2 9.1 / 7.8, 2000^2 20.0 / 11.8, 4096 x 1024 23.1 / 11.8,
-// 100000 x 130 34.8 / 20.5, 4096^2 49.6 / 27.9, 1024 x 16384 49.1 / 26.9, 8192^2 185 / 102; both are two launches, grids
-// below 512^2 take the host's time for them either way.)
+// 100000 x 130 34.8 / 20.5, 4096^2 49.6 / 27.9, 1024 x 16384 49.1 / 26.9, 8192^2 185 / 102; both with two launches.)
 static void choose_in_place(GroupPlan* g) {
   if (g->rank != 2 || g->orig_rank != 2 || !g->out_unit || g->out_dtype == GR_I64 || g->stage_mask) return;
   const int64_t R = g->dims[0], C = g->dims[1], row = g->out_coef[0];
@@ -751,6 +754,7 @@ static void choose_in_place(GroupPlan* g) {
   const int64_t across = (C + g->cphase + 4 * g->BX - 1) / (4 * g->BX);
   g->VR = across * (R / (8 * (int64_t)g->BY)) >= 256 ? 8 : 4;
   if (saved_cells(*g).rows + saved_cells(*g).cols > (int64_t)1 << 30) g->in_place = false;
+  g->in_place_once = g->in_place && in_place_tiles(*g) <= kOnceTiles;
 }
 
 // Small or ragged matrix products: tiles of 64 x 64 (128 x 32, 32 x 128) with clamped loads (gemm_tile_body), after the

@@ -146,7 +146,7 @@ std::string dump(const std::vector<std::unique_ptr<GroupPlan>>& groups) {
       }
       for (const ConstSlot& cs : g->consts) o << " c" << (int)cs.dtype << ":" << bits_of(cs.value);
       for (const Phase& p : g->phases) o << " ph" << p.op << "," << (int)p.in_dtype << "," << (int)p.out_dtype << "," << p.value << "," << (p.node ? p.node->id : 0);
-      o << "\n out_base=" << g->out_base << " unit=" << g->out_unit << " dt=" << (int)g->out_dtype << " per_row=" << g->out_per_row << " in_place=" << g->in_place << "," << g->self_row << "," << g->self_col << " sched=" << g->BX << ","
+      o << "\n out_base=" << g->out_base << " unit=" << g->out_unit << " dt=" << (int)g->out_dtype << " per_row=" << g->out_per_row << " in_place=" << g->in_place << "," << g->in_place_once << "," << g->self_row << "," << g->self_col << " sched=" << g->BX << ","
         << g->BY << "," << g->VR << "," << g->UC << "," << g->NP << "," << g->row_threads << "," << g->row_iters << "," << g->xcd_remap << "," << g->cphase << "," << g->stage_mask << "," << g->tail << "," << g->flat << "," << g->pair_k << "," << g->pair_lane << "," << g->red_bx << "," << g->red_wide << "," << g->red_tight << "," << g->nt << ","
         << g->red_mode << "," << g->red_vec << "," << g->red_out << "," << g->red_len << "," << g->red_kept_rank << "," << g->scan_mode << "," << g->scan_vec << ","
         << g->scan_chunk << "," << g->scan_nchunk << "," << g->gemv_mode << "," << g->M << "," << g->K << "," << g->N << "," << g->mat_group << ","

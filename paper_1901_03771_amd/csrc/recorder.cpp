@@ -232,6 +232,7 @@ gr_status gr_ctx_set_option(gr_ctx* ctx, const char* key, int64_t value) {
   else if (k == "rowred_rows") ctx->opt_rowred_rows = value;
   else if (k == "moments") ctx->opt_moments = value;
   else if (k == "assign_in_place") ctx->opt_assign_in_place = value;
+  else if (k == "assign_polls") { if (value < 0 || value > ((int64_t)1 << 24)) return fail(ctx, GR_ERR_ARG, "assign_polls: 0 to 2^24"); ctx->opt_assign_polls = value; }
   else if (k == "gemm_bn") ctx->opt_gemm_bn = value;
   else if (k == "gemm_kstep") ctx->opt_gemm_kstep = value;
   else if (k == "gemm_split") ctx->opt_gemm_split = value;

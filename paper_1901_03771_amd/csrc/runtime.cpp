@@ -231,7 +231,7 @@ static void disk_store(const std::string& path, const std::string& key, const st
 static void kernel_entry_points(const GroupPlan& g, std::string* name, bool* combine, int* scan) {
   *name = kernel_name(g);
   *combine = (g.kind == GroupKind::GEMV && g.gemv_mode >= 1) || g.kind == GroupKind::REDUCE || g.kind == GroupKind::GEMM;
-  *scan = g.kind == GroupKind::SCAN ? (g.scan_mode == 4 ? 0 : g.scan_mode >= 2 ? 2 : 1) : (g.kind == GroupKind::REDUCE && g.red_mode == 0 && !g.pair ? 3 : (g.kind == GroupKind::MAP && g.in_place ? 4 : 0));
+  *scan = g.kind == GroupKind::SCAN ? (g.scan_mode == 4 ? 0 : g.scan_mode >= 2 ? 2 : 1) : (g.kind == GroupKind::REDUCE && g.red_mode == 0 && !g.pair ? 3 : (g.kind == GroupKind::MAP && g.in_place ? (g.in_place_once ? 5 : 4) : 0));
 }
 
 // Loads a code object and publishes the kernel in the in-memory cache.
@@ -251,6 +251,7 @@ static gr_status finish_kernel(gr_ctx* c, const std::string& sig, const std::str
     }
     if (scan == 2) GR_HIP(c, hipModuleGetFunction(&k.fn2, k.module, "gr_scan_clear"));
     if (scan == 4) GR_HIP(c, hipModuleGetFunction(&k.fn2, k.module, "gr_map_save"));
+    if (scan == 5) GR_HIP(c, hipModuleGetFunction(&k.fn2, k.module, "gr_map_clear"));
     if (scan == 3) GR_HIP(c, hipModuleGetFunction(&k.fn3, k.module, (k.name + "_wide").c_str()));
   }
   auto ins = c->cache.emplace(sig, std::move(k));
@@ -484,7 +485,9 @@ static int64_t scan_line_tile_cells(const GroupPlan& g) {
 static int reduce_slabs(const GroupPlan& g, bool tight) { return tight && g.red_mode == 0 ? g.red_tight : g.slabs; }
 static size_t workspace_need(const GroupPlan& g, bool tight) {
   switch (g.kind) {
-    case GroupKind::MAP: return g.in_place ? (size_t)(saved_cells(g).rows + saved_cells(g).cols) * 4 : 0;
+    case GroupKind::MAP:
+      if (g.in_place && !g.in_place_once) return (size_t)(saved_cells(g).rows + saved_cells(g).cols) * 4;
+      return g.in_place ? (size_t)in_place_tiles(g) * ((size_t)in_place_saved(g) * 4 + 8) : 0;   // (saved cells, then a mark per tile)
     case GroupKind::REDUCE: return reduce_slabs(g, tight) > 1 && g.red_out > 0 ? (size_t)reduce_slabs(g, tight) * (size_t)g.red_out * itemsize(g.out_dtype) * (g.pair ? 3 : 1) : 0;
     case GroupKind::SCAN: {
       int64_t total = 1;
@@ -540,7 +543,8 @@ static gr_status get_workspace(gr_ctx* c, const GroupPlan& g, void** ws) {
 // and the launch uses tag 1 -- for requests that must not allocate, for requests recorded for
 // replay, and while the caller's stream is being captured into a HIP graph (a replay would repeat
 // the tag, and memset nodes are not recorded here).
-static gr_status scan_cells(gr_ctx* c, const GroupPlan& g, size_t need, void** cells, uint32_t* tag) {
+// `own`: memory that the caller has for such cells (NULL: the workspace).
+static gr_status scan_cells(gr_ctx* c, const GroupPlan& g, size_t need, void** cells, uint32_t* tag, void* own = nullptr) {
   *tag = 0;
   bool plain = c->static_mode || c->capture != nullptr || c->device < 0;
   if (!plain) {
@@ -553,6 +557,7 @@ static gr_status scan_cells(gr_ctx* c, const GroupPlan& g, size_t need, void** c
     // earlier launch has made it large enough (its cells are cleared like any other; tag 1 is older
     // than every launch number still to come)
     if (!c->static_mode && !c->capture && c->device >= 0 && c->scan_cells && need <= c->scan_cells_bytes) { *cells = c->scan_cells; return GR_OK; }
+    if (own) { *cells = own; return GR_OK; }
     return get_workspace(c, g, cells);
   }
   bool zero = false;
@@ -600,9 +605,24 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
         gr_status wst = get_workspace(c, g, &ws);
         if (wst != GR_OK) return wst;
         s[L.extra] = (uint64_t)(uintptr_t)ws;
+      }
+      if (g.in_place && !g.in_place_once) {
         const SavedCells sv = saved_cells(g);
         gr_status st = launch(c, k->fn2, "gr_map_save", (sv.rows / 4 + sv.cols + 255) / 256, s);
         if (st != GR_OK) return st;
+      }
+      if (g.in_place_once) {
+        const int64_t tiles = in_place_tiles(g);
+        void* marks = nullptr;
+        uint32_t tag = 0;
+        gr_status wst = scan_cells(c, g, (size_t)tiles * 8, &marks, &tag, (char*)ws + (size_t)tiles * (size_t)in_place_saved(g) * 4);
+        if (wst != GR_OK) return wst;
+        s[L.extra + 1] = (uint64_t)(uintptr_t)marks;
+        s[L.extra + 2] = (uint64_t)(tag ? tag : 1u) | (uint64_t)c->opt_assign_polls << 32;
+        if (!tag) {
+          gr_status st = launch(c, k->fn2, "gr_map_clear", (tiles + 255) / 256, s);
+          if (st != GR_OK) return st;
+        }
       }
       return launch(c, k->fn, k->name, grid, s);
     }

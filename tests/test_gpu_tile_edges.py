@@ -399,6 +399,27 @@ def test_assignments_evaluated_in_place(env, rows, cols, dtype):
             assert np.array_equal(t.cpu().numpy(), a), (name, window)
 
 
+# few tiles, in one launch: tiles that wait for the ones around them, that look once and save (nearly all of them then, and read what others
+# saved), sweep after sweep; the most tiles of that way, and one more
+@pytest.mark.parametrize("rows,cols", [(70, 1030), (1000, 1000), (1537, 1900), (1538, 1900), (12290, 200)])
+@pytest.mark.parametrize("polls", [0, 1, 16, 1 << 20])
+def test_assignments_in_place_whether_tiles_wait_or_save(env, rows, cols, polls):
+    gr, ctx, torch = env
+    ctx.set_option("assign_polls", polls)
+    try:
+        for name, program in IN_PLACE.items():
+            a = torch.randint(-50, 50, (rows, cols), device="cuda", dtype=torch.int32)
+            want, u = a.clone(), ctx.array(a)
+            for sweep in range(4):
+                box, value = program(u)
+                u[box] = value
+                box, value = program(want)
+                want[box] = value.clone()
+            assert torch.equal(a, want), name
+    finally:
+        ctx.set_option("assign_polls", 16)
+
+
 def test_assignments_not_evaluated_in_place(env):
     # values that read another array as well, other strides, a destination read further away: copied back as before
     gr, ctx, torch = env

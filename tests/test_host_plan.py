@@ -951,6 +951,22 @@ def test_assignments_in_place_keep_their_values_in_registers(ctx, tmp_path, capf
     assert _registers_of(source, tmp_path)[1] == 0
 
 
+@pytest.mark.parametrize("name", sorted(IN_PLACE_VALUES))
+def test_assignments_in_place_of_few_tiles_keep_their_values_in_registers(ctx, tmp_path, capfd, monkeypatch, name):
+    monkeypatch.setenv("GR_LOG", "1")
+    monkeypatch.setenv("GR_CACHE_DIR", str(tmp_path / "kernels"))
+    monkeypatch.setenv("GR_KERNEL_PACK", "")
+    ctx.set_option("dry_run", 1)
+    ctx.set_option("interp", 0)
+    u = ctx.spec((1000, 1000))
+    box, value = IN_PLACE_VALUES[name](u)
+    capfd.readouterr()
+    u[box] = value
+    source = capfd.readouterr().err.split("---- generated kernel ----\n")[-1]
+    assert "gr_map_save_store(" in source
+    assert _registers_of(source, tmp_path)[1] == 0
+
+
 @pytest.mark.parametrize("arrays", [1, 2, 3, 5, 6, 8, 9, 12])
 def test_columns_with_their_squared_deviations_compile_for_any_number_of_loads(ctx, tmp_path, arrays):
     # eight, four, two rows at a time, or one (whose share of a batch is a whole number)
