@@ -36,13 +36,28 @@ namespace gr {
 constexpr size_t kStaticScratchBytes = (size_t)16 << 20;
 }  // namespace gr
 
+namespace gr {
+constexpr size_t kSpareNodes = 4096;
+
+// A request being fingerprinted (plan cache): its nodes in depth-first order, and the fingerprint.
+struct Walk {
+  std::vector<Node*> nodes, stack;
+  std::vector<int64_t> key;
+  std::vector<uint64_t> order;
+  uint64_t hash = 0;
+  void clear() { nodes.clear(); stack.clear(); key.clear(); order.clear(); }
+};
+}  // namespace gr
+
 struct gr_ctx {
   int device = -1;
   hipStream_t stream = nullptr;
   std::string err;
 
   // nodes
-  std::unordered_map<uint64_t, gr::Node*> nodes;
+  gr::NodeTable nodes;
+  std::vector<gr::Node*> spare_nodes;   // of freed nodes, for new ones (kSpareNodes at most)
+  std::vector<gr::Node*> free_work;     // node_maybe_free's list, kept for its memory
   uint64_t next_id = 1;
   bool any_storage_alias = false;  // some node's data has lived inside another node's buffer (direct slice assignment)
   // pending reductions, scans and contractions by expression hash (merging of equal ones at record time)
@@ -121,6 +136,8 @@ struct gr_ctx {
   // plan cache: fingerprint hash -> remembered requests
   std::unordered_multimap<uint64_t, std::unique_ptr<gr::PlanEntry>> plan_cache;
   uint64_t walk_epoch = 0, plan_clock = 0;
+  gr::Walk walk;                        // make_plan's lists, kept for their memory
+  std::vector<uint64_t> launch_args;    // launch_group's argument block, likewise
 
   // workspace for two-stage kernels
   void* workspace = nullptr;

@@ -15,9 +15,19 @@
 
 #include "../../include/grumpy_hip.h"
 
+/* Where a Context keeps the address of its gr_ctx (attribute _cell): 0 once closed.  Every array holds its context's, so that a
+ * recorded operation and a dropped handle reach the library without looking up an attribute. */
 typedef struct {
   PyObject_HEAD
-  PyObject* ctx;   /* the binding's Context object (attribute _addr: address of the gr_ctx, 0 once closed) */
+  unsigned long long address;
+} CellObject;
+
+static PyTypeObject Cell_Type;
+
+typedef struct {
+  PyObject_HEAD
+  PyObject* ctx;   /* the binding's Context object */
+  CellObject* cell;
   unsigned long long h;
   PyObject* owner; /* whatever keeps alive the device memory of the leaves this node still reads: a leaf's
                       tensor, or a tuple of the operands' owners */
@@ -49,19 +59,25 @@ static PyObject* hook_getitem;  /* (a, key) -> Array */
 static PyObject* hook_setitem;  /* (a, key, value) -> None */
 static PyObject* hook_pow;      /* (a, e) -> Array */
 static PyObject* hook_reduce;   /* (op, a, axis, keepdims) -> Array */
-static PyObject* str_addr;
+static PyObject *str_cell, *str_dtype, *str_is_cuda, *str_shape, *str_stride, *str_data_ptr;
 static PyObject* str_check;
 
 #define IS_ARRAY(o) PyObject_TypeCheck((o), &ArrayBase_Type)
 
-/* Address of the gr_ctx behind a Context object; NULL with an exception set if it is closed. */
-static gr_ctx* ctx_of(PyObject* ctx) {
-  PyObject* a = PyObject_GetAttr(ctx, str_addr);
-  if (!a) return NULL;
-  void* p = PyLong_AsVoidPtr(a);
-  Py_DECREF(a);
-  if (!p && !PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, "the context of this array has been closed");
-  return (gr_ctx*)p;
+/* The gr_ctx of a cell; NULL with an exception set if its context is closed. */
+static gr_ctx* open_ctx(CellObject* cell) {
+  if (!cell || !cell->address) {
+    PyErr_SetString(PyExc_RuntimeError, "the context of this array has been closed");
+    return NULL;
+  }
+  return (gr_ctx*)(uintptr_t)cell->address;
+}
+
+/* The cell of a Context object, a new reference; NULL with an exception set. */
+static CellObject* cell_of(PyObject* ctx) {
+  PyObject* c = PyObject_GetAttr(ctx, str_cell);
+  if (c && Py_TYPE(c) != &Cell_Type) { Py_DECREF(c); PyErr_SetString(PyExc_TypeError, "not a context of this binding"); return NULL; }
+  return (CellObject*)c;
 }
 
 /* Raises the binding's error for a non-zero status (Context.check does). */
@@ -84,7 +100,7 @@ static PyObject* merged_owner(PyObject* a, PyObject* b) {
   return PyTuple_Pack(2, a, b);
 }
 
-static PyObject* new_array(PyTypeObject* type, PyObject* ctx, unsigned long long h, PyObject* owner_a, PyObject* owner_b, int view) {
+static PyObject* new_array(PyTypeObject* type, PyObject* ctx, CellObject* cell, unsigned long long h, PyObject* owner_a, PyObject* owner_b, int view) {
   ArrayObject* a = (ArrayObject*)type->tp_alloc(type, 0);
   PyObject* owner = NULL;
   if (a && (owner_a || owner_b)) {
@@ -92,12 +108,13 @@ static PyObject* new_array(PyTypeObject* type, PyObject* ctx, unsigned long long
     if (!owner && PyErr_Occurred()) { Py_DECREF(a); a = NULL; }
   }
   if (!a) {
-    gr_ctx* c = ctx_of(ctx);
-    if (c) p_release(c, h); else PyErr_Clear();
+    if (cell->address) p_release((gr_ctx*)(uintptr_t)cell->address, h);
     return PyErr_NoMemory();
   }
   Py_INCREF(ctx);
+  Py_INCREF(cell);
   a->ctx = ctx;
+  a->cell = cell;
   a->h = h;
   a->owner = owner;
   a->view = (char)view;
@@ -109,27 +126,23 @@ static int array_init(ArrayObject* self, PyObject* args, PyObject* kw) {
   unsigned long long h;
   if (kw && PyDict_Size(kw)) { PyErr_SetString(PyExc_TypeError, "Array(ctx, handle)"); return -1; }
   if (!PyArg_ParseTuple(args, "OK", &ctx, &h)) return -1;
+  CellObject* cell = cell_of(ctx);
+  if (!cell) return -1;
   Py_INCREF(ctx);
   Py_XSETREF(self->ctx, ctx);
+  Py_XSETREF(self->cell, cell);
   self->h = h;
   return 0;
 }
 
 static void array_dealloc(ArrayObject* self) {
-  if (self->ctx) {
-    PyObject *et, *ev, *tb;
-    PyErr_Fetch(&et, &ev, &tb);
-    PyObject* a = PyObject_GetAttr(self->ctx, str_addr);
-    if (a) {
-      void* p = PyLong_AsVoidPtr(a);
-      Py_DECREF(a);
-      if (p && p_release) p_release((gr_ctx*)p, self->h);
-    }
-    PyErr_Clear();
-    PyErr_Restore(et, ev, tb);
-  }
+  if (self->cell && self->cell->address && p_release) p_release((gr_ctx*)(uintptr_t)self->cell->address, self->h);
+  PyObject *et, *ev, *tb;
+  PyErr_Fetch(&et, &ev, &tb);
   Py_CLEAR(self->ctx);
+  Py_CLEAR(self->cell);
   Py_CLEAR(self->owner);
+  PyErr_Restore(et, ev, tb);
   Py_TYPE(self)->tp_free((PyObject*)self);
 }
 
@@ -153,28 +166,28 @@ static PyObject* do_binary(int op, PyObject* a, PyObject* b) {
     if (IS_ARRAY(b)) {
       ArrayObject* y = (ArrayObject*)b;
       if (x->ctx != y->ctx) { PyErr_SetString(PyExc_ValueError, "arrays belong to different contexts"); return NULL; }
-      gr_ctx* c = ctx_of(x->ctx);
+      gr_ctx* c = open_ctx(x->cell);
       if (!c) return NULL;
       st = p_binary(c, (gr_op)op, x->h, y->h, &out);
     } else {
       double v; int is_int;
       if (!as_scalar(b, &v, &is_int)) return PyObject_CallFunction(hook_binary, "iOO", op, a, b);
-      gr_ctx* c = ctx_of(x->ctx);
+      gr_ctx* c = open_ctx(x->cell);
       if (!c) return NULL;
       st = p_binary_scalar(c, (gr_op)op, x->h, v, is_int, 0, &out);
     }
     if (st) return raise_status(x->ctx, st);
-    return new_array(Py_TYPE(a), x->ctx, out, x->owner, IS_ARRAY(b) ? ((ArrayObject*)b)->owner : NULL, 0);
+    return new_array(Py_TYPE(a), x->ctx, x->cell, out, x->owner, IS_ARRAY(b) ? ((ArrayObject*)b)->owner : NULL, 0);
   }
   if (IS_ARRAY(b)) {
     ArrayObject* y = (ArrayObject*)b;
     double v; int is_int;
     if (!as_scalar(a, &v, &is_int)) return PyObject_CallFunction(hook_binary, "iOO", op, a, b);
-    gr_ctx* c = ctx_of(y->ctx);
+    gr_ctx* c = open_ctx(y->cell);
     if (!c) return NULL;
     st = p_binary_scalar(c, (gr_op)op, y->h, v, is_int, 1, &out);
     if (st) return raise_status(y->ctx, st);
-    return new_array(Py_TYPE(b), y->ctx, out, y->owner, NULL, 0);
+    return new_array(Py_TYPE(b), y->ctx, y->cell, out, y->owner, NULL, 0);
   }
   return PyObject_CallFunction(hook_binary, "iOO", op, a, b);
 }
@@ -182,12 +195,12 @@ static PyObject* do_binary(int op, PyObject* a, PyObject* b) {
 static PyObject* do_unary(int op, PyObject* a) {
   if (!IS_ARRAY(a)) { PyErr_SetString(PyExc_TypeError, "no array operand"); return NULL; }
   ArrayObject* x = (ArrayObject*)a;
-  gr_ctx* c = ctx_of(x->ctx);
+  gr_ctx* c = open_ctx(x->cell);
   if (!c) return NULL;
   gr_array out = 0;
   int st = p_unary(c, (gr_op)op, x->h, &out);
   if (st) return raise_status(x->ctx, st);
-  return new_array(Py_TYPE(a), x->ctx, out, x->owner, NULL, 0);
+  return new_array(Py_TYPE(a), x->ctx, x->cell, out, x->owner, NULL, 0);
 }
 
 static PyObject* nb_add(PyObject* a, PyObject* b) { return do_binary(GR_ADD, a, b); }
@@ -210,12 +223,12 @@ static PyObject* nb_matmul(PyObject* a, PyObject* b) {
   if (!IS_ARRAY(a) || !IS_ARRAY(b)) { PyErr_SetString(PyExc_TypeError, "dot: both operands must be arrays"); return NULL; }
   ArrayObject *x = (ArrayObject*)a, *y = (ArrayObject*)b;
   if (x->ctx != y->ctx) { PyErr_SetString(PyExc_ValueError, "arrays belong to different contexts"); return NULL; }
-  gr_ctx* c = ctx_of(x->ctx);
+  gr_ctx* c = open_ctx(x->cell);
   if (!c) return NULL;
   gr_array out = 0;
   int st = p_dot(c, x->h, y->h, &out);
   if (st) return raise_status(x->ctx, st);
-  return new_array(Py_TYPE(a), x->ctx, out, x->owner, y->owner, 0);
+  return new_array(Py_TYPE(a), x->ctx, x->cell, out, x->owner, y->owner, 0);
 }
 
 /* Index key -> gr_slice arguments.  1 = parsed, 0 = not a tuple of slices of ints (use the hook), -1 = error. */
@@ -253,12 +266,12 @@ static PyObject* array_subscript(PyObject* a, PyObject* key) {
   int ok = parse_key(key, &n, start, stop, step, hs, he);
   if (ok < 0) return NULL;
   if (!ok) return PyObject_CallFunction(hook_getitem, "OO", a, key);
-  gr_ctx* c = ctx_of(x->ctx);
+  gr_ctx* c = open_ctx(x->cell);
   if (!c) return NULL;
   gr_array out = 0;
   int st = p_slice(c, x->h, n, start, stop, step, hs, he, &out);
   if (st) return raise_status(x->ctx, st);
-  return new_array(Py_TYPE(a), x->ctx, out, x->owner, NULL, 1);
+  return new_array(Py_TYPE(a), x->ctx, x->cell, out, x->owner, NULL, 1);
 }
 
 static int array_ass_subscript(PyObject* a, PyObject* key, PyObject* value) {
@@ -275,7 +288,7 @@ static int array_ass_subscript(PyObject* a, PyObject* key, PyObject* value) {
     Py_DECREF(r);
     return 0;
   }
-  gr_ctx* c = ctx_of(x->ctx);
+  gr_ctx* c = open_ctx(x->cell);
   if (!c) return -1;
   gr_array dst = 0;
   int st = p_slice(c, x->h, n, start, stop, step, hs, he, &dst);
@@ -289,7 +302,7 @@ static int array_ass_subscript(PyObject* a, PyObject* key, PyObject* value) {
 
 static PyObject* array_materialize(PyObject* a, PyObject* unused) {
   ArrayObject* x = (ArrayObject*)a;
-  gr_ctx* c = ctx_of(x->ctx);
+  gr_ctx* c = open_ctx(x->cell);
   if (!c) return NULL;
   int st = p_materialize(c, x->h);
   if (st) return raise_status(x->ctx, st);
@@ -301,13 +314,15 @@ static PyObject* array_materialize(PyObject* a, PyObject* unused) {
 /* _materialize_into(address, bytes, tensor, static): gr_materialize_into (or its non-allocating variant) into the
  * caller's buffer.  An array that had no storage is bound to that buffer and lets go of its inputs: the tensor
  * becomes what keeps it alive.  One that had storage (and every view) is only copied and keeps what it had. */
-static PyObject* array_materialize_into(PyObject* a, PyObject* args) {
+static PyObject* array_materialize_into(PyObject* a, PyObject* const* args, Py_ssize_t nargs) {
   ArrayObject* x = (ArrayObject*)a;
-  unsigned long long ptr, nbytes;
-  PyObject* tensor;
-  int is_static = 0;
-  if (!PyArg_ParseTuple(args, "KKO|p", &ptr, &nbytes, &tensor, &is_static)) return NULL;
-  gr_ctx* c = ctx_of(x->ctx);
+  if (nargs < 3 || nargs > 4) { PyErr_SetString(PyExc_TypeError, "_materialize_into(address, bytes, tensor, static)"); return NULL; }
+  const unsigned long long ptr = PyLong_AsUnsignedLongLong(args[0]), nbytes = PyLong_AsUnsignedLongLong(args[1]);
+  if (PyErr_Occurred()) return NULL;
+  PyObject* tensor = args[2];
+  const int is_static = nargs > 3 ? PyObject_IsTrue(args[3]) : 0;
+  if (is_static < 0) return NULL;
+  gr_ctx* c = open_ctx(x->cell);
   if (!c) return NULL;
   int had = 1;
   if (!x->view) {
@@ -323,17 +338,17 @@ static PyObject* array_materialize_into(PyObject* a, PyObject* args) {
 
 static PyObject* array_T(PyObject* a, void* unused) {
   ArrayObject* x = (ArrayObject*)a;
-  gr_ctx* c = ctx_of(x->ctx);
+  gr_ctx* c = open_ctx(x->cell);
   if (!c) return NULL;
   gr_array out = 0;
   int st = p_transpose(c, x->h, NULL, &out);
   if (st) return raise_status(x->ctx, st);
-  return new_array(Py_TYPE(a), x->ctx, out, x->owner, NULL, 1);
+  return new_array(Py_TYPE(a), x->ctx, x->cell, out, x->owner, NULL, 1);
 }
 
 static PyObject* array_ndim(PyObject* a, void* unused) {
   ArrayObject* x = (ArrayObject*)a;
-  gr_ctx* c = ctx_of(x->ctx);
+  gr_ctx* c = open_ctx(x->cell);
   if (!c) return NULL;
   int n = 0;
   int st = p_ndim(c, x->h, &n);
@@ -343,7 +358,7 @@ static PyObject* array_ndim(PyObject* a, void* unused) {
 
 static PyObject* array_shape(PyObject* a, void* unused) {
   ArrayObject* x = (ArrayObject*)a;
-  gr_ctx* c = ctx_of(x->ctx);
+  gr_ctx* c = open_ctx(x->cell);
   if (!c) return NULL;
   int n = 0;
   int64_t shape[GR_MAX_NDIM];
@@ -361,10 +376,11 @@ static PyObject* array_shape(PyObject* a, void* unused) {
 }
 
 /* reduce(op, a, axis, keepdims): axis None (all axes), an int, or a sequence of ints */
-static PyObject* mod_reduce(PyObject* m, PyObject* args) {
-  int op, keep;
-  PyObject *a, *axis;
-  if (!PyArg_ParseTuple(args, "iOOp", &op, &a, &axis, &keep)) return NULL;
+static PyObject* mod_reduce(PyObject* m, PyObject* const* args, Py_ssize_t nargs) {
+  if (nargs != 4) { PyErr_SetString(PyExc_TypeError, "reduce(op, a, axis, keepdims)"); return NULL; }
+  PyObject *a = args[1], *axis = args[2];
+  const int op = (int)PyLong_AsLong(args[0]), keep = PyObject_IsTrue(args[3]);
+  if (keep < 0 || PyErr_Occurred()) return NULL;
   if (!IS_ARRAY(a)) { PyErr_SetString(PyExc_TypeError, "no array operand"); return NULL; }
   ArrayObject* x = (ArrayObject*)a;
   int axes[GR_MAX_NDIM + 1], n = 0;
@@ -388,12 +404,12 @@ static PyObject* mod_reduce(PyObject* m, PyObject* args) {
     n = (int)cnt;
     Py_DECREF(seq);
   }
-  gr_ctx* c = ctx_of(x->ctx);
+  gr_ctx* c = open_ctx(x->cell);
   if (!c) return NULL;
   gr_array out = 0;
   int st = p_reduce(c, (gr_op)op, x->h, axes, n, keep, &out);
   if (st) return raise_status(x->ctx, st);
-  return new_array(Py_TYPE(a), x->ctx, out, x->owner, NULL, 0);
+  return new_array(Py_TYPE(a), x->ctx, x->cell, out, x->owner, NULL, 0);
 }
 
 /* A tuple of plain integers as int64 values; 0 if it is anything else (no exception set). */
@@ -408,33 +424,65 @@ static int int64_tuple(PyObject* t, Py_ssize_t n, int64_t* out) {
   return 1;
 }
 
+/* An array over device memory described by Python objects; NULL without an exception for descriptions that this file does not
+ * marshal (the ctypes route takes them). */
+static PyObject* make_leaf(PyObject* type, PyObject* ctx, PyObject* address, long dtype, PyObject* shape, PyObject* strides, PyObject* owner) {
+  int64_t sh[GR_MAX_NDIM], st[GR_MAX_NDIM];
+  if (!PyType_Check(type) || !PyType_IsSubtype((PyTypeObject*)type, &ArrayBase_Type) || !PyTuple_Check(shape) || !PyLong_Check(address)) return NULL;
+  const Py_ssize_t n = PyTuple_GET_SIZE(shape);
+  if (n > GR_MAX_NDIM || !int64_tuple(shape, n, sh) || (strides != Py_None && !int64_tuple(strides, n, st))) return NULL;
+  void* ptr = PyLong_AsVoidPtr(address);
+  CellObject* cell = PyErr_Occurred() ? NULL : cell_of(ctx);
+  if (!cell || !cell->address || dtype < 0 || dtype > 1000) { Py_XDECREF(cell); PyErr_Clear(); return NULL; }
+  gr_array h = 0;
+  const int status = p_array_from_device((gr_ctx*)(uintptr_t)cell->address, ptr, (gr_dtype)dtype, (int)n, sh, strides == Py_None ? NULL : st, &h);
+  PyObject* r = status ? raise_status(ctx, status) : new_array((PyTypeObject*)type, ctx, cell, h, owner, NULL, 0);
+  Py_DECREF(cell);
+  return r;
+}
+
 /* leaf(Array type, ctx, address, dtype, shape, strides or None, owner) -> Array, or None for arguments that this file does
- * not marshal (the ctypes route takes them): gr_array_from_device.  Every recorded program wraps its inputs on every pass,
- * and three array marshallings through ctypes cost more than recording all its operations (normalize, five inputs:
- * 13.4 us of host time per request before, 8.4 with this). */
+ * not marshal: gr_array_from_device.  Every recorded program wraps its inputs on every pass, and three array marshallings
+ * through ctypes cost more than recording all its operations (normalize, five inputs: 13.4 us of host time per request
+ * before, 8.4 with this). */
 static PyObject* mod_leaf(PyObject* m, PyObject* const* args, Py_ssize_t nargs) {
   if (nargs != 7) { PyErr_SetString(PyExc_TypeError, "leaf(type, ctx, address, dtype, shape, strides, owner)"); return NULL; }
-  PyObject *type = args[0], *ctx = args[1], *shape = args[4], *strides = args[5], *owner = args[6];
-  int64_t sh[GR_MAX_NDIM], st[GR_MAX_NDIM];
-  if (!PyType_Check(type) || !PyType_IsSubtype((PyTypeObject*)type, &ArrayBase_Type) || !PyTuple_Check(shape) || !PyLong_Check(args[2]) || !PyLong_Check(args[3])) Py_RETURN_NONE;
-  const Py_ssize_t n = PyTuple_GET_SIZE(shape);
-  if (n > GR_MAX_NDIM || !int64_tuple(shape, n, sh) || (strides != Py_None && !int64_tuple(strides, n, st))) Py_RETURN_NONE;
-  void* ptr = PyLong_AsVoidPtr(args[2]);
+  if (!PyLong_Check(args[3])) Py_RETURN_NONE;
   const long dtype = PyLong_AsLong(args[3]);
-  gr_ctx* c = PyErr_Occurred() ? NULL : ctx_of(ctx);
-  if (!c || dtype < 0 || dtype > 1000) { PyErr_Clear(); Py_RETURN_NONE; }
-  gr_array h = 0;
-  const int status = p_array_from_device(c, ptr, (gr_dtype)dtype, (int)n, sh, strides == Py_None ? NULL : st, &h);
-  if (status) return raise_status(ctx, status);
-  return new_array((PyTypeObject*)type, ctx, h, owner, NULL, 0);
+  if (dtype == -1 && PyErr_Occurred()) { PyErr_Clear(); Py_RETURN_NONE; }
+  PyObject* r = make_leaf(args[0], args[1], args[2], dtype, args[4], args[5], args[6]);
+  if (r || PyErr_Occurred()) return r;
+  Py_RETURN_NONE;
+}
+
+/* wrap(Array type, ctx, tensor, {element type: code}) -> Array over a tensor on the GPU, or None for anything this file does not
+ * marshal (an element type without a code, a tensor elsewhere, an object that is no tensor): leaf() of the tensor's
+ * attributes without the interpreter in between. */
+static PyObject* mod_wrap(PyObject* m, PyObject* const* args, Py_ssize_t nargs) {
+  if (nargs != 4 || !PyDict_Check(args[3])) { PyErr_SetString(PyExc_TypeError, "wrap(type, ctx, tensor, codes)"); return NULL; }
+  PyObject *t = args[2], *r = NULL, *shape = NULL, *stride = NULL, *address = NULL, *on_gpu = NULL;
+  PyObject* element = PyObject_GetAttr(t, str_dtype);
+  PyObject* code = element ? PyDict_GetItemWithError(args[3], element) : NULL;   /* (borrowed) */
+  if (code && PyLong_Check(code) && (on_gpu = PyObject_GetAttr(t, str_is_cuda)) && on_gpu == Py_True && (shape = PyObject_GetAttr(t, str_shape)) &&
+      (stride = PyObject_CallMethodNoArgs(t, str_stride)) && (address = PyObject_CallMethodNoArgs(t, str_data_ptr)))
+    r = make_leaf(args[0], args[1], address, PyLong_AsLong(code), shape, stride, t);
+  else PyErr_Clear();
+  Py_XDECREF(element);
+  Py_XDECREF(on_gpu);
+  Py_XDECREF(shape);
+  Py_XDECREF(stride);
+  Py_XDECREF(address);
+  if (r || PyErr_Occurred()) return r;
+  Py_RETURN_NONE;
 }
 
 /* program_run(program address, tuple of input addresses, output address) -> status: gr_program_run without
  * ctypes in between (a replayed request of a small array costs less than marshalling its arguments twice) */
-static PyObject* mod_program_run(PyObject* m, PyObject* args) {
-  unsigned long long prog, out;
-  PyObject* ptrs;
-  if (!PyArg_ParseTuple(args, "KO!K", &prog, &PyTuple_Type, &ptrs, &out)) return NULL;
+static PyObject* mod_program_run(PyObject* m, PyObject* const* args, Py_ssize_t nargs) {
+  if (nargs != 3 || !PyTuple_Check(args[1])) { PyErr_SetString(PyExc_TypeError, "program_run(program, tuple of input addresses, output address)"); return NULL; }
+  const unsigned long long prog = PyLong_AsUnsignedLongLong(args[0]), out = PyLong_AsUnsignedLongLong(args[2]);
+  if (PyErr_Occurred()) return NULL;
+  PyObject* ptrs = args[1];
   void* v[64];
   Py_ssize_t n = PyTuple_GET_SIZE(ptrs);
   if (n > 64) { PyErr_SetString(PyExc_ValueError, "more than 64 inputs"); return NULL; }
@@ -452,7 +500,7 @@ static PyNumberMethods array_as_number = {
 static PyMappingMethods array_as_mapping = {.mp_subscript = array_subscript, .mp_ass_subscript = array_ass_subscript};
 static PyMethodDef array_methods[] = {
     {"materialize", array_materialize, METH_NOARGS, "Evaluates the node (gr_materialize) and returns self."},
-    {"_materialize_into", array_materialize_into, METH_VARARGS, "Evaluates the node into a caller's buffer (gr_materialize_into[_static]) and returns self."},
+    {"_materialize_into", (PyCFunction)(void (*)(void))array_materialize_into, METH_FASTCALL, "Evaluates the node into a caller's buffer (gr_materialize_into[_static]) and returns self."},
     {NULL, NULL, 0, NULL}};
 static PyMemberDef array_members[] = {
     {"ctx", T_OBJECT, offsetof(ArrayObject, ctx), READONLY, "the Context the node belongs to"},
@@ -481,20 +529,32 @@ static PyTypeObject ArrayBase_Type = {
     .tp_new = PyType_GenericNew,
 };
 
+static PyMemberDef cell_members[] = {{"address", T_ULONGLONG, offsetof(CellObject, address), 0, "address of the gr_ctx, 0 once closed"}, {NULL, 0, 0, 0, NULL}};
+
+static PyTypeObject Cell_Type = {
+    PyVarObject_HEAD_INIT(NULL, 0)
+    .tp_name = "paper_1901_03771_amd._fastbind.Cell",
+    .tp_basicsize = sizeof(CellObject),
+    .tp_flags = Py_TPFLAGS_DEFAULT,
+    .tp_doc = "Where a Context keeps the address of its gr_ctx.",
+    .tp_members = cell_members,
+    .tp_new = PyType_GenericNew,
+};
+
 /* ---- module ----------------------------------------------------------------------------- */
 
-static PyObject* mod_unary(PyObject* m, PyObject* args) {
-  int op;
-  PyObject* a;
-  if (!PyArg_ParseTuple(args, "iO", &op, &a)) return NULL;
-  return do_unary(op, a);
+static PyObject* mod_unary(PyObject* m, PyObject* const* args, Py_ssize_t nargs) {
+  if (nargs != 2) { PyErr_SetString(PyExc_TypeError, "unary(op, a)"); return NULL; }
+  const int op = (int)PyLong_AsLong(args[0]);
+  if (op == -1 && PyErr_Occurred()) return NULL;
+  return do_unary(op, args[1]);
 }
 
-static PyObject* mod_binary(PyObject* m, PyObject* args) {
-  int op;
-  PyObject *a, *b;
-  if (!PyArg_ParseTuple(args, "iOO", &op, &a, &b)) return NULL;
-  return do_binary(op, a, b);
+static PyObject* mod_binary(PyObject* m, PyObject* const* args, Py_ssize_t nargs) {
+  if (nargs != 3) { PyErr_SetString(PyExc_TypeError, "binary(op, a, b)"); return NULL; }
+  const int op = (int)PyLong_AsLong(args[0]);
+  if (op == -1 && PyErr_Occurred()) return NULL;
+  return do_binary(op, args[1], args[2]);
 }
 
 static int take_address(PyObject* d, const char* name, void** out) {
@@ -533,11 +593,12 @@ static PyObject* mod_set_hooks(PyObject* m, PyObject* args) {
 }
 
 static PyMethodDef module_methods[] = {
-    {"unary", mod_unary, METH_VARARGS, "unary(op, a): gr_unary"},
-    {"binary", mod_binary, METH_VARARGS, "binary(op, a, b): gr_binary / gr_binary_scalar"},
-    {"reduce", mod_reduce, METH_VARARGS, "reduce(op, a, axis, keepdims): gr_reduce"},
+    {"unary", (PyCFunction)(void (*)(void))mod_unary, METH_FASTCALL, "unary(op, a): gr_unary"},
+    {"binary", (PyCFunction)(void (*)(void))mod_binary, METH_FASTCALL, "binary(op, a, b): gr_binary / gr_binary_scalar"},
+    {"reduce", (PyCFunction)(void (*)(void))mod_reduce, METH_FASTCALL, "reduce(op, a, axis, keepdims): gr_reduce"},
     {"leaf", (PyCFunction)(void (*)(void))mod_leaf, METH_FASTCALL, "leaf(type, ctx, address, dtype, shape, strides, owner): gr_array_from_device, None if not marshalled here"},
-    {"program_run", mod_program_run, METH_VARARGS, "program_run(program, input addresses, output address) -> status: gr_program_run"},
+    {"wrap", (PyCFunction)(void (*)(void))mod_wrap, METH_FASTCALL, "wrap(type, ctx, tensor, codes): leaf of a tensor on the GPU, None if not marshalled here"},
+    {"program_run", (PyCFunction)(void (*)(void))mod_program_run, METH_FASTCALL, "program_run(program, input addresses, output address) -> status: gr_program_run"},
     {"bind", mod_bind, METH_O, "bind({name: address}): entry points of the loaded library"},
     {"set_hooks", mod_set_hooks, METH_VARARGS, "set_hooks(binary, getitem, setitem, pow, reduce): Python fallbacks"},
     {NULL, NULL, 0, NULL}};
@@ -545,11 +606,18 @@ static PyMethodDef module_methods[] = {
 static struct PyModuleDef moduledef = {PyModuleDef_HEAD_INIT, "_fastbind", "Fast paths of the lazy-array binding.", -1, module_methods};
 
 PyMODINIT_FUNC PyInit__fastbind(void) {
-  if (PyType_Ready(&ArrayBase_Type) < 0) return NULL;
+  if (PyType_Ready(&ArrayBase_Type) < 0 || PyType_Ready(&Cell_Type) < 0) return NULL;
   PyObject* m = PyModule_Create(&moduledef);
   if (!m) return NULL;
-  str_addr = PyUnicode_InternFromString("_addr");
+  str_cell = PyUnicode_InternFromString("_cell");
+  str_dtype = PyUnicode_InternFromString("dtype");
+  str_is_cuda = PyUnicode_InternFromString("is_cuda");
+  str_shape = PyUnicode_InternFromString("shape");
+  str_stride = PyUnicode_InternFromString("stride");
+  str_data_ptr = PyUnicode_InternFromString("data_ptr");
   str_check = PyUnicode_InternFromString("check");
+  Py_INCREF(&Cell_Type);
+  if (PyModule_AddObject(m, "Cell", (PyObject*)&Cell_Type) < 0) { Py_DECREF(&Cell_Type); Py_DECREF(m); return NULL; }
   Py_INCREF(&ArrayBase_Type);
   if (PyModule_AddObject(m, "ArrayBase", (PyObject*)&ArrayBase_Type) < 0) { Py_DECREF(&ArrayBase_Type); Py_DECREF(m); return NULL; }
   return m;

@@ -20,6 +20,26 @@ constexpr int MAXD = GR_MAX_NDIM;
 
 enum class Kind : uint8_t { LEAF, SCALAR, CONST, UNARY, BINARY, SLICE, TRANSPOSE, REDUCE, DOT, SCAN, RESHAPE };
 
+struct Node;
+
+// The predecessors of a node: two at most.
+class Inputs {
+ public:
+  Node** begin() { return p_; }
+  Node** end() { return p_ + n_; }
+  Node* const* begin() const { return p_; }
+  Node* const* end() const { return p_ + n_; }
+  size_t size() const { return n_; }
+  bool empty() const { return n_ == 0; }
+  Node* operator[](size_t i) const { return p_[i]; }
+  void push_back(Node* n) { p_[n_++] = n; }
+  void clear() { n_ = 0; }
+
+ private:
+  Node* p_[2] = {nullptr, nullptr};
+  size_t n_ = 0;
+};
+
 struct Node {
   uint64_t id = 0;
   Kind kind = Kind::LEAF;
@@ -27,7 +47,7 @@ struct Node {
   gr_dtype dtype = GR_F32;
   int ndim = 0;
   int64_t shape[MAXD] = {0};
-  std::vector<Node*> in;  // predecessors (each holds one consumer reference)
+  Inputs in;  // predecessors (each holds one consumer reference)
   int handle_refs = 0;
   int consumer_refs = 0;
   uint64_t shash = 0;  // hash of the expression below this node (materialised nodes: of their identity)
@@ -75,6 +95,57 @@ struct Node {
   bool is_view() const { return kind == Kind::SLICE || kind == Kind::TRANSPOSE; }
   bool is_compute() const { return kind == Kind::UNARY || kind == Kind::BINARY || kind == Kind::REDUCE || kind == Kind::DOT || kind == Kind::SCAN || kind == Kind::RESHAPE; }
   bool has_data() const { return materialized || planned; }
+};
+
+// The nodes of a context by their id: open addressing, a slot per node and as many free ones.  Every recorded operation enters one,
+// looks up two or three and removes one again; a node-based map allocates and frees for each.
+class NodeTable {
+ public:
+  Node* get(uint64_t id) const {
+    if (slots_.empty()) return nullptr;
+    for (size_t i = home(id);; i = (i + 1) & mask()) {
+      if (slots_[i].id == id) return slots_[i].node;
+      if (!slots_[i].node) return nullptr;
+    }
+  }
+  void put(Node* n) {
+    if (2 * (count_ + 1) > slots_.size()) grow();
+    size_t i = home(n->id);
+    while (slots_[i].node) i = (i + 1) & mask();
+    slots_[i] = {n->id, n};
+    ++count_;
+  }
+  void erase(uint64_t id) {
+    if (slots_.empty()) return;
+    size_t i = home(id);
+    while (slots_[i].node && slots_[i].id != id) i = (i + 1) & mask();
+    if (!slots_[i].node) return;
+    --count_;
+    // later entries of the run move up where that brings them no further than their home
+    for (size_t j = (i + 1) & mask(); slots_[j].node; j = (j + 1) & mask())
+      if (((j - home(slots_[j].id)) & mask()) >= ((j - i) & mask())) { slots_[i] = slots_[j]; i = j; }
+    slots_[i] = {0, nullptr};
+  }
+  template <class F>
+  void each(F&& f) const { for (const Slot& s : slots_) if (s.node) f(s.node); }
+  void clear() { slots_.clear(); count_ = 0; }
+
+ private:
+  struct Slot { uint64_t id = 0; Node* node = nullptr; };   // (ids start at 1)
+  size_t mask() const { return slots_.size() - 1; }
+  size_t home(uint64_t id) const { return (size_t)((id * 0x9e3779b97f4a7c15ull) >> shift_); }
+  void grow() {
+    std::vector<Slot> old;
+    old.swap(slots_);
+    slots_.resize(old.empty() ? 256 : 2 * old.size());
+    shift_ = 64;
+    for (size_t n = slots_.size(); n > 1; n /= 2) --shift_;
+    count_ = 0;
+    for (const Slot& s : old) if (s.node) put(s.node);
+  }
+  std::vector<Slot> slots_;
+  size_t count_ = 0;
+  int shift_ = 63;
 };
 
 // Node containers are ordered by node id (recording order), never by address: plans must not
@@ -153,6 +224,8 @@ inline bool heavy_op(const Instr& in) {
                                 (in.kind == IKind::UNARY && (in.op == GR_EXP || in.op == GR_LOG || in.op == GR_SQRT || in.op == GR_TANH || in.op == GR_ERF)));
 }
 
+struct ArgLayout;
+
 // One sub-graph of the ordered list of Algorithm 1, ready for code generation.
 struct GroupPlan {
   GroupKind kind = GroupKind::MAP;
@@ -176,7 +249,7 @@ struct GroupPlan {
 
   // MAP: single-point program (boundary tiles, cache key); `prog` holds the per-lane patch
   // program and is only built when a kernel has to be generated
-  NodeSet owned;
+  std::vector<const Node*> owned;   // ordered by id
   std::vector<Instr> prog1;
   int result1 = -1;
 
@@ -235,6 +308,8 @@ struct GroupPlan {
   int unroll = 8;     // gemv column-accumulate: rows in flight per lane
 
   std::string signature;
+  void* kernel = nullptr;                // (gr_ctx::Kernel*) of this signature once it is loaded; a context's kernels stay where they are until it goes
+  mutable std::shared_ptr<const ArgLayout> layout;   // where the launch's arguments sit, worked out at the first launch
   std::string general;                   // pair_k: signature of the lane groups' kernel of the same program, which serves other row lengths too
 };
 

@@ -1672,7 +1672,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
     pop_output_group(g);
     choose_map_schedule(c, g, !(r == pl.root && pl.out));
     if (r == pl.root && pl.out && pl.out->in_place && src == r && r->ndim > 0) choose_in_place(g);
-    g->owned = owned;
+    g->owned.assign(owned.begin(), owned.end());
   }
 
   for (const Node* n : b.members_seen) g->members.push_back(n);
@@ -1712,7 +1712,8 @@ gr_status expand_patch(gr_ctx* c, GroupPlan* g) {
   for (int k = 0; k < n; ++k) tmp.orig_dims[k] = g->orig_dims[k];
   tmp.consts = g->consts;
   Builder b;
-  b.g = &tmp; b.owned = &g->owned; b.rank = n; b.dims = tmp.orig_dims; b.prog = &tmp.prog;
+  const NodeSet owned(g->owned.begin(), g->owned.end());
+  b.g = &tmp; b.owned = &owned; b.rank = n; b.dims = tmp.orig_dims; b.prog = &tmp.prog;
   const Node* src = map_source(r);
   IndexMap im(src->ndim);
   for (int d = 0; d < src->ndim; ++d) im[d] = DimMap{d, 1, 0};

@@ -31,12 +31,6 @@ namespace {
 constexpr size_t MAX_ENTRIES = 512;
 constexpr size_t MAX_NODES = 4096;  // larger requests are planned afresh (the walk itself would dominate)
 
-struct Walk {
-  std::vector<Node*> nodes;
-  std::vector<int64_t> key;
-  uint64_t hash = 0;
-};
-
 int64_t bits_of(double v) {
   int64_t b;
   std::memcpy(&b, &v, sizeof b);
@@ -47,7 +41,8 @@ int64_t bits_of(double v) {
 bool fingerprint(gr_ctx* c, Node* root, const OutSpec* out, Walk* w) {
   const uint64_t epoch = ++c->walk_epoch;
   std::vector<Node*>& nodes = w->nodes;
-  std::vector<Node*> stack{root};
+  std::vector<Node*>& stack = w->stack;
+  stack.push_back(root);
   while (!stack.empty()) {
     Node* n = stack.back();
     stack.pop_back();
@@ -96,13 +91,16 @@ bool fingerprint(gr_ctx* c, Node* root, const OutSpec* out, Walk* w) {
     for (Node* p : n->in) k.push_back(p->walk_idx);
   }
   // order of the node ids
-  std::vector<int> by_id(nodes.size());
-  for (size_t i = 0; i < nodes.size(); ++i) by_id[i] = (int)i;
-  std::sort(by_id.begin(), by_id.end(), [&](int a, int b) { return nodes[a]->id < nodes[b]->id; });
-  for (int i : by_id) k.push_back(i);
-  uint64_t h = 1469598103934665603ull;
-  for (int64_t v : k) { h ^= (uint64_t)v; h *= 1099511628211ull; h ^= h >> 29; }
-  w->hash = h;
+  static_assert(MAX_NODES <= 4096, "a node's number takes twelve bits");
+  for (size_t i = 0; i < nodes.size(); ++i) w->order.push_back(nodes[i]->id << 12 | i);
+  std::sort(w->order.begin(), w->order.end());
+  for (uint64_t v : w->order) k.push_back((int64_t)(v & 4095));
+  // (four chains: one would wait for its own products)
+  uint64_t h[4] = {1469598103934665603ull, 2, 3, 4};
+  const size_t n = k.size();
+  for (size_t i = 0; i < n; ++i) { uint64_t& x = h[i & 3]; x ^= (uint64_t)k[i]; x *= 1099511628211ull; x ^= x >> 29; }
+  for (int i = 1; i < 4; ++i) { h[0] ^= h[i]; h[0] *= 1099511628211ull; h[0] ^= h[0] >> 29; }
+  w->hash = h[0];
   return true;
 }
 
@@ -179,7 +177,14 @@ Plan::~Plan() {
 
 gr_status make_plan(gr_ctx* c, Node* root, Plan* plan) {
   if (!c->opt_plan_cache || root->kind == Kind::SCALAR) return make_plan_uncached(c, root, plan);
-  Walk w;
+  // (the context's lists are taken out while they are in use: planning a request may plan another one)
+  struct Taken {
+    gr_ctx* c;
+    Walk w;
+    explicit Taken(gr_ctx* ctx) : c(ctx), w(std::move(ctx->walk)) { w.clear(); }
+    ~Taken() { c->walk = std::move(w); }
+  } taken(c);
+  Walk& w = taken.w;
   if (!fingerprint(c, root, plan->out, &w)) return make_plan_uncached(c, root, plan);
   PlanEntry* hit = nullptr;
   auto range = c->plan_cache.equal_range(w.hash);
@@ -189,7 +194,7 @@ gr_status make_plan(gr_ctx* c, Node* root, Plan* plan) {
   if (hit) {
     size_t si = 0;
     for_each_slot(hit->groups, [&](const Node*& p) { int i = hit->slots[si++]; p = i >= 0 ? w.nodes[i] : nullptr; });
-    // the sets of owned nodes are ordered by id: emptied (no node is looked at) and filled again
+    // the lists of owned nodes, ordered by id as the fingerprint is: emptied (no node is looked at) and filled again
     for (auto& up : hit->groups)
       for (GroupPlan* g : {up.get(), up->pair.get()}) {
         if (!g) continue;
@@ -197,7 +202,7 @@ gr_status make_plan(gr_ctx* c, Node* root, Plan* plan) {
         for (AccessGroup& ag : g->groups) if (ag.leaf && !ag.ident.empty()) ag.ident[0] = (int64_t)ag.leaf->id;
         g->owned.clear();
         const size_t n = (size_t)hit->slots[si++];
-        for (size_t j = 0; j < n; ++j) g->owned.insert(w.nodes[hit->slots[si++]]);
+        for (size_t j = 0; j < n; ++j) g->owned.push_back(w.nodes[hit->slots[si++]]);
       }
     if (c->opt_plan_cache >= 2) {
       Plan fresh;
@@ -247,7 +252,7 @@ gr_status make_plan(gr_ctx* c, Node* root, Plan* plan) {
   for (Node* r : plan->planned_nodes) { int i = number_of(r); if (i < 0) ok = false; e->planned.push_back(i); }
   if (!ok) return GR_OK;
   evict_if_full(c);
-  e->key = std::move(w.key);
+  e->key = w.key;
   e->out_honoured = plan->out_honoured;
   e->on_loan = true;
   e->last_use = ++c->plan_clock;

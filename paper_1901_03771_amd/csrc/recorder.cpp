@@ -19,9 +19,8 @@ gr_status fail(gr_ctx* c, gr_status s, const std::string& msg) {
 }
 
 Node* lookup(gr_ctx* c, gr_array a) {
-  auto it = c->nodes.find(a);
-  if (it == c->nodes.end() || it->second->handle_refs <= 0) return nullptr;
-  return it->second;
+  Node* n = c->nodes.get(a);
+  return n && n->handle_refs > 0 ? n : nullptr;
 }
 
 // Element counts and element offsets stay below 2^40 so that byte offsets and every product of two
@@ -40,11 +39,17 @@ bool count_fits(const int64_t* shape, int ndim) {
 }
 
 Node* new_node(gr_ctx* c, Kind kind) {
-  Node* n = new Node();
+  Node* n;
+  if (c->spare_nodes.empty()) n = new Node();
+  else {
+    n = c->spare_nodes.back();
+    c->spare_nodes.pop_back();
+    *n = Node();
+  }
   n->id = c->next_id++;
   n->kind = kind;
   n->handle_refs = 1;
-  c->nodes[n->id] = n;
+  c->nodes.put(n);
   c->stats.nodes_recorded++;
   c->stats.nodes_alive++;
   return n;
@@ -63,7 +68,10 @@ static void forget_pending(gr_ctx* c, const Node* n) {
 
 // Frees every node that has lost its last reference, iteratively.
 void node_maybe_free(gr_ctx* c, Node* n0) {
-  std::vector<Node*> work{n0};
+  if (n0->handle_refs > 0 || n0->consumer_refs > 0) return;
+  std::vector<Node*> work;
+  work.swap(c->free_work);   // (a caller's allocator may come back here)
+  work.push_back(n0);
   while (!work.empty()) {
     Node* n = work.back();
     work.pop_back();
@@ -78,10 +86,7 @@ void node_maybe_free(gr_ctx* c, Node* n0) {
       // buffer then passes to it instead of being freed
       Node* heir = nullptr;
       if (c->any_storage_alias)
-        for (auto& kv : c->nodes) {
-          Node* m = kv.second;
-          if (m != n && m->materialized && m->cow_alias && m->data == n->data) { heir = m; break; }
-        }
+        c->nodes.each([&](Node* m) { if (m != n && m->materialized && m->cow_alias && m->data == n->data && (!heir || m->id < heir->id)) heir = m; });
       if (heir) { heir->owns_data = true; heir->alloc_bytes = n->alloc_bytes; heir->cow_alias = false; }
       else ctx_free(c, n->data, n->alloc_bytes);
     }
@@ -89,15 +94,17 @@ void node_maybe_free(gr_ctx* c, Node* n0) {
     if (n->kind == Kind::REDUCE || n->kind == Kind::DOT || n->kind == Kind::SCAN) forget_pending(c, n);
     c->nodes.erase(n->id);
     c->stats.nodes_alive--;
-    delete n;
+    if (c->spare_nodes.size() < kSpareNodes) c->spare_nodes.push_back(n);
+    else delete n;
   }
+  if (work.capacity() > c->free_work.capacity()) work.swap(c->free_work);
 }
 
 // A materialised node no longer needs its predecessors (Section 2: later
 // requests read its data instead of recomputing it).
 void drop_inputs(gr_ctx* c, Node* n) {
-  std::vector<Node*> ins;
-  ins.swap(n->in);
+  const Inputs ins = n->in;
+  n->in.clear();
   for (Node* p : ins)
     if (--p->consumer_refs == 0 && p->handle_refs == 0) node_maybe_free(c, p);
 }
@@ -178,11 +185,10 @@ static gr_array finish(gr_ctx* c, Node* n) {
   if (c->opt_merge) {
     auto range = c->pending_expensive.equal_range(n->shash);
     for (auto it = range.first; it != range.second; ++it) {
-      auto f = c->nodes.find(it->second);
-      if (f == c->nodes.end() || f->second->materialized || f->second->planned) continue;
+      Node* e = c->nodes.get(it->second);
+      if (!e || e->materialized || e->planned) continue;
       std::set<std::pair<uint64_t, uint64_t>> assumed;
-      if (!same_expr(f->second, n, assumed)) continue;
-      Node* e = f->second;
+      if (!same_expr(e, n, assumed)) continue;
       e->handle_refs++;
       n->handle_refs = 0;
       node_maybe_free(c, n);
@@ -339,22 +345,16 @@ gr_status gr_unary(gr_ctx* ctx, gr_op op, gr_array a, gr_array* out) {
   return GR_OK;
 }
 
-gr_status gr_binary(gr_ctx* ctx, gr_op op, gr_array a, gr_array b, gr_array* out) {
-  if (!ctx || !out) return GR_ERR_ARG;
-  if (enum_arg(op) == GR_POW_INT) {
-    // x ** 2 with an integer scalar 2 is recorded as square(x), NumPy's own fast path; no other power
-    // is in the vocabulary
-    const Node* x = lookup(ctx, a);
-    const Node* e = lookup(ctx, b);
-    if (!x || !e) return fail(ctx, GR_ERR_HANDLE, "binary: bad handle");
-    if (e->kind != Kind::SCALAR || !e->is_int || e->value != 2.0 || x->kind == Kind::SCALAR)
-      return fail(ctx, GR_ERR_UNSUPPORTED, "binary: the only power recorded is array ** 2 with an integer scalar");
-    return gr_unary(ctx, GR_SQUARE, a, out);
-  }
-  if (!is_binary(enum_arg(op))) return fail(ctx, GR_ERR_ARG, "binary: not a binary op");
-  Node* x = lookup(ctx, a);
-  Node* y = lookup(ctx, b);
-  if (!x || !y) return fail(ctx, GR_ERR_HANDLE, "binary: bad handle");
+// x ** 2 with an integer scalar 2 is recorded as square(x), NumPy's own fast path; no other power is in the vocabulary
+static gr_status power(gr_ctx* ctx, gr_array a, const Node* e, gr_array* out) {
+  const Node* x = lookup(ctx, a);
+  if (!x || !e) return fail(ctx, GR_ERR_HANDLE, "binary: bad handle");
+  if (e->kind != Kind::SCALAR || !e->is_int || e->value != 2.0 || x->kind == Kind::SCALAR)
+    return fail(ctx, GR_ERR_UNSUPPORTED, "binary: the only power recorded is array ** 2 with an integer scalar");
+  return gr_unary(ctx, GR_SQUARE, a, out);
+}
+
+static gr_status binary(gr_ctx* ctx, gr_op op, Node* x, Node* y, gr_array* out) {
   bool wx = x->kind == Kind::SCALAR, wy = y->kind == Kind::SCALAR;
   if (wx && wy) return fail(ctx, GR_ERR_UNSUPPORTED, "binary: two bare scalars");
   gr_dtype dt = wx ? y->dtype : x->dtype;
@@ -404,16 +404,35 @@ gr_status gr_binary(gr_ctx* ctx, gr_op op, gr_array a, gr_array b, gr_array* out
   return GR_OK;
 }
 
+gr_status gr_binary(gr_ctx* ctx, gr_op op, gr_array a, gr_array b, gr_array* out) {
+  if (!ctx || !out) return GR_ERR_ARG;
+  if (enum_arg(op) == GR_POW_INT) return power(ctx, a, lookup(ctx, b), out);
+  if (!is_binary(enum_arg(op))) return fail(ctx, GR_ERR_ARG, "binary: not a binary op");
+  Node* x = lookup(ctx, a);
+  Node* y = lookup(ctx, b);
+  if (!x || !y) return fail(ctx, GR_ERR_HANDLE, "binary: bad handle");
+  return binary(ctx, op, x, y, out);
+}
+
 gr_status gr_binary_scalar(gr_ctx* ctx, gr_op op, gr_array a, double value, int is_integer, int scalar_on_left,
                            gr_array* out) {
   if (!ctx || !out) return GR_ERR_ARG;
   if (!is_binary(enum_arg(op)) && enum_arg(op) != GR_POW_INT) return fail(ctx, GR_ERR_ARG, "binary: not a binary op");
-  gr_array s = 0;
-  gr_status st = gr_scalar(ctx, value, is_integer, &s);
-  if (st != GR_OK) return st;
-  st = scalar_on_left ? gr_binary(ctx, op, s, a, out) : gr_binary(ctx, op, a, s, out);
-  gr_release(ctx, s);
-  return st;
+  if (is_integer && value != std::floor(value)) return fail(ctx, GR_ERR_ARG, "scalar: is_integer set on a fractional value");
+  // the scalar, numbered and counted like one of gr_scalar, but never given out
+  Node s;
+  s.id = ctx->next_id++;
+  s.kind = Kind::SCALAR;
+  s.value = value;
+  s.is_int = is_integer != 0;
+  ctx->stats.nodes_recorded++;
+  Node* x = lookup(ctx, a);
+  if (enum_arg(op) == GR_POW_INT) {
+    if (scalar_on_left) return fail(ctx, x ? GR_ERR_UNSUPPORTED : GR_ERR_HANDLE, x ? "binary: the only power recorded is array ** 2 with an integer scalar" : "binary: bad handle");
+    return power(ctx, a, &s, out);
+  }
+  if (!x) return fail(ctx, GR_ERR_HANDLE, "binary: bad handle");
+  return scalar_on_left ? binary(ctx, op, &s, x, out) : binary(ctx, op, x, &s, out);
 }
 
 gr_status gr_slice(gr_ctx* ctx, gr_array a, int nspec, const int64_t* start, const int64_t* stop,

@@ -271,13 +271,15 @@ static void bound_pending(gr_ctx* c);
 struct AsGeneral {
   GroupPlan& g;
   const int k, lane;
-  explicit AsGeneral(GroupPlan& plan) : g(plan), k(plan.pair_k), lane(plan.pair_lane) { g.pair_k = g.pair_lane = 0; g.signature.swap(g.general); }
-  ~AsGeneral() { g.pair_k = k; g.pair_lane = lane; g.signature.swap(g.general); }
+  void* const kernel;
+  explicit AsGeneral(GroupPlan& plan) : g(plan), k(plan.pair_k), lane(plan.pair_lane), kernel(plan.kernel) { g.pair_k = g.pair_lane = 0; g.kernel = nullptr; g.signature.swap(g.general); }
+  ~AsGeneral() { g.pair_k = k; g.pair_lane = lane; g.kernel = kernel; g.signature.swap(g.general); }
   AsGeneral(const AsGeneral&) = delete;
   AsGeneral& operator=(const AsGeneral&) = delete;
 };
 
 gr_status prepare_group(gr_ctx* c, GroupPlan& g) {
+  if (g.kernel) return GR_OK;
   if (g.pair_k) {
     AsGeneral general(g);
     gr_status st = prepare_group(c, g);
@@ -371,23 +373,26 @@ gr_status compile_group(gr_ctx* c, GroupPlan& g, gr_ctx::Kernel** out) {
     if (st == GR_OK && c->pending.count(g.general)) st = collect_job(c, g.general, nullptr);
     if (st != GR_OK) return st;
   }
-  auto it = c->cache.find(g.signature);
-  if (it != c->cache.end()) {
+  if (!g.kernel) {
+    auto it = c->cache.find(g.signature);
+    if (it != c->cache.end()) g.kernel = &it->second;
+  }
+  if (g.kernel) {
     c->stats.cache_hits++;
-    *out = &it->second;
+    *out = (gr_ctx::Kernel*)g.kernel;
     if (c->opt_plan_cache >= 2) {
       // self-checking mode: the signature has to determine the source; a plan whose source differs from the one
       // its cached kernel was compiled from would run a kernel written for other assumptions
       gr_status est = expand_patch(c, &g);
       if (est != GR_OK) return est;
-      if (std::hash<std::string>()(generate_source(g)) != it->second.src_hash)
+      if (std::hash<std::string>()(generate_source(g)) != (*out)->src_hash)
         return fail(c, GR_ERR_UNSUPPORTED, "kernel cache: this sub-graph's source differs from the source its signature was compiled from (" + kernel_name(g) + ")");
     }
     return GR_OK;
   }
   gr_status st = prepare_group(c, g);
   if (st != GR_OK) return st;
-  it = c->cache.find(g.signature);
+  auto it = c->cache.find(g.signature);
   if (it != c->cache.end()) { *out = &it->second; return GR_OK; }  // served from disk
   return collect_job(c, g.signature, out);
 }
@@ -579,11 +584,22 @@ static gr_status scan_cells(gr_ctx* c, const GroupPlan& g, size_t need, void** c
   return GR_OK;
 }
 
+static const ArgLayout& layout_of(const GroupPlan& g) {
+  if (!g.layout) g.layout = std::make_shared<const ArgLayout>(arg_layout(g));
+  return *g.layout;
+}
+
 gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* out_ptr, void* pair_out_ptr) {
-  ArgLayout L = arg_layout(g);
-  ArgLayout L2;
-  if (g.pair) L2 = arg_layout(*g.pair);
-  std::vector<uint64_t> s(L.total + (g.pair ? L2.total : 0), 0);
+  const ArgLayout& L = layout_of(g);
+  const ArgLayout& L2 = layout_of(g.pair ? *g.pair : g);
+  struct Taken {   // (the context's block, taken out while it is filled)
+    gr_ctx* c;
+    std::vector<uint64_t> v;
+    explicit Taken(gr_ctx* ctx) : c(ctx) { v.swap(c->launch_args); }
+    ~Taken() { v.swap(c->launch_args); }
+  } taken(c);
+  std::vector<uint64_t>& s = taken.v;
+  s.assign(L.total + (g.pair ? L2.total : 0), 0);
   if (c->capture) c->capture->cur_patch.clear();
   gr_status fst = fill_args(c, g, L, out_ptr, s.data());
   if (fst != GR_OK) return fst;
@@ -884,7 +900,7 @@ gr_status execute_plan(gr_ctx* c, Plan* plan, Node* root, void* user_out, bool c
     // interpreter instead of waiting; the job stays pending and a later request collects it.
     // (option "interp" = 2: every map sub-graph the interpreter covers, compiled or not)
     const bool try_interp = !c->static_mode && !c->capture &&
-                            (c->opt_interp >= 2 || (c->opt_interp == 1 && still_compiling(c, g.signature)));
+                            (c->opt_interp >= 2 || (c->opt_interp == 1 && !g.kernel && still_compiling(c, g.signature)));
     if (no_compile) k = &dry_kernel;
     if (no_compile && c->opt_plan_cache >= 2) {
       // self-checking dry run: nothing is compiled, but the source is generated and has to be the one that any
@@ -1170,13 +1186,14 @@ gr_status gr_ctx_destroy(gr_ctx* ctx) {
   if (ctx->device >= 0) (void)hipStreamSynchronize(ctx->stream);
   (void)collect_all_jobs(ctx, false);  // finished code objects go to the on-disk cache; nothing is loaded any more
   std::vector<Node*> all;
-  for (auto& kv : ctx->nodes) all.push_back(kv.second);
+  ctx->nodes.each([&](Node* n) { all.push_back(n); });
   for (Node* n : all) {
     if (n->owns_data && n->data) ctx_free(ctx, n->data, n->alloc_bytes);
     if (n->shadow && n->shadow != n->lent) ctx_free(ctx, n->shadow, n->alloc_bytes);
     delete n;
   }
   ctx->nodes.clear();
+  for (Node* n : ctx->spare_nodes) delete n;
   while (!ctx->programs.empty()) program_free(ctx, ctx->programs.back());
   if (ctx->workspace) ctx_free(ctx, ctx->workspace, ctx->workspace_bytes);
   if (ctx->scan_cells) ctx_free(ctx, ctx->scan_cells, ctx->scan_cells_bytes);
@@ -1293,8 +1310,7 @@ static bool reads_range(const Node* n, uintptr_t lo, uintptr_t hi, std::set<cons
 // Gives a node whose data lives inside another array's storage (the result of a direct slice
 // assignment) a buffer of its own.
 static gr_status unshare(gr_ctx* ctx, gr_array id) {
-  auto it = ctx->nodes.find(id);  // (not lookup(): the node may be held by views only, without a handle)
-  Node* n = it == ctx->nodes.end() ? nullptr : it->second;
+  Node* n = ctx->nodes.get(id);  // (not lookup(): the node may be held by views only, without a handle)
   if (!n || !n->cow_alias) return GR_OK;
   size_t bytes = (size_t)n->count() * itemsize(n->dtype);
   void* buf = ctx_alloc(ctx, bytes);
@@ -1378,7 +1394,7 @@ static gr_status assign_in_place(gr_ctx* ctx, Node* v, const Node* base, const O
     if (ctx->opt_interp >= 2) ok = false;
     else {
       st = prepare_group(ctx, g);
-      if (st == GR_OK && ctx->opt_interp == 1 && still_compiling(ctx, g.signature)) ok = false;
+      if (st == GR_OK && ctx->opt_interp == 1 && !g.kernel && still_compiling(ctx, g.signature)) ok = false;
     }
   }
   if (st == GR_OK && ok) {
@@ -1433,19 +1449,18 @@ extern "C" gr_status gr_assign(gr_ctx* ctx, gr_array dst, gr_array value) {
   //    evaluate them now.  Results of earlier direct assignments that still live inside this
   //    storage get their own copy.
   std::vector<gr_array> pending, aliases;
-  for (auto& kv : ctx->nodes) {
-    Node* n = kv.second;
-    if (n == v || n->kind == Kind::SCALAR) continue;
+  ctx->nodes.each([&](Node* n) {
+    if (n == v || n->kind == Kind::SCALAR) return;
     if (n->materialized) {
       // (also one that only views refer to: the destination itself may be a view of it)
       if (n->cow_alias) { uintptr_t a, b; extent_of(n, &a, &b); if (a < hi && lo < b) aliases.push_back(n->id); }
-      continue;
+      return;
     }
-    if (n->handle_refs <= 0) continue;
-    if (n->is_view()) { const Node* vb; int64_t o, st[MAXD]; if (resolve_view_rt(n, &vb, &o, st)) continue; }  // aliases see the new contents
+    if (n->handle_refs <= 0) return;
+    if (n->is_view()) { const Node* vb; int64_t o, st[MAXD]; if (resolve_view_rt(n, &vb, &o, st)) return; }  // aliases see the new contents
     std::set<const Node*> seen;
     if (reads_range(n, lo, hi, &seen)) pending.push_back(n->id);
-  }
+  });
   for (gr_array id : pending) {
     gr_status st = gr_materialize(ctx, id);
     if (st != GR_OK) return st;
@@ -1496,11 +1511,10 @@ extern "C" gr_status gr_assign(gr_ctx* ctx, gr_array dst, gr_array value) {
       // 2b. The value reads the destination's storage where it does not write it (a stencil sweep).
       //     Write it into a second buffer, copy the cells outside the destination, swap the buffers:
       //     views resolve through the owning node, so they all see the new storage.
-      clear_planned(&plan);
       Node* b = const_cast<Node*>(base);
       std::vector<gr_array> inside;
-      for (auto& kv : ctx->nodes)
-        if (kv.second->materialized && kv.second->cow_alias && kv.second->data == b->data) inside.push_back(kv.first);
+      if (ctx->any_storage_alias) ctx->nodes.each([&](Node* n) { if (n->materialized && n->cow_alias && n->data == b->data) inside.push_back(n->id); });
+      if (!inside.empty()) clear_planned(&plan);
       for (gr_array id : inside) {
         st = unshare(ctx, id);
         if (st != GR_OK) return st;
@@ -1512,6 +1526,8 @@ extern "C" gr_status gr_assign(gr_ctx* ctx, gr_array dst, gr_array value) {
       // the cells outside the box: nothing to copy
       bool mirrored = b->shadow != nullptr && (b->shadow == b->lent || bytes == b->alloc_bytes);
       for (int k = 0; mirrored && k < b->ndim; ++k) mirrored = b->shadow_start[k] == start[k] && b->shadow_len[k] == d->shape[k];
+      const bool again = !mirrored || !inside.empty();   // (in a loop of sweeps the plan at hand is run as it is)
+      if (again && inside.empty()) clear_planned(&plan);
       if (!mirrored) drop_shadow(ctx, b);
       // the second buffer: the mirror left by the last sweep, else the buffer the caller lent, else a new one
       void* fresh = mirrored ? b->shadow : (b->lent ? b->lent : ctx_alloc(ctx, bytes));
@@ -1519,10 +1535,10 @@ extern "C" gr_status gr_assign(gr_ctx* ctx, gr_array dst, gr_array value) {
       b->shadow = nullptr;
       Plan p2;
       p2.out = &spec;
-      st = make_plan(ctx, v, &p2);
-      if (st == GR_OK && !p2.out_honoured) st = fail(ctx, GR_ERR_UNSUPPORTED, "assign: plan changed between two passes");
-      if (st == GR_OK) st = execute_plan(ctx, &p2, v, fresh, false);
-      clear_planned(&p2);
+      if (again) st = make_plan(ctx, v, &p2);
+      if (st == GR_OK && again && !p2.out_honoured) st = fail(ctx, GR_ERR_UNSUPPORTED, "assign: plan changed between two passes");
+      if (st == GR_OK) st = execute_plan(ctx, again ? &p2 : &plan, v, fresh, false);
+      clear_planned(again ? &p2 : &plan);
       // the cells around the box: per dimension a slab below and a slab above it
       int64_t shp[MAXD], off = 0;
       for (int k = 0; k < b->ndim; ++k) shp[k] = b->shape[k];

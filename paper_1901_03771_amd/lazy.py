@@ -149,7 +149,9 @@ class Context:
         st = L.gr_ctx_create(ctypes.byref(self._p), int(device), ctypes.c_void_p(stream or 0))
         if st:
             raise GrError(st, L.gr_last_error(None).decode())
-        self._addr = self._p.value or 0  # what the C fast paths read; 0 once closed
+        if _fastbind is not None:
+            self._cell = _fastbind.Cell()  # what the C fast paths read; 0 once closed
+            self._cell.address = self._p.value or 0
         self.device = int(device)
         self._programs = set()  # recorded requests (Program): they die with the context
         _LIVE.add(self)
@@ -159,7 +161,8 @@ class Context:
         return Program(root, leaves)
 
     def close(self):
-        self._addr = 0
+        if getattr(self, "_cell", None) is not None:
+            self._cell.address = 0
         for prog in list(getattr(self, "_programs", ())):
             prog._p = None              # the library frees a context's programs with it
         if self._p:
@@ -258,7 +261,12 @@ class Context:
         tensor of the same shape lent to the library (gr_array_lend_buffer): stencil sweeps assigned into the array
         then alternate between the two tensors instead of going through a temporary; ``Array.current(t, second)``
         tells which of them holds the contents."""
-        if second is not None:
+        if second is None:
+            if _fastbind is not None:
+                a = _fastbind.wrap(Array, self, t, _TORCH_DTYPES)
+                if a is not None:
+                    return a
+        else:
             a = self.array(t)
             if tuple(second.shape) != tuple(t.shape) or second.dtype != t.dtype or not second.is_contiguous():
                 raise ValueError("the second buffer must be a contiguous tensor of the same shape and element type")

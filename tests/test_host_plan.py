@@ -1435,3 +1435,32 @@ print("ok")
         env["GRUMPY_NO_FASTBIND"] = "1"
     r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
+
+
+# the table of nodes: thousands alive at a time, dropped in any order, handles that are stale, a context closed under its arrays
+@pytest.mark.parametrize("count", [1, 255, 256, 5000])
+def test_nodes_are_found_until_their_last_reference_goes(count):
+    rng = np.random.default_rng(count)
+    c = gr.Context(device=-1)
+    leaf = c.spec((7, 3))
+    alive = c.stats()["nodes_alive"]
+    kept = {}
+    for i in range(count):
+        a = leaf * float(i)
+        kept[a.h] = (a, i)
+        if rng.random() < 0.5 and len(kept) > 1:                    # (its scalar goes with it)
+            del kept[list(kept)[rng.integers(len(kept))]]
+    del a
+    assert c.stats()["nodes_alive"] == alive + 2 * len(kept)
+    for h, (a, i) in kept.items():
+        assert a.h == h and a.shape == (7, 3) and f"leaves=[{leaf.h}]" in a.plan()
+    del a
+    stale = next(iter(kept))
+    kept.pop(stale)
+    n = ctypes.c_int()
+    assert gr.lib().gr_ndim(c._p, stale, ctypes.byref(n)) == 1 and gr.lib().gr_release(c._p, stale) == 1     # GR_ERR_HANDLE
+    kept.clear()
+    assert c.stats()["nodes_alive"] == alive
+    c.close()
+    with pytest.raises((RuntimeError, gr.GrError)):
+        leaf * 2.0
