@@ -137,7 +137,7 @@ struct Em {
       case GR_LOG: return "gr_logf(" + x + ")";
       case GR_SQRT: return "gr_sqrtf(" + x + ")";
       case GR_SQUARE: return "(" + x + " * " + x + ")";
-      case GR_TANH: return "tanhf(" + x + ")";
+      case GR_TANH: return "gr_tanhf(" + x + ")";
       case GR_ERF: return "gr_erff(" + x + ")";
     }
     switch (op) {  // i32: two's-complement wrap-around through unsigned arithmetic
@@ -196,7 +196,16 @@ struct Em {
 const char* const kDeviceMath =
 #include "device_math.h"
     ;
+const char* const kDeviceTanh =
+#include "device_tanh.h"
+    ;
 #undef GR_DEVICE_MATH_SOURCE
+
+bool calls(const GroupPlan& g, int op) {
+  for (const std::vector<Instr>* p : {&g.prog, &g.prog1})
+    for (const Instr& in : *p) if (in.kind == IKind::UNARY && in.op == op) return true;
+  return false;
+}
 
 void prelude(Em& e) {
   // every pointer the kernels dereference is a global-memory pointer (arguments arrive as
@@ -245,7 +254,7 @@ void prelude(Em& e) {
          "    t = (x == 0.0f || x == __builtin_inff()) ? x : t;\n"
          "  }\n"
          "  return t;\n}\n"
-         << kDeviceMath << "\n"
+         << kDeviceMath << "\n" << (calls(e.g, GR_TANH) || (e.g.pair && calls(*e.g.pair, GR_TANH)) ? std::string(kDeviceTanh) + "\n" : std::string()) <<
          "static __device__ __forceinline__ float gr_xor(float v, int m) { return __shfl_xor(v, m, 64); }\n"
          "static __device__ __forceinline__ int gr_xor(int v, int m) { return __shfl_xor(v, m, 64); }\n"
          "static __device__ __forceinline__ long long gr_xor(long long v, int m) {\n"

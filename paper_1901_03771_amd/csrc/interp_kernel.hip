@@ -18,6 +18,7 @@
 #define GR_KEEP_BRANCH __builtin_amdgcn_sched_barrier(0)
 #define GR_DEVICE_MATH_SOURCE(...) __VA_ARGS__
 #include "device_math.h"
+#include "device_tanh.h"
 #undef GR_DEVICE_MATH_SOURCE
 
 static __device__ __forceinline__ float gi_maxf(float a, float b) { return (a >= b || a != a) ? a : b; }
@@ -64,7 +65,7 @@ __global__ __launch_bounds__(256) void gr_interp_map_kernel(GrInterpArgs a) {
         case GI_FLOG: r = __float_as_uint(gr_logf(fx)); break;
         case GI_FSQRT: r = __float_as_uint(sqrtf(fx)); break;
         case GI_FSQUARE: r = __float_as_uint(fx * fx); break;
-        case GI_FTANH: r = __float_as_uint(tanhf(fx)); break;
+        case GI_FTANH: r = __float_as_uint(gr_tanhf(fx)); break;
         case GI_FERF: r = __float_as_uint(gr_erff(fx)); break;
         case GI_FADD: r = __float_as_uint(fx + fy); break;
         case GI_FSUB: r = __float_as_uint(fx - fy); break;
@@ -121,7 +122,7 @@ static __device__ __forceinline__ void gi_run(const GrInterpArgs& a, int pc, con
         case GI_FLOG: r = __float_as_uint(gr_logf(fx)); break;
         case GI_FSQRT: r = __float_as_uint(sqrtf(fx)); break;
         case GI_FSQUARE: r = __float_as_uint(fx * fx); break;
-        case GI_FTANH: r = __float_as_uint(tanhf(fx)); break;
+        case GI_FTANH: r = __float_as_uint(gr_tanhf(fx)); break;
         case GI_FERF: r = __float_as_uint(gr_erff(fx)); break;
         case GI_FADD: r = __float_as_uint(fx + fy); break;
         case GI_FSUB: r = __float_as_uint(fx - fy); break;

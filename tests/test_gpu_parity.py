@@ -185,6 +185,26 @@ def test_sqrt_of_every_float32(env):
     assert checked == (1 << 31) + (1 << 24) + ((1 << 32) - 0x81000000) // 256
 
 
+def test_tanh_of_every_eighth_float32(env):
+    """Within 2 ulp of the exact value (double precision), odd, 1 from 10 on, NaN for NaN; the interpreter gives the same bits."""
+    gr, ctx, torch = env
+    for lo in range(0, 0x41200000, 1 << 27):
+        x = torch.arange(lo, min(lo + (1 << 27), 0x41200000), 8, dtype=torch.int32, device="cuda").view(torch.float32)
+        got, exact = gr.tanh(ctx.array(x)).torch().double(), torch.tanh(x.double())
+        ulp = torch.ldexp(torch.ones_like(exact), (torch.frexp(exact)[1] - 24).clamp(min=-149))
+        assert ((got - exact).abs() <= 2 * ulp).all(), lo
+    x = torch.tensor([0.0, -0.0, 10.0, 50.0, 3e38, float("inf"), float("nan"), 0.75, 0.7499999, 1e-45, 9.01, 9.02], device="cuda")
+    x = torch.cat([x, -x, torch.randn(5000, device="cuda")])
+    got = gr.tanh(ctx.array(x)).torch()
+    assert (got[2:6] == 1).all() and torch.isnan(got[6]) and torch.isnan(got[18]) and torch.signbit(got[1])
+    assert torch.equal(got[:12].view(torch.int32)[:6], (-got[12:24]).view(torch.int32)[:6]) and torch.equal(got[7:12], -got[19:24])
+    other = gr.Context()
+    other.set_option("interp", 2)
+    assert torch.equal(gr.tanh(other.array(x)).torch().view(torch.int32), got.view(torch.int32))
+    other.sync()
+    other.close()
+
+
 def test_erf_of_every_float32_below_four(env, env_interp):
     # The generated kernels and the interpreter evaluate erf with a function of their own (two polynomial
     # pieces and the hardware's power of two).  Against the oracle's erf (binary64, rounded once) for every
