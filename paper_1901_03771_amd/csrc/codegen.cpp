@@ -3111,6 +3111,110 @@ void gemm_tile_body(Em& e, const EpiLoad& epi_load) {
   o << "}\n";
 }
 
+// Short sums, and small results with any sum: every wave takes a block of 32 x 32 and loads its operands in the order in which the
+// matrix instructions want them, straight into registers; nothing goes through LDS and no wave waits for another one before the end.
+// UC = 1: the waves of a workgroup lie side by side (BY x BX).  Bound by stores and by the latency of a wave's few loads, which the
+// other waves of its SIMD hide: many small waves, where tiles of 64 x 64 and 128 x 128 leave one or two workgroups to a compute unit that load,
+// multiply and store one after the other.
+// UC = 8: a workgroup is one block, whose values of k eight waves divide among themselves; they meet in LDS, and every lane finishes two
+// results.  Bound by latency: as many compute units as there are blocks work on a result that is a few tiles of 64 x 64, and a chain of
+// matrix instructions is an eighth as long.
+// (operands in fragment order come at about 20 bytes per cycle and compute unit where they are contiguous along k, see gemm_tile_body for long sums)
+void gemm_block_body(Em& e, const EpiLoad& epi_load) {
+  const GroupPlan& g = e.g;
+  std::ostream& o = e.o;
+  const int KW = g.UC, WN = KW > 1 ? 1 : g.BX / 32, NK = 16;   // NK: values of k per step of the loop
+  const bool kc[2] = {g.groups[g.mat_group].coef[1] == 1, g.groups[g.vec_group].coef[0] == 1};
+  const char* nm[2] = {"A", "B"};
+  o << "  const unsigned lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lh = lane >> 5;\n"
+       "  const long long NSPLIT = " << e.S(e.L.extra + 3) << ", KCH = " << e.S(e.L.ocoef + 1) << ";\n"
+       "  const unsigned tiles_n = (unsigned)((N + " << g.BX - 1 << ") / " << g.BX << "), tiles = tiles_n * (unsigned)((M + " << g.BY - 1 << ") / " << g.BY << "), total = tiles * (unsigned)NSPLIT;\n"
+       // (neighbouring tiles share operand rows: they go to the same XCD, workgroups are dealt round-robin over the 8)
+       "  const unsigned per = (total + 7) / 8, job = (blockIdx.x % 8) * per + blockIdx.x / 8;\n"
+       "  if (blockIdx.x / 8 >= per || job >= total) return;\n"
+       "  const unsigned split = job / tiles, tile = job % tiles;\n"
+       "  const long long m0 = (long long)(tile / tiles_n) * " << g.BY << (KW > 1 ? "" : " + wave / " + std::to_string(WN) + " * 32") << ", n0 = (long long)(tile % tiles_n) * " << g.BX << (KW > 1 ? "" : " + wave % " + std::to_string(WN) + " * 32") << ";\n";
+  if (KW == 1) o << "  if (m0 >= M || n0 >= N) return;\n";
+  o << "  const long long k0 = split * KCH, k1 = k0 + KCH < K ? k0 + KCH : K;\n";
+  // (a wave's share of k: whole groups of eight)
+  if (KW > 1) o << "  const long long share = ((k1 > k0 ? k1 - k0 : 0) + " << 8 * KW - 1 << ") / " << 8 * KW << " * 8, kb = k0 + wave * share, ke = kb + share < k1 ? kb + share : k1;\n";
+  else o << "  const long long kb = k0, ke = k1;\n";
+  o << "  const GM float* pA = A + (m0 + l32 < M ? m0 + l32 : M - 1) * am + (kb + 4 * lh) * ak;\n"
+       "  const GM float* pB = B + (n0 + l32 < N ? n0 + l32 : N - 1) * bn + (kb + 4 * lh) * bk;\n"
+       "  f16v acc, acc2;\n#pragma unroll\n  for (int q = 0; q < 16; ++q) acc[q] = acc2[q] = 0.0f;\n"
+       "  const int n = ke > kb ? (int)(ke - kb) : 0;\n  int k = 0;\n";
+  auto whole = [&](const char* to, int groups) {   // groups of eight values of k, all there
+    for (int x = 0; x < 2; ++x)
+      for (int gr = 0; gr < groups; ++gr) {
+        const std::string v = std::string(to) + nm[x] + std::to_string(gr), st = x == 0 ? "ak" : "bk";
+        if (kc[x]) o << "    " << v << " = *(const GM f4u*)(p" << nm[x] << " + " << 8 * gr << ");\n";
+        else for (int t = 0; t < 4; ++t) o << "    " << v << "[" << t << "] = p" << nm[x] << "[" << 8 * gr + t << " * " << st << "];\n";
+      }
+    o << "    pA += " << 8 * groups << " * ak; pB += " << 8 * groups << " * bk;\n";
+  };
+  auto products = [&](const char* from, int groups) {
+    for (int gr = 0; gr < groups; ++gr)
+      for (int t = 0; t < 4; ++t) {
+        const char* ac = t % 2 ? "acc2" : "acc";
+        const std::string i = std::to_string(gr) + "[" + std::to_string(t) + "]";
+        o << "    " << ac << " = __builtin_amdgcn_mfma_f32_32x32x2f32(" << from << "A" << i << ", " << from << "B" << i << ", " << ac << ", 0, 0, 0);\n";
+      }
+  };
+  o << "  f4 ";
+  for (const char* set : {"u", "v"}) for (int x = 0; x < 2; ++x) for (int gr = 0; gr < NK / 8; ++gr) o << (set[0] == 'u' && x == 0 && gr == 0 ? "" : ", ") << set << nm[x] << gr;
+  o << ";\n  if (n >= " << NK << ") {\n";
+  whole("u", NK / 8);
+  // (two steps at a time, so that the next one's registers have names of their own)
+  o << "    for (; k + " << 3 * NK << " <= n; k += " << 2 * NK << ") {\n";
+  whole("v", NK / 8);
+  products("u", NK / 8);
+  whole("u", NK / 8);
+  products("v", NK / 8);
+  o << "    }\n    if (k + " << 2 * NK << " <= n) {\n";
+  whole("v", NK / 8);
+  products("u", NK / 8);
+  products("v", NK / 8);
+  o << "      k += " << 2 * NK << ";\n    } else {\n";
+  products("u", NK / 8);
+  o << "      k += " << NK << ";\n    }\n  }\n"
+       // what is left: a whole group of eight, and positions of which those past the end are zero in both operands
+       "  if (k + 8 <= n) {\n";
+  whole("u", 1);
+  products("u", 1);
+  o << "    k += 8;\n  }\n  if (k < n) {\n    const int left = n - k - 4 * (int)lh;\n";
+  for (int x = 0; x < 2; ++x)
+    for (int t = 0; t < 4; ++t)
+      o << "    { const float w = p" << nm[x] << "[(long long)(" << t << " < left ? " << t << " : left - 1) * " << (x == 0 ? "ak" : "bk") << "]; u" << nm[x] << "0[" << t << "] = " << t << " < left ? w : 0.0f; }\n";
+  products("u", 1);
+  o << "  }\n  acc += acc2;\n  GM float* const out = (GM float*)" << e.slot(e.L.out) << ";\n";
+  if (KW == 1) {
+    // a block inside the result stores without a look at every element
+    o << "  GM float* const po = out + (m0 + 4 * lh) * N + n0 + l32;\n  const bool inside = m0 + 32 <= M && n0 + 32 <= N;\n";
+    for (int guarded = 0; guarded < 2; ++guarded) {
+      o << (guarded ? "  else {\n" : "  if (inside) {\n");
+      const std::string body = captured(e, [&] {
+        o << "#pragma unroll\n    for (int ql = 0; ql < 4; ++ql) {\n      const int q = 4 * qh + ql;\n"
+             "      const long long row = m0 + 8 * qh + 4 * lh + ql, col = n0 + l32;\n" << (guarded ? "      if (row < M && col < N) {\n" : "      {\n") << "        const float cacc = acc[q];\n";
+        emit_scalar_program(e, g.prog, g.results, epi_load, "cacc", "t", "        ");
+        o << "        po[(8 * qh + ql) * N] = t" << g.results[0] << ";\n      }\n    }\n";
+      });
+      emit_unrolled(o, {{"qh", 4}}, body, "    ");
+      o << "  }\n";
+    }
+  } else {
+    o << "  __shared__ float sm[" << KW << "][1024];\n"
+         "#pragma unroll\n  for (int q = 0; q < 16; ++q) sm[wave][q * 64 + lane] = acc[q];\n  __syncthreads();\n"
+         "#pragma unroll\n  for (int i = 0; i < " << 16 / KW << "; ++i) {\n    const unsigned at = threadIdx.x + i * " << 64 * KW << ", q = at / 64, ln = at % 64;\n    float w[" << KW << "];\n"
+         "#pragma unroll\n    for (int x = 0; x < " << KW << "; ++x) w[x] = sm[x][at];\n"
+         "#pragma unroll\n    for (int d = 1; d < " << KW << "; d *= 2)\n#pragma unroll\n      for (int x = 0; x < " << KW << "; x += 2 * d) w[x] += w[x + d];\n"
+         "    const long long row = m0 + 8 * (q / 4) + 4 * (ln / 32) + q % 4, col = n0 + ln % 32;\n"
+         "    if (row < M && col < N) {\n      const float cacc = w[0];\n      if (NSPLIT > 1) ((GM float*)" << e.slot(e.L.ocoef) << ")[(split * M + row) * N + col] = cacc;\n      else {\n";
+    emit_scalar_program(e, g.prog, g.results, epi_load, "cacc", "t", "        ");
+    o << "        out[row * N + col] = t" << g.results[0] << ";\n      }\n    }\n  }\n";
+  }
+  o << "}\n";
+}
+
 // C = A.B for f32 on MFMA (v_mfma_f32_32x32x2_f32: f32 inputs, f32 accumulation), the one place
 // on this path that is a dense contraction.  A workgroup of four waves owns a 128x128 tile of
 // C; each wave a 64x64 quarter as 2x2 MFMA blocks (64 accumulator VGPRs).  K advances in steps
@@ -3143,7 +3247,7 @@ void gen_gemm(Em& e) {
   prelude(e);
   e.o << "typedef float f16v __attribute__((ext_vector_type(16)));\n";
   if (g.VR == 2 && g.UC == 2) split_helpers(e);
-  kernel_head(e, "gr_gemm", g.VR == 2 && g.UC == 2 ? 512 : 256);
+  kernel_head(e, "gr_gemm", gemm_threads(g));
   e.o << "  const long long M = " << e.S(e.L.extra) << ", N = " << e.S(e.L.extra + 1) << ", K = " << e.S(e.L.extra + 2) << ";\n";
   group_pointers(e, "  ");
   e.o << "  const GM float* const A = q" << g.mat_group << "; const GM float* const B = q" << g.vec_group << ";\n";
@@ -3159,6 +3263,11 @@ void gen_gemm(Em& e) {
     return s2.str();
   };
   auto emit_combine = [&]() { gemm_combine(e, epi_load); };
+  if (g.VR == 4) {   // blocks of 32 x 32 from registers
+    gemm_block_body(e, epi_load);
+    emit_combine();
+    return;
+  }
   if (g.VR == 3) {   // small tiles, clamped loads
     gemm_tile_body(e, epi_load);
     emit_combine();

@@ -757,6 +757,43 @@ static void choose_in_place(GroupPlan* g) {
   g->in_place_once = g->in_place && in_place_tiles(*g) <= kOnceTiles;
 }
 
+// Products that are blocks of 32 x 32 from registers (gemm_block_body), before all other choices.
+// - k over the waves of a workgroup: results of fewer than 16 tiles of 64 x 64, whatever the sum, and sums of up to 384 for up to 512 blocks, two
+//   to a compute unit.  (us, tiles of 64 x 64 or 128 x 32 / this: 64^3 4.9 / 3.6, 300 x 46 x 320 5.3 / 3.4, with a bias and tanh 8.6 / 3.8, 46 x 296 x 320 10.6 /
+//   4.9, 300^3 10.8 / 5.0, 500 x 300 x 500 10.9 / 5.2, 1000 x 350 x 500 11.2 / 8.8; 625 blocks of 800 x 300 x 800 11.2 / 10.6, 1024 of 1000 x 200 x 1000
+//   9.3 / 11.1.  Longer sums: 256 x 512 x 256 9.9 / 6.3, but 512^3 11.3 / 9.5 to 13 by layout: from 16 tiles on all of them stay.)  Long sums are split over
+//   workgroups as well: by 0.0062 us per value of k and round of 256 blocks, 2.7 for the second launch and 0.08 per part that it adds up (97 x 1491 x 40 10.3 / 8.1,
+//   50 x 4800 x 32 11.8 / 9.4, 200 x 500 x 200, unsplit, 10.8 / 6.0).
+// - waves side by side: more blocks, ragged operands, sums of up to 32 and at most 10^7 results (100000 x 9 x 40 13.5 / 9.6, 30000 x 20 x 200 13.4 / 12, 3000 x 20 x 3000 16.1 / 13.9,
+//   4936 x 27 x 1131 14.1 / 11.8; 2000 x 33 x 4000 15.8 / 16.7, 16384 x 16 x 4096 53 / 64), and sums of up to 128 whose results pass through a function of many
+//   instructions, which the larger tiles run when their products are done (tanh: 4936 x 27 x 1131 27.5 / 17.3, 11845 x 48 x 2066 77 / 60, 16384 x 100 x 1000 82 / 61,
+//   4096 x 128 x 4096 91 / 64, 8000 x 64 x 1000 29.6 / 26.1, 5000 x 128 x 300 12.9 / 12.9).  Operands of 32 columns and fewer are read once by taller tiles.
+static bool choose_gemm_blocks(GroupPlan* g) {
+  const int64_t M = g->M, N = g->N, K = g->K;
+  const int64_t blocks = ((M + 31) / 32) * ((N + 31) / 32), tiles = ((M + 63) / 64) * ((N + 63) / 64);
+  if (tiles < 16 || (blocks <= 512 && K <= 384)) {
+    double cost = 0;
+    int best = 1;
+    for (int ks = 1; ks <= g->slabs; ++ks) {
+      const double us = (double)gemm_split_extent(K, ks) * 0.0062 * std::max(1.0, (double)(blocks * ks) / 256.0) + (ks > 1 ? 2.7 + 0.08 * ks + (double)ks * (double)M * (double)N * 1.8e-6 : 0.0);
+      if (ks == 1 || us < cost * 0.97) { cost = us; best = ks; }
+    }
+    g->UC = 8;
+    g->BX = g->BY = 32;
+    g->slabs = best;
+  } else {
+    int heavy = 0;   // (a division, a root, an exponential are a third of the others)
+    for (const Instr& in : g->prog) if (heavy_op(in)) heavy += in.kind == IKind::UNARY && (in.op == GR_TANH || in.op == GR_ERF) ? 3 : 1;
+    if (M <= 32 || N <= 32 || !((K <= 32 && M * N <= 10000000 && g->VR != 2) || (heavy >= 3 && K <= 128))) return false;
+    g->UC = 1;
+    g->BX = g->BY = 64;
+    g->slabs = 1;
+  }
+  g->VR = 4;
+  g->NP = 1;
+  return true;
+}
+
 // Small or ragged matrix products: tiles of 64 x 64 (128 x 32, 32 x 128) with clamped loads (gemm_tile_body), after the
 // choice between the kernels with tiles of 128 and 256.
 // The split of K: cheapest by rounds of 256 workgroups times steps of 32 values of k at 0.62 us, 5 for the launch and the first
@@ -777,13 +814,14 @@ static void choose_in_place(GroupPlan* g) {
 // between the kernels, so that a request that must not allocate takes the kernel that the same request would take
 // otherwise (and that is loaded by then); g->slabs, which stays within its scratch array, bounds the splits.
 void choose_gemm_tiles(GroupPlan* g, int wanted) {
-  if (g->VR == 2 && g->BX != 128) return;
   const int64_t M = g->M, N = g->N, K = g->K;
   auto fits = [&](const AccessGroup& x, int kdim, int64_t other) {
     if (x.coef[kdim] == 1) return K >= 4;
     return x.coef[1 - kdim] == 1 && other >= 4 && x.coef[kdim] > 0 && x.coef[kdim] < ((int64_t)1 << 32);
   };
   if (M < 1 || N < 1 || K > (int64_t)1 << 30 || !fits(g->groups[g->mat_group], 1, M) || !fits(g->groups[g->vec_group], 0, N)) return;
+  if (choose_gemm_blocks(g)) return;
+  if (g->VR == 2 && g->BX != 128) return;
   const int64_t tm = N <= 32 ? 128 : (M <= 32 ? 32 : 64), tn = N <= 32 ? 32 : (M <= 32 ? 128 : 64);
   const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
   if (tiles > (int64_t)1 << 24) return;
@@ -1958,7 +1996,7 @@ std::string describe_plan(const Plan& plan) {
     first = true;
     for (const Node* n : g.leaves) { s << (first ? "" : ",") << n->id; first = false; }
     s << "] loads=" << [&] { int k = 0; for (const Instr& in : (g.kind == GroupKind::MAP ? g.prog1 : g.prog)) if (in.kind == IKind::LOAD) ++k; return k; }();
-    if (g.kind == GroupKind::GEMM) s << " M=" << g.M << " N=" << g.N << " K=" << g.K << " tile=" << (g.VR == 3 ? g.BY : g.BX == 256 ? 256 : 128) << "x" << g.BX << (g.VR == 3 ? " clamped" : g.VR == 2 ? " direct" : "");
+    if (g.kind == GroupKind::GEMM) s << " M=" << g.M << " N=" << g.N << " K=" << g.K << " tile=" << (g.VR >= 3 ? g.BY : g.BX == 256 ? 256 : 128) << "x" << g.BX << (g.VR == 4 ? (g.UC > 1 ? " clamped, k over waves" : " clamped, from registers") : g.VR == 3 ? " clamped" : g.VR == 2 ? " direct" : "");
     if (g.kind == GroupKind::GEMM && g.slabs > 1) s << " split=" << g.slabs;
     if (g.kind == GroupKind::GEMV) s << " mode=" << (g.gemv_mode == 2 ? "row-dot+column-accumulate" : (g.gemv_mode ? "column-accumulate" : "row-dot")) << " M=" << g.M << " K=" << g.K;
     if (g.pair) {

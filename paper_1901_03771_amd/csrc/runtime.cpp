@@ -746,8 +746,8 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
         if (wst != GR_OK) return wst;
         s[L.ocoef] = (uint64_t)(uintptr_t)ws;
       }
-      const int64_t small = ((g.M + g.BY - 1) / g.BY) * ((g.N + g.BX - 1) / g.BX) * nsplit;   // (VR = 3: BY x BX tiles, a multiple of 8 workgroups)
-      gr_status st = launch(c, k->fn, k->name, g.VR == 3 ? (small + 7) / 8 * 8 : tiles * nsplit, s, g.VR == 2 && g.UC == 2 ? 512 : 256);
+      const int64_t small = ((g.M + g.BY - 1) / g.BY) * ((g.N + g.BX - 1) / g.BX) * nsplit;   // (VR = 3, 4: BY x BX tiles, a multiple of 8 workgroups)
+      gr_status st = launch(c, k->fn, k->name, g.VR >= 3 ? (small + 7) / 8 * 8 : tiles * nsplit, s, gemm_threads(g));
       if (st != GR_OK || nsplit <= 1) return st;
       return launch(c, k->fn2, k->name + "_combine", (g.M * g.N + 255) / 256, s);
     }

@@ -325,6 +325,52 @@ def test_products_with_clamped_tiles(env, m, k, n, layout):
     assert np.array_equal(out.cpu().numpy(), ref, equal_nan=True)
 
 
+# blocks of 32 x 32 from registers: k over the waves of a workgroup (w, also split over workgroups) and waves side by side (r), on both sides of every rule; sums that
+# leave waves without a share, end within a group of eight, a step and two steps; small integers: exact in any order
+@pytest.mark.parametrize("m,k,n,way", [
+    (33, 9, 65, "w"), (64, 15, 31, "w"), (1, 16, 40, "w"), (40, 17, 1, "w"), (100, 65, 97, "w"), (512, 384, 1024, "w"), (511, 129, 1000, "w"), (512, 385, 1024, "-"), (545, 64, 1024, "-"),
+    (545, 31, 1022, "r"), (545, 33, 1022, "-"), (3130, 9, 3190, "r"), (3163, 9, 3163, "-"), (65, 30, 12000, "r"), (9000, 31, 70, "r"), (17000, 31, 32, "-"), (192, 2000, 320, "w"), (33, 9000, 30, "w"), (256, 400, 256, "-")])
+@pytest.mark.parametrize("layout", ["nn", "tn", "nt", "tt"])
+def test_products_of_blocks_from_registers(env, m, k, n, way, layout):
+    gr, ctx, torch = env
+    rng = np.random.default_rng(24)
+    a = rng.integers(-4, 5, (m, k) if layout[0] == "n" else (k, m)).astype(f32)
+    b = rng.integers(-4, 5, (k, n) if layout[1] == "n" else (n, k)).astype(f32)
+    c = rng.integers(-9, 9, n).astype(f32)
+
+    def prog(xp, a, b, c):
+        return (a if layout[0] == "n" else xp.transpose(a)) @ (b if layout[1] == "n" else xp.transpose(b)) * 2.0 + c
+
+    if layout == "nn" or min(m, n) >= 4:    # (an operand of fewer than four rows that lie along its other dimension takes the general kernel)
+        plan = prog(gr, *(ctx.spec(v.shape) for v in (a, b, c))).plan()
+        assert ("w" if "k over waves" in plan else "r" if "from registers" in plan else "-") == way
+    got, ref = both(env, prog, a=a, b=b, c=c)
+    assert np.array_equal(got, ref)
+    a[a.shape[0] // 2, a.shape[1] // 2] = np.inf      # stays in its row
+    ta, tb, tc = (torch.from_numpy(v).cuda() for v in (a, b, c))
+    guard = torch.full((m * n + 128,), 7.0, device="cuda")
+    out = guard[64:64 + m * n].view(m, n)
+    prog(gr, *(ctx.array(t) for t in (ta, tb, tc))).materialize_into(out)
+    assert (guard[:64] == 7.0).all() and (guard[64 + m * n:] == 7.0).all()
+    ref = prog(ora, *(ora.array(v) for v in (a, b, c))).numpy()
+    assert np.array_equal(out.cpu().numpy(), ref, equal_nan=True)
+
+
+def test_short_products_under_a_long_function_take_blocks(env):
+    gr, ctx, torch = env
+    for m, k, n, way in ((2100, 128, 700, True), (2100, 129, 700, False), (4096, 128, 4096, True)):
+        rng = np.random.default_rng(25)
+        a, b, c = rng.standard_normal((m, k)).astype(f32), rng.standard_normal((k, n)).astype(f32) * f32(0.1), rng.standard_normal(n).astype(f32)
+        prog = lambda xp, a, b, c: xp.tanh(a @ b + c)
+        assert ("from registers" in prog(gr, *(ctx.spec(v.shape) for v in (a, b, c))).plan()) == way
+        t = [torch.from_numpy(v).cuda() for v in (a, b, c)]
+        got = prog(gr, *(ctx.array(v) for v in t)).torch()
+        exact = torch.tanh(t[0].double() @ t[1].double() + t[2].double())
+        # (a sum of k products in two chains: k / 2 + 2 roundings of what |a| |b| + |c| adds up to, and two ulp of the result)
+        bound = (k / 2 + 2) * 2.0 ** -24 * (t[0].double().abs() @ t[1].double().abs() + t[2].double().abs()) + 2.0 ** -22
+        assert ((got.double() - exact).abs() <= bound).all()
+
+
 def test_static_entry_near_the_scratch_limit_takes_fewer_partial_sums(env):
     # column sums whose partial results do not fit beside the stored prefix sums (16680000 of 16777216 bytes): still served
     gr, ctx, torch = env
