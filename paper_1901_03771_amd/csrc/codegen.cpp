@@ -2460,16 +2460,27 @@ void emit_colacc_combine(Em& e, const std::string& kname) {
   e.o << "  const long long M = " << e.S(e.L.extra) << ", SLABS = " << e.S(e.L.extra + 3) << ";\n";
   e.o << "  const GM float* const ws = (const GM float*)" << e.slot(e.L.extra + 2) << ";\n";
   group_pointers(e, "  ", {g.mat_group, g.vec_group});
-  e.o << "  const int tx = threadIdx.x % 16, sg = threadIdx.x / 16;\n";
-  e.o << "  const long long m = (long long)blockIdx.x * 16 + tx;\n";
-  e.o << "  __shared__ float sm[16][17];\n  float part = 0.0f;\n";
-  e.o << "  if (m < M) {\n    long long s = sg;\n"
-         "    for (; s + 112 < SLABS; s += 128) {\n      float v[8];\n"
-         "#pragma unroll\n      for (int u = 0; u < 8; ++u) v[u] = ws[(s + 16 * u) * M + m];\n"
-         "#pragma unroll\n      for (int u = 0; u < 8; ++u) part += v[u];\n    }\n"
-         "    for (; s < SLABS; s += 16) part += ws[s * M + m];\n  }\n";
-  e.o << "  sm[sg][tx] = part;\n  __syncthreads();\n";
-  e.o << "  if (sg == 0 && m < M) {\n    float acc = sm[0][tx];\n    for (int y = 1; y < 16; ++y) acc += sm[y][tx];\n";
+  // (few columns: four of a workgroup instead of sixteen, and a lane adds up its partial vectors in one round of loads; 384 and fewer, as the pieces
+  // of a vector become short: 60000 x 333 21.0 -> 20.3 us, 378142 x 41 4.7 -> 4.0 of the kernel, but 120000 x 512 44.2 -> 44.7, 65536 x 2048 85.6 -> 90.5)
+  e.o << "  const bool few = M <= " << kCombineFew << ";\n"
+         "  const int tx = few ? threadIdx.x % 4 : threadIdx.x % 16, sg = few ? threadIdx.x / 4 : threadIdx.x / 16;\n"
+         "  const long long m = (long long)blockIdx.x * (few ? 4 : 16) + tx;\n"
+         "  __shared__ float sm[16][17];\n  float part = 0.0f, acc;\n"
+         "  if (few) {\n"
+         "    const int rows = (int)SLABS, of = (int)M, mc = m < M ? (int)m : 0;\n"
+         "    for (int s = sg; s < rows; s += 512) {\n      float v[8];\n"
+         "#pragma unroll\n      for (int u = 0; u < 8; ++u) v[u] = ws[(long long)(s + 64 * u < rows ? s + 64 * u : s) * of + mc];\n"
+         "#pragma unroll\n      for (int u = 0; u < 8; ++u) part += s + 64 * u < rows ? v[u] : 0.0f;\n    }\n"
+         "    for (int d = 4; d < 64; d *= 2) part += gr_xor(part, d);\n"
+         "    if ((threadIdx.x & 63) < 4) sm[threadIdx.x >> 6][tx] = part;\n    __syncthreads();\n    acc = (sm[0][tx] + sm[1][tx]) + (sm[2][tx] + sm[3][tx]);\n"
+         "  } else {\n"
+         "    if (m < M) {\n      long long s = sg;\n"
+         "      for (; s + 112 < SLABS; s += 128) {\n        float v[8];\n"
+         "#pragma unroll\n        for (int u = 0; u < 8; ++u) v[u] = ws[(s + 16 * u) * M + m];\n"
+         "#pragma unroll\n        for (int u = 0; u < 8; ++u) part += v[u];\n      }\n"
+         "      for (; s < SLABS; s += 16) part += ws[s * M + m];\n    }\n"
+         "    sm[sg][tx] = part;\n    __syncthreads();\n    acc = sm[0][tx];\n    for (int y = 1; y < 16; ++y) acc += sm[y][tx];\n  }\n";
+  e.o << "  if (sg == 0 && m < M) {\n";
   gemv_epilogue(e, "m", "acc", "    ");
   e.o << "    ((GM float*)" << e.slot(e.L.out) << ")[m] = t" << g.results[0] << ";\n  }\n}\n";
 }
@@ -2516,14 +2527,33 @@ void gen_gemv_colacc(Em& e) {
 // Row-dot contraction, its epilogue, and the column-accumulate contraction that consumes the
 // epilogue's result, in one pass over the matrix: a row stays in registers between
 // z = X[i,:].w, r_i = epilogue(z) and g += X[i,:] * r_i.
+// Bound by HBM where the waves, two per SIMD, have loads enough under way: one row at a time of 16 lanes each is 64 of them for 512 columns and
+// eight for 41, and a load's latency is then paid once per row (378142 x 41: 50.9 us, 1.2 TB/s, 46 rows in turn at 1.1 us each).  With `unroll` rows
+// at a time the loads of all of them come first; the end of a ragged row is one 16-byte load that starts earlier, instead of four under
+// conditions that every row waited for as well; sums over the row's lanes are additions from neighbouring lanes' registers (of 16 lanes with the
+// bits of the exchange through LDS); and lane u takes the epilogue of row u, which all lanes took for each row.
+// (us of a logistic-regression step, before and after: 378142 x 41 53.8 / 15.7, 1000000 x 16 110 / 17.7, 300001 x 27 42.9 / 11.2, 249354 x 100 40.1 / 21.9,
+// 526145 x 117 88.4 / 43.5, 1000000 x 64 98 / 46.5, 262144 x 192 39.9 / 35.9, 60000 x 333 26.3 / 20.3, 30000 x 700 24.8 / 19.5, 10000 x 2040 25.4 / 21.8)
 void gen_gemv_pair(Em& e, Em& e2) {
   const GroupPlan& g = e.g;
-  const int LPR = g.LPR, KV = g.KV, RPB = 256 / LPR, CH = LPR * 4;
+  const int LPR = g.LPR, KV = g.KV, RPB = 256 / LPR, CH = LPR * 4, UN = g.unroll;
   const AccessGroup& mg = g.groups[g.mat_group];
   const AccessGroup& vg = g.groups[g.vec_group];
   (void)mg;
   const bool vec_unit = vg.coef[1] == 1;
   prelude(e);
+  if (UN > 1) {
+    // gr_from: the value of lane u of a row's lanes; gr_row_sum: the sum over them, in each of them
+    e.o << "#define GR_DPP(v, c) __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), c, 0xf, 0xf, true))\n";
+    if (LPR == 64) e.o << "#define gr_from(v, u) __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), u))\n";
+    else if (LPR == 16) e.o << "#define gr_from(v, u) GR_DPP(v, 0x150 + u)\n";   // row_newbcast
+    else e.o << "#define gr_from(v, u) __uint_as_float(__builtin_amdgcn_ds_swizzle(__float_as_uint(v), 0x18 | u << 5))\n";
+    e.o << "static __device__ __forceinline__ float gr_row_sum(float v) {\n"
+        << (LPR == 64 ? "  v += gr_xor(v, 32); v += gr_xor(v, 16);\n" : "")
+        << (LPR == 8 ? "  v += GR_DPP(v, 0x141); v += GR_DPP(v, 0x4e); v += GR_DPP(v, 0xb1);\n"   // half mirror, quads turned by two and by one
+                     : "  v += GR_DPP(v, 0x128); v += GR_DPP(v, 0x124); v += GR_DPP(v, 0x122); v += GR_DPP(v, 0x121);\n")   // turns by 8, 4, 2 and 1 lanes
+        << "  return v;\n}\n";
+  }
   kernel_head(e, "gr_gemv_pair");
   e.o << "  const long long M = " << e.S(e.L.extra) << ", K = " << e.S(e.L.extra + 1) << ", SLABS = " << e.S(e.L.extra + 3) << ";\n";
   e.o << "  GM float* const ws = (GM float*)" << e.slot(e.L.extra + 2) << ";\n";
@@ -2534,27 +2564,76 @@ void gen_gemv_pair(Em& e, Em& e2) {
   e.o << "  GM float* const out = (GM float*)" << e.slot(e.L.out) << ";\n";
   e.o << "  const long long rs = ((M + SLABS - 1) / SLABS + " << RPB - 1 << ") / " << RPB << " * " << RPB << ";\n";
   e.o << "  const long long rbeg = (long long)blockIdx.x * rs, rend = (rbeg + rs < M) ? rbeg + rs : M;\n";
-  e.o << "  float wv[" << KV << "][4], acc[" << KV << "][4];\n";
-  e.o << "#pragma unroll\n  for (int q = 0; q < " << KV << "; ++q) {\n    const long long k0 = (long long)q * " << CH << " + lane * 4;\n"
-         "    for (int j = 0; j < 4; ++j) { wv[q][j] = (k0 + j < K) ? V[(k0 + j) * vk] : 0.0f; acc[q][j] = 0.0f; }\n  }\n";
-  e.o << "  for (long long row = rbeg + rib; row < rend; row += " << RPB << ") {\n";
-  e.o << "    const GM float* const Ar = A + row * am;\n    float xv[" << KV << "][4];\n";
-  e.o << "#pragma unroll\n    for (int q = 0; q < " << KV << "; ++q) {\n      const long long k0 = (long long)q * " << CH << " + lane * 4;\n"
-         "      if (k0 + 4 <= K) { const f4u w = " << e.ld(g.mat_group, "f4u", "Ar + k0") << "; xv[q][0] = w[0]; xv[q][1] = w[1]; xv[q][2] = w[2]; xv[q][3] = w[3]; }\n"
-         "      else { for (int j = 0; j < 4; ++j) xv[q][j] = (k0 + j < K) ? Ar[k0 + j] : 0.0f; }\n    }\n";
-  e.o << "    float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};\n"
-         "#pragma unroll\n    for (int q = 0; q < " << KV << "; ++q)\n#pragma unroll\n      for (int j = 0; j < 4; ++j) z[j] = __builtin_fmaf(xv[q][j], wv[q][j], z[j]);\n"
-         "    float zz = (z[0] + z[1]) + (z[2] + z[3]);\n";
-  for (int m = LPR / 2; m > 0; m >>= 1) e.o << "    zz += gr_xor(zz, " << m << ");\n";
-  gemv_epilogue(e, "row", "zz", "    ");
-  e.o << "    const float rr = t" << g.results[0] << ";\n    if (lane == 0) out[row] = rr;\n";
-  e.o << "#pragma unroll\n    for (int q = 0; q < " << KV << "; ++q)\n#pragma unroll\n      for (int j = 0; j < 4; ++j) acc[q][j] = __builtin_fmaf(xv[q][j], rr, acc[q][j]);\n  }\n";
+  if (UN == 1) {
+    e.o << "  float wv[" << KV << "][4], acc[" << KV << "][4];\n";
+    e.o << "#pragma unroll\n  for (int q = 0; q < " << KV << "; ++q) {\n    const long long k0 = (long long)q * " << CH << " + lane * 4;\n"
+           "    for (int j = 0; j < 4; ++j) { wv[q][j] = (k0 + j < K) ? V[(k0 + j) * vk] : 0.0f; acc[q][j] = 0.0f; }\n  }\n";
+    e.o << "  for (long long row = rbeg + rib; row < rend; row += " << RPB << ") {\n";
+    e.o << "    const GM float* const Ar = A + row * am;\n    float xv[" << KV << "][4];\n";
+    e.o << "#pragma unroll\n    for (int q = 0; q < " << KV << "; ++q) {\n      const long long k0 = (long long)q * " << CH << " + lane * 4;\n"
+           "      if (k0 + 4 <= K) { const f4u w = " << e.ld(g.mat_group, "f4u", "Ar + k0") << "; xv[q][0] = w[0]; xv[q][1] = w[1]; xv[q][2] = w[2]; xv[q][3] = w[3]; }\n"
+           "      else { for (int j = 0; j < 4; ++j) xv[q][j] = (k0 + j < K) ? Ar[k0 + j] : 0.0f; }\n    }\n";
+    e.o << "    float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};\n"
+           "#pragma unroll\n    for (int q = 0; q < " << KV << "; ++q)\n#pragma unroll\n      for (int j = 0; j < 4; ++j) z[j] = __builtin_fmaf(xv[q][j], wv[q][j], z[j]);\n"
+           "    float zz = (z[0] + z[1]) + (z[2] + z[3]);\n";
+    for (int m = LPR / 2; m > 0; m >>= 1) e.o << "    zz += gr_xor(zz, " << m << ");\n";
+    gemv_epilogue(e, "row", "zz", "    ");
+    e.o << "    const float rr = t" << g.results[0] << ";\n    if (lane == 0) out[row] = rr;\n";
+    e.o << "#pragma unroll\n    for (int q = 0; q < " << KV << "; ++q)\n#pragma unroll\n      for (int j = 0; j < 4; ++j) acc[q][j] = __builtin_fmaf(xv[q][j], rr, acc[q][j]);\n  }\n";
+  } else {
+    // (the last chunk: a lane whose elements reach past the row's end reads the four before the end instead, and keeps those from its own first one on)
+    e.o << "  const long long klast = " << (KV - 1) * CH << " + lane * 4, kb = klast + 4 <= K ? klast : K - 4;\n  const int skip = (int)(klast - kb < 4 ? klast - kb : 4);\n";
+    e.o << "  float wv[" << KV << "][4], acc[" << KV << "][4];\n";
+    e.o << "#pragma unroll\n  for (int q = 0; q < " << KV << "; ++q) {\n    const long long k0 = q == " << KV - 1 << " ? kb : (long long)q * " << CH << " + lane * 4;\n"
+           "#pragma unroll\n    for (int j = 0; j < 4; ++j) { wv[q][j] = V[(k0 + j) * vk]; acc[q][j] = 0.0f; }\n  }\n";
+    e.o << "  const int mine = lane < " << UN << " ? lane : 0;\n";
+    e.o << "  const GM float* Ar = A + (rbeg + rib) * am;\n  long long row = rbeg + rib;\n";
+    auto batch = [&](bool some, const char* ind) {
+      const std::string I = ind;
+      for (int u = 0; u < UN; ++u) {
+        if (some && u) e.o << I << "const bool in" << u << " = row + " << u * RPB << " < rend;\n";
+        e.o << I << "const GM float* const A" << u << " = " << (u == 0 ? "Ar" : some ? "in" + std::to_string(u) + " ? Ar + " + std::to_string(u * RPB) + " * am : Ar" : "Ar + " + std::to_string(u * RPB) + " * am") << ";\n";
+        for (int q = 0; q < KV; ++q)
+          e.o << I << "f4u x" << u << "_" << q << " = " << e.ld(g.mat_group, "f4u", "A" + std::to_string(u) + " + " + (q == KV - 1 ? std::string("kb") : std::to_string(q * CH) + " + lane * 4")) << ";\n";
+      }
+      e.o << I << "__builtin_amdgcn_sched_barrier(0);\n";
+      for (int u = 0; u < UN; ++u) {
+        const std::string x = "x" + std::to_string(u) + "_", z = "z" + std::to_string(u);
+        e.o << I << "float " << z << ";\n" << I << "{\n";
+        for (int j = 0; j < 4; ++j) e.o << I << "  " << x << KV - 1 << "[" << j << "] = skip <= " << j << " ? " << x << KV - 1 << "[" << j << "] : 0.0f;\n";
+        for (int j = 0; j < 4; ++j) {
+          e.o << I << "  float y" << j << " = " << x << "0[" << j << "] * wv[0][" << j << "];\n";
+          for (int q = 1; q < KV; ++q) e.o << I << "  y" << j << " = __builtin_fmaf(" << x << q << "[" << j << "], wv[" << q << "][" << j << "], y" << j << ");\n";
+        }
+        e.o << I << "  " << z << " = gr_row_sum((y0 + y1) + (y2 + y3));\n" << I << "}\n";
+      }
+      // lane u of a row's lanes takes the epilogue of row u, for all of them
+      e.o << I << "float zz = z0;\n";
+      for (int u = 1; u < UN; ++u) e.o << I << "zz = mine == " << u << " ? z" << u << " : zz;\n";
+      e.o << I << "const long long at = row + mine * " << RPB << ", ro = " << (some ? "at < rend ? at : row" : "at") << ";\n";
+      gemv_epilogue(e, "ro", "zz", ind);
+      e.o << I << "const float rr = t" << g.results[0] << ";\n" << I << "if (lane < " << UN << (some ? " && at < rend" : "") << ") out[at] = rr;\n";
+      for (int u = 0; u < UN; ++u) {
+        e.o << I << (some && u ? "if (in" + std::to_string(u) + ") " : std::string()) << "{\n" << I << "  const float r = gr_from(rr, " << u << ");\n";
+        for (int q = 0; q < KV; ++q)
+          for (int j = 0; j < 4; ++j) e.o << I << "  acc[" << q << "][" << j << "] = __builtin_fmaf(x" << u << "_" << q << "[" << j << "], r, acc[" << q << "][" << j << "]);\n";
+        e.o << I << "}\n";
+      }
+    };
+    e.o << "  for (; row + " << (UN - 1) * RPB << " < rend; row += " << UN * RPB << ", Ar += " << UN * RPB << " * am) {\n";
+    batch(false, "    ");
+    e.o << "  }\n  if (row < rend) {\n";
+    batch(true, "    ");
+    e.o << "  }\n";
+  }
   // lanes with the same position in different row groups of a wave own the same columns
   e.o << "#pragma unroll\n  for (int q = 0; q < " << KV << "; ++q)\n#pragma unroll\n    for (int j = 0; j < 4; ++j) {\n";
   for (int m = LPR; m < 64; m <<= 1) e.o << "      acc[q][j] += gr_xor(acc[q][j], " << m << ");\n";
   e.o << "    }\n";
   e.o << "  __shared__ float sm[4][" << CH * KV << "];\n";
-  e.o << "  if ((threadIdx.x & 63) < " << LPR << ") {\n#pragma unroll\n    for (int q = 0; q < " << KV << "; ++q)\n      for (int j = 0; j < 4; ++j) sm[threadIdx.x >> 6][q * " << CH << " + lane * 4 + j] = acc[q][j];\n  }\n";
+  if (UN == 1) e.o << "  if ((threadIdx.x & 63) < " << LPR << ") {\n#pragma unroll\n    for (int q = 0; q < " << KV << "; ++q)\n      for (int j = 0; j < 4; ++j) sm[threadIdx.x >> 6][q * " << CH << " + lane * 4 + j] = acc[q][j];\n  }\n";
+  else e.o << "  if ((threadIdx.x & 63) < " << LPR << ") {\n#pragma unroll\n    for (int q = 0; q < " << KV << "; ++q)\n#pragma unroll\n      for (int j = 0; j < 4; ++j)\n"
+              "        if (q < " << KV - 1 << " || skip <= j) sm[threadIdx.x >> 6][(q < " << KV - 1 << " ? q * " << CH << " + lane * 4 : (int)kb) + j] = acc[q][j];\n  }\n";
   e.o << "  __syncthreads();\n";
   e.o << "  for (int k = threadIdx.x; k < " << CH * KV << "; k += 256)\n    if (k < K) ws[(long long)blockIdx.x * K + k] = ((sm[0][k] + sm[1][k]) + sm[2][k]) + sm[3][k];\n}\n";
   // second stage with the second sub-graph's epilogue; its argument block follows the first one

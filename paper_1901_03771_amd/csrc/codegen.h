@@ -39,6 +39,9 @@ constexpr int kReduceLanes = 512;
 // Splits of a reduction from which on the kernel that combines the partial results of 1024 outputs and more takes several lanes per output.
 constexpr int kCombineSplits = 16;
 
+// Columns up to which the kernel that combines the partial vectors of a matrix-vector product takes four of them per workgroup instead of sixteen.
+constexpr int kCombineFew = 384;
+
 // Lanes of a workgroup of a matrix product's kernel.
 inline unsigned gemm_threads(const GroupPlan& g) { return g.VR == 4 ? 64u * (g.UC > 1 ? (unsigned)g.UC : 4u) : (g.VR == 2 && g.UC == 2 ? 512u : 256u); }
 

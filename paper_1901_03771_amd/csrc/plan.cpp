@@ -1814,8 +1814,15 @@ static void fuse_gemv_pairs(gr_ctx* c, Plan* plan) {
                        A.M == B.K && A.K == B.M;
     bool feeds = vb.leaf == A.root && vb.base == 0 && vb.coef[1] == 1;
     if (!same_matrix || !feeds || A.K > 2048 || A.M < 1) continue;
-    A.LPR = A.K <= 512 ? 16 : 64;
+    // Lanes of a row, and rows that they take at a time.  32 columns and fewer leave half of 16 lanes without any (us, 16 / 8 lanes: 1000000 x 16 31.1 /
+    // 22.9, 300001 x 27 14.9 / 13.2).  Six rows where a lane holds four columns (two, four, six, eight rows: 378142 x 41 24.0, 18.0, 15.7, 17.2; 1000000 x 16 27.8,
+    // 20.4, 17.7, 20.0), two beyond (one, two, four: 524288 x 128 62.9, 43.7, 45.7; 100000 x 200 24.9, 18.5, 20.1; 20000 x 1500 28.9, 25.9, 29.2); one where whole 16-byte
+    // loads of wide rows fill a long range, which reads at HBM's rate so (262144 x 512 86.0 / 87.3, 131072 x 1024 81.6 / 84; 60000 x 448 24.9 / 22.7, 20000 x 2048 34.1 / 32.6)
+    // and for rows of three columns, without 16 bytes.
+    A.LPR = A.K <= 32 ? 8 : A.K <= 512 ? 16 : 64;
     A.KV = (int)std::max<int64_t>(1, (A.K + (int64_t)A.LPR * 4 - 1) / ((int64_t)A.LPR * 4));
+    const bool whole = A.KV >= 4 && A.K % (A.LPR * 4) == 0 && A.M > 16 * 512 * (256 / A.LPR);
+    A.unroll = A.K < 4 || whole ? 1 : (A.KV == 1 ? 6 : 2);
     int rpb = 256 / A.LPR;
     int64_t slabs = std::min<int64_t>(512, (A.M + rpb - 1) / rpb);  // measured: 256 -> 115 us, 512 -> 94 us, 1024 -> 96 us, 4096 -> 109 us
     if (c->opt_gemv_slabs > 0) slabs = std::min<int64_t>(c->opt_gemv_slabs, (A.M + rpb - 1) / rpb);

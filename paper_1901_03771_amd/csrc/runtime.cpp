@@ -772,7 +772,7 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
         s2[L2.extra + 3] = (uint64_t)g.slabs;
         gr_status st = launch(c, k->fn, k->name, g.slabs, s);
         if (st != GR_OK) return st;
-        return launch(c, k->fn2, k->name + "_combine", (p.M + 15) / 16, s);
+        return launch(c, k->fn2, k->name + "_combine", p.M <= kCombineFew ? (p.M + 3) / 4 : (p.M + 15) / 16, s);
       }
       if (g.gemv_mode == 0) {
         int rpb = 256 / g.LPR;
@@ -786,7 +786,7 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
       int64_t ncb = (g.M + (int64_t)g.BX * 4 - 1) / ((int64_t)g.BX * 4);
       gr_status st = launch(c, k->fn, k->name, ncb * g.slabs, s);
       if (st != GR_OK) return st;
-      return launch(c, k->fn2, k->name + "_combine", (g.M + 15) / 16, s);
+      return launch(c, k->fn2, k->name + "_combine", g.M <= kCombineFew ? (g.M + 3) / 4 : (g.M + 15) / 16, s);
     }
   }
   return GR_OK;

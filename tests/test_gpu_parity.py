@@ -642,6 +642,36 @@ def test_gemv_pair_matches_two_pass_execution(env):
     ctx2.close()
 
 
+# rows of fewer, as many and more columns than lanes, chunks and the four of a load; rows that leave each count of a group's share
+@pytest.mark.parametrize("rows,cols", [(1, 9), (2, 16), (5, 31), (33, 32), (257, 33), (12289, 63), (100003, 64), (4097, 65), (8193, 128), (9000, 191), (777, 257), (65, 500), (20001, 512),
+                                       (3, 513), (517, 1021), (2049, 1024), (140001, 256), (1031, 2045), (640, 2048), (3000, 385)])
+def test_fused_contractions_of_several_rows_at_a_time(env, rows, cols):
+    gr, ctx, torch = env
+    rng = np.random.default_rng(rows + cols)
+    X = (rng.standard_normal((rows, cols)) / np.sqrt(cols)).astype(f32)
+    w, y = rng.standard_normal(cols).astype(f32), rng.random(rows).astype(f32)
+    Xd, wd, yd = (ctx.array(torch.from_numpy(a).cuda()) for a in (X, w, y))
+    r = 1.0 / (1.0 + gr.exp(-(Xd @ wd))) - yd
+    g = (Xd.T @ r) * 0.5
+    g.materialize()
+    r64 = 1.0 / (1.0 + np.exp(-(X.astype(np.float64) @ w))) - y
+    # a sum of n products in 32 bits: each of up to log-many or n / 512 additions in turn costs half a unit of the terms' magnitudes; r's own errors come through X^T
+    unit = 2.0 ** -24
+    z_scale = np.abs(X).astype(np.float64) @ np.abs(w)
+    r_err = unit * (8 + cols / 16) * (0.25 * z_scale + 1.0)
+    assert (np.abs(r.numpy() - r64) <= r_err).all()
+    g_err = 0.5 * (np.abs(X).T.astype(np.float64) @ (unit * (8 + rows / 256) * np.abs(r64) + r_err))
+    assert (np.abs(g.numpy() - 0.5 * (X.T.astype(np.float64) @ r64)) <= g_err).all()
+    X[rows // 2, cols // 2] = np.inf     # reaches its row and its column, and the others only through that row
+    X[rows // 2, :cols // 2] = 0.0
+    X[rows // 2, cols // 2 + 1:] = 0.0
+    w[cols // 2] = abs(w[cols // 2]) + 1.0
+    Xd, wd = ctx.array(torch.from_numpy(X).cuda()), ctx.array(torch.from_numpy(w).cuda())
+    r = 1.0 / (1.0 + gr.exp(-(Xd @ wd))) - yd
+    g = (Xd.T @ r).numpy()
+    assert np.isfinite(r.numpy()).all() and np.isfinite(np.delete(g, cols // 2)).all() and not np.isfinite(g[cols // 2])
+
+
 # ------------------------------------------------------------- slice assignment ----
 def test_jacobi_listing6(env):
     gr, ctx, torch = env
