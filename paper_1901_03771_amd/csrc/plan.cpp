@@ -762,7 +762,8 @@ static void choose_in_place(GroupPlan* g) {
 //   to a compute unit.  (us, tiles of 64 x 64 or 128 x 32 / this: 64^3 4.9 / 3.6, 300 x 46 x 320 5.3 / 3.4, with a bias and tanh 8.6 / 3.8, 46 x 296 x 320 10.6 /
 //   4.9, 300^3 10.8 / 5.0, 500 x 300 x 500 10.9 / 5.2, 1000 x 350 x 500 11.2 / 8.8; 625 blocks of 800 x 300 x 800 11.2 / 10.6, 1024 of 1000 x 200 x 1000
 //   9.3 / 11.1.  Longer sums: 256 x 512 x 256 9.9 / 6.3, but 512^3 11.3 / 9.5 to 13 by layout: from 16 tiles on all of them stay.)  Long sums are split over
-//   workgroups as well: by 0.0062 us per value of k and round of 256 blocks, 2.7 for the second launch and 0.08 per part that it adds up (97 x 1491 x 40 10.3 / 8.1,
+//   workgroups as well: by 0.0062 us per value of k and round of 256 blocks (420 x 3250 x 124 transposed by 3, 4, 5, 9 parts: 168 workgroups 14.1, 224 12.4, 280 17.0, 504 13.7),
+//   2.7 for the second launch and 0.08 per part that it adds up (97 x 1491 x 40 10.3 / 8.1,
 //   50 x 4800 x 32 11.8 / 9.4, 200 x 500 x 200, unsplit, 10.8 / 6.0).
 // - waves side by side: more blocks, ragged operands, sums of up to 32 and at most 10^7 results (100000 x 9 x 40 13.5 / 9.6, 30000 x 20 x 200 13.4 / 12, 3000 x 20 x 3000 16.1 / 13.9,
 //   4936 x 27 x 1131 14.1 / 11.8; 2000 x 33 x 4000 15.8 / 16.7, 16384 x 16 x 4096 53 / 64), and sums of up to 128 whose results pass through a function of many
@@ -775,7 +776,7 @@ static bool choose_gemm_blocks(GroupPlan* g) {
     double cost = 0;
     int best = 1;
     for (int ks = 1; ks <= g->slabs; ++ks) {
-      const double us = (double)gemm_split_extent(K, ks) * 0.0062 * std::max(1.0, (double)(blocks * ks) / 256.0) + (ks > 1 ? 2.7 + 0.08 * ks + (double)ks * (double)M * (double)N * 1.8e-6 : 0.0);
+      const double us = (double)gemm_split_extent(K, ks) * 0.0062 * (double)((blocks * ks + 255) / 256) + (ks > 1 ? 2.7 + 0.08 * ks + (double)ks * (double)M * (double)N * 1.8e-6 : 0.0);
       if (ks == 1 || us < cost * 0.97) { cost = us; best = ks; }
     }
     g->UC = 8;
