@@ -2710,8 +2710,8 @@ void split_helpers(Em& e) {
          "static __device__ __forceinline__ bool gr_odd(unsigned low, float big) { return __builtin_amdgcn_ballot_w64((low & 0xffffu) != 0u || big >= 0x1p48f) != 0ull; }\n";
 }
 
-// Matrix product of large operands, each contiguous along one of its dimensions (K a multiple of 16; M and N need
-// not be multiples of the tile: edge tiles load clamped rows and store only what exists): one workgroup per tile of the
+// Matrix product of large operands, each contiguous along one of its dimensions (edge tiles load clamped rows and store only what exists; K no
+// multiple of 16, and groups of four that are not whole, with two groups of waves only: GroupPlan::NP): one workgroup per tile of the
 // result, tiles of 256 x 256 (four waves with a 128 x 128 quarter each as 4 x 4 matrix-core blocks, 256
 // accumulator registers per lane) or 128 x 128 (one or two groups of four waves, 2 x 2 blocks per wave).
 //   * Tiles of 16 values of k go from global memory straight into LDS (global_load_lds_dwordx4: lane L of a
@@ -2777,7 +2777,13 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
   if (split) o << "  const long long tiles = tiles_n * ((M + " << T - 1 << ") / " << T << "), tile = blockIdx.x % tiles, split = blockIdx.x / tiles;\n"
                   "  const long long kbeg = split * " << e.S(e.L.ocoef + 1) << ", KE = kbeg + " << e.S(e.L.ocoef + 1) << " < K ? kbeg + " << e.S(e.L.ocoef + 1) << " : K;\n";
   else o << "  const long long tile = blockIdx.x, kbeg = 0, KE = K;\n";
-  o << "  const long long bm0 = (tile / tiles_n) * " << T << ", bn0 = (tile % tiles_n) * " << T << ";\n"
+  // (ragged extents, see GroupPlan::NP: the last tile of a dimension that a row-contiguous operand has in groups of four starts T from its end
+  // and overlaps the one before with the same values)
+  auto first = [&](const char* index, const char* lim, bool shifted) {
+    const std::string at = std::string(index) + " * " + std::to_string(T), end = std::string(lim) + " - " + std::to_string(T);
+    return shifted ? "(" + at + " < " + end + " ? " + at + " : " + end + ")" : at;
+  };
+  o << "  const long long bm0 = " << first("(tile / tiles_n)", "M", g.NP & kGemmShiftM) << ", bn0 = " << first("(tile % tiles_n)", "N", g.NP & kGemmShiftN) << ";\n"
        "  f16v acc[" << NB << "][" << NB << "];\n"
        "  for (int i = 0; i < " << NB << "; ++i) for (int j = 0; j < " << NB << "; ++j) for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;\n"
        "  const unsigned wv = __builtin_amdgcn_readfirstlane(wave);\n"
@@ -2843,6 +2849,21 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
     if (&x == &ops[0]) rot << "    ";
   }
   const std::string rot_text = rot.str();
+  // What K leaves beyond its whole steps, fewer than 16 values, with float32 instructions from registers, in the second group, which has no more
+  // steps than the first: loaded at once, zero beyond the end.
+  auto rest = [&]() {
+    if (!(g.NP & kGemmRestK)) return;
+    o << "  { const long long krest = kbeg + 16 * nkt;\n  if (krest < KE && group == 1) {\n    float ar[8][" << NB << "], br[8][" << NB << "];\n";
+    for (const Op& x : ops) {
+      const std::string n = x.n, X = n == "a" ? "A" : "B", w0 = n == "a" ? "wm" : "wn";
+      o << "#pragma unroll\n    for (int i = 0; i < " << NB << "; ++i) {\n"
+           "      const long long at = " << x.org << " + " << w0 << " + " << (x.kc ? "32 * i + l32" : std::to_string(NB) + " * l32 + i") << ";\n"
+           "      const GM float* const p = " << X << " + (at < " << x.lim << " ? at : " << x.lim << " - 1) * " << (n == "a" ? "am" : "bn") << ";\n"
+           "#pragma unroll\n      for (int s = 0; s < 8; ++s) { const long long k = krest + 2 * s + lh; const float v = p[(k < KE ? k : krest) * " << (n == "a" ? "ak" : "bk") << "]; " << n << "r[s][i] = k < KE ? v : 0.0f; }\n    }\n";
+    }
+    o << "#pragma unroll\n    for (int s = 0; s < 8; ++s)\n#pragma unroll\n      for (int i = 0; i < " << NB << "; ++i)\n#pragma unroll\n        for (int j = 0; j < " << NB
+      << "; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[s][i], br[s][j], acc[i][j], 0, 0, 0);\n  } }\n";
+  };
   if (two) {
     // Values t (t < 4) and 4 + t of a lane's eight are k = 4 h + t and 8 + 4 h + t in half-wave h, for both operands.
     // Block blk of an operand's tile in role 0.
@@ -2936,6 +2957,7 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
     fetch(2, "t + 3", ind);
     o << ind << "++t;\n    }\n"
          "    if (mine < n0) __builtin_amdgcn_s_barrier();\n  }\n";
+    rest();
     o << "#pragma unroll\n  for (int i = 0; i < 2; ++i)\n#pragma unroll\n    for (int j = 0; j < 2; ++j)\n#pragma unroll\n      for (int q = 0; q < 16; ++q) acc[i][j][q] += tail[i][j][q];\n";
     // the groups add up their sums: each takes one row of blocks
     o << "  f16v own[2];\n"

@@ -42,6 +42,10 @@ constexpr int kCombineSplits = 16;
 // Columns up to which the kernel that combines the partial vectors of a matrix-vector product takes four of them per workgroup instead of sixteen.
 constexpr int kCombineFew = 384;
 
+// Ragged extents that a direct-to-LDS matrix product has compiled in (GroupPlan::NP): values of k beyond whole steps of 16, and
+// dimensions, no multiple of four, along which an operand is contiguous.
+constexpr int kGemmRestK = 16, kGemmShiftM = 32, kGemmShiftN = 64;
+
 // Lanes of a workgroup of a matrix product's kernel.
 inline unsigned gemm_threads(const GroupPlan& g) { return g.VR == 4 ? 64u * (g.UC > 1 ? (unsigned)g.UC : 4u) : (g.VR == 2 && g.UC == 2 ? 512u : 256u); }
 

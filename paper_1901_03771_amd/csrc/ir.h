@@ -262,7 +262,7 @@ struct GroupPlan {
 
   // schedule
   int BX = 64, BY = 4, VR = 1, UC = 1;  // MAP
-  int NP = 1;                            // ROWRED: vec4 positions per lane
+  int NP = 1;                            // ROWRED: vec4 positions per lane; GEMM: 1 + what is ragged (choose_gemm_tiles, gemm_ragged)
   int row_threads = 64;                  // ROWRED: lanes cooperating on one row (1 to 16, 64, 128, 256, or 1024 for more than 16384 elements)
   int row_iters = 1;                     // ROWRED: rows a lane group takes in one launch (short rows, one value per row)
   int pair_k = 0;                        // ROWRED: row length, if a row combines an operand of each of the two kept dimensions and a lane

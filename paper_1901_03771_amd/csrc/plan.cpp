@@ -795,6 +795,11 @@ static bool choose_gemm_blocks(GroupPlan* g) {
   return true;
 }
 
+// The extents of a direct-to-LDS product that are not whole steps of k or groups of four (kGemmRestK, kGemmShiftM, kGemmShiftN).
+int gemm_ragged(const GroupPlan& g) {
+  return (g.K % 16 ? kGemmRestK : 0) + (g.groups[g.mat_group].coef[1] != 1 && g.M % 4 ? kGemmShiftM : 0) + (g.groups[g.vec_group].coef[0] != 1 && g.N % 4 ? kGemmShiftN : 0);
+}
+
 // Small or ragged matrix products: tiles of 64 x 64 (128 x 32, 32 x 128) with clamped loads (gemm_tile_body), after the
 // choice between the kernels with tiles of 128 and 256.
 // The split of K: cheapest by rounds of 256 workgroups times steps of 32 values of k at 0.62 us, 5 for the launch and the first
@@ -811,10 +816,16 @@ static bool choose_gemm_blocks(GroupPlan* g) {
 // tanh 40.5 clamped, 38 direct in two parts.  (us, direct / this: 512^3 15.5 / 11.3, 1024 x 512 x 512 17.5 / 14.2, 224 x 192 x 1856 12.8 / 8.5,
 // 528 x 208 x 2320 14.7 / 14.7, 448 x 768 x 1456 23.0 / 22.8; stay: 368 x 2160 x 1296 28.3 / 32.8, 1296 x 3264 x 208 26.8 / 35.2, 3056 x 448 x 896 27.7 / 31.8,
 // 2048^3 119 / 151.  The choice missed the faster one of 45 products by 7 % at most, 4096 x 784 x 512 plain 36.3 / 38.9.)
+// Ragged extents (gemm_ragged) go to the direct kernel where it is estimated 7 % faster: always its two groups of waves and pieces, up to
+// any number of workgroups; 4 more for every round, which stores before the next one loads, and 2 for the rest of k; `former` splits of K on
+// the other side, as many as before they fitted the direct kernel, so that no chain gets longer.  Sums of fewer than 256 values for large results stay where they were.
+// (us, 64 x 64 clamped / direct, errors against 64 bits: 1967 x 1499 x 1767 transposed 115 / 84, 4.9e-7 / 1.7e-7; 4729 x 589 x 749 transposed 51 / 40, 3.1e-7 / 1.2e-7;
+// 1109 x 6941 x 349 65 / 56; 1779 x 1191 x 1699 72 / 66; 4177 x 1071 x 1371 121 / 118; 2599 x 157 x 7349 76 / 82; 1289 x 905 x 6105 144 / 151; 5091 x 459 x 817 49 / 58;
+// 529 x 849 x 337 12.1 / 17.8: the last four stay.)
 // `wanted`: splits of K that the larger tiles would take if they may store any number of partial tiles.  It decides
 // between the kernels, so that a request that must not allocate takes the kernel that the same request would take
 // otherwise (and that is loaded by then); g->slabs, which stays within its scratch array, bounds the splits.
-void choose_gemm_tiles(GroupPlan* g, int wanted) {
+void choose_gemm_tiles(GroupPlan* g, int wanted, int former) {
   const int64_t M = g->M, N = g->N, K = g->K;
   auto fits = [&](const AccessGroup& x, int kdim, int64_t other) {
     if (x.coef[kdim] == 1) return K >= 4;
@@ -826,11 +837,15 @@ void choose_gemm_tiles(GroupPlan* g, int wanted) {
   const int64_t tm = N <= 32 ? 128 : (M <= 32 ? 32 : 64), tn = N <= 32 ? 32 : (M <= 32 ? 128 : 64);
   const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
   if (tiles > (int64_t)1 << 24) return;
-  if (g->VR != 2) {
+  const int ragged = g->VR == 2 ? gemm_ragged(*g) : 0;
+  if (g->VR != 2 || (ragged && K < 256)) {
     const bool rows_of_k = g->groups[g->mat_group].coef[1] == 1 && g->groups[g->vec_group].coef[0] == 1;
-    if (K <= 128 && M * N >= (int64_t)1 << 22) return;               // stores
-    if (tn == 32 && tiles >= 256) return;                            // one pass over a tall operand
-    if (rows_of_k && M * N >= (int64_t)1 << 23) return;              // many large tiles, both operands contiguous along k
+    if ((K <= 128 && M * N >= (int64_t)1 << 22) ||                   // stores
+        (tn == 32 && tiles >= 256) ||                                // one pass over a tall operand
+        (rows_of_k && M * N >= (int64_t)1 << 23)) {                  // many large tiles, both operands contiguous along k
+      if (ragged) { g->VR = 1; g->slabs = former; }
+      return;
+    }
   }
   // Every accumulator adds two chains: at least half as many splits as the larger tiles would take, so that no chain gets
   // longer, and no more than those, so that the partial tiles need no more memory (of a request that must not allocate).
@@ -845,20 +860,20 @@ void choose_gemm_tiles(GroupPlan* g, int wanted) {
     }
     return best_ks;
   };
-  const int before = g->slabs, best_ks = cheapest(before);
+  const int before = ragged ? former : g->slabs, best_ks = cheapest(before);
   if (g->VR == 2) {
-    const int ks = cheapest(wanted);
+    const int ks = cheapest(ragged ? former : wanted);
     auto rounds = [](int64_t workgroups) { return (double)((workgroups + 255) / 256); };
     auto split = [&](double launch, double traffic, int n) { return n > 1 ? launch + traffic * (double)n * (double)M * (double)N * 8e-6 : 0.0; };
     const int64_t wgs = ((M + 127) / 128) * ((N + 127) / 128) * wanted;
-    const bool pieces = wgs <= 256;   // (two groups of waves per workgroup, see gemm_big_body)
-    const double direct = rounds(wgs) * (double)((gemm_split_extent(K, wanted) + 15) / 16) * (pieces ? 0.75 : 0.86) + 4.5 + split(3.4, 0.18, wanted);
+    const bool pieces = wgs <= 256 || ragged;   // (two groups of waves per workgroup, see gemm_big_body)
+    const double direct = rounds(wgs) * (double)((gemm_split_extent(K, wanted) + 15) / 16) * (pieces ? 0.75 : 0.86) + (ragged ? 2.5 + 4.0 * rounds(wgs) : 4.5) + split(3.4, 0.18, wanted);
     const double clamped = rounds(tiles * ks) * (double)((gemm_split_extent(K, ks) + 31) / 32) * 0.56 + 4.0 + split(2.7, 0.22, ks);
     double epilogue = 0.0;   // vector instructions per result, at 39 of a lane per picosecond
     for (const Instr& in : g->prog)
       if (in.kind == IKind::UNARY || in.kind == IKind::BINARY) epilogue += heavy_op(in) ? 40.0 : 1.0;
     epilogue *= (double)M * (double)N / 3.9e7;
-    if ((clamped + (ks > 1 ? 0.0 : epilogue)) * (pieces ? 1.0 : 1.05) > direct + (wanted > 1 ? 0.0 : epilogue)) return;
+    if ((clamped + (ks > 1 ? 0.0 : epilogue)) * (ragged ? 0.93 : pieces ? 1.0 : 1.05) > direct + (wanted > 1 ? 0.0 : epilogue)) return;
   }
   g->VR = 3;
   g->UC = 1;
@@ -1316,6 +1331,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
     // few output tiles and a long contraction: split K over workgroups (about 512 of them, at
     // least 128 k per split); the partial tiles are combined by a second kernel
     g->slabs = 1;
+    int former = 1;   // splits of K by what a product that does not fit the direct kernels takes
     int wanted = 0;   // splits of K by the direct 128 x 128 kernel if any number of partial tiles may be stored
     // columns of the output tile of one workgroup: 128, or 32 for narrow results and where the last
     // 128-wide tile would be more than half empty (measured, 65536 x 64 x 64: 14.5 us against 21.8 us;
@@ -1348,21 +1364,25 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
       const int64_t tiles = ((g->M + 255) / 256) * ((g->N + 255) / 256), rounds = (tiles + 255) / 256;
       // other: the extent of the operand's dimension that is not k (a multiple of four where that dimension is the
       // contiguous one: its elements are loaded in groups of four)
-      auto fits = [](const AccessGroup& x, int kdim, int64_t other) {   // kdim: which of the operand's two dimensions is k
+      auto fits = [](const AccessGroup& x, int kdim) {   // kdim: which of the operand's two dimensions is k
         if (x.structural_zero[0] || x.structural_zero[1]) return false;
         const int64_t sk = x.coef[kdim], so = x.coef[1 - kdim];
         if (sk == 1 && so != 1) return so >= 16 && so < ((int64_t)1 << 21);
-        if (so == 1 && sk != 1) return sk >= 128 && sk < ((int64_t)1 << 24) && other % 4 == 0;
+        if (so == 1 && sk != 1) return sk >= 128 && sk < ((int64_t)1 << 24);
         return false;
       };
       // Edge tiles are whole tiles of work: the result must fill 85 % of its rounds over the 256 compute units, 65 %
       // where M or N is not a multiple of 128 (the 128-wide kernel's guarded edge tiles make it slower there; measured
       // on 4000^3: 136 against 97 TFLOP/s, 8000^3: 144 against 114, 10000 x 4096 x 10000, seven rounds 85 % full: 126 against 117).
       const int64_t need = (g->M % 128 == 0 && g->N % 128 == 0) ? 17 : 13;
-      const bool direct = c->opt_gemm_big && c->opt_gemm_bn == 0 && g->K % 16 == 0 && g->K >= 32 && fits(ag, 1, g->M) && fits(bg, 0, g->N);
+      // (ragged extents, see below: two groups of waves, whose sums of pieces stay nearer 64 bits than the two float32 chains of clamped tiles; one of
+      // the other kernels would not: 1470 x 832 x 1216 transposed 2.7e-7 clamped, 3.6e-7 with one float32 chain)
+      const int ragged = gemm_ragged(*g);
+      former = g->slabs;
+      const bool direct = c->opt_gemm_big && c->opt_gemm_bn == 0 && g->K >= 32 && fits(ag, 1) && fits(bg, 0);
       // (with K split over workgroups every split has to hold whole steps of k and at least two of them: the last one is the shortest)
       const bool split_ok = g->slabs == 1 || g->K - (g->slabs - 1) * gemm_split_extent(g->K, g->slabs) >= 32;
-      if (direct && g->slabs == 1 && g->M >= 256 && g->N >= 256 && g->M * g->N * 20 >= rounds * 256 * 65536 * need) {
+      if (direct && !ragged && g->slabs == 1 && g->M >= 256 && g->N >= 256 && g->M * g->N * 20 >= rounds * 256 * 65536 * need) {
         g->BX = 256;
         g->VR = 2;   // (marks the kernels whose tiles go straight into LDS)
         g->UC = 1;
@@ -1384,7 +1404,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
             const int64_t kch = gemm_split_extent(g->K, ks);
             if (ks > 1 && (kch < 128 || g->K - (ks - 1) * kch < 32 || (int64_t)ks * g->M * g->N > room)) continue;
             const int64_t wgs = tiles128 * ks, rnd = (wgs + 255) / 256, steps = (kch + 15) / 16;
-            const double cost = (double)rnd * (double)steps * (wgs <= 256 ? 0.85 : 0.95) + (ks > 1 ? 6.0 + (double)ks * (double)g->M * (double)g->N * 8.0 / 5e6 : 0.0);
+            const double cost = (double)rnd * (double)steps * (wgs <= 256 || ragged ? 0.85 : 0.95) + (ks > 1 ? 6.0 + (double)ks * (double)g->M * (double)g->N * 8.0 / 5e6 : 0.0);
             if (best_ks == 0 || cost < best * 0.97) { best = cost; best_ks = ks; }
           }
           return best_ks;
@@ -1401,14 +1421,15 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
         g->UC = 1;
       }
     }
-    if (c->opt_gemm_bn == 0 && c->opt_gemm_kstep == 0 && c->opt_gemm_split == 0 && c->opt_gemm_big && c->opt_gemm_clamped) choose_gemm_tiles(g, wanted ? wanted : g->slabs);
+    if (c->opt_gemm_bn == 0 && c->opt_gemm_kstep == 0 && c->opt_gemm_split == 0 && c->opt_gemm_big && c->opt_gemm_clamped) choose_gemm_tiles(g, wanted ? wanted : g->slabs, former);
     // The direct kernel with 128 x 128 tiles (UC: groups of four waves in a workgroup): two groups divide a tile's steps and multiply pieces
     // where compute units have one workgroup each, one group with float32 instructions where they hold several at a time, which overlap
     // each other's loads, epilogues and arithmetic.
     // (us, one group / two: 256 workgroups or fewer: 4096 x 512 x 784 41.8 / 34.7, 2048^3 132 / 119.5, 512 x 2848 x 2352 70 / 60, 2048 x 128 x 2048
     // 14.8 / 13.3; more: 12800 x 64 x 768 22.1 / 26.1, 6000 x 128 x 1500 32.2 / 35.1, 12800 x 256 x 768 53.1 / 54.7,
     // 5120 x 384 x 2560 97 / 97, 3000 x 512 x 2048 66 to 71 / 62.)
-    if (g->VR == 2 && g->BX == 128) g->UC = ((g->M + 127) / 128) * ((g->N + 127) / 128) * (wanted ? wanted : g->slabs) <= 256 ? 2 : 1;
+    if (g->VR == 2) g->NP = 1 + gemm_ragged(*g);
+    if (g->VR == 2 && g->BX == 128) g->UC = ((g->M + 127) / 128) * ((g->N + 127) / 128) * (wanted ? wanted : g->slabs) <= 256 || g->NP > 1 ? 2 : 1;
   } else if (dot && !(dot == r && dot_as_reduce(dot) && c->opt_fusion)) {
     // ---- contraction with pointwise epilogue ------------------------------
     g->kind = GroupKind::GEMV;

@@ -761,3 +761,37 @@ def test_products_of_positive_operands_do_not_lean_to_one_side(env, m, n, k):
     ctx.set_option("gemm_clamped", 1)
     want = a.double() @ b.double()
     assert float((got - want).norm() / want.norm()) <= 1.5 * 2.0 ** -24 / 3 * (k / 2) ** 0.5
+
+
+# products of any extents through the kernels that load their tiles straight into LDS: what is left of k after whole steps (also in the last
+# part of a divided k, and with infinities there), last tiles that start before their place, next to nothing left of a tile
+@pytest.mark.parametrize("m,n,k,split", [(129, 130, 33, 0), (255, 381, 47, 0), (385, 255, 63, 0), (513, 642, 207, 0), (301, 203, 1031, 0), (642, 257, 335, 2), (1157, 1283, 97, 3), (2050, 2047, 45, 0),
+                                         (3999, 3997, 81, 0), (4093, 3842, 95, 0)])
+@pytest.mark.parametrize("layout", ["nn", "tn", "nt", "tt"])
+def test_direct_products_of_ragged_extents(env, m, n, k, split, layout):
+    gr, ctx, torch = env
+    g = torch.Generator(device="cuda").manual_seed(m + n + k)
+    whole = lambda *shape: torch.randint(-4, 5, shape, generator=g, device="cuda").float()
+    a, b, bias = whole(m, k), whole(k, n), whole(n)
+    ta, tb = (v.t().contiguous() if t == "t" else v for v, t in ((a, layout[0]), (b, layout[1])))
+    buf = torch.full((m * n + 8192,), -77.0, device="cuda")
+    inner = buf[4096:4096 + m * n].view(m, n)
+    ctx.set_option("gemm_clamped", 0)
+    ctx.set_option("gemm_split", split)
+    try:
+        for odd in (False, True):
+            if odd:
+                ta[(k - 1, 5) if layout[0] == "t" else (5, k - 1)] = float("inf")
+            A, B = ctx.array(ta), ctx.array(tb)
+            out = (gr.transpose(A) if layout[0] == "t" else A) @ (gr.transpose(B) if layout[1] == "t" else B) + ctx.array(bias)
+            if n % 128 == 0 or n % 128 > 64:   # (32-wide tiles where the last 128 columns are mostly empty)
+                assert "tile=128x128 direct" in out.plan(), out.plan()
+            out.materialize_into(inner)
+            ctx.sync()
+            A64, B64 = (ta.t() if layout[0] == "t" else ta).double(), b.double()
+            want = (A64.contiguous() @ B64 + bias.double()).float()   # (whole numbers below 2^24: exact in any order)
+            assert torch.equal(torch.nan_to_num(inner, nan=123.0), torch.nan_to_num(want, nan=123.0))
+            assert bool((buf[:4096] == -77.0).all()) and bool((buf[4096 + m * n:] == -77.0).all())
+    finally:
+        ctx.set_option("gemm_clamped", 1)
+        ctx.set_option("gemm_split", 0)
