@@ -1868,10 +1868,18 @@ void gen_scan(Em& e) {
   };
   auto tile_value = [](const Instr&, int id) { return "l" + std::to_string(id) + "[j]"; };
 
-  // ---- kernel 2 of 3 (both modes): exclusive scan of each line's chunk totals, in place (at most 4096 chunks)
+  // ---- kernel 2 of 3 (both modes): exclusive scan of each line's chunk totals, in place (at most 4096 chunks): a workgroup per line, a lane per
+  // line of many with few chunks (1352 x 15783 down the columns, 8 chunks: 13.6 us by workgroups, nearly all of it their launches, 4.8 by
+  // lanes; the whole sum 70.0 and 61.2, of int32 1856 x 9173 72.5 and 64.5, 300 x 16381 27.2 and 18.2; up to 32 chunks, or for fewer lines, the loads of a lane cost
+  // more: 1000 x 1001, 32 chunks, 11.3 by workgroups, 16.5 by lanes).  The additions of a lane are those of the workgroup, in the same order.
   auto offsets_kernel = [&]() {
     kernel_head(e, "gr_scan_offsets");
     e.o << "  const long long NCHUNK = " << e.S(e.L.extra + 3) << ";\n";
+    e.o << "  if (NCHUNK <= " << kScanFewChunks << " && " << e.S(e.L.extra) << " >= " << kScanManyLines << ") {\n    const long long line = (long long)blockIdx.x * 256 + threadIdx.x;\n    if (line >= " << e.S(e.L.extra) << ") return;\n"
+        << "    GM " << TA << "* const wl = (GM " << TA << "*)" << e.slot(e.L.extra + 2) << " + line * NCHUNK;\n    const int n = (int)NCHUNK;\n    " << TA << " x[" << kScanFewChunks << "];\n"
+        << "#pragma unroll\n    for (int u = 0; u < " << kScanFewChunks << "; ++u) x[u] = gr_comb0(" << ident << ", wl[u < n ? u : 0]);\n"
+        << "#pragma unroll\n    for (int d = 1; d < " << kScanFewChunks << "; d *= 2)\n#pragma unroll\n      for (int u = " << kScanFewChunks - 1 << "; u >= d; --u) x[u] = gr_comb0(x[u - d], x[u]);\n"
+        << "#pragma unroll\n    for (int u = 0; u < " << kScanFewChunks << "; ++u) if (u < n) wl[u] = gr_comb0(" << ident << ", u ? x[u ? u - 1 : 0] : " << ident << ");\n    return;\n  }\n";
     e.o << "  GM " << TA << "* const w = (GM " << TA << "*)" << e.slot(e.L.extra + 2) << " + (long long)blockIdx.x * NCHUNK;\n";
     e.o << "  __shared__ long long gr_sm[4];\n";
     e.o << "  const int per = (int)((NCHUNK + 255) / 256);\n  const long long c0 = (long long)threadIdx.x * per;\n";

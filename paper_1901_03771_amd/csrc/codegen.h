@@ -39,6 +39,9 @@ constexpr int kReduceLanes = 512;
 // Splits of a reduction from which on the kernel that combines the partial results of 1024 outputs and more takes several lanes per output.
 constexpr int kCombineSplits = 16;
 
+// Chunks of a scanned line up to which, and lines from which on, a lane, not a workgroup, scans their totals.
+constexpr int kScanFewChunks = 16, kScanManyLines = 4096;
+
 // Columns up to which the kernel that combines the partial vectors of a matrix-vector product takes four of them per workgroup instead of sixteen.
 constexpr int kCombineFew = 384;
 

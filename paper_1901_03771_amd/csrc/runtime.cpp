@@ -713,7 +713,7 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
           s[L.extra + 2] = (uint64_t)(uintptr_t)ws;
           gr_status st = launch(c, k->fn2, "gr_scan_sums", blocks, s);
           if (st != GR_OK) return st;
-          st = launch(c, k->fn3, "gr_scan_offsets", g.red_out, s);
+          st = launch(c, k->fn3, "gr_scan_offsets", g.scan_nchunk <= kScanFewChunks && g.red_out >= kScanManyLines ? (g.red_out + 255) / 256 : g.red_out, s);
           if (st != GR_OK) return st;
         }
         return launch(c, k->fn, k->name, blocks, s);
@@ -724,7 +724,7 @@ gr_status launch_group(gr_ctx* c, const GroupPlan& g, gr_ctx::Kernel* k, void* o
         s[L.extra + 2] = (uint64_t)(uintptr_t)ws;
         gr_status st = launch(c, k->fn2, "gr_scan_sums", g.red_out * g.scan_nchunk, s);
         if (st != GR_OK) return st;
-        st = launch(c, k->fn3, "gr_scan_offsets", g.red_out, s);
+        st = launch(c, k->fn3, "gr_scan_offsets", g.scan_nchunk <= kScanFewChunks && g.red_out >= kScanManyLines ? (g.red_out + 255) / 256 : g.red_out, s);
         if (st != GR_OK) return st;
       }
       return launch(c, k->fn, k->name, g.red_out * g.scan_nchunk, s);

@@ -795,3 +795,17 @@ def test_direct_products_of_ragged_extents(env, m, n, k, split, layout):
     finally:
         ctx.set_option("gemm_clamped", 1)
         ctx.set_option("gemm_split", 0)
+
+
+# down the columns of a few hundred to a few thousand rows: two chunks to just over as many as a lane takes, in its first and last column, at and around a workgroup's lanes
+@pytest.mark.parametrize("rows,cols", [(300, 16381), (700, 9001), (1352, 15783), (2200, 7001), (2500, 7425), (5000, 3001), (40000, 257), (2600, 255)])
+def test_chunk_totals_of_many_lines(env, rows, cols):
+    gr, ctx, torch = env
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    whole = torch.randint(-6, 7, (rows, cols), generator=g, device="cuda")
+    for dtype in (torch.float32, torch.int32):
+        x = whole.to(dtype)
+        out = gr.cumsum(ctx.array(x), 0)
+        got = torch.from_numpy(out.numpy()).cuda()
+        want = torch.cumsum(whole, 0)     # (whole numbers below 2^24: exact in any order)
+        assert torch.equal(got.to(torch.int64), want), (dtype, out.plan() if not out.is_materialized else "")
