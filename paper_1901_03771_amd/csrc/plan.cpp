@@ -1402,6 +1402,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
           int best_ks = 0;
           for (int ks = least; ks <= 64; ++ks) {
             const int64_t kch = gemm_split_extent(g->K, ks);
+            if (ks > 1 && ragged && former <= 2) break;   // (clamped tiles may need no partial tiles there: a request that must not allocate fits then as before)
             if (ks > 1 && (kch < 128 || g->K - (ks - 1) * kch < 32 || (int64_t)ks * g->M * g->N > room)) continue;
             const int64_t wgs = tiles128 * ks, rnd = (wgs + 255) / 256, steps = (kch + 15) / 16;
             const double cost = (double)rnd * (double)steps * (wgs <= 256 || ragged ? 0.85 : 0.95) + (ks > 1 ? 6.0 + (double)ks * (double)g->M * (double)g->N * 8.0 / 5e6 : 0.0);
