@@ -2589,11 +2589,12 @@ void gen_gemv_pair(Em& e, Em& e2) {
     e.o << "    const float rr = t" << g.results[0] << ";\n    if (lane == 0) out[row] = rr;\n";
     e.o << "#pragma unroll\n    for (int q = 0; q < " << KV << "; ++q)\n#pragma unroll\n      for (int j = 0; j < 4; ++j) acc[q][j] = __builtin_fmaf(xv[q][j], rr, acc[q][j]);\n  }\n";
   } else {
-    // (the last chunk: a lane whose elements reach past the row's end reads the four before the end instead, and keeps those from its own first one on)
+    // (the last chunk: a lane whose elements reach past the row's end reads the four before the end instead, and keeps those from its own first one on: zero in
+    // both operands, as zero times an infinite weight is no number)
     e.o << "  const long long klast = " << (KV - 1) * CH << " + lane * 4, kb = klast + 4 <= K ? klast : K - 4;\n  const int skip = (int)(klast - kb < 4 ? klast - kb : 4);\n";
     e.o << "  float wv[" << KV << "][4], acc[" << KV << "][4];\n";
     e.o << "#pragma unroll\n  for (int q = 0; q < " << KV << "; ++q) {\n    const long long k0 = q == " << KV - 1 << " ? kb : (long long)q * " << CH << " + lane * 4;\n"
-           "#pragma unroll\n    for (int j = 0; j < 4; ++j) { wv[q][j] = V[(k0 + j) * vk]; acc[q][j] = 0.0f; }\n  }\n";
+           "#pragma unroll\n    for (int j = 0; j < 4; ++j) { const float v = V[(k0 + j) * vk]; wv[q][j] = q < " << KV - 1 << " || skip <= j ? v : 0.0f; acc[q][j] = 0.0f; }\n  }\n";
     e.o << "  const int mine = lane < " << UN << " ? lane : 0;\n";
     e.o << "  const GM float* Ar = A + (rbeg + rib) * am;\n  long long row = rbeg + rib;\n";
     auto batch = [&](bool some, const char* ind) {

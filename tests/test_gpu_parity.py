@@ -672,6 +672,33 @@ def test_fused_contractions_of_several_rows_at_a_time(env, rows, cols):
     assert np.isfinite(r.numpy()).all() and np.isfinite(np.delete(g, cols // 2)).all() and not np.isfinite(g[cols // 2])
 
 
+# a weight that is no finite number, in each of the last four columns, of rows whose end lies within a load of eight, sixteen and sixty-four
+# lanes: it reaches a row through that row's own element, also where other lanes load the row's end
+@pytest.mark.parametrize("cols", [9, 31, 41, 117, 333, 700, 2045])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_fused_contractions_with_a_weight_that_is_not_finite(env, cols, value):
+    gr, ctx, torch = env
+    rng = np.random.default_rng(cols)
+    X = (rng.uniform(0.5, 1.5, (1031, cols)) * rng.choice([-1.0, 1.0], (1031, cols))).astype(f32)
+    y = rng.random(1031).astype(f32)
+    Xd, yd = (ctx.array(torch.from_numpy(a).cuda()) for a in (X, y))
+    for back in range(1, 5):
+        w = rng.standard_normal(cols).astype(f32)
+        w[cols - back] = value
+        r = 1.0 / (1.0 + gr.exp(-(Xd @ ctx.array(torch.from_numpy(w).cuda())))) - yd
+        g = (Xd.T @ r) * 0.5
+        assert "mode=row-dot+column-accumulate" in g.plan()
+        g.materialize()
+        if np.isnan(value):
+            assert np.isnan(r.numpy()).all() and np.isnan(g.numpy()).all()
+            continue
+        ref = np.where(X[:, cols - back] * value > 0, f32(1.0) - y, -y)    # (z is an infinity of either sign)
+        assert np.array_equal(r.numpy(), ref), back
+        # (1031 terms, at most 103 additions in turn, half a unit of the terms' magnitudes each)
+        g64 = 0.5 * (X.T.astype(np.float64) @ ref)
+        assert (np.abs(g.numpy() - g64) <= 103 * 2.0 ** -24 * (np.abs(X).T.astype(np.float64) @ np.abs(ref))).all(), back
+
+
 # ------------------------------------------------------------- slice assignment ----
 def test_jacobi_listing6(env):
     gr, ctx, torch = env
