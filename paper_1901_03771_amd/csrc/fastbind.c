@@ -100,6 +100,15 @@ static PyObject* merged_owner(PyObject* a, PyObject* b) {
   return PyTuple_Pack(2, a, b);
 }
 
+/* Gives a handle back.  The release may call an allocator written in Python, which must not meet the exception that is being raised. */
+static void release_handle(CellObject* cell, unsigned long long h) {
+  if (!cell || !cell->address || !p_release) return;
+  PyObject *et, *ev, *tb;
+  PyErr_Fetch(&et, &ev, &tb);
+  p_release((gr_ctx*)(uintptr_t)cell->address, h);
+  PyErr_Restore(et, ev, tb);
+}
+
 static PyObject* new_array(PyTypeObject* type, PyObject* ctx, CellObject* cell, unsigned long long h, PyObject* owner_a, PyObject* owner_b, int view) {
   ArrayObject* a = (ArrayObject*)type->tp_alloc(type, 0);
   PyObject* owner = NULL;
@@ -108,8 +117,8 @@ static PyObject* new_array(PyTypeObject* type, PyObject* ctx, CellObject* cell, 
     if (!owner && PyErr_Occurred()) { Py_DECREF(a); a = NULL; }
   }
   if (!a) {
-    if (cell->address) p_release((gr_ctx*)(uintptr_t)cell->address, h);
-    return PyErr_NoMemory();
+    release_handle(cell, h);
+    return PyErr_Occurred() ? NULL : PyErr_NoMemory();
   }
   Py_INCREF(ctx);
   Py_INCREF(cell);
@@ -136,9 +145,9 @@ static int array_init(ArrayObject* self, PyObject* args, PyObject* kw) {
 }
 
 static void array_dealloc(ArrayObject* self) {
-  if (self->cell && self->cell->address && p_release) p_release((gr_ctx*)(uintptr_t)self->cell->address, self->h);
   PyObject *et, *ev, *tb;
   PyErr_Fetch(&et, &ev, &tb);
+  if (self->cell && self->cell->address && p_release) p_release((gr_ctx*)(uintptr_t)self->cell->address, self->h);
   Py_CLEAR(self->ctx);
   Py_CLEAR(self->cell);
   Py_CLEAR(self->owner);

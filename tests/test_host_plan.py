@@ -1437,6 +1437,55 @@ print("ok")
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
 
 
+@pytest.mark.parametrize("fast", [True, False])
+def test_exceptions_pass_arrays_that_free_through_a_python_allocator(fast):
+    # a temporary that dies while an exception unwinds calls the allocator's Python function in the middle of it
+    import subprocess
+    import sys
+    code = r'''
+from paper_1901_03771_amd import lazy as gr
+ctx = gr.Context(device=-1)
+ctx.set_option("dry_run", 2)
+freed = []
+def free(address):
+    freed.append(address)
+    {}["the callback's own, caught by the binding"]
+ctx.set_allocator(lambda n: 0x100000 + 0x1000 * len(freed), free)
+x = ctx.spec((8, 8))
+def raises(i):
+    raise KeyError(i)
+def in_a_list(i):
+    return [(x * 3.0).materialize(), raises(i)]
+def as_an_argument(i):
+    return gr.exp((x * 2.0).materialize(), raises(i))
+def as_an_operand(i):
+    return (x + 1.0).materialize() - raises(i)
+def of_the_operation_itself(i):
+    try:
+        (x * 2.0).materialize() @ "oops"
+    except TypeError:
+        raise KeyError(i) from None
+def out_of_a_frame(i):
+    y = (x * 4.0).materialize()
+    raises(i)
+for f in (in_a_list, as_an_argument, as_an_operand, of_the_operation_itself, out_of_a_frame):
+    for i in range(3):
+        try:
+            f(i)
+        except KeyError as e:
+            assert e.args == (i,), f
+        else:
+            raise AssertionError(f)
+assert len(freed) == 15, freed
+print("ok")
+'''
+    env = dict(os.environ, PYTHONPATH=ROOT)
+    if not fast:
+        env["GRUMPY_NO_FASTBIND"] = "1"
+    r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
+
+
 # the table of nodes: thousands alive at a time, dropped in any order, handles that are stale, a context closed under its arrays
 @pytest.mark.parametrize("count", [1, 255, 256, 5000])
 def test_nodes_are_found_until_their_last_reference_goes(count):
