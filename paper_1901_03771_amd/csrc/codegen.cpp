@@ -2787,12 +2787,14 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
                   "  const long long kbeg = split * " << e.S(e.L.ocoef + 1) << ", KE = kbeg + " << e.S(e.L.ocoef + 1) << " < K ? kbeg + " << e.S(e.L.ocoef + 1) << " : K;\n";
   else o << "  const long long tile = blockIdx.x, kbeg = 0, KE = K;\n";
   // (ragged extents, see GroupPlan::NP: the last tile of a dimension that a row-contiguous operand has in groups of four starts T from its end
-  // and overlaps the one before with the same values)
-  auto first = [&](const char* index, const char* lim, bool shifted) {
-    const std::string at = std::string(index) + " * " + std::to_string(T), end = std::string(lim) + " - " + std::to_string(T);
-    return shifted ? "(" + at + " < " + end + " ? " + at + " : " + end + ")" : at;
+  // and overlaps the one before.  It stores only what lies from its place, bm1 and bn1, on: a wave that meets a value its pieces cannot hold sums
+  // otherwise, and the two tiles' waves do not hold the same rows and columns, so the bits that both have stored would depend on which came last)
+  const bool shift_m = g.NP & kGemmShiftM, shift_n = g.NP & kGemmShiftN;
+  auto first = [&](const char* place, const char* lim, bool shifted) {
+    const std::string end = std::string(lim) + " - " + std::to_string(T);
+    return shifted ? "(" + std::string(place) + " < " + end + " ? " + place + " : " + end + ")" : std::string(place);
   };
-  o << "  const long long bm0 = " << first("(tile / tiles_n)", "M", g.NP & kGemmShiftM) << ", bn0 = " << first("(tile % tiles_n)", "N", g.NP & kGemmShiftN) << ";\n"
+  o << "  const long long bm1 = (tile / tiles_n) * " << T << ", bn1 = (tile % tiles_n) * " << T << ", bm0 = " << first("bm1", "M", shift_m) << ", bn0 = " << first("bn1", "N", shift_n) << ";\n"
        "  f16v acc[" << NB << "][" << NB << "];\n"
        "  for (int i = 0; i < " << NB << "; ++i) for (int j = 0; j < " << NB << "; ++j) for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;\n"
        "  const unsigned wv = __builtin_amdgcn_readfirstlane(wave);\n"
@@ -3061,9 +3063,14 @@ void gemm_big_body(Em& e, const EpiLoad& epi_load) {
          "        const float cacc = " << (two ? "own[j][q]" : "acc[i][j][q]") << ";\n";
     std::string res = "cacc";
     if (!split) { emit_scalar_program(e, g.prog, g.results, epi_load, "cacc", "t", "        "); res = "t" + std::to_string(g.results[0]); }
-    if (ops[1].kc) o << "        if (row_at < M && col_at < N) out[row * N + col] = " << res << ";\n      }\n      (void)ov;\n";
-    else o << "        ov[j] = " << res << ";\n      }\n"
-              "      if (row_at < M && bn0 + wn + " << NB << " * l32 < N) *(GM " << RV << "u*)(out + row * N + bn0 + wn + " << NB << " * l32) = ov;\n";
+    const std::string in_rows = std::string(shift_m ? "row_at >= bm1 && " : "") + "row_at < M";
+    if (ops[1].kc) o << "        if (" << in_rows << " && col_at < N) out[row * N + col] = " << res << ";\n      }\n      (void)ov;\n";
+    else {
+      o << "        ov[j] = " << res << ";\n      }\n"
+           "      const long long at = bn0 + wn + " << NB << " * l32;\n"
+           "      if (" << in_rows << " && at < N" << (shift_n ? " && at >= bn1" : "") << ") *(GM " << RV << "u*)(out + row * N + at) = ov;\n";
+      if (shift_n) o << "      else if (" << in_rows << " && at + 1 == bn1) out[row * N + bn1] = ov[1];\n";   // (NB = 2: the second of a pair)
+    }
   });
   if (two) emit_unrolled(o, {{"q", 16}}, body, "    ");
   else emit_unrolled(o, {{"i", NB}, {"q", 16}}, body, "    ");

@@ -797,6 +797,39 @@ def test_direct_products_of_ragged_extents(env, m, n, k, split, layout):
         ctx.set_option("gemm_split", 0)
 
 
+# a value that pieces cannot hold, in a row or column that only the last tile has: what that tile shares with the one before keeps the bits that it has
+# without such a value, also where the last tile (the 257th and on of a chip that runs 256) ends long after the others
+@pytest.mark.parametrize("m,n,layout", [(2049, 2176, "tn"), (2175, 2176, "tt"), (128, 32833, "nn"), (131, 250, "tn"), (390, 507, "tn"), (258, 255, "nn"), (190, 253, "tn")])
+@pytest.mark.parametrize("value", [1e-35, 2.0 ** 50])
+def test_what_ragged_tiles_share_is_stored_once(env, m, n, layout, value):
+    gr, ctx, torch = env
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+    k, m1, n1 = 331, (m - 1) // 128 * 128, (n - 1) // 128 * 128    # (the last tile's own first row and column: other rows and columns of their wave are shared)
+    a, b = torch.randn(m, k, generator=g, device="cuda"), torch.randn(k, n, generator=g, device="cuda")
+
+    def product():
+        A, B = (ctx.array(v.t().contiguous() if t == "t" else v) for v, t in ((a, layout[0]), (b, layout[1])))
+        out = (gr.transpose(A) if layout[0] == "t" else A) @ (gr.transpose(B) if layout[1] == "t" else B)
+        assert "tile=128x128 direct" in out.plan(), out.plan()
+        return out.torch()
+
+    ctx.set_option("gemm_clamped", 0)
+    try:
+        want = product()
+        if layout[0] == "t":
+            a[m1, 5] = a[m1, 17] = value     # (in steps of both groups of waves)
+        if layout[1] == "n":
+            b[5, n1] = b[17, n1] = value
+        for _ in range(20):
+            got = product()
+            assert torch.equal(got[:m1, :n1], want[:m1, :n1])
+    finally:
+        ctx.set_option("gemm_clamped", 1)
+    exact = a.double() @ b.double()
+    # (331 products in sums of at most 331 parts, the pieces' own error within one of them)
+    assert ((got.double() - exact).abs() <= 332 * 2.0 ** -24 * (a.double().abs() @ b.double().abs())).all()
+
+
 # down the columns of a few hundred to a few thousand rows: two chunks to just over as many as a lane takes, in its first and last column, at and around a workgroup's lanes
 @pytest.mark.parametrize("rows,cols", [(300, 16381), (700, 9001), (1352, 15783), (2200, 7001), (2500, 7425), (5000, 3001), (40000, 257), (2600, 255)])
 def test_chunk_totals_of_many_lines(env, rows, cols):
