@@ -600,8 +600,8 @@ void gen_map(Em& e) {
 //   that finds a tile beside it saved takes the cells there from what was saved; whatever it loaded itself, before it looked, from a tile
 //   that was not marked so is old, since marks precede stores.  So no workgroup depends on another one's progress.  Marks carry the number
 //   of the launch; they and saved cells are written with relaxed agent-scope atomics that have completed (vmcnt) before what they precede
-//   is issued.  Bound by launches: ten sweeps of 760 x 1536 96 -> 69 us, 100 x 300 97 -> 60, 4535 x 400 102 -> 90 by one launch instead of two;
-//   with the memory busy the marks' two round trips take 10 us and hold the chip's workgroups meanwhile: 4096^2 278 -> 345, 8000^2 1030 -> 1960.
+//   is issued.  Bound by launches: ten sweeps of 1000^2 72 -> 68 us, 4535 x 400 101 -> 88, 100 x 300 97 -> 60 by one launch instead of two;
+//   with more tiles than are there at a time the marks' round trips hold the chip's workgroups: 2300^2 129 -> 142, 4096^2 279 -> 369.
 void gen_map_in_place(Em& e) {
   const GroupPlan& g = e.g;
   const int TC = g.BX * 4, TR = g.BY * g.VR, HT = g.halo[0], HB = g.halo[1], HL = g.halo[2], HR = g.halo[3];

@@ -713,9 +713,12 @@ void choose_map_schedule(gr_ctx* c, GroupPlan* g, bool own_output) {
   g->tail = (g->rank >= 2 && !g->flat && C < 64 && (C & 3) && g->UC == 1 && !g->stage_mask) ? (int)(C & 3) : 0;
 }
 
-// Tiles up to which such a map is one launch: three per compute unit (ten sweeps, us, two launches / one: 252 tiles of 1000^2 96 / 68, 568 of
-// 4535 x 400 102 / 90, 752 of 1500 x 1900 108.5 / 106, 1000 of 2000^2 117 / 116, 2048 of 4096^2 278 / 345).
-constexpr int64_t kOnceTiles = 768;
+// Tiles up to which such a map is one launch: two per compute unit, which are all there at the same time, so that a tile that looks at the marks around its
+// own finds them.  (Ten sweeps, us, two launches / one, Jacobi's five points and values four rows and columns away: 252 tiles of 1000^2 72 / 68 and 81 / 57, 284
+// of 4535 x 400 101 / 88 and 104 / 82, 376 of 1500 x 1900 109 / 104 and 121 / 103, 456 of 1800^2 113 / 111 and 119 / 104, 512 of 2040^2 116 / 116.5 and 134 / 110; 576
+// of 4600 x 1020 129.5 / 136 and 168 / 160, 594 of 2100^2 126 / 139 and 166 / 190, 648 of 2300^2 129 / 142 and 168 / 230, 768 of 1000 x 6000 129.5 / 149 and 177 / 338,
+// 2176 of 4096^2 279 / 369.)
+constexpr int64_t kOnceTiles = 512;
 
 // A map that is to write the array it reads at shifted positions, element (r, c) from elements a few rows and columns
 // away (a sweep of a stencil over a grid with a single buffer): every array read is a scalar or lies over the output with its strides.

@@ -419,6 +419,12 @@ IN_PLACE = {   # destination and value of a slice assignment that reads its own 
 }
 
 
+def in_place_launches(ctx):
+    """Launches that saved the cells around tiles, and assignments of one launch (whose kernel's name starts like theirs)."""
+    once = ctx.profile_read("gr_map_save_store")[0]
+    return ctx.profile_read("gr_map_save")[0] - once, once
+
+
 # one tile, tiles that end at, before and behind the box, rows shorter than a tile (several tile rows of lanes), one column of the last tile
 @pytest.mark.parametrize("rows,cols", [(8, 20), (17, 66), (33, 257), (34, 258), (35, 259), (64, 263), (66, 514), (131, 300), (1030, 1282), (2500, 600), (4000, 24)])
 @pytest.mark.parametrize("dtype", [f32, np.int32])
@@ -446,23 +452,28 @@ def test_assignments_evaluated_in_place(env, rows, cols, dtype):
 
 
 # few tiles, in one launch: tiles that wait for the ones around them, that look once and save (nearly all of them then, and read what others
-# saved), sweep after sweep; the most tiles of that way, and one more
-@pytest.mark.parametrize("rows,cols", [(70, 1030), (1000, 1000), (1537, 1900), (1538, 1900), (12290, 200)])
+# saved), sweep after sweep; the most tiles of that way (512 for all of these values), and a row of tiles more
+@pytest.mark.parametrize("rows,cols,once", [(70, 1030, True), (1000, 1000, True), (2040, 1900, True), (2054, 1900, False), (16380, 200, True), (16390, 200, False)])
 @pytest.mark.parametrize("polls", [0, 1, 16, 1 << 20])
-def test_assignments_in_place_whether_tiles_wait_or_save(env, rows, cols, polls):
+def test_assignments_in_place_whether_tiles_wait_or_save(env, rows, cols, once, polls):
     gr, ctx, torch = env
     ctx.set_option("assign_polls", polls)
+    ctx.set_option("profile", 1)
     try:
         for name, program in IN_PLACE.items():
             a = torch.randint(-50, 50, (rows, cols), device="cuda", dtype=torch.int32)
             want, u = a.clone(), ctx.array(a)
+            ctx.profile_reset()
             for sweep in range(4):
                 box, value = program(u)
                 u[box] = value
                 box, value = program(want)
                 want[box] = value.clone()
             assert torch.equal(a, want), name
+            nothing = name.startswith("from the") and cols < 260
+            assert in_place_launches(ctx) in ([(0, 4)] if once else [(4, 0), (0, 0)] if nothing else [(4, 0)]), name
     finally:
+        ctx.set_option("profile", 0)
         ctx.set_option("assign_polls", 16)
 
 
