@@ -47,8 +47,8 @@ extern "C" {
  *                     from their mean (var, std) come out of one pass; 0 = a pass each
  *   "assign_in_place" 1 (default) = a slice assignment whose value reads the destination's storage up to four rows or
  *                     columns away, and that storage only, is evaluated in place, after a launch that saves the cells around its
- *                     tiles where these are many (two-dimensional boxes with unit steps along the rows, 32-bit elements); 0 = the
- *                     value gets a buffer of its own and is copied back
+ *                     tiles where these are many (two-dimensional boxes with unit steps along the rows, 32-bit elements); 2 = after that
+ *                     launch for any number of tiles; 0 = the value gets a buffer of its own and is copied back
  *   "assign_polls"    how often a workgroup of such an assignment of few tiles looks whether the tiles around its own have been loaded
  *                     before it saves the cells that they read and goes on (default 16; 0 to 2^24; results do not depend on it)
  *   "nontemporal"     1 (default) = loads of arrays that are read once carry the non-temporal hint,

@@ -728,7 +728,7 @@ constexpr int64_t kOnceTiles = 512;
 // would leave compute units without a tile (1000^2: 7.8 against 8.5).
 // (us per sweep, value in a buffer of its own and copied back / in place: 1000^2 9.1 / 7.8, 2000^2 20.0 / 11.8, 4096 x 1024 23.1 / 11.8,
 // 100000 x 130 34.8 / 20.5, 4096^2 49.6 / 27.9, 1024 x 16384 49.1 / 26.9, 8192^2 185 / 102; both with two launches.)
-static void choose_in_place(GroupPlan* g) {
+static void choose_in_place(gr_ctx* c, GroupPlan* g) {
   if (g->rank != 2 || g->orig_rank != 2 || !g->out_unit || g->out_dtype == GR_I64 || g->stage_mask) return;
   const int64_t R = g->dims[0], C = g->dims[1], row = g->out_coef[0];
   if (C < 16 || R < 2 || row < C || R > 1 << 30 || C > 1 << 30) return;
@@ -757,7 +757,7 @@ static void choose_in_place(GroupPlan* g) {
   const int64_t across = (C + g->cphase + 4 * g->BX - 1) / (4 * g->BX);
   g->VR = across * (R / (8 * (int64_t)g->BY)) >= 256 ? 8 : 4;
   if (saved_cells(*g).rows + saved_cells(*g).cols > (int64_t)1 << 30) g->in_place = false;
-  g->in_place_once = g->in_place && in_place_tiles(*g) <= kOnceTiles;
+  g->in_place_once = g->in_place && c->opt_assign_in_place < 2 && in_place_tiles(*g) <= kOnceTiles;
 }
 
 // Products that are blocks of 32 x 32 from registers (gemm_block_body), before all other choices.
@@ -1735,7 +1735,7 @@ static gr_status build_group(gr_ctx* c, Planner& pl, Node* r, GroupPlan* g, std:
     collapse_dims(g, barrier, ps, 1);
     pop_output_group(g);
     choose_map_schedule(c, g, !(r == pl.root && pl.out));
-    if (r == pl.root && pl.out && pl.out->in_place && src == r && r->ndim > 0) choose_in_place(g);
+    if (r == pl.root && pl.out && pl.out->in_place && src == r && r->ndim > 0) choose_in_place(c, g);
     g->owned.assign(owned.begin(), owned.end());
   }
 

@@ -425,30 +425,35 @@ def in_place_launches(ctx):
     return ctx.profile_read("gr_map_save")[0] - once, once
 
 
-# one tile, tiles that end at, before and behind the box, rows shorter than a tile (several tile rows of lanes), one column of the last tile
+# one tile, tiles that end at, before and behind the box, rows shorter than a tile (several tile rows of lanes), one column of the last tile; both ways
 @pytest.mark.parametrize("rows,cols", [(8, 20), (17, 66), (33, 257), (34, 258), (35, 259), (64, 263), (66, 514), (131, 300), (1030, 1282), (2500, 600), (4000, 24)])
 @pytest.mark.parametrize("dtype", [f32, np.int32])
-def test_assignments_evaluated_in_place(env, rows, cols, dtype):
+@pytest.mark.parametrize("launches", [1, 2])
+def test_assignments_evaluated_in_place(env, rows, cols, dtype, launches):
     gr, ctx, torch = env
-    for name, program in IN_PLACE.items():
-        for window in (0, 1):   # the whole array, or a window that starts off a 16-byte boundary, whose surroundings stay
-            a = np.random.default_rng(31).integers(-50, 50, (rows + 5 * window, cols + 6 * window)).astype(dtype)
-            t = torch.from_numpy(a).cuda()
-            cut = np.s_[2 * window:2 * window + rows, 3 * window:3 * window + cols]
-            u, ref = ctx.array(t[cut]), a[cut]
-            ctx.set_option("profile", 1)
-            ctx.profile_reset()
-            for _ in range(2):
-                box, value = program(u)
-                u[box] = value
-                box, value = program(ref)
-                ref[box] = value.copy()
-            ctx.sync()
-            saved = ctx.profile_read("gr_map_save")[0]
-            ctx.set_option("profile", 0)
-            # (along the rows only, in one column of tiles: nothing around a tile to save)
-            assert saved == 2 or (name.startswith("from the") and cols < 260), (name, window)
-            assert np.array_equal(t.cpu().numpy(), a), (name, window)
+    ctx.set_option("assign_in_place", launches)
+    ctx.set_option("profile", 1)
+    try:
+        for name, program in IN_PLACE.items():
+            for window in (0, 1):   # the whole array, or a window that starts off a 16-byte boundary, whose surroundings stay
+                a = np.random.default_rng(31).integers(-50, 50, (rows + 5 * window, cols + 6 * window)).astype(dtype)
+                t = torch.from_numpy(a).cuda()
+                cut = np.s_[2 * window:2 * window + rows, 3 * window:3 * window + cols]
+                u, ref = ctx.array(t[cut]), a[cut]
+                ctx.profile_reset()
+                for _ in range(2):
+                    box, value = program(u)
+                    u[box] = value
+                    box, value = program(ref)
+                    ref[box] = value.copy()
+                ctx.sync()
+                # (along the rows only, in one column of tiles: nothing around a tile to save)
+                nothing = name.startswith("from the") and cols < 260
+                assert in_place_launches(ctx) in ([(0, 2)] if launches == 1 else [(2, 0), (0, 0)] if nothing else [(2, 0)]), (name, window)
+                assert np.array_equal(t.cpu().numpy(), a), (name, window)
+    finally:
+        ctx.set_option("profile", 0)
+        ctx.set_option("assign_in_place", 1)
 
 
 # few tiles, in one launch: tiles that wait for the ones around them, that look once and save (nearly all of them then, and read what others
