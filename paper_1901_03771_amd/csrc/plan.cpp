@@ -788,6 +788,7 @@ static bool choose_gemm_blocks(GroupPlan* g) {
   } else {
     int heavy = 0;   // (a division, a root, an exponential are a third of the others)
     for (const Instr& in : g->prog) if (heavy_op(in)) heavy += in.kind == IKind::UNARY && (in.op == GR_TANH || in.op == GR_ERF) ? 3 : 1;
+    if (tiles >= (int64_t)1 << 24) return false;   // (a launch has fewer than 2^32 lanes; wider tiles are fewer)
     if (M <= 32 || N <= 32 || !((K <= 32 && M * N <= 10000000 && g->VR != 2) || (heavy >= 3 && K <= 128))) return false;
     g->UC = 1;
     g->BX = g->BY = 64;

@@ -869,6 +869,16 @@ def test_products_near_a_size_take_the_same_kernel(ctx):
     assert tiles(512, 512, 512) == "128x128 direct"
 
 
+@pytest.mark.parametrize("m,n,blocks", [((1 << 29) - 64, 80, True), ((1 << 29) - 63, 80, False), (1 << 29, 64, True), (1 << 29, 80, False), (1 << 29, 96, False)])
+def test_products_of_small_blocks_keep_to_the_lanes_of_a_launch(ctx, m, n, blocks):
+    # a launch has fewer than 2^32 lanes: where tiles of 64 x 64 would be 2^24 and more workgroups, wider ones are not
+    plan = gr.tanh(ctx.spec((m, 9)) @ ctx.spec((9, n)) + ctx.spec((n,))).plan()
+    tile, way = re.search(r"tile=(\d+x\d+)(.*)", plan).groups()
+    assert ("from registers" in way) == blocks
+    rows, cols = (int(v) for v in tile.split("x"))
+    assert -(-m // rows) * -(-n // cols) * 256 < 1 << 32
+
+
 @pytest.mark.parametrize("rows", [3, 30, 64, 300, 700, 4096, 20000, 300000, 5000000])
 def test_column_sums_bound_the_chain_of_additions(ctx, rows):
     # a lane adds up at most 256 elements in turn, or blocks of 64 of them; no output is left to fewer lanes than the chip has where rows suffice
