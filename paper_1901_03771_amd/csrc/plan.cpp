@@ -767,7 +767,9 @@ static void choose_in_place(gr_ctx* c, GroupPlan* g) {
 //   9.3 / 11.1.  Longer sums: 256 x 512 x 256 9.9 / 6.3, but 512^3 11.3 / 9.5 to 13 by layout: from 16 tiles on all of them stay.)  Long sums are split over
 //   workgroups as well: by 0.0062 us per value of k and round of 256 blocks (420 x 3250 x 124 transposed by 3, 4, 5, 9 parts: 168 workgroups 14.1, 224 12.4, 280 17.0, 504 13.7),
 //   2.7 for the second launch and 0.08 per part that it adds up (97 x 1491 x 40 10.3 / 8.1,
-//   50 x 4800 x 32 11.8 / 9.4, 200 x 500 x 200, unsplit, 10.8 / 6.0).
+//   50 x 4800 x 32 11.8 / 9.4, 200 x 500 x 200, unsplit, 10.8 / 6.0).  From about 2000 values of k per workgroup on tiles would be faster (320 x 8192 x 192 20.5 / 20,
+//   320 x 16384 x 192 31.5 / 35, 192 x 49000 x 192 50 / 58) with larger errors (3.0e-7 / 2.2e-7, 4.1e-7 / 3.0e-7, 5.4e-7 / 3.8e-7: chains four times as long) and four
+//   times the partial results: these sums stay here.
 // - waves side by side: more blocks, ragged operands, sums of up to 32 and at most 10^7 results (100000 x 9 x 40 13.5 / 9.6, 30000 x 20 x 200 13.4 / 12, 3000 x 20 x 3000 16.1 / 13.9,
 //   4936 x 27 x 1131 14.1 / 11.8; 2000 x 33 x 4000 15.8 / 16.7, 16384 x 16 x 4096 53 / 64), and sums of up to 128 whose results pass through a function of many
 //   instructions, which the larger tiles run when their products are done (tanh: 4936 x 27 x 1131 27.5 / 17.3, 11845 x 48 x 2066 77 / 60, 16384 x 100 x 1000 82 / 61,
